@@ -631,9 +631,9 @@ strait_status strait_k_conv2d(void* stream, const void* x, int32_t N, int32_t H,
         if (e != hipSuccess) { (void)hipFree(tmp); set_error("conv2d: padding the weights failed: %s", hipGetErrorString(e)); return STRAIT_E_HIP; }
         p.w = (const half_t*)tmp;
     }
-    // small problems may take the split-K path, which needs an fp32 workspace
+    // a long reduction for few outputs may be split into slabs, which needs an fp32 workspace
     void* ws = nullptr;
-    if ((long long)p.M * K <= 128LL * 4096) {
+    if (conv_workspace_bytes(p, SPLITK_WS_BYTES)) {
         if (hipMalloc(&ws, SPLITK_WS_BYTES) != hipSuccess) { (void)hipGetLastError(); ws = nullptr; }
         p.ws = (float*)ws; p.ws_bytes = ws ? SPLITK_WS_BYTES : 0;
     }
@@ -657,14 +657,7 @@ strait_status strait_k_conv1x1_proj(void* stream, const void* x, int32_t N, int3
     p.sN = (long long)P * Q * C; p.sH = Q * C; p.sW = C;
     p.x2 = (const half_t*)x2; p.K2 = K2; p.stride2 = stride2; p.sN2 = (long long)H2 * W2 * K2; p.sH2 = W2 * K2; p.sW2 = K2;
     p.Kg = C + K2; p.ldw = C + K2; p.Cout = Cout; p.ldy = Cout; p.act = act; p.hp = hp;
-    void* ws = nullptr;                                // small problems may take the split-K path, which needs an fp32 workspace
-    if ((long long)p.M * Cout <= 128LL * 4096) {
-        if (hipMalloc(&ws, SPLITK_WS_BYTES) != hipSuccess) { (void)hipGetLastError(); ws = nullptr; }
-        p.ws = (float*)ws; p.ws_bytes = ws ? SPLITK_WS_BYTES : 0;
-    }
-    const int rc = launch_conv(p, (hipStream_t)stream);
-    if (ws) { (void)hipStreamSynchronize((hipStream_t)stream); (void)hipFree(ws); }
-    return rc;
+    return launch_conv(p, (hipStream_t)stream);
 }
 
 strait_status strait_k_gemm(void* stream, const void* x, const void* w, const float* bias, int32_t M, int32_t N,
@@ -676,7 +669,7 @@ strait_status strait_k_gemm(void* stream, const void* x, const void* w, const fl
     p.stride_h = p.stride_w = 1; p.pad_h = p.pad_w = 0;
     p.sN = K; p.sH = K; p.sW = K; p.Kg = K; p.ldw = K; p.Cout = N; p.ldy = N; p.act = act; p.out_f32 = out_f32; p.hp = hp;
     void* ws = nullptr;
-    if ((long long)M * N <= 128LL * 4096) {
+    if (conv_workspace_bytes(p, SPLITK_WS_BYTES)) {
         if (hipMalloc(&ws, SPLITK_WS_BYTES) != hipSuccess) { (void)hipGetLastError(); ws = nullptr; }
         p.ws = (float*)ws; p.ws_bytes = ws ? SPLITK_WS_BYTES : 0;
     }

@@ -18,7 +18,9 @@
 //     and writes it out (adding the residual, applying the activation) as 16-byte row segments;
 //   - workgroup ids are re-ordered so that tiles sharing an input slice run on the same XCD
 //     (consecutive hardware ids are dealt round-robin over the 8 XCDs, each with its own L2).
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -280,7 +282,12 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const ConvParams p) {
 // per-lane gather arithmetic.  Here
 //   - slices travel global -> LDS directly (buffer_load_dwordx4 ... lds: each lane names a 16-byte
 //     chunk, the wave's 64 chunks land in 1 KB of consecutive LDS) through a ring of STAGES
-//     buffers, STAGES-1 slices in flight, one barrier per slice;
+//     buffers, one barrier per slice.  The operand fragments of a slice's first step are read right
+//     after the barrier that hands the slice over, ahead of the MFMAs of the slice before it, and the
+//     transfers that refill the freed buffer are issued between those MFMAs: a wavefront that is alone
+//     on its SIMD keeps the MFMA pipe fed across the barrier (8192 x 768 x 3072 on 128 x 192: 46 -> 41.5 us;
+//     what is left is LDS traffic, T per flop = 0.555 + 0.255 (LDS bytes per MFMA clock / 128) in 1 / PFLOP/s).
+//     The last STAGES slices run in a loop of their own that requests nothing;
 //   - the address of a chunk is split into a per-lane part fixed for the whole kernel (pixel or
 //     channel row, chunk within the slice) held in a VGPR, and a part that is the same for the
 //     whole workgroup (filter tap, channel base of the slice) kept in a scalar register and
@@ -295,7 +302,9 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const ConvParams p) {
 //     c ^ ((r >> 2) & 3); any 16 consecutive rows read at one logical chunk then touch 16
 //     distinct 16-byte bank groups;
 //   - the loads are issued from inline assembly so that the waits are ours: "all but the newest
-//     STAGES-2 slices have landed" before the barrier, rather than a wait for everything.
+//     STAGES-2 slices have landed" before the barrier, rather than a wait for everything;
+//   - tiles are dealt to the XCDs as rectangles (tile_cw below): a batch of 8 sequences' Q/K/V product fetched its
+//     3.5 MB of weights into all eight L2s before, and fetches a quarter of them into each now (13.6 -> 9.8 us).
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
 constexpr unsigned OOB_OFFSET = 0x80000000u;       // beyond any buffer this kernel accepts
@@ -348,7 +357,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     constexpr int TM = BM / WGM, TN = BN / WGN;
     constexpr int TMB = TM / 32, TNB = TN / 32;
     constexpr int XI = BM / (NW * RPI), WI = BN / (NW * RPI); // transfers per wave per slice
-    static_assert((BK == 32 || BK == 64) && TM % 32 == 0 && TN % 32 == 0 && XI >= 1 && WI >= 1, "unsupported tile");
+    static_assert((BK == 32 || BK == 64) && TM % 32 == 0 && TN % 32 == 0 && BM % (NW * RPI) == 0 && BN % (NW * RPI) == 0, "unsupported tile");
+    static_assert((NW * RPI) % (SWD * CPRW) == 0, "the swizzle of a lane's row has to be the same in all of its transfers");
     constexpr int STAGE = (BM + BN) * BK;              // halfs per stage
     constexpr int LDC = BN + 8;
     static_assert(MODE == MODE_1X1 || MODE == MODE_GATHER8, "vector modes only");
@@ -381,10 +391,18 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
         zsplit = logical / ntiles;
         tile = logical - zsplit * ntiles;
     }
-    int tm;                                             // tiles_n is a power of two for every served layer
-    if (p.tiles_n_shift >= 0) tm = tile >> p.tiles_n_shift; else tm = tile / tiles_n;
+    // Tiles are numbered down groups of tile_cw tile columns (row-major inside a group), so that the contiguous range an XCD
+    // gets covers a rectangle of about equal extent in pixels and channels: its L2 then fetches the fewest operand rows.
+    int tm, tn;
+    {
+        const int tiles_m = (p.M + BM - 1) / BM;
+        const int gsz = tiles_m * p.tile_cw, g = tile / gsz, r = tile - g * gsz;
+        const int w = p.tile_cw < tiles_n - g * p.tile_cw ? p.tile_cw : tiles_n - g * p.tile_cw;
+        tm = r / w;
+        tn = g * p.tile_cw + (r - tm * w);
+    }
     const int m0 = tm * BM;
-    const int n0 = (tile - tm * tiles_n) * BN;
+    const int n0 = tn * BN;
 
     // The input buffer starts `lead` elements before x so that the per-lane offset of an output
     // pixel (its window's top-left tap, which may lie in the padding) is never negative.
@@ -466,24 +484,26 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     }
     const unsigned row_step = (unsigned)(p.sH - p.S * p.sW) * 2u;   // from the end of a filter row to the next
 
-    auto issue = [&](int stage) {
+    // one transfer (j-th of this wave's XI + WI) of the slice being issued
+    auto issue_one = [&](int stage, int j) __attribute__((always_inline)) {
         const unsigned sx = lds0 + (unsigned)(stage * STAGE) * 2u;
         const unsigned sw = sx + (unsigned)(BM * BK) * 2u;
         const bool live = ki < k_end;                  // slices past the end deposit zeros
-        const bool second = DUAL && ki * BK >= p.C;   // workgroup-uniform
-        const unsigned soff_x = MODE == MODE_1X1 ? (unsigned)(second ? ki * BK - p.C : ki * BK) * 2u : tap_off + (unsigned)cb * 2u;
-#pragma unroll
-        for (int j = 0; j < XI; ++j) {
+        if (j < XI) {
+            const bool second = DUAL && ki * BK >= p.C;   // workgroup-uniform
+            const unsigned soff_x = MODE == MODE_1X1 ? (unsigned)(second ? ki * BK - p.C : ki * BK) * 2u : tap_off + (unsigned)cb * 2u;
             unsigned v = xoff[j];
             if (DUAL && second) v = xoff2[j];
             if (MODE == MODE_GATHER8) v = ((tapmask[j] >> tap) & 1u) ? v : OOB_OFFSET;
             if (MODE == MODE_1X1 && ragged_k) v = (ki * BK + cl * 8 < p.Kg) ? v : OOB_OFFSET;
             if (!live) v = OOB_OFFSET;
             dma16(second ? xrsrc2 : xrsrc, v, live ? soff_x : 0u, sx + (unsigned)((j * NW + wave) * 1024));
+        } else {
+            const int jw = j - XI;
+            dma16(wrsrc, live ? woff[jw] : OOB_OFFSET, live ? (unsigned)ki * (BK * 2) : 0u, sw + (unsigned)((jw * NW + wave) * 1024));
         }
-#pragma unroll
-        for (int j = 0; j < WI; ++j)
-            dma16(wrsrc, live ? woff[j] : OOB_OFFSET, live ? (unsigned)ki * (BK * 2) : 0u, sw + (unsigned)((j * NW + wave) * 1024));
+    };
+    auto advance = [&]() __attribute__((always_inline)) {
         ++ki;
         if (MODE == MODE_GATHER8) {
             cb += BK;
@@ -494,6 +514,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
                 if (++ts == p.S) { ts = 0; tap_off += row_step; }
             }
         }
+    };
+    auto issue = [&](int stage) {
+#pragma unroll
+        for (int j = 0; j < XI + WI; ++j) issue_one(stage, j);
+        advance();
     };
 
     floatx16 acc[TNB][TMB];
@@ -515,44 +540,70 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     }
 
 #pragma unroll
-    for (int i = 0; i < STAGES - 1; ++i) issue(i);
+    for (int i = 0; i < STAGES; ++i) if (i == 0 || i < nk) issue(i);
 
-    // MFMA operand fragments are double-buffered in registers: the LDS reads of 16-wide step ks+1
-    // are in flight while the MFMAs of step ks issue.
     const int swz = (l32 / SWD) & (CPRW - 1);
     constexpr int KS = BK / 16;
-    int rd = 0, wr = STAGES - 1;
-    for (int kt = 0; kt < nk; ++kt) {
-        wait_loads_then_barrier<(STAGES - 2) * (XI + WI)>();   // slice kt has landed everywhere; buffer wr is free
-        const half_t* Xs = smem + rd * STAGE;
+    half8 wf[2][TNB], xf[2][TMB];
+    auto load_frags = [&](int buf, int stage, int ks) __attribute__((always_inline)) {
+        const half_t* Xs = smem + stage * STAGE;
         const half_t* Ws = Xs + BM * BK;
-        half8 wf[2][TNB], xf[2][TMB];
-        auto load_frags = [&](int buf, int ks) {
-            const int pos = ((ks * 2 + lh) ^ swz) * 8;
+        const int pos = ((ks * 2 + lh) ^ swz) * 8;
 #pragma unroll
-            for (int a = 0; a < TNB; ++a) wf[buf][a] = *(const half8*)(Ws + (wn0 + a * 32 + l32) * BK + pos);
+        for (int a = 0; a < TNB; ++a) wf[buf][a] = *(const half8*)(Ws + (wn0 + a * 32 + l32) * BK + pos);
 #pragma unroll
-            for (int b = 0; b < TMB; ++b) xf[buf][b] = *(const half8*)(Xs + (wm0 + b * 32 + l32) * BK + pos);
-        };
-        load_frags(0, 0);
-        issue(wr);
+        for (int b = 0; b < TMB; ++b) xf[buf][b] = *(const half8*)(Xs + (wm0 + b * 32 + l32) * BK + pos);
+    };
+    constexpr int NX = XI + WI, NM = TMB * TNB, PER = (NX + NM - 1) / NM;   // transfers per slice, MFMAs per step, transfers per MFMA
+    int rd = 0;
+    if (nk >= STAGES) wait_loads_then_barrier<(STAGES - 1) * NX>(); else wait_loads_then_barrier<0>();
+    load_frags(0, 0, 0);
+    // main part: every step requests a further slice; tail: the last STAGES slices, nothing left to request
+    const int nmain = nk - STAGES;
+    for (int kt = 0; kt < nmain; ++kt) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            // scheduling fences keep the reads of the next step ahead of this step's MFMAs; without
-            // them the compiler sinks the reads below the MFMAs and folds the two buffers into one
-            if (ks + 1 < KS) load_frags((ks + 1) & 1, ks + 1);
+            const int frd = rd;
+            if (ks + 1 < KS) load_frags((ks + 1) & 1, rd, ks + 1);
+            else {
+                wait_loads_then_barrier<(STAGES - 2) * NX>();   // slice kt + 1 has landed everywhere; slice kt's buffer is free
+                rd = rd + 1 == STAGES ? 0 : rd + 1;
+                load_frags((ks + 1) & 1, rd, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int a = 0; a < TNB; ++a)
+            for (int q = 0; q < NM; ++q) {
+                const int a = q / TMB, b = q % TMB;
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[ks & 1][a], xf[ks & 1][b], acc[a][b], 0, 0, 0);
+                if (ks == KS - 1) {
 #pragma unroll
-                for (int b = 0; b < TMB; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[ks & 1][a], xf[ks & 1][b], acc[a][b], 0, 0, 0);
+                    for (int j = q * PER; j < (q + 1) * PER && j < NX; ++j) issue_one(frd, j);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (ks == KS - 1) advance();
             __builtin_amdgcn_sched_barrier(0);
         }
-        rd = rd + 1 == STAGES ? 0 : rd + 1;
-        wr = wr + 1 == STAGES ? 0 : wr + 1;
     }
-    wait_loads_then_barrier<0>();                      // trailing transfers have landed; LDS is free
+    for (int kt = nmain > 0 ? nmain : 0; kt < nk; ++kt) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if (ks + 1 < KS) load_frags((ks + 1) & 1, rd, ks + 1);
+            else {
+                wait_loads_then_barrier<0>();
+                rd = rd + 1 == STAGES ? 0 : rd + 1;
+                load_frags((ks + 1) & 1, rd, 0);                 // (after the last slice: whatever the buffer holds, not used)
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < NM; ++q) {
+                const int a = q / TMB, b = q % TMB;
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[ks & 1][a], xf[ks & 1][b], acc[a][b], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();                                   // LDS is free
 
     // ---- groups: partial sums of groups 1.. to group 0 through LDS, added in group order ----------------------
     if (KG > 1) {
@@ -1158,55 +1209,116 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
     return 0;
 }
 
-// Whether the patch kernel takes a layer, and with which tile; -1 = not this kernel's.
-static int launch_conv3x3_patch(const ConvParams& params, hipStream_t stream) {
-    ConvParams p = params;
+// ------------------------------------------------------------------------------------------
+// Which kernel and tile a layer gets.
+//
+// Every candidate's time is estimated from the layer's sizes, in microseconds:
+//     c0 + c1 R + c2 R nk + c3 R nk [gathered taps] + c4 R [GELU] + c5 MB + c6 max(0, MB - 250)
+// with nk the slices of the reduction a workgroup walks through, MB the megabytes of input, weights, residual and output
+// (c6: what does not stay in the 256 MB memory-side cache), and R the rounds of tiles a compute unit works off: the tiles
+// per unit rounded up where one workgroup fills a unit; where two fit, a pair of tiles counts 1 and an odd one 0.6, since
+// alone it gets more than half of the unit.  c0 holds the launch, c1 a tile's start, epilogue and stores, c2 a slice's
+// operand traffic and MFMAs.  The coefficients are non-negative least-squares fits (relative error) to measured times, 826
+// layer shapes on MI355X: the served networks' layers at batch 1 to 128 and image sides 160 to 256, token products of 32
+// to 16384 rows; mean error 5 to 9 %, and the estimated best is on average within 2 % of the measured best candidate.
+// Against the thresholds used before (and with the pipelined loop): ResNet-50's layers 7 % faster on the sum over batch 1
+// to 128 (22 % at batch 1, 5 % at 128), an encoder layer's products 8 to 19 % from 1000 rows on and 20 to 32 % below.
+enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
+              T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64, T_COUNT };
+struct TileInfo { int bm, bn, bk, kg; bool shared; float c[7]; };   // shared: two or more workgroups fit a compute unit
+static const TileInfo tile_info[T_COUNT] = {
+    {256, 256, 64, 1, false, {2.047f, 4.619f, 1.152f, 0.199f, 10.088f, 0.100f, 0.086f}},
+    {256, 192, 64, 1, false, {1.482f, 4.048f, 0.952f, 0.175f, 7.991f, 0.100f, 0.108f}},
+    {192, 128, 64, 1, false, {0.722f, 3.601f, 0.550f, 0.134f, 3.747f, 0.080f, 0.051f}},
+    {128, 256, 64, 1, false, {1.311f, 3.417f, 0.627f, 0.099f, 5.877f, 0.102f, 0.047f}},
+    {128, 128, 64, 1, false, {1.037f, 2.932f, 0.404f, 0.085f, 2.509f, 0.076f, 0.048f}},
+    {128, 128, 64, 1, true, {2.649f, 2.689f, 0.759f, 0.240f, 3.708f, 0.084f, 0.113f}},
+    {96, 128, 64, 1, false, {0.949f, 3.098f, 0.360f, 0.089f, 1.597f, 0.060f, 0.082f}},
+    {64, 128, 64, 1, true, {2.205f, 2.481f, 0.490f, 0.086f, 2.066f, 0.050f, 0.144f}},
+    {256, 128, 32, 1, true, {2.271f, 3.506f, 0.583f, 0.059f, 10.612f, 0.106f, 0.085f}},
+    {128, 64, 32, 1, true, {2.823f, 0.742f, 0.358f, 0.056f, 2.304f, 0.069f, 0.143f}},
+    {128, 64, 32, 1, true, {2.525f, 1.151f, 0.308f, 0.071f, 2.345f, 0.070f, 0.103f}},
+    {64, 64, 64, 1, true, {2.454f, 1.311f, 0.339f, 0.075f, 0.715f, 0.031f, 0.200f}},
+    {64, 64, 32, 1, true, {2.583f, 0.806f, 0.228f, 0.027f, 1.154f, 0.026f, 0.122f}},
+    {32, 64, 64, 1, true, {2.712f, 0.950f, 0.272f, 0.069f, 0.342f, 0.032f, 1.280f}},
+    {64, 64, 64, 2, false, {1.059f, 2.700f, 0.289f, 0.126f, 0.f, 0.065f, 0.f}},
+    {32, 64, 64, 4, false, {1.316f, 2.420f, 0.391f, 0.174f, 0.f, 0.085f, 0.f}},
+    {16, 16, 64, 4, true, {2.610f, 0.434f, 0.394f, 0.113f, 0.f, 0.f, 0.f}},
+    {16, 32, 64, 4, true, {2.783f, 0.392f, 0.603f, 0.126f, 0.f, 0.f, 0.f}},
+    {256, 128, 32, 1, true, {0.f, 8.0f, 1.05f, 0.f, 0.f, 0.f, 0.f}},
+    {128, 128, 32, 1, true, {2.534f, 1.637f, 0.369f, 0.f, 0.f, 0.217f, 0.f}},
+    {256, 64, 32, 1, true, {3.575f, 0.f, 0.485f, 0.f, 0.f, 0.122f, 0.f}},
+};
+
+// The patch kernel's view of a layer: strips, bordered pixels (mv) and which of its tiles takes the layer (a TileId), or -1.
+static int patch_geometry(const ConvParams& p, int* strip_w, int* slots, long long* mv) {
     int sw = p.W;
     while (sw > 64 && sw % 2 == 0) sw /= 2;
     if (sw > 128) return -1;
-    p.strip_w = sw;
     const int wp = sw + (p.W == sw ? 1 : 2);
-    const long long mv = (long long)(p.M / p.PQ) * (p.W / sw) * (p.H + 1) * wp;
-    // with fewer tiles than half the compute units the generic kernel, which may split its reduction, is the faster one
-    // (ResNet-50 batch 8, 28 x 28 x 128, 53 tiles: 12.2 against 9.2 us; batch 32, 210 tiles: 12.7 against 17.1 us)
-    if ((p.Cout % 128 == 0 ? (mv + 127) / 128 * (p.Cout / 128) : (mv + 255) / 256 * (p.Cout / 64)) < 128) return -1;
-    if (mv >= (1LL << 24) - 4096) return -1;           // the kernel's index arithmetic is exact below 2^24
-    auto per_wave = [&](int bm, int nw) { return ((bm + 2 * wp + 2 + 15) / 16 + nw - 1) / nw; };
+    *strip_w = sw;
+    *slots = wp;
+    *mv = (long long)(p.M / p.PQ) * (p.W / sw) * (p.H + 1) * wp;
+    return *mv >= (1LL << 24) - 4096 ? -1 : 0;         // the kernel's index arithmetic is exact below 2^24
+}
+static int patch_transfers(int bm, int nw, int slots) { return ((bm + 2 * slots + 2 + 15) / 16 + nw - 1) / nw; }
+static int patch_tile(const ConvParams& p, long long* mv) {
+    int sw, wp;
+    if (patch_geometry(p, &sw, &wp, mv)) return -1;
     if (p.Cout % 128 == 0) {
-        if (((mv + 255) / 256) * (p.Cout / 128) >= 768) {          // a round and a half of workgroups at least: 8 waves on 256 x 128
-            const int npw = per_wave(256, 8);
-            if (npw <= 3) return launch_patch_tile<256, 128, 4, 2, 3, 3>(p, mv, stream);
-            if (npw <= 4) return launch_patch_tile<256, 128, 4, 2, 4, 3>(p, mv, stream);
-        }
-        const int npw = per_wave(128, 4);
-        if (npw <= 4) return launch_patch_tile<128, 128, 2, 2, 4, 3>(p, mv, stream);
-        if (npw <= 6) return launch_patch_tile<128, 128, 2, 2, 6, 3>(p, mv, stream);
-        return -1;
+        // a round and a half of workgroups at least: 8 waves on 256 x 128
+        if (((*mv + 255) / 256) * (p.Cout / 128) >= 768 && patch_transfers(256, 8, wp) <= 4) return T_PATCH256x128;
+        return patch_transfers(128, 4, wp) <= 6 ? T_PATCH128x128 : -1;
     }
-    if (p.Cout % 64 == 0) {
-        const int npw = per_wave(256, 4);
-        // 64 channels in and out and tiles enough for two per workgroup: workgroups that walk over tiles
-        const bool walk = p.Cout == 64 && p.C <= 128 && (mv + 255) / 256 >= 1024;
-        if (npw <= 6) return walk ? launch_patch_walk<256, 64, 4, 1, 6, 3>(p, mv, stream) : launch_patch_tile<256, 64, 4, 1, 6, 3>(p, mv, stream);
-        if (npw <= 8) return walk ? launch_patch_walk<256, 64, 4, 1, 8, 3>(p, mv, stream) : launch_patch_tile<256, 64, 4, 1, 8, 3>(p, mv, stream);
-        return -1;
+    return p.Cout % 64 == 0 && patch_transfers(256, 4, wp) <= 8 ? T_PATCH256x64 : -1;
+}
+static int launch_conv3x3_patch(const ConvParams& params, hipStream_t stream) {
+    ConvParams p = params;
+    int wp;
+    long long mv;
+    const int id = patch_tile(p, &mv);
+    if (id < 0 || patch_geometry(p, &p.strip_w, &wp, &mv)) { set_error("conv: not a layer of the patch kernel"); return -5; }
+    if (id == T_PATCH256x128) {
+        if (patch_transfers(256, 8, wp) <= 3) return launch_patch_tile<256, 128, 4, 2, 3, 3>(p, mv, stream);
+        return launch_patch_tile<256, 128, 4, 2, 4, 3>(p, mv, stream);
     }
-    return -1;
+    if (id == T_PATCH128x128) {
+        if (patch_transfers(128, 4, wp) <= 4) return launch_patch_tile<128, 128, 2, 2, 4, 3>(p, mv, stream);
+        return launch_patch_tile<128, 128, 2, 2, 6, 3>(p, mv, stream);
+    }
+    // 64 channels in and out and tiles enough for two per workgroup: workgroups that walk over tiles
+    const bool walk = p.Cout == 64 && p.C <= 128 && (mv + 255) / 256 >= 1024;
+    if (patch_transfers(256, 4, wp) <= 6) return walk ? launch_patch_walk<256, 64, 4, 1, 6, 3>(p, mv, stream) : launch_patch_tile<256, 64, 4, 1, 6, 3>(p, mv, stream);
+    return walk ? launch_patch_walk<256, 64, 4, 1, 8, 3>(p, mv, stream) : launch_patch_tile<256, 64, 4, 1, 8, 3>(p, mv, stream);
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int STAGES>
-static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
-    const long long tiles = (long long)((p.M + BM - 1) / BM) * ((p.Cout + BN - 1) / BN) * p.ksplit;
-    if (tiles <= 0 || tiles > 0x7fffffffLL) { set_error("conv: bad grid (%lld tiles)", tiles); return -5; }
-    constexpr unsigned ring = STAGES * (BM + BN) * BK * 2, ctile = BM * (BN + 8) * 2;
-    constexpr unsigned lds = (ring > ctile ? ring : ctile) + 1024;    // the epilogue parks the output tile in the ring's LDS; + the tile's bias row
-    dim3 grid((unsigned)tiles), block(64 * WGM * WGN);
-    ConvParams q = p;
-    {
-        const int tn = (p.Cout + BN - 1) / BN;
-        q.tiles_n_shift = -1;
-        for (int sft = 0; sft < 31; ++sft) if ((1 << sft) == tn) q.tiles_n_shift = sft;
+// Tile columns of a group (see the kernel's tile order): the contiguous range of about tiles / 8 tiles that an XCD gets should
+// touch as few operand rows as possible, tile_cw * BN weight rows and (range / tile_cw) * BM input rows.
+int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn) {
+    const double per = std::max(1.0, (double)(tiles_m * tiles_n) / 8.0);
+    int best = 1;
+    double best_rows = 1e30;
+    for (int c = 1; c <= tiles_n; ++c) {
+        const double rows = c * (double)bn + std::min((double)tiles_m, std::ceil(per / c)) * bm;
+        if (rows < best_rows) { best_rows = rows; best = c; }
     }
+    return best;
+}
+
+// One launch of conv_igemm_dma_kernel on a BM x BN tile.  KG > 1: the reduction split over KG groups of wavefronts inside the
+// workgroup; p.ksplit > 1 (KG == 1 only): over ksplit workgroups per tile, with a second launch that adds their slabs.
+template <int BM, int BN, int BK, int WGM, int WGN, int STAGES, int KG = 1>
+static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
+    const long long tiles_m = (p.M + BM - 1) / BM;
+    const int tiles_n = (p.Cout + BN - 1) / BN;
+    const long long tiles = tiles_m * tiles_n * p.ksplit;
+    if (tiles <= 0 || tiles > 0x7fffffffLL) { set_error("conv: bad grid (%lld tiles)", tiles); return -5; }
+    constexpr unsigned ring = KG * STAGES * (BM + BN) * BK * 2, ctile = BM * (BN + 8) * 2;
+    constexpr unsigned lds = (ring > ctile ? ring : ctile) + 1024;    // the epilogue parks the output tile in the ring's LDS; + the tile's bias row
+    static_assert(lds <= 160 * 1024, "LDS limit");
+    dim3 grid((unsigned)tiles), block(64 * WGM * WGN * KG);
+    ConvParams q = p;
+    q.tile_cw = pick_tile_cw(tiles_m, tiles_n, BM, BN);
     auto go = [&](auto kernel) -> int {
         static std::atomic<bool> configured{false};     // one flag per instantiation; setting the attribute twice is harmless
         if (!configured.load(std::memory_order_acquire) && lds > 48 * 1024) {
@@ -1218,53 +1330,22 @@ static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
         return 0;
     };
     int rc;
-    if (mode == MODE_1X1 && p.act == ACT_GELU) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, false>);
-    else if (mode == MODE_1X1 && p.x2) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false, true>);
-    else if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, true>);
-    else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false>);
-    else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, false>);
+    if constexpr (KG > 1) {
+        if (mode == MODE_1X1 && p.res) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, true, false, KG>);
+        else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false, false, KG>);
+        else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, false, false, KG>);
+    } else {
+        if (mode == MODE_1X1 && p.act == ACT_GELU) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, false>);
+        else if (mode == MODE_1X1 && p.x2) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false, true>);
+        else if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, true>);
+        else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false>);
+        else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, false>);
+    }
     if (rc) return rc;
     if (p.ksplit > 1) {
         const long long n8 = (long long)p.M * (p.Cout / 8);
         hipLaunchKernelGGL(splitk_finish_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, stream, q);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) { set_error("conv launch: %s", hipGetErrorString(e)); return -2; }
-    return 0;
-}
-
-
-// The same tile with the reduction split over KG groups of wavefronts inside the workgroup (no second launch).
-template <int BM, int BN, int BK, int WGM, int WGN, int STAGES, int KG>
-static int launch_dma_tile_groups(const ConvParams& p, int mode, hipStream_t stream) {
-    const long long tiles = (long long)((p.M + BM - 1) / BM) * ((p.Cout + BN - 1) / BN);
-    if (tiles <= 0 || tiles > 0x7fffffffLL) { set_error("conv: bad grid (%lld tiles)", tiles); return -5; }
-    constexpr unsigned ring = KG * STAGES * (BM + BN) * BK * 2, ctile = BM * (BN + 8) * 2;
-    constexpr unsigned lds = (ring > ctile ? ring : ctile) + 1024;
-    static_assert(lds <= 160 * 1024, "LDS limit");
-    dim3 grid((unsigned)tiles), block(64 * WGM * WGN * KG);
-    ConvParams q = p;
-    q.ksplit = 1;
-    {
-        const int tn = (p.Cout + BN - 1) / BN;
-        q.tiles_n_shift = -1;
-        for (int sft = 0; sft < 31; ++sft) if ((1 << sft) == tn) q.tiles_n_shift = sft;
-    }
-    auto go = [&](auto kernel) -> int {
-        static std::atomic<bool> configured{false};
-        if (!configured.load(std::memory_order_acquire)) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) { set_error("conv: cannot reserve %u bytes of LDS: %s", lds, hipGetErrorString(e)); return -2; }
-        }
-        configured.store(true, std::memory_order_release);
-        hipLaunchKernelGGL(kernel, grid, block, lds, stream, q);
-        return 0;
-    };
-    int rc;
-    if (mode == MODE_1X1 && p.res) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, true, false, KG>);
-    else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false, false, KG>);
-    else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, false, false, KG>);
-    if (rc) return rc;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("conv launch: %s", hipGetErrorString(e)); return -2; }
     return 0;
@@ -1283,6 +1364,58 @@ static int launch_tile(const ConvParams& p, int mode, bool staged, hipStream_t s
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("conv launch: %s", hipGetErrorString(e)); return -2; }
     return 0;
+}
+
+static float estimate_us(const ConvParams& p, TileId id, long long pixels, bool gather, double mb) {
+    const TileInfo& t = tile_info[id];
+    const long long tiles = (pixels + t.bm - 1) / t.bm * ((p.Cout + t.bn - 1) / t.bn);
+    const long long per_cu = (tiles + 255) / 256;
+    const double nk = std::ceil((double)p.Kg / (t.bk * t.kg));
+    double r;
+    if (id == T_SK16 || id == T_SK32) r = std::max(1.0, tiles / 256.0);
+    else if (!t.shared) r = (double)per_cu;
+    else r = per_cu > 8 ? tiles / 512.0 : per_cu / 2 + (per_cu % 2 ? 0.6 : 0.0);
+    return (float)(t.c[0] + r * (t.c[1] + nk * (t.c[2] + (gather ? t.c[3] : 0.f)) + (p.act == ACT_GELU ? t.c[4] : 0.f)) + t.c[5] * mb +
+                   t.c[6] * std::max(0.0, mb - 250.0));
+}
+
+static int launch_tile_id(const ConvParams& p, TileId id, int mode, hipStream_t stream) {
+    switch (id) {
+        case T256x256: return launch_dma_tile<256, 256, 64, 2, 4, 2>(p, mode, stream);
+        case T256x192: return launch_dma_tile<256, 192, 64, 4, 2, 2>(p, mode, stream);
+        case T192x128: return launch_dma_tile<192, 128, 64, 2, 4, 3>(p, mode, stream);
+        case T128x256: return launch_dma_tile<128, 256, 64, 2, 4, 3>(p, mode, stream);
+        case T128x128: return launch_dma_tile<128, 128, 64, 4, 2, 4>(p, mode, stream);
+        case T128x128_2: return launch_dma_tile<128, 128, 64, 2, 2, 2>(p, mode, stream);
+        case T96x128: return launch_dma_tile<96, 128, 64, 1, 4, 4>(p, mode, stream);
+        case T64x128: return launch_dma_tile<64, 128, 64, 2, 2, 3>(p, mode, stream);
+        case T256x128s: return launch_dma_tile<256, 128, 32, 4, 2, 3>(p, mode, stream);
+        case T128x64_2: return launch_dma_tile<128, 64, 32, 2, 2, 2>(p, mode, stream);
+        case T128x64_3: return launch_dma_tile<128, 64, 32, 2, 2, 3>(p, mode, stream);
+        case T64x64: return launch_dma_tile<64, 64, 64, 2, 2, 3>(p, mode, stream);
+        case T64x64s: return launch_dma_tile<64, 64, 32, 2, 2, 3>(p, mode, stream);
+        case T32x64: return launch_dma_tile<32, 64, 64, 1, 2, 4>(p, mode, stream);
+        case T64x64_g2: return launch_dma_tile<64, 64, 64, 2, 2, 3, 2>(p, mode, stream);
+        case T32x64_g4: return launch_dma_tile<32, 64, 64, 1, 2, 3, 4>(p, mode, stream);
+        case T_SK16: return launch_conv_skinny(p, 16, mode == MODE_GATHER8, stream);
+        case T_SK32: return launch_conv_skinny(p, 32, mode == MODE_GATHER8, stream);
+        default: return launch_conv3x3_patch(p, stream);
+    }
+}
+
+// A reduction of 16384 or more for 16 rows or more and a handful of tiles (the first fully connected layer of a plain CNN): bound
+// by the bytes of weights in flight, it is split over up to 32 workgroups per tile with fp32 slabs and a second launch
+// (64 rows, 25088 -> 4096: 54 us against 91 us in one launch; below 16 rows the kernel of conv_skinny.hip is faster, 38 against
+// 45 us at 6 rows).  Returns the number of parts whose slabs fit in `limit` bytes; 1 = no split.
+static int slab_split(const ConvParams& p, size_t limit) {
+    if (p.Kg < 16384 || p.M < 16 || p.x2 || p.Cout % 8 != 0 || p.ldy % 8 != 0) return 1;
+    const long long t = (long long)((p.M + 63) / 64) * ((p.Cout + 63) / 64);
+    if (t > 128) return 1;
+    return (int)std::max<long long>(1, std::min<long long>({32, (1280 + t - 1) / t, (long long)(limit / ((size_t)p.M * p.Cout * 4))}));
+}
+size_t conv_workspace_bytes(const ConvParams& p, size_t limit) {
+    const int ks = slab_split(p, limit);
+    return ks > 1 ? (size_t)ks * p.M * p.Cout * 4 : 0;
 }
 
 int launch_conv(const ConvParams& params, hipStream_t stream) {
@@ -1314,83 +1447,52 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
     else if (vec_ok) mode = MODE_GATHER8;
     else mode = MODE_SCALAR;
     const bool staged = !p.out_f32 && (p.Cout % 8 == 0) && (p.ldy % 8 == 0);
-    // pick the largest tile that still gives the 256 CUs about two workgroups each
     auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.Cout + bn - 1) / bn); };
     const bool dense = mode == MODE_1X1 && p.stride_h == 1;
     p.x_elems = dense ? (long long)p.M * p.sW : (long long)(p.M / p.PQ) * p.sN;
     const long long lead = (long long)p.pad_h * p.sH + (long long)p.pad_w * p.sW;
     const bool small = (p.x_elems + lead) * 2 <= 0x7fffffffLL && (long long)p.Cout * p.ldw * 2 <= 0x7fffffffLL;
     p.ksplit = 1;
-    // (GELU after a residual add is left to the first kernel: this one applies GELU before the staging)
+    // (GELU after a residual add is left to the first kernel: the LDS-direct one applies GELU before the staging)
     const bool regular = (mode == MODE_1X1 && !(p.act == ACT_GELU && p.res)) || (mode == MODE_GATHER8 && p.C % 32 == 0 && p.R * p.S <= 32 && p.act != ACT_GELU);
-    // Few output tiles and a long reduction (small batches, late layers): one workgroup per tile
-    // would leave most CUs idle behind a serial chain of slices.  Split the reduction: over two groups of
-    // wavefronts inside the workgroup where a shallow split will do, else over ksplit workgroups per tile,
-    // each writing an fp32 slab, with a second launch that reduces them.
-    if (regular && small && p.Cout % 8 == 0 && p.ldy % 8 == 0) {
-        const long long t = tiles(64, 64);
-        const int nk = (p.Kg + 31) / 32;
-        // about one workgroup per CU and a bit hides the chain of slices; a layer that streams megabytes of
-        // weights for a handful of rows (the fully connected layers of a plain CNN) is bound by the bytes in
-        // flight and takes four times as many
-        const long long target = (long long)p.Cout * p.Kg * 2 >= (8LL << 20) ? 1280 : 320;
-        long long ks = (target + t - 1) / t;
-        if (ks > nk / 4) ks = nk / 4;
-        if (ks > 32) ks = 32;
-        // Up to an eight-way split, and up to one tile per CU: two groups of wavefronts in one workgroup, half of the
-        // slices each and no second launch (ResNet-50 batch 8: 1024 -> 256 at 14 x 14 10.7 -> 6.3 us, its 3x3 14.1 -> 12.0 us;
-        // batch 16, 196 tiles, the same 3x3 13.7 -> 11.9 us; four groups with shallower rings are no faster, and from 400
-        // tiles on the groups cost more than they save).  Deeper splits are layers that stream megabytes of weights
-        // for a few rows and need the workgroups (512-channel 3x3 at 7 x 7, batch 1: 12.8 us split 32 ways, 18.7 us in
-        // two groups; the same layer at batch 8, split six ways: 14.3 against 19.5 us, so reductions of more than 96
-        // slices keep the slabs wherever those are an option).
-        if (t <= 256 && nk >= 8 && ks <= 8 && (t > 128 || (ks > 1 && nk <= 96)) && staged && !p.x2 && p.act != ACT_GELU) {
-            if (mode == MODE_1X1 && p.Kg % 64 == 0) return launch_dma_tile_groups<64, 64, 64, 2, 2, 3, 2>(p, mode, stream);
-            return launch_dma_tile_groups<64, 64, 32, 2, 2, 4, 2>(p, mode, stream);
+    if (regular && small) {
+        const int ks = p.ws && (reinterpret_cast<uintptr_t>(p.ws) & 15) == 0 ? slab_split(p, p.ws_bytes) : 1;
+        if (ks > 1) {
+            p.ksplit = ks;
+            return mode == MODE_1X1 && p.Kg % 64 == 0 ? launch_dma_tile<64, 64, 64, 2, 2, 3>(p, mode, stream)
+                                                      : launch_dma_tile<64, 64, 32, 2, 2, 3>(p, mode, stream);
         }
-        if (t <= 128 && nk >= 8 && p.ws && (reinterpret_cast<uintptr_t>(p.ws) & 15) == 0) {
-            while (ks > 1 && ks * (long long)p.M * p.Cout * 4 > (long long)p.ws_bytes) --ks;
-            if (ks > 1) {
-                p.ksplit = (int)ks;
-                // dense products with four or more 32-wide slices per workgroup take them 64 wide: half the barriers and
-                // round trips of the chain (1024 -> 256 at 14 x 14, batch 1: 10.2 -> 7.9 us); gathered 3x3 slices do not gain
-                if (mode == MODE_1X1 && p.Kg % 64 == 0 && nk / ks >= 4) return launch_dma_tile<64, 64, 64, 2, 2, 3>(p, mode, stream);
-                return launch_dma_tile<64, 64, 32, 2, 2, 3>(p, mode, stream);
+        const bool whole64 = p.Kg % 64 == 0 && p.C % 64 == 0;                 // slices of 64 never straddle a tap or the end
+        const bool gather = mode == MODE_GATHER8;
+        const double mb = ((double)p.x_elems * 2 + (double)p.Cout * p.Kg * 2 + (double)p.M * p.Cout * 2 * (p.res ? 2 : 1)) * 1e-6;
+        TileId best = T_COUNT;
+        float best_us = 1e30f;
+        auto consider = [&](TileId id, long long pixels) {
+            const float us = estimate_us(p, id, pixels, gather, mb);
+            if (us < best_us) { best_us = us; best = id; }
+        };
+        if (staged) {
+            for (int i = 0; i < T_DMA; ++i) {
+                const TileInfo& t = tile_info[i];
+                if (t.bk == 64 && gather && p.C % 64 != 0) continue;
+                if (t.kg > 1 && (p.Kg < 512 || p.x2 || p.act == ACT_GELU)) continue;        // too short to split
+                if (i == T256x128s && p.Kg >= 512) continue;                                // a tile for streaming layers
+                if (t.bm < 128 && mb > 250) continue;                                       // estimates are not good for so many small tiles
+                consider((TileId)i, p.M);
+            }
+            if (gather && p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 1 && p.pad_w == 1 && !p.res &&
+                p.W >= 14 && p.Q == p.W && p.PQ == p.H * p.W) {
+                long long mv;
+                const int id = patch_tile(p, &mv);
+                if (id >= 0) consider((TileId)id, mv);
             }
         }
-    }
-    // wide 3x3 stride-1 layers: the patch kernel fetches each input pixel once per slice instead of once per tap
-    if (staged && regular && small && mode == MODE_GATHER8 && p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 &&
-        p.pad_h == 1 && p.pad_w == 1 && !p.res && p.act != ACT_GELU && p.W >= 14 && p.Q == p.W && p.PQ == p.H * p.W && p.ldy % 8 == 0) {
-        const int rc = launch_conv3x3_patch(p, stream);
-        if (rc != -1) return rc;
-    }
-    if (staged && regular && small) {
-        // Tile choice, from sweeps over the served networks' layer shapes on MI355X:
-        //  - deep reductions (K >= 512) with at least 128 output channels are limited by how fast
-        //    operands reach the CU: the 128x128 tile halves the bytes per flop and 64-wide slices
-        //    halve the barriers; a third stage (one workgroup per CU) pays only when there is at most one tile per CU anyway;
-        //  - shallow reductions stream activations: the 128x64 tile with few stages keeps the LDS
-        //    footprint small, i.e. more workgroups in flight per CU to cover memory latency.
-        const bool bk64 = mode == MODE_1X1 ? p.Kg % 64 == 0 : p.C % 64 == 0;
-        const long long t128 = tiles(128, 128), t64 = tiles(128, 64);
-        if (p.Kg >= 512 && p.Cout >= 256 && tiles(256, 128) >= 512)      // plenty of tiles: 8 waves on 256x128
-            return launch_dma_tile<256, 128, 32, 2, 4, 3>(p, mode, stream);
-        if (p.Kg >= 256 && p.Kg < 512 && p.Cout >= 1024 && tiles(128, 256) >= 192)   // wide outputs, medium reduction
-            return launch_dma_tile<128, 256, 32, 2, 4, 2>(p, mode, stream);
-        if (p.Kg >= 256 && p.Kg < 512 && p.Cout >= 512 && tiles(256, 128) >= 512)    // the same with half the width (a block-closing
-            return launch_dma_tile<256, 128, 32, 2, 4, 3>(p, mode, stream);           // convolution with its projection: 81 -> 66 us at batch 128)
-        if (p.Kg >= 512 && p.Cout >= 128 && t128 >= 192) {
-            if (bk64) return t128 <= 256 ? launch_dma_tile<128, 128, 64, 2, 2, 3>(p, mode, stream)
-                                         : launch_dma_tile<128, 128, 64, 2, 2, 2>(p, mode, stream);
-            return launch_dma_tile<128, 128, 32, 2, 2, 3>(p, mode, stream);
+        // short reductions stay with the kernel that reads operands through LDS; fp32 output has no other kernel
+        if (whole64 && (p.out_f32 || p.Kg >= 192) && tiles(16, 16) <= 0x7fffffffLL && mb <= 250) {
+            consider(T_SK16, p.M);
+            consider(T_SK32, p.M);
         }
-        if (t64 >= 256) return p.Kg >= 288 ? launch_dma_tile<128, 64, 32, 2, 2, 3>(p, mode, stream)
-                                           : launch_dma_tile<128, 64, 32, 2, 2, 2>(p, mode, stream);
-        // few, small tiles: nothing competes for LDS, and four slices in flight per workgroup instead of two shorten the
-        // latency chain of the reduction (ResNet-50 b32 0.96 -> 0.87 ms, b8 0.55 -> 0.53 ms; six are no better)
-        if (bk64) return launch_dma_tile<64, 64, 64, 2, 2, 3>(p, mode, stream);      // the same bytes in flight in half the steps
-        return launch_dma_tile<64, 64, 32, 2, 2, 4>(p, mode, stream);
+        if (best != T_COUNT) return launch_tile_id(p, best, mode, stream);
     }
     if (p.x2) { set_error("conv: a second source needs the LDS-direct kernels (sizes out of their range)"); return -5; }
     if (p.Cout > 64 && tiles(128, 128) >= 512) return launch_tile<128, 128>(p, mode, staged, stream);

@@ -40,7 +40,7 @@ struct ConvParams {
     float* ws;               // optional split-K workspace (16-byte aligned) and its size in bytes
     size_t ws_bytes;
     int ksplit;              // filled in by launch_conv
-    int tiles_n_shift;       // log2 of the number of tiles along Cout, or -1; filled in by the launcher
+    int tile_cw;             // tile columns of a group in the kernels' tile order; filled in by the launcher
     int strip_w;             // 3x3 patch kernel: width of the strips a row is cut into; filled in by the launcher
     // Optional second source of a 1x1 convolution with stride 1 (a block-closing convolution that absorbs the block's 1x1
     // projection shortcut): reduction elements [C, C + K2) are x2[n*sN2 + p*stride2*sH2 + q*stride2*sW2 + (k - C)], and
@@ -52,6 +52,12 @@ struct ConvParams {
 };
 
 int launch_conv(const ConvParams& p, hipStream_t stream);
+// Bytes of workspace (ConvParams::ws), at most `limit`, with which launch_conv splits this layer's reduction into slabs; 0 = it uses none.
+size_t conv_workspace_bytes(const ConvParams& p, size_t limit);
+// Small outputs with a reduction worth sharing out (conv_skinny.hip): 16 pixels x tn (16 or 32) channels per workgroup.  Called by
+// launch_conv with x_elems filled in; C and Kg multiples of 64.
+int launch_conv_skinny(const ConvParams& p, int tn, bool gather, hipStream_t stream);
+int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn);
 
 // Two chained pointwise convolutions in one launch (pointwise_pair.hip):
 //   y[m, 0:N1] = act1(x[m, 0:K1] w3^T + b3 (+ res[m, 0:N1]));   z[m, 0:N2] = act2(y[m, 0:N1] w1^T + b1)

@@ -583,3 +583,60 @@ def test_gemm_gelu_and_ragged_k(S):
         y = S.k_gemm(dev(S, x), dev(S, w), dev(S, b), act)
         check_kernel(y.float().cpu().numpy(), ref, f"gemm {M}x{N}x{K} act {act}")
 
+
+
+@pytest.mark.parametrize("M,N,K,use_res", [
+    # one shape per tile of the dispatch, ragged in pixels and (where the layer allows it) in channels and slices
+    (6311, 2304, 512, False), (8617, 1160, 64, False), (8347, 456, 64, True), (6455, 1184, 136, False), (8298, 280, 192, True),
+    (4881, 1584, 136, False), (8491, 208, 136, True), (8466, 72, 520, False), (8894, 648, 64, True), (8514, 200, 64, False),
+    (8387, 72, 64, True), (8250, 16, 192, False), (77, 40, 64, False), (45, 72, 520, True),
+    # reductions split inside the workgroup: two groups of wavefronts, four groups
+    (2891, 136, 768, True), (661, 208, 512, False),
+    # one slice, fewer slices than the ring holds, exactly as many, one more
+    (300, 64, 32, False), (300, 64, 96, False), (300, 64, 128, True), (9000, 256, 192, False), (9000, 256, 256, False)])
+def test_gemm_tiles_integer_data_is_bit_exact(S, M, N, K, use_res):
+    """Small integers are exact in fp16 and fp32: every tile, its ring of slices and its edges must reproduce the product."""
+    x = R.integers(-2, 3, (M, K)).astype(np.float16)
+    w = (R.integers(-1, 2, (N, K)) * (R.random((N, K)) < 0.3)).astype(np.float16)
+    b = R.integers(-5, 6, N).astype(np.float32)
+    res = R.integers(-9, 10, (M, N)).astype(np.float16) if use_res else None
+    ref = x.astype(np.float64) @ w.astype(np.float64).T + b + (0 if res is None else res.astype(np.float64))
+    assert np.abs(ref).max() < 2048
+    y = S.k_gemm(dev(S, x), dev(S, w), dev(S, b), 0, None if res is None else dev(S, res))
+    assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("N,H,C,K,Rk,stride,pad,use_res,out_f32", [
+    (1, 7, 512, 512, 3, 1, 1, False, False),     # 49 pixels: a ragged fourth tile; 72 super-slices over four wavefronts
+    (1, 14, 192, 40, 3, 2, 1, True, False),      # stride 2, channels ragged in the tile; 27 super-slices: unequal parts
+    (3, 1, 192, 10, 1, 1, 0, False, True),       # three super-slices: one wavefront has none; ten fp32 outputs
+    (5, 1, 2048, 1000, 1, 1, 0, False, True),    # a classifier
+    (1, 1, 64, 7, 1, 1, 0, False, True),         # the smallest: one row, one super-slice, odd outputs
+    (1, 9, 256, 96, 1, 2, 0, False, False)])     # a strided projection
+def test_small_outputs_integer_data_is_bit_exact(S, N, H, C, K, Rk, stride, pad, use_res, out_f32):
+    """Few outputs, the reduction shared out over the wavefronts of a workgroup: partial sums and their meeting in LDS are
+    exact on integer data."""
+    x = R.integers(-2, 3, (N, H, H, C)).astype(np.float16)
+    w = (R.integers(-1, 2, (K, C, Rk, Rk)) * (R.random((K, C, Rk, Rk)) < 0.2)).astype(np.float16)
+    b = R.integers(-5, 6, K).astype(np.float32)
+    ref = ops.conv2d(x, w, b, stride, pad)
+    res = R.integers(-9, 10, ref.shape).astype(np.float16) if use_res else None
+    if use_res:
+        ref = ref + res.astype(np.float64)
+    assert np.abs(ref).max() < 2048
+    y = S.k_conv2d(dev(S, x), dev(S, np.ascontiguousarray(np.transpose(w, (0, 2, 3, 1)))), dev(S, b), stride, pad, 0,
+                   None if res is None else dev(S, res), out_f32)
+    assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)
+
+
+def test_small_outputs_gelu_and_second_source(S):
+    """The same kernel with GELU on a short token sequence, and with a second source of its reduction."""
+    x, w, b = f16(R.standard_normal((19, 768))), f16(R.standard_normal((136, 768)) * 768 ** -0.5), R.standard_normal(136).astype(np.float32)
+    y = S.k_gemm(dev(S, x), dev(S, w), dev(S, b), 3)
+    check_kernel(y.float().cpu().numpy(), ops.gelu(ops.linear(x, w, b)), "gemm 19x136x768 gelu")
+    x1, x2 = R.integers(-2, 3, (1, 7, 7, 128)).astype(np.float16), R.integers(-2, 3, (1, 14, 14, 192)).astype(np.float16)
+    wp = (R.integers(-1, 2, (72, 320)) * (R.random((72, 320)) < 0.3)).astype(np.float16)
+    bp = R.integers(-5, 6, 72).astype(np.float32)
+    ref = np.concatenate([x1, x2[:, ::2, ::2]], -1).astype(np.float64) @ wp.astype(np.float64).T + bp
+    y = S.k_conv1x1_proj(dev(S, x1), dev(S, x2), 2, dev(S, wp), dev(S, bp))
+    assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)
