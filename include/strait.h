@@ -93,12 +93,13 @@ typedef struct {
 
 /* Completion record of one batch (Section 5.1: latency runs from enqueue to the result being
  * back in host memory; Section 3.2: measured H2D time; Section 3.3: measured kernel latency).
- * Times in ms are device-side (hipEventElapsedTime); *_ns are host CLOCK_MONOTONIC. */
+ * Times in ms are device-side (timestamps of the device's constant-rate clock, taken by the copy kernels);
+ * *_ns are host CLOCK_MONOTONIC. */
 typedef struct {
     int32_t model_id, priority, batch, instance;
     int64_t t_enqueue_ns;      /* host time at entry of strait_submit                       */
     int64_t t_issued_ns;       /* host time when everything had been enqueued               */
-    int64_t t_done_ns;         /* host time the completion thread saw the D2H copy finish   */
+    int64_t t_done_ns;         /* host time the result was seen to be in host memory        */
     float h2d_ms;              /* input copy                                                */
     float kernel_ms;           /* first kernel start to last kernel end                     */
     float d2h_ms;              /* output copy                                               */
@@ -165,9 +166,9 @@ strait_status strait_ctx_set_branch_streams(strait_ctx* ctx, int32_t enabled);
 
 /* How inputs travel from the instance's pinned buffer to the device (Section 2 of the paper: inputs are
  * "copied to the GPU's memory" before the kernels run; the first-in first-out link of Section 3.2).
- * Inputs of at most max_bytes are read over the host link by a copy kernel on the copy stream; larger
- * ones go by hipMemcpyAsync on the same stream.  Both sit between the same two events, so records and
- * the link model see no difference.  Default 8 MiB (every serving-sized batch): under concurrent
+ * Inputs of at most max_bytes are read over the host link by a copy kernel, on the compute stream if that is idle and on
+ * a copy stream beside its work otherwise; larger ones go by hipMemcpyAsync on a copy stream.  Both sit between the
+ * same two timestamps, so records and the link model see no difference.  Default 8 MiB (every serving-sized batch): under concurrent
  * serving the asynchronous copy call of such sizes was measured to block its caller for milliseconds
  * now and then, a kernel launch never.  0 = always hipMemcpyAsync. */
 strait_status strait_ctx_set_h2d_kernel_limit(strait_ctx* ctx, int64_t max_bytes);
@@ -193,7 +194,8 @@ strait_status strait_model_staging(const strait_model* m, int32_t instance, void
 
 /* Submit a batch at a priority level: picks an idle instance (E_BUSY if none -- never blocks),
  * copies `host_in` into the instance's pinned buffer, enqueues H2D copy, kernel sequence and
- * D2H copy without any host synchronisation, and returns a ticket.  `host_in` may be reused
+ * D2H copy without any host synchronisation (the D2H copy of a result of 4 MB or more is enqueued by the
+ * library's completion thread once the kernels are done), and returns a ticket.  `host_in` may be reused
  * as soon as the call returns; `host_out` must stay valid until strait_wait returns.
  * If `host_in` is the staging buffer of an instance (strait_model_staging), that instance is the one
  * used (E_BUSY if it is not idle) and the data are taken from there without a host copy; they must

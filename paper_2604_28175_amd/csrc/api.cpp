@@ -4,12 +4,18 @@
 // pinned buffer and an asynchronous host-to-device copy on a copy stream; the kernel sequence
 // on the compute stream that belongs to the batch's priority level (Section 3.1), made to wait
 // for the copy through an event; the device-to-host copy of the result into pinned memory.
-// Nothing synchronises with the host in between.  One completion thread per compute stream
-// waits for batches in issue order, stamps the host completion time (Section 5.1: latency ends
-// when the result is back in host memory), reads the event timings that Strait's predictor
-// would be fed (measured H2D time, measured kernel latency) and hands the result over.
+// Nothing synchronises with the host in between.  A small input whose compute stream has nothing
+// else to do goes in on the compute stream itself: there is nothing to overlap with, and the
+// hand-over between two streams takes about 20 us.  The copy kernels take the timestamps that
+// Strait's predictor is fed (measured H2D time, measured kernel latency) and set the flags that say
+// the result has arrived (elementwise.hip); the host polls those: the thread that waits for the
+// batch, or the compute stream's completion thread when nobody waits yet.  Whoever sees the flags
+// stamps the host completion time (Section 5.1: latency ends when the result is back in host
+// memory) and hands the result over, a large one chunk by chunk while the rest is on the link.
+#include <sched.h>
 #include <time.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -37,6 +43,21 @@ static int64_t now_ns() {
     return (int64_t)ts.tv_sec * 1000000000LL + ts.tv_nsec;
 }
 
+// Results of this size and more leave on a copy stream, beside the next batch's kernels (12.6 MB of a 64-sequence encoder batch:
+// 0.24 ms of host link); below, the hand-over costs more than it hides.  The thread that completes the batch enqueues the copy when
+// it sees the kernels done: a wait enqueued ahead would hold back whatever shares the copy stream's hardware queue (there are
+// four of those, so two copy streams may be one queue), the next batches' inputs for instance.
+static const size_t kOutOnCopyStream = 4u << 20;
+
+// Enqueues the result's way out behind the kernel sequence on `s`.
+static int enqueue_output(Model& m, Instance& in, Ticket* t, hipStream_t s) {
+    const size_t bytes = m.out_bytes(t->batch);
+    t->chunks = (unsigned)((bytes + OUT_CHUNK - 1) / OUT_CHUNK);
+    t->out_pending = bytes >= kOutOnCopyStream;
+    if (t->out_pending) return launch_stamp(in.ctl_dev, STAMP_K1, s, nullptr, nullptr, 0, t->seq);
+    return launch_copy_out(in.dev_out, in.pinned_out_dev, bytes, in.ctl_dev, in.counters + 1, t->seq, false, t->hp, s);
+}
+
 // A yielding low-priority batch (strait_ctx_set_lp_yield): its kernel sequence is enqueued by the stream's worker thread
 // in segments of a few layers, at most two segments in flight, and before each further segment the thread waits while a
 // high-priority batch is in flight on the GPU (at most kMaxYieldNs per segment, so that the wait always ends).  What
@@ -49,7 +70,7 @@ static int issue_in_segments(Context* ctx, StreamWorker* w, Ticket* t) {
     const int n = (int)m.ops.size();
     int seg;
     { std::lock_guard<std::mutex> lk(ctx->mu); seg = ctx->lp_yield_layers > 0 ? ctx->lp_yield_layers : n; }
-    if (hipStreamWaitEvent(s, in.ev_h2d1, 0) != hipSuccess || hipEventRecord(in.ev_k0, s) != hipSuccess) return STRAIT_E_HIP;
+    if (hipStreamWaitEvent(s, in.ev_h2d, 0) != hipSuccess || launch_stamp(in.ctl_dev, STAMP_K0, s)) return STRAIT_E_HIP;
     int k = 0;
     for (int first = 0; first < n; first += seg, ++k) {
         if (k >= 1) {
@@ -64,10 +85,91 @@ static int issue_in_segments(Context* ctx, StreamWorker* w, Ticket* t) {
         if (hipEventRecord(in.ev_seg[k & 1], s) != hipSuccess) return STRAIT_E_HIP;
         if (k >= 1 && hipEventSynchronize(in.ev_seg[(k - 1) & 1]) != hipSuccess) return STRAIT_E_HIP;   // one segment of look-ahead
     }
-    if (hipEventRecord(in.ev_k1, s) != hipSuccess) return STRAIT_E_HIP;
-    if (launch_copy_mapped(in.dev_out, in.pinned_out_dev, m.out_bytes(t->batch), t->hp, s)) return STRAIT_E_HIP;
-    if (hipEventRecord(in.ev_done, s) != hipSuccess) return STRAIT_E_HIP;
+    return enqueue_output(m, in, t, s);
+}
+
+// Polls until the GPU has written `seq`.  The wait ends: a kernel that is enqueued on `s` already writes it, and every few
+// milliseconds the stream is asked whether it has failed, or has run dry without.
+static int await_flag(const uint32_t* flag, unsigned seq, hipStream_t s) {
+    int64_t asked = 0;
+    for (unsigned n = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++n) {
+        __builtin_ia32_pause();
+        if (n & 255) continue;
+        sched_yield();
+        const int64_t now = now_ns();
+        if (asked == 0) asked = now;
+        if (now - asked < 5000000) continue;
+        asked = now;
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipErrorNotReady) { (void)hipGetLastError(); continue; }
+        if (e != hipSuccess || __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq) return STRAIT_E_HIP;
+    }
     return 0;
+}
+
+// Takes chunks of the result and copies each to the caller's buffer as it arrives, until none is left to take.  Two threads can be at it:
+// one copies large results out of the pinned buffer at about 31 GB/s, the link brings 52.
+static void copy_chunks(Ticket* t, Instance& in, hipStream_t s) {
+    const size_t bytes = t->model->out_bytes(t->batch);
+    const unsigned chunks = t->chunks;
+    for (unsigned c; (c = t->chunk_next.fetch_add(1, std::memory_order_relaxed)) < chunks;) {
+        const size_t at = (size_t)c * OUT_CHUNK;
+        const int rc = await_flag(&in.ctl->flag[c], t->seq, s);
+        if (c + 1 == chunks) t->t_last.store(now_ns(), std::memory_order_relaxed);
+        if (rc) t->copy_status.store(rc, std::memory_order_relaxed);
+        else memcpy((char*)t->host_out + at, (const char*)in.pinned_out + at, std::min<size_t>(OUT_CHUNK, bytes - at));
+        t->chunk_done.fetch_add(1, std::memory_order_release);
+    }
+}
+
+static hipStream_t output_stream(Context* ctx, const Ticket* t) { return t->out_pending ? ctx->copy[t->copy] : ctx->workers[t->worker]->stream; }
+
+// Sees the result into the caller's buffer.  *done: host time at which its last part was seen in host memory.
+static int await_result(Context* ctx, StreamWorker* w, Ticket* t, int64_t* done) {
+    Instance& in = t->model->inst[t->instance];
+    hipStream_t s = output_stream(ctx, t);
+    if (t->out_pending) {
+        if (await_flag(&in.ctl->k1_seq, t->seq, w->stream)) return STRAIT_E_HIP;
+        std::lock_guard<std::mutex> lk(ctx->copy_mu[t->copy]);
+        if (launch_copy_out(in.dev_out, in.pinned_out_dev, t->model->out_bytes(t->batch), in.ctl_dev, in.counters + 1, t->seq, true, t->hp, s)) return STRAIT_E_HIP;
+    }
+    if (t->chunks > 1) {
+        std::lock_guard<std::mutex> lk(ctx->mu);
+        t->chunks_coming.store(true, std::memory_order_release);
+        ctx->cv_done.notify_all();
+    }
+    copy_chunks(t, in, s);
+    while (t->chunk_done.load(std::memory_order_acquire) < t->chunks) __builtin_ia32_pause();   // the other thread's last memcpy
+    *done = t->t_last.load(std::memory_order_relaxed);
+    return t->copy_status.load(std::memory_order_relaxed);
+}
+
+// Sees a ticket that has left its stream's queue through to its end: result, record, completion.
+static void complete_ticket(Context* ctx, StreamWorker* w, Ticket* t) {
+    Instance& in = t->model->inst[t->instance];
+    int status = 0;
+    if (t->deferred) status = issue_in_segments(ctx, w, t);
+    int64_t done = 0;
+    if (!status) status = await_result(ctx, w, t, &done);
+    if (!done) done = now_ns();
+    w->outstanding.fetch_sub(1, std::memory_order_acq_rel);
+    if (t->prio == STRAIT_PRIO_HIGH) ctx->hp_in_flight.fetch_sub(1, std::memory_order_acq_rel);
+    if (!status) {
+        const volatile uint64_t* st = in.ctl->stamp;
+        auto ms = [&](uint64_t from, uint64_t to) { return (float)((double)(int64_t)(to - from) * ctx->ms_per_tick); };
+        const uint64_t k0 = t->k0_stamped ? st[STAMP_K0] : st[STAMP_H2D1];
+        t->rec.h2d_ms = ms(st[STAMP_H2D0], st[STAMP_H2D1]);
+        t->rec.kernel_ms = ms(k0, st[STAMP_K1]);
+        t->rec.d2h_ms = ms(st[STAMP_K1], st[STAMP_DONE]);
+        t->rec.total_ms = ms(st[STAMP_H2D0], st[STAMP_DONE]);
+    }
+    {
+        std::lock_guard<std::mutex> lk(ctx->mu);
+        t->rec.t_done_ns = done;
+        t->status = status;
+        t->done.store(true, std::memory_order_release);
+        ctx->cv_done.notify_all();       // under the lock: the waiter may delete the ticket as soon as it sees it done
+    }
 }
 
 static void worker_loop(Context* ctx, StreamWorker* w) {
@@ -81,28 +183,7 @@ static void worker_loop(Context* ctx, StreamWorker* w) {
             t = w->q.front();
             w->q.pop_front();
         }
-        Instance& in = t->model->inst[t->instance];
-        int status = 0;
-        if (t->deferred) status = issue_in_segments(ctx, w, t);
-        hipError_t e = status ? hipSuccess : hipEventSynchronize(in.ev_done);
-        const int64_t done = now_ns();
-        if (t->prio == STRAIT_PRIO_HIGH) ctx->hp_in_flight.fetch_sub(1, std::memory_order_acq_rel);
-        if (e != hipSuccess) status = STRAIT_E_HIP;
-        else if (!status) {
-            memcpy(t->host_out, in.pinned_out, t->model->out_bytes(t->batch));
-            float ms = 0.f;
-            if (hipEventElapsedTime(&ms, in.ev_h2d0, in.ev_h2d1) == hipSuccess) t->rec.h2d_ms = ms;
-            if (hipEventElapsedTime(&ms, in.ev_k0, in.ev_k1) == hipSuccess) t->rec.kernel_ms = ms;
-            if (hipEventElapsedTime(&ms, in.ev_k1, in.ev_done) == hipSuccess) t->rec.d2h_ms = ms;
-            if (hipEventElapsedTime(&ms, in.ev_h2d0, in.ev_done) == hipSuccess) t->rec.total_ms = ms;
-        }
-        {
-            std::lock_guard<std::mutex> lk(ctx->mu);
-            t->rec.t_done_ns = done;
-            t->status = status;
-            t->done = true;
-        }
-        ctx->cv_done.notify_all();
+        complete_ticket(ctx, w, t);
     }
 }
 
@@ -122,6 +203,13 @@ strait_status strait_ctx_create(const strait_ctx_desc* d, strait_ctx** out) {
     strait_ctx* c = new (std::nothrow) strait_ctx();
     if (!c) { set_error("out of host memory"); return STRAIT_E_NOMEM; }
     c->device = d->device;
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, d->device) != hipSuccess || khz <= 0) {
+        delete c;
+        set_error("ctx_create: the device's clock rate is not known");
+        return STRAIT_E_HIP;
+    }
+    c->ms_per_tick = 1.0 / khz;
     for (int i = 0; i < d->n_hp; ++i) c->hp.push_back((hipStream_t)d->hp_streams[i]);
     for (int i = 0; i < d->n_lp; ++i) c->lp.push_back((hipStream_t)d->lp_streams[i]);
     for (int i = 0; i < d->n_copy; ++i) c->copy.push_back((hipStream_t)d->copy_streams[i]);
@@ -238,7 +326,9 @@ static void free_instance(Instance& in) {
     if (in.splitk_ws) (void)hipFree(in.splitk_ws);
     for (void* b : in.bufs) if (b) (void)hipFree(b);
     if (in.side) { (void)hipStreamSynchronize(in.side); (void)hipStreamDestroy(in.side); }
-    hipEvent_t evs[9] = {in.ev_h2d0, in.ev_h2d1, in.ev_k0, in.ev_k1, in.ev_done, in.ev_fork, in.ev_join, in.ev_seg[0], in.ev_seg[1]};
+    if (in.ctl) (void)hipHostFree(in.ctl);
+    if (in.counters) (void)hipFree(in.counters);
+    hipEvent_t evs[5] = {in.ev_h2d, in.ev_fork, in.ev_join, in.ev_seg[0], in.ev_seg[1]};
     for (hipEvent_t e : evs) if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : in.layer_ev) if (e) (void)hipEventDestroy(e);
     for (auto& kv : in.graphs) (void)hipGraphExecDestroy(kv.second);
@@ -250,6 +340,8 @@ static void free_model(strait_model* m) {
     for (void* d : m->dev_allocs) (void)hipFree(d);
     delete m;
 }
+
+static const size_t COUNTER_BYTES = (2 + OUT_MAX_CHUNKS + 2) / 4 * 16;   // one for the input, one for the chunks, one per chunk; whole 16 bytes
 
 strait_status strait_model_load(strait_ctx* c, const strait_model_desc* d, strait_model** out) {
     if (!c || !d || !out || !d->weights) { set_error("model_load: null argument"); return STRAIT_E_INVALID; }
@@ -279,9 +371,10 @@ strait_status strait_model_load(strait_ctx* c, const strait_model_desc* d, strai
             ok = hipMalloc(&b, bytes) == hipSuccess;
             in.bufs.push_back(b);
         }
-        ok = ok && hipEventCreate(&in.ev_h2d0) == hipSuccess && hipEventCreate(&in.ev_h2d1) == hipSuccess &&
-             hipEventCreate(&in.ev_k0) == hipSuccess && hipEventCreate(&in.ev_k1) == hipSuccess &&
-             hipEventCreate(&in.ev_done) == hipSuccess &&
+        ok = ok && hipHostMalloc((void**)&in.ctl, sizeof(HostControl), hipHostMallocDefault) == hipSuccess &&
+             hipHostGetDevicePointer((void**)&in.ctl_dev, in.ctl, 0) == hipSuccess &&
+             hipMalloc((void**)&in.counters, COUNTER_BYTES) == hipSuccess &&
+             hipEventCreateWithFlags(&in.ev_h2d, hipEventDisableTiming) == hipSuccess &&
              hipEventCreateWithFlags(&in.ev_seg[0], hipEventDisableTiming) == hipSuccess &&
              hipEventCreateWithFlags(&in.ev_seg[1], hipEventDisableTiming) == hipSuccess &&
              hipStreamCreateWithFlags(&in.side, hipStreamNonBlocking) == hipSuccess &&      // default priority
@@ -299,7 +392,8 @@ strait_status strait_model_load(strait_ctx* c, const strait_model_desc* d, strai
         }
         // The runtime sets a stream's hardware queue up at the first launch on it, which takes milliseconds:
         // do that here and not under the first batch that happens to use this instance's side stream.
-        if (launch_fill_zero(in.splitk_ws, 256, in.side) != 0) { free_model(m); return STRAIT_E_HIP; }
+        memset(in.ctl, 0, sizeof(HostControl));
+        if (launch_fill_zero(in.counters, COUNTER_BYTES, in.side) != 0) { free_model(m); return STRAIT_E_HIP; }
         // valid lengths default to the full sequence
         if (m->arch == STRAIT_ARCH_ENCODER || m->arch == STRAIT_ARCH_VIT) {
             std::vector<int32_t> full(d->max_batch, m->seq);
@@ -382,33 +476,45 @@ static size_t compute_index(const Context* c, int prio, unsigned n) {
     return prio == STRAIT_PRIO_HIGH ? n % c->hp.size() : c->hp.size() + n % c->lp.size();
 }
 
-// Stage the input in the instance's pinned buffer (no lock: this is the slow part and instances are
-// independent), then enqueue event / copy / event on copy stream `ci` as one uninterrupted group.
-static int enqueue_h2d(strait_model* m, Instance& in, int batch, const void* host_in, const int32_t* valid_len, size_t ci) {
-    Context* c = m->ctx;
-    hipStream_t cs = c->copy[ci];
-    const size_t inb = m->in_bytes(batch);
-    if (host_in != in.pinned_in) memcpy(in.pinned_in, host_in, inb);
-    int32_t* pv = nullptr;
-    if (m->arch == STRAIT_ARCH_ENCODER) {
-        const size_t off = (m->in_bytes(m->max_batch) + 255) / 256 * 256;
-        pv = (int32_t*)((char*)in.pinned_in + off);
+// Whether an input goes in by the copy kernel: inputs of serving-sized batches do (an asynchronous copy call of such a size now
+// and then blocks its caller for milliseconds).
+static bool input_by_kernel(const strait_model* m, int batch) {
+    std::lock_guard<std::mutex> lk(m->ctx->mu);
+    return m->in_bytes(batch) <= m->ctx->h2d_kernel_limit && (m->in_bytes(batch) & 3) == 0;
+}
+// The input (and the valid lengths) into the instance's pinned buffer and on to the device through `s`; mu: the stream's mutex, or null if
+// the caller holds it.  An input that is not in the pinned buffer yet goes piece by piece, so that the host's copy of one piece
+// and the link's of the one before go on together; the link (52 GB/s) is the slower of the two, so each piece can be half as
+// large again as the one before it.  A batch of 1.5 MB: 374 us from submission to result in one piece, 355 in three.
+static int send_input(const strait_model* m, Instance& in, int batch, const void* host_in, const int32_t* valid_len, bool by_kernel, hipStream_t s,
+                      std::mutex* mu) {
+    const size_t inb = m->in_bytes(batch), off = (m->in_bytes(m->max_batch) + 255) / 256 * 256;
+    const size_t lens = m->arch == STRAIT_ARCH_ENCODER ? (size_t)batch * 4 : 0;
+    if (lens) {
+        int32_t* pv = (int32_t*)((char*)in.pinned_in + off);
         for (int i = 0; i < batch; ++i) pv[i] = valid_len[i] < 0 ? 0 : (valid_len[i] > m->seq ? m->seq : valid_len[i]);
     }
-    size_t kernel_limit;
-    { std::lock_guard<std::mutex> ck(c->mu); kernel_limit = c->h2d_kernel_limit; }
-    std::lock_guard<std::mutex> lk(c->copy_mu[ci]);
-    HIP_TRY(hipEventRecord(in.ev_h2d0, cs));
-    if (inb <= kernel_limit && (inb & 3) == 0) {
-        // inputs of serving-sized batches go in by a kernel that reads the pinned buffer over the host link: an
-        // asynchronous copy call of this size now and then blocks its caller for milliseconds
-        if (launch_copy_mapped(in.pinned_in_dev, in.dev_in, inb, 0, cs)) return STRAIT_E_HIP;
-        if (pv && launch_copy_mapped((const char*)in.pinned_in_dev + ((const char*)pv - (const char*)in.pinned_in), in.dev_valid, (size_t)batch * 4, 0, cs)) return STRAIT_E_HIP;
-    } else {
-        HIP_TRY(hipMemcpyAsync(in.dev_in, in.pinned_in, inb, hipMemcpyHostToDevice, cs));
-        if (pv) HIP_TRY(hipMemcpyAsync(in.dev_valid, pv, (size_t)batch * 4, hipMemcpyHostToDevice, cs));
+    const void* lsrc = lens ? (const char*)in.pinned_in_dev + off : nullptr;
+    void* ldst = lens ? in.dev_valid : nullptr;
+    const bool staged = host_in == in.pinned_in;
+    size_t piece = staged ? inb : by_kernel ? 512u << 10 : 4u << 20;
+    for (size_t at = 0; at < inb;) {
+        const size_t n = inb - at <= piece + piece / 2 ? inb - at : piece;
+        const bool first = at == 0, last = at + n == inb;
+        if (!staged) memcpy((char*)in.pinned_in + at, (const char*)host_in + at, n);
+        std::unique_lock<std::mutex> lk;
+        if (mu) lk = std::unique_lock<std::mutex>(*mu);
+        if (by_kernel) {
+            if (launch_copy_in((const char*)in.pinned_in_dev + at, (char*)in.dev_in + at, n, lsrc, ldst, last ? lens : 0, in.ctl_dev, in.counters, first, last, s))
+                return STRAIT_E_HIP;
+        } else {
+            if (first && launch_stamp(in.ctl_dev, STAMP_H2D0, s)) return STRAIT_E_HIP;
+            HIP_TRY(hipMemcpyAsync((char*)in.dev_in + at, (const char*)in.pinned_in + at, n, hipMemcpyHostToDevice, s));
+            if (last && launch_stamp(in.ctl_dev, STAMP_H2D1, s, lsrc, ldst, lens)) return STRAIT_E_HIP;
+        }
+        at += n;
+        piece += piece / 2 & ~(size_t)15;
     }
-    HIP_TRY(hipEventRecord(in.ev_h2d1, cs));
     return 0;
 }
 
@@ -449,37 +555,63 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
     }
     const size_t widx = compute_index(c, prio, si);
     const size_t cidx = ci % c->copy.size();
-    hipStream_t s = c->workers[widx]->stream;
+    StreamWorker* w = c->workers[widx];
+    hipStream_t s = w->stream;
     hipStream_t cs = c->copy[cidx];
     rc = hipSetDevice(c->device) == hipSuccess ? 0 : STRAIT_E_HIP;
-    if (!rc) rc = enqueue_h2d(m, in, batch, host_in, valid_len, cidx);
-    t->model = m; t->instance = idx; t->prio = prio; t->batch = batch; t->host_out = host_out;
+    const bool by_kernel = input_by_kernel(m, batch);
+    t->model = m; t->instance = idx; t->prio = prio; t->batch = batch; t->host_out = host_out; t->worker = widx;
+    t->copy = cidx;
+    if (++in.seq == 0) ++in.seq;         // 0: no number
+    t->seq = in.seq;
     t->rec.model_id = m->id; t->rec.priority = prio; t->rec.batch = batch; t->rec.instance = idx;
     t->rec.t_enqueue_ns = t_enq;
     bool yielding;
     { std::lock_guard<std::mutex> lk(c->mu); yielding = prio == STRAIT_PRIO_LOW && c->lp_yield_layers > 0; }
     t->hp = hp_flag(c, prio);
     if (prio == STRAIT_PRIO_HIGH) c->hp_in_flight.fetch_add(1, std::memory_order_acq_rel);
+    auto h2d_on_copy_stream = [&]() {
+        int r = send_input(m, in, batch, host_in, valid_len, by_kernel, cs, &c->copy_mu[cidx]);
+        std::lock_guard<std::mutex> lk(c->copy_mu[cidx]);
+        if (!r) r = hipEventRecord(in.ev_h2d, cs) == hipSuccess ? 0 : STRAIT_E_HIP;
+        return r;
+    };
     if (yielding) {
         // the stream's worker thread enqueues the kernels, segment by segment (issue_in_segments)
         t->deferred = true;
+        t->k0_stamped = true;
+        if (!rc) rc = h2d_on_copy_stream();
         if (!rc) {
             t->rec.t_issued_ns = now_ns();
             std::lock_guard<std::mutex> lk(c->mu);
-            c->workers[widx]->q.push_back(t);
+            w->outstanding.fetch_add(1, std::memory_order_acq_rel);
+            w->q.push_back(t);
         }
     } else {
-        std::lock_guard<std::mutex> slk(c->compute_mu[widx]);
-        if (!rc) rc = hipStreamWaitEvent(s, in.ev_h2d1, 0) == hipSuccess ? 0 : STRAIT_E_HIP;
-        if (!rc) rc = hipEventRecord(in.ev_k0, s) == hipSuccess ? 0 : STRAIT_E_HIP;
-        if (!rc) rc = run_batch(*m, in, batch, s, hp_flag(c, prio));
-        if (!rc) rc = hipEventRecord(in.ev_k1, s) == hipSuccess ? 0 : STRAIT_E_HIP;
-        if (!rc) rc = launch_copy_mapped(in.dev_out, in.pinned_out_dev, m->out_bytes(batch), hp_flag(c, prio), s);
-        if (!rc) rc = hipEventRecord(in.ev_done, s) == hipSuccess ? 0 : STRAIT_E_HIP;
+        // A small input goes in on an idle compute stream itself; otherwise it travels beside the batches ahead of it (enqueued
+        // before this stream's mutex is taken, so that a batch that is being issued does not hold its transfer up).
+        std::unique_lock<std::mutex> slk(c->compute_mu[widx], std::defer_lock);
+        bool in_line = false;
+        if (by_kernel && w->outstanding.load(std::memory_order_acquire) == 0) {
+            slk.lock();
+            in_line = w->outstanding.load(std::memory_order_acquire) == 0;
+        }
+        if (in_line) {
+            if (!rc) rc = send_input(m, in, batch, host_in, valid_len, true, s, nullptr);
+        } else {
+            if (!rc) rc = h2d_on_copy_stream();
+            if (!slk.owns_lock()) slk.lock();
+            if (!rc) rc = hipStreamWaitEvent(s, in.ev_h2d, 0) == hipSuccess ? 0 : STRAIT_E_HIP;
+            if (!rc) rc = launch_stamp(in.ctl_dev, STAMP_K0, s) ? STRAIT_E_HIP : 0;
+            t->k0_stamped = true;
+        }
+        if (!rc) rc = run_batch(*m, in, batch, s, t->hp);
+        if (!rc) rc = enqueue_output(*m, in, t, s);
         if (!rc) {
             t->rec.t_issued_ns = now_ns();
             std::lock_guard<std::mutex> lk(c->mu);          // tickets join the worker's queue in stream order
-            c->workers[widx]->q.push_back(t);
+            w->outstanding.fetch_add(1, std::memory_order_acq_rel);
+            w->q.push_back(t);
         }
     }
     if (rc) {
@@ -498,8 +630,7 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
 
 strait_status strait_poll(strait_ticket t, int32_t* done) {
     if (!t || !done) { set_error("poll: null argument"); return STRAIT_E_INVALID; }
-    std::lock_guard<std::mutex> lk(t->model->ctx->mu);
-    *done = t->done ? 1 : 0;
+    *done = t->done.load(std::memory_order_acquire) ? 1 : 0;
     return STRAIT_OK;
 }
 
@@ -507,9 +638,31 @@ strait_status strait_wait(strait_ticket t, strait_record* rec) {
     if (!t) { set_error("wait: null ticket"); return STRAIT_E_INVALID; }
     Model* m = t->model;
     Context* c = m->ctx;
+    StreamWorker* w = c->workers[t->worker];
+    // The next result of its stream is fetched by the thread that waits for it (no hand-over between threads); while another
+    // thread is at it, look on for a while before going to sleep (a wake-up takes as long as some batches).
+    bool mine = false;
     {
-        std::unique_lock<std::mutex> lk(c->mu);
-        c->cv_done.wait(lk, [&] { return t->done; });
+        std::lock_guard<std::mutex> lk(c->mu);
+        if (!w->q.empty() && w->q.front() == t && !t->deferred) { w->q.pop_front(); mine = true; }
+    }
+    if (mine) {
+        (void)hipSetDevice(c->device);
+        complete_ticket(c, w, t);
+    } else {
+        auto can_help = [&] { return t->chunks_coming.load(std::memory_order_acquire) && t->chunk_next.load(std::memory_order_relaxed) < t->chunks; };
+        bool done = false;
+        while (!done) {
+            const int64_t t0 = now_ns();
+            while (!t->done.load(std::memory_order_acquire) && !can_help() && now_ns() - t0 < 500000)
+                for (int i = 0; i < 32; ++i) __builtin_ia32_pause();
+            {
+                std::unique_lock<std::mutex> lk(c->mu);
+                c->cv_done.wait(lk, [&] { return t->done.load(std::memory_order_acquire) || can_help(); });
+                done = t->done.load(std::memory_order_acquire);
+            }
+            if (!done) copy_chunks(t, m->inst[t->instance], output_stream(c, t));
+        }
     }
     if (rec) *rec = t->rec;
     const int status = t->status;
@@ -531,10 +684,15 @@ strait_status strait_copy_in(strait_model* m, int32_t instance, strait_priority 
     if (m->arch == STRAIT_ARCH_ENCODER && !valid_len) { set_error("copy_in: the encoder needs valid_len"); return STRAIT_E_INVALID; }
     Context* c = m->ctx;
     HIP_TRY(hipSetDevice(c->device));
-    rc = enqueue_h2d(m, m->inst[instance], batch, host_in, valid_len, (size_t)instance % c->copy.size());
-    if (rc) return rc;
+    Instance& in = m->inst[instance];
+    const size_t ci = (size_t)instance % c->copy.size();
+    if ((rc = send_input(m, in, batch, host_in, valid_len, input_by_kernel(m, batch), c->copy[ci], &c->copy_mu[ci]))) return rc;
+    {
+        std::lock_guard<std::mutex> lk(c->copy_mu[ci]);
+        HIP_TRY(hipEventRecord(in.ev_h2d, c->copy[ci]));
+    }
     std::lock_guard<std::mutex> slk(c->compute_mu[compute_index(c, prio, (unsigned)instance)]);
-    HIP_TRY(hipStreamWaitEvent(compute_stream(c, prio, instance), m->inst[instance].ev_h2d1, 0));
+    HIP_TRY(hipStreamWaitEvent(compute_stream(c, prio, instance), in.ev_h2d, 0));
     return STRAIT_OK;
 }
 

@@ -45,33 +45,130 @@ int launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Small transfers between pinned host memory that the GPU can address and device memory, done by a kernel:
-// results on their way out, and inputs of up to a few megabytes on their way in.  (A hipMemcpyAsync of such a
-// size, in either direction, now and then blocks the submitting thread for milliseconds when other streams are
-// busy; a kernel launch does not.)  Both pointers 16-byte aligned, bytes a multiple of 4.  Four independent
-// 16-byte loads per thread and round keep enough requests in flight to fill the host link on the way in.
-__global__ void __launch_bounds__(256) copy_mapped_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, size_t n4, int hp) {
-    if (hp) __builtin_amdgcn_s_setprio(3);
+// Transfers between pinned host memory that the GPU can address and device memory, done by kernels: results on their way out,
+// and inputs of up to a few megabytes on their way in.  (A hipMemcpyAsync of such a size, in either direction, now and then
+// blocks the submitting thread for milliseconds when other streams are busy; a kernel launch does not.)  They also take the
+// timestamps of a batch's record (the device's constant-rate clock, written to the instance's pinned control block) and
+// the outgoing one tells the host that the result is there.  An event record costs about 3.6 us between two dependent launches and
+// a wait on one 12 us from the last kernel to the waiting thread; the stamps cost nothing and the flag 7 us.
+__device__ __forceinline__ void copy_range(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, size_t n4, unsigned block, unsigned blocks) {
+    // four independent 16-byte loads per thread and round keep enough requests in flight to fill the host link on the way in
     const size_t n16 = n4 >> 2;
-    const size_t step = (size_t)gridDim.x * 256;
-    size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t step = (size_t)blocks * 256;
+    size_t i = (size_t)block * 256 + threadIdx.x;
     for (; i + 3 * step < n16; i += 4 * step) {
         const uint4 a = ((const uint4*)src)[i], b = ((const uint4*)src)[i + step], c = ((const uint4*)src)[i + 2 * step], d = ((const uint4*)src)[i + 3 * step];
         ((uint4*)dst)[i] = a; ((uint4*)dst)[i + step] = b; ((uint4*)dst)[i + 2 * step] = c; ((uint4*)dst)[i + 3 * step] = d;
     }
     for (; i < n16; i += step) ((uint4*)dst)[i] = ((const uint4*)src)[i];
     const size_t tail = n16 << 2;
-    if (blockIdx.x == 0 && tail + threadIdx.x < n4) dst[tail + threadIdx.x] = src[tail + threadIdx.x];
+    if (block == 0 && tail + threadIdx.x < n4) dst[tail + threadIdx.x] = src[tail + threadIdx.x];
 }
-int launch_copy_mapped(const void* src, void* dst, size_t bytes, int hp, hipStream_t stream) {
-    if (bytes == 0) return 0;
-    if (!src || !dst || (reinterpret_cast<uintptr_t>(src) & 15) || (reinterpret_cast<uintptr_t>(dst) & 15) || (bytes & 3)) {
-        set_error("mapped copy: 16-byte aligned buffers and a multiple of 4 bytes required"); return -1;
+
+// A piece of an input (and, for token models, the valid lengths behind it): dst <- src, dst2 <- src2.  The first piece stamps STAMP_H2D0,
+// the last STAMP_H2D1.
+__global__ void __launch_bounds__(256) copy_in_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, size_t n4,
+                                                      const uint32_t* __restrict__ src2, uint32_t* __restrict__ dst2, unsigned n4b,
+                                                      HostControl* ctl, unsigned* counters, int first, int last) {
+    if (first && blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(&ctl->stamp[STAMP_H2D0], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    copy_range(src, dst, n4, blockIdx.x, gridDim.x);
+    if (blockIdx.x == 0)
+        for (unsigned i = threadIdx.x; i < n4b; i += 256) dst2[i] = src2[i];
+    if (!last) return;
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(&counters[0], 1u) == gridDim.x - 1) {      // the last workgroup to arrive
+        counters[0] = 0;
+        __hip_atomic_store(&ctl->stamp[STAMP_H2D1], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+int launch_copy_in(const void* src, void* dst, size_t bytes, const void* src2, void* dst2, size_t bytes2, HostControl* ctl, unsigned* counters,
+                   bool first, bool last, hipStream_t stream) {
+    if (!src || !dst || !ctl || !counters || bytes == 0 || (bytes & 3) || (bytes2 & 3) || bytes2 > (1u << 20) || (bytes2 && (!src2 || !dst2)) ||
+        ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15)) {
+        set_error("copy in: 16-byte aligned buffers and multiples of 4 bytes required"); return -1;
     }
     const size_t n4 = bytes / 4, n16 = n4 / 4;
     const unsigned blocks = (unsigned)std::min<size_t>(256, std::max<size_t>(1, (n16 + 255) / 256));
-    hipLaunchKernelGGL(copy_mapped_kernel, dim3(blocks), dim3(256), 0, stream, (const uint32_t*)src, (uint32_t*)dst, n4, hp);
-    STRAIT_CHECK_LAUNCH("mapped copy");
+    hipLaunchKernelGGL(copy_in_kernel, dim3(blocks), dim3(256), 0, stream, (const uint32_t*)src, (uint32_t*)dst, n4, (const uint32_t*)src2,
+                       (uint32_t*)dst2, (unsigned)(bytes2 / 4), ctl, counters, first ? 1 : 0, last ? 1 : 0);
+    STRAIT_CHECK_LAUNCH("copy in");
+    return 0;
+}
+
+// One timestamp between launches that do not take it themselves.  With src: also dst <- src (n4 words, before the stamp: the valid
+// lengths behind an input that a copy engine brings).  With a sequence number: afterwards ctl->k1_seq = seq, which tells the
+// host that the kernels before this one are done.
+__global__ void __launch_bounds__(256) stamp_kernel(HostControl* ctl, int which, const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, unsigned n4,
+                                                    unsigned seq) {
+    for (unsigned i = threadIdx.x; i < n4; i += 256) dst[i] = src[i];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    __hip_atomic_store(&ctl->stamp[which], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (seq) __hip_atomic_store(&ctl->k1_seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* src, void* dst, size_t bytes, unsigned seq) {
+    if (!ctl || which < 0 || which >= 8 || (bytes & 3) || bytes > (1u << 20) || (bytes && (!src || !dst))) { set_error("stamp: bad argument"); return -1; }
+    hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(bytes ? 256 : 64), 0, stream, ctl, which, (const uint32_t*)src, (uint32_t*)dst, (unsigned)(bytes / 4), seq);
+    STRAIT_CHECK_LAUNCH("stamp");
+    return 0;
+}
+
+// Result, in chunks of OUT_CHUNK bytes, each in OUT_PARTS parts of which a workgroup takes every gridDim.x-th: when the last part of
+// chunk c is written, flag[c] becomes `seq`, so that the host can move a chunk on while the next ones are on the link.  Stamps
+// STAMP_K1 (first workgroup starts; unless `k1_taken`) and STAMP_DONE.  counters[1 + c] count a chunk's parts, counters[0] the
+// chunks; both are left at zero.
+// Few workgroups: 16 of them keep the link busy (12.6 MB in 0.24 ms), and other batches run beside this.  The stores go through the
+// caches (sc0 sc1) and each workgroup waits for its own to be acknowledged before it counts a part: a system-scope fence would
+// instead write back the L2s, which hold other batches' data.
+__device__ __forceinline__ void store_through(void* p, uint4 v) {
+    typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+    const uint4v r = {v.x, v.y, v.z, v.w};
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(r) : "memory");
+}
+__global__ void __launch_bounds__(256) copy_out_kernel(const char* __restrict__ src, char* __restrict__ dst, size_t bytes, unsigned parts, unsigned chunks,
+                                                       HostControl* ctl, unsigned* counters, unsigned seq, int k1_taken, int hp) {
+    if (hp) __builtin_amdgcn_s_setprio(3);
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !k1_taken)
+        __hip_atomic_store(&ctl->stamp[STAMP_K1], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    for (unsigned part = blockIdx.x; part < parts; part += gridDim.x) {
+        const size_t at = (size_t)part * (OUT_CHUNK / OUT_PARTS), n = bytes - at < OUT_CHUNK / OUT_PARTS ? bytes - at : OUT_CHUNK / OUT_PARTS;
+        const size_t n16 = n >> 4;
+        const uint4* s16 = (const uint4*)(src + at);
+        uint4* d16 = (uint4*)(dst + at);
+        size_t i = threadIdx.x;
+        for (; i + 768 < n16; i += 1024) {
+            const uint4 a = s16[i], b = s16[i + 256], c = s16[i + 512], d = s16[i + 768];
+            store_through(d16 + i, a); store_through(d16 + i + 256, b); store_through(d16 + i + 512, c); store_through(d16 + i + 768, d);
+        }
+        for (; i < n16; i += 256) store_through(d16 + i, s16[i]);
+        const size_t tail = (n16 << 2) + threadIdx.x;
+        if (tail < n >> 2) __hip_atomic_store((uint32_t*)(dst + at) + tail, ((const uint32_t*)(src + at))[tail], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const unsigned c = part / OUT_PARTS;
+        const unsigned mine = parts - c * OUT_PARTS < OUT_PARTS ? parts - c * OUT_PARTS : OUT_PARTS;     // parts of this chunk
+        if (threadIdx.x == 0 && atomicAdd(&counters[1 + c], 1u) == mine - 1) {
+            counters[1 + c] = 0;
+            if (atomicAdd(&counters[0], 1u) == chunks - 1) {
+                counters[0] = 0;
+                __hip_atomic_store(&ctl->stamp[STAMP_DONE], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            __hip_atomic_store(&ctl->flag[c], seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+}
+int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, hipStream_t stream) {
+    if (!src || !dst || !ctl || !counters || bytes == 0 || (bytes & 3) || bytes > (size_t)OUT_CHUNK * OUT_MAX_CHUNKS ||
+        ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15)) {
+        set_error("copy out: 16-byte aligned buffers, a multiple of 4 bytes and at most %zu bytes required", (size_t)OUT_CHUNK * OUT_MAX_CHUNKS); return -1;
+    }
+    const unsigned chunks = (unsigned)((bytes + OUT_CHUNK - 1) / OUT_CHUNK);
+    const unsigned parts = (unsigned)((bytes + OUT_CHUNK / OUT_PARTS - 1) / (OUT_CHUNK / OUT_PARTS));
+    const unsigned blocks = std::min(parts, 16u);
+    hipLaunchKernelGGL(copy_out_kernel, dim3(blocks), dim3(256), 0, stream, (const char*)src, (char*)dst, bytes, parts, chunks, ctl, counters, seq,
+                       k1_taken ? 1 : 0, hp);
+    STRAIT_CHECK_LAUNCH("copy out");
     return 0;
 }
 

@@ -116,8 +116,19 @@ int launch_argmax_f16(const half_t* x, int rows, int n, long long row_stride, in
                       hipStream_t stream);
 // Weight preparation on the device (load time): BatchNorm fold + OIHW -> kernel layout.
 int launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
-// Copies `bytes` (multiple of 4) from device memory to host memory the GPU can address, with a kernel.
-int launch_copy_mapped(const void* src, void* dst, size_t bytes, int hp, hipStream_t stream);
+// ---- transfers by kernel, with the timestamps and the completion flags of a batch (elementwise.hip)
+enum { STAMP_H2D0 = 0, STAMP_H2D1 = 1, STAMP_K0 = 2, STAMP_K1 = 3, STAMP_DONE = 4, STAMP_COUNT = 8 };
+constexpr unsigned OUT_CHUNK = 256u << 10, OUT_PARTS = 8, OUT_MAX_CHUNKS = 4096;
+struct HostControl {                     // in pinned host memory, written by the GPU
+    uint64_t stamp[STAMP_COUNT];         // device clock (hipDeviceAttributeWallClockRate)
+    uint32_t k1_seq, pad[7];             // sequence number of the last batch whose kernels are done (results that leave on a copy stream)
+    uint32_t flag[OUT_MAX_CHUNKS];       // ... of the last batch whose chunk of the result has arrived
+};
+// counters: one unsigned (copy in), 1 + OUT_MAX_CHUNKS of them (copy out), in device memory, zero before the first launch and after each
+int launch_copy_in(const void* src, void* dst, size_t bytes, const void* src2, void* dst2, size_t bytes2, HostControl* ctl, unsigned* counters,
+                   bool first, bool last, hipStream_t stream);
+int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* src = nullptr, void* dst = nullptr, size_t bytes = 0, unsigned seq = 0);
+int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, hipStream_t stream);
 
 void set_error(const char* fmt, ...);
 

@@ -81,7 +81,11 @@ struct Instance {
     int32_t* dev_valid = nullptr;
     float* splitk_ws = nullptr;        // fp32 slabs of split-K convolutions (small batches)
     std::vector<void*> bufs;
-    hipEvent_t ev_h2d0 = nullptr, ev_h2d1 = nullptr, ev_k0 = nullptr, ev_k1 = nullptr, ev_done = nullptr;
+    HostControl* ctl = nullptr;        // pinned: timestamps and completion flags of the batch in flight, written by the GPU
+    HostControl* ctl_dev = nullptr;    // the same memory as the GPU addresses it
+    unsigned* counters = nullptr;      // device: [0] copy in, [1 ..] copy out (see kernels.hpp)
+    unsigned seq = 0;                  // sequence number of the batch in flight: what its completion flags will read
+    hipEvent_t ev_h2d = nullptr;       // input on the device, where a copy stream brings it
     hipEvent_t ev_seg[2] = {nullptr, nullptr};   // ends of the two plan segments a yielding low-priority batch has in flight
     hipStream_t side = nullptr;        // default priority, non-blocking: carries branches that do not depend on each other
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -124,9 +128,19 @@ struct Ticket {
     int instance = 0, prio = 0, batch = 0;
     void* host_out = nullptr;
     strait_record rec{};
-    bool done = false;
+    std::atomic<bool> done{false};
     int status = 0;
     bool deferred = false;             // kernels not enqueued yet: the stream's worker issues them segment by segment
+    bool k0_stamped = false;           // kernel start has a stamp of its own (else it is the end of the input copy)
+    unsigned seq = 0;
+    size_t worker = 0;                 // index of its compute stream in Context::workers
+    size_t copy = 0;                   // index of its copy stream in Context::copy
+    unsigned chunks = 0;               // of its result (OUT_CHUNK bytes each)
+    std::atomic<unsigned> chunk_next{0}, chunk_done{0};   // handed out to a copying thread / copied to the caller's buffer
+    std::atomic<bool> chunks_coming{false};               // the copy off the device is enqueued: another thread may lend a hand
+    std::atomic<int64_t> t_last{0};    // host time at which the last chunk was seen to be there
+    std::atomic<int> copy_status{0};
+    bool out_pending = false;          // large result: its copy is enqueued when the kernels are seen done
     int hp = 0;                        // wave-priority flag its kernels are launched with
 };
 
@@ -134,6 +148,7 @@ struct StreamWorker {
     hipStream_t stream = nullptr;
     std::thread th;
     std::deque<Ticket*> q;
+    std::atomic<int> outstanding{0};   // batches submitted to this stream whose result has not arrived
 };
 
 struct Context {
@@ -147,6 +162,7 @@ struct Context {
     std::mutex mu;                          // guards worker queues, ticket completion, counters
     std::condition_variable cv_work, cv_done;
     bool stop = false;
+    double ms_per_tick = 1e-5;              // of the device clock the stamps are taken from
     bool wave_priority = true;
     bool use_graphs = false;
     long long proj_min_pixels = 1;          // the same for pairs that absorb a projection shortcut: three launches become one

@@ -346,6 +346,32 @@ def test_input_copy_by_kernel_and_by_copy_engine_give_the_same_result(ctx):
         m.free()
 
 
+@pytest.mark.parametrize("batch", [1, 2, 6, 33])
+def test_transfers_in_pieces_bring_every_byte(ctx, batch):
+    """128 KB in and 128 KB + 4 B out per sequence: results of one part, of whole chunks and a few bytes, and one that leaves on a copy
+    stream; inputs of one and of several pieces; two batches in flight, so one input goes in on the compute stream and one
+    beside it.  Same kernels as the copy-call sub-steps: identical bit for bit."""
+    S = ctx.S
+    md = synth.encoder(3, layers=1, hidden=256, heads=4, ffn=256, seq=256)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=2)
+    try:
+        xs = [synth.token_batch(md, batch, seed, min_len=32) for seed in (1, 2)]
+        refs = []
+        for x, vl in xs:
+            m.copy_in(0, S.PRIO_LOW, x, vl)
+            m.run(0, S.PRIO_LOW, batch)
+            refs.append(m.copy_out(0, S.PRIO_LOW, batch))
+        for _ in range(3):
+            outs = [m.new_output(batch) for _ in xs]
+            tickets = [m.submit(S.PRIO_LOW, x, vl, o) for (x, vl), o in zip(xs, outs)]
+            for t in tickets:
+                rec = m.wait(t)
+                assert rec.h2d_ms > 0 and rec.kernel_ms > 0 and rec.d2h_ms > 0
+            assert all(np.array_equal(o, r) for o, r in zip(outs, refs))
+    finally:
+        m.free()
+
+
 def test_submit_from_the_staging_buffer_makes_no_host_copy_and_gives_the_same_result(ctx):
     S = ctx.S
     md = synth.resnet50(4, hw=64)
