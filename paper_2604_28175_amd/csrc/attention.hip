@@ -4,21 +4,26 @@
 //
 //   out[b, i, h*64 + :] = softmax_j( q_i . k_j / sqrt(64) ,  j < valid_len[b] ) @ V
 //
-// One workgroup per (sequence, head); wavefront w owns query rows 32w .. 32w+31.  Sequences of up to 128 keys
-// run 4 wavefronts and keep 4 key blocks of scores in registers, up to 256 keys 8 wavefronts and 8 blocks (a
-// Vision Transformer's 197 tokens), so K and V are staged once per head whatever the length; S need not be a
-// multiple of anything: query rows at or beyond S are neither read nor written, key rows at or beyond
-// valid_len never leave zero-filled LDS.
-//   - K is staged in LDS as [key][d] and V transposed as [d][key], rows at or beyond
-//     valid_len zero-filled, so masked keys can never inject non-finite values;
-//   - scores^T = K Q^T with v_mfma_f32_32x32x16_f16 (K rows are the "A" operand), which leaves
-//     each lane holding 16 keys x up to 4 key blocks of ONE query: the row maximum and sum need
-//     a single exchange with lane ^ 32;
-//   - the probabilities, rounded to fp16, are already laid out as the "B" operand of
-//     out^T = V^T P^T provided V^T's reduction index is enumerated in the same (permuted) key
-//     order, which the two 8-byte LDS reads per operand do;
+// A workgroup of 4 wavefronts takes all query rows of one (sequence, head), or one of two halves of them, in blocks of 32
+// rows that the wavefronts take in turn; S need not be a multiple of anything: query rows at or beyond S are neither
+// read nor written, and key rows at or beyond valid_len arrive in LDS as zeros, so that masked keys can never inject
+// non-finite values.
+//   - K and V go to LDS as they lie in memory, 128 bytes a row, without passing through registers (buffer_load_dwordx4 ... lds;
+//     the buffer ends at row valid_len, and what lies beyond reads as zero).  The 16-byte chunk c of row r sits at
+//     c ^ (r & 7) for K, whose operand is 8 rows at one chunk, and at c ^ (bits of r & 7 reversed) for V, whose operand is 4
+//     rows at 4 chunks: neither read has a bank conflict;
+//   - scores^T = K Q^T with v_mfma_f32_32x32x16_f16 (K rows are the "A" operand), which leaves each lane holding 16 of a
+//     block's 32 keys for ONE query: the row maximum and sum need a single exchange with lane ^ 32;
+//   - 64 keys at a time with a running maximum: 121 registers whatever the length.  Keeping all scores of 197 keys took 176
+//     and left one workgroup of 8 wavefronts per compute unit, which then loaded, computed and stored in turn;
+//   - the probabilities, rounded to fp16, are already laid out as the "B" operand of out^T = V^T P^T provided V^T's reduction
+//     index is enumerated in the same (permuted) key order: ds_read_b64_tr_b16 transposes 4 keys x 16 features on the way
+//     to the registers, two of them per operand;
 //   - 32-key blocks and 16-key steps that lie entirely beyond valid_len are skipped.
-#include <atomic>
+// Measured (12 heads): 64 x 197 keys 41.5 -> 23.8 us (77 MB moved: 3.2 TB/s; between the vector units' exponentials, about 10 us,
+// and the loads, which the three workgroups of a compute unit all issue at the start), 7 x 197 12.4 -> 6.5, 64 x 128 17.1 ->
+// 11.4, 8 x 128 7.4 -> 4.8 (a launch and two memory round trips).
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -26,167 +31,179 @@ namespace strait {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef __fp16 fp16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int ATT_D = 64;
-constexpr int ATT_LDK = ATT_D + 8;       // K tile row pitch (halfs)
+constexpr int ATT_WAVES = 4;
+constexpr int ATT_KB = 2;                // blocks of 32 keys per step
+constexpr unsigned ATT_ROW = ATT_D * 2;  // bytes of a K or V row in LDS
 
-template <int NKB>                       // key blocks of 32 held in registers = wavefronts: sequences of up to 32 * NKB keys
-__global__ void __launch_bounds__(64 * NKB) attention_kernel(const half_t* __restrict__ qkv, const int32_t* __restrict__ valid_len,
-                                                         int S, int heads, half_t* __restrict__ out, int hp) {
-    constexpr int ATT_SMAX = 32 * NKB;
-    constexpr int ATT_LDV = ATT_SMAX + 8;    // V^T tile row pitch (halfs)
-    extern __shared__ __attribute__((aligned(16))) half_t att_lds[];
-    half_t* Ks = att_lds;                    // [ATT_SMAX][ATT_LDK]
-    half_t* Vt = att_lds + ATT_SMAX * ATT_LDK;   // [ATT_D][ATT_LDV]
+// One wave-wide transfer of 64 x 16 bytes: lane i's chunk at rsrc.base + voff goes to LDS byte address lds_base + 16 i.
+__device__ __forceinline__ void att_dma16(intx4 rsrc, unsigned voff, unsigned lds_base) {
+    const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(m0v), "v"(voff), "s"(rsrc) : "memory");
+}
+// The value of this lane and of lane ^ 32: {lanes 0-31's, lanes 32-63's}.
+__device__ __forceinline__ float2 both_halves(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    const unsigned lo = r[0], hi = r[1];
+    return {__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi)};
+}
+
+__global__ void __launch_bounds__(64 * ATT_WAVES, 4) attention_kernel(const half_t* __restrict__ qkv, const int32_t* __restrict__ valid_len, int S, int heads,
+                                                                      int seq_heads, int blocks_per_wg, half_t* __restrict__ out, int hp) {
+    extern __shared__ __attribute__((aligned(16))) char att_lds[];      // K rows, then V rows, valid_len rounded up to 16 of each
     if (hp) __builtin_amdgcn_s_setprio(3);
-
-    const int b = blockIdx.x / heads, h = blockIdx.x % heads;
-    const int hidden = heads * ATT_D;
-    const long long row_pitch = 3LL * hidden;
-    const half_t* base = qkv + (long long)b * S * row_pitch + h * ATT_D;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int part = blockIdx.x / seq_heads, sh = blockIdx.x - part * seq_heads;
+    const int b = sh / heads, h = sh - b * heads;
+    const int nq = (S + 31) >> 5;
+    const int qb0 = part * blocks_per_wg, qb1 = qb0 + blocks_per_wg < nq ? qb0 + blocks_per_wg : nq;
+    const int hidden = heads * ATT_D, pitch = 3 * hidden;
+    const half_t* seq = qkv + (long long)b * S * pitch;
     int L = valid_len[b];
     L = L < 0 ? 0 : (L > S ? S : L);
 
-    const int tid = threadIdx.x;
-    const int nkb = (L + 31) >> 5;          // key blocks that hold at least one valid key
-    // ---- stage K and V^T: every row of the key blocks in use, zeros at and beyond valid_len ----
-    // a thread moves 8 features of two neighbouring keys: the transposed V tile is then written two keys (one dword)
-    // at a time
-    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-    for (int id = tid; id < nkb * 16 * 8; id += 64 * NKB) {
-        const int key = (id >> 3) * 2, c8 = id & 7;
-        half8 k0, k1, v0, v1;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { k0[j] = k1[j] = v0[j] = v1[j] = (half_t)0; }
-        if (key < L) {
-            k0 = *(const half8*)(base + key * row_pitch + hidden + c8 * 8);
-            v0 = *(const half8*)(base + key * row_pitch + 2 * hidden + c8 * 8);
-        }
-        if (key + 1 < L) {
-            k1 = *(const half8*)(base + (key + 1) * row_pitch + hidden + c8 * 8);
-            v1 = *(const half8*)(base + (key + 1) * row_pitch + 2 * hidden + c8 * 8);
-        }
-        *(half8*)(Ks + key * ATT_LDK + c8 * 8) = k0;
-        *(half8*)(Ks + (key + 1) * ATT_LDK + c8 * 8) = k1;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) *(half2v*)(Vt + (c8 * 8 + j) * ATT_LDV + key) = half2v{v0[j], v1[j]};
+    // ---- stage K and V: pieces of 8 rows, a lane brings chunk (lane & 7) of row lane >> 3, swizzled
+    const unsigned pieces = (unsigned)(L + 15) / 16 * 2;
+    const unsigned lds0 = (unsigned)(uintptr_t)att_lds, lds_v = lds0 + pieces * 8 * ATT_ROW;
+    if (qb0 * 32 < L) {
+        const unsigned long long a = (unsigned long long)seq;
+        const intx4 rsrc = {(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), L * pitch * 2, 0x00020000};   // raw buffer of L rows
+        const unsigned r = lane >> 3, c = lane & 7, rev = ((r & 1) << 2) | (r & 2) | (r >> 2);
+        const unsigned row = r * (unsigned)pitch * 2u + (unsigned)h * ATT_ROW, step = (unsigned)pitch * 16u;
+        const unsigned koff = row + (unsigned)hidden * 2u + ((c ^ r) << 4), voff = row + (unsigned)hidden * 4u + ((c ^ rev) << 4);
+        for (unsigned p = wave; p < pieces; p += ATT_WAVES) att_dma16(rsrc, koff + p * step, lds0 + p * 8 * ATT_ROW);
+        for (unsigned p = wave; p < pieces; p += ATT_WAVES) att_dma16(rsrc, voff + p * step, lds_v + p * 8 * ATT_ROW);
     }
-    __syncthreads();
-
-    const int lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, lh = lane >> 5;
-    const int q0 = wave * 32;
-    if (q0 >= S) return;
-    const bool row_ok = q0 + l32 < S;       // a ragged last block: rows at or beyond S are not written
-    half_t* orow = out + ((long long)b * S + q0 + l32) * hidden + h * ATT_D;
-    if (q0 >= L) {                          // whole query block is padding: defined output, no work
-        half4 z = {(half_t)0, (half_t)0, (half_t)0, (half_t)0};
-        if (row_ok) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) *(half4*)(orow + 8 * i + 4 * lh) = z;
-        }
-        return;
-    }
-
     half8 qf[4];
-    const half_t* qrow = base + (long long)(row_ok ? q0 + l32 : S - 1) * row_pitch;   // ... and read a row that exists
+    auto load_q = [&](int qb) {
+        if (qb >= qb1 || qb * 32 >= L) return;
+        const int q = qb * 32 + l32 < S ? qb * 32 + l32 : S - 1;        // a ragged last block reads a row that exists
+        const half_t* qrow = seq + (long long)q * pitch + h * ATT_D;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) qf[ks] = *(const half8*)(qrow + ks * 16 + lh * 8);
+        for (int ks = 0; ks < 4; ++ks) qf[ks] = *(const half8*)(qrow + ks * 16 + lh * 8);
+    };
+    load_q(qb0 + wave);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
-    floatx16 sc[NKB];
+    const char* krow = att_lds + l32 * ATT_ROW;
+    unsigned kchunk[4];
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sc[kb][v] = 0.f;
-        if (kb < nkb) {
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const half8 kf = *(const half8*)(Ks + (kb * 32 + l32) * ATT_LDK + ks * 16 + lh * 8);
-                sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[ks], sc[kb], 0, 0, 0);
-            }
-        }
-    }
-    // lane holds scores of query q0+l32 against keys kb*32 + 8g + 4*lh + j  (v = 4g + j)
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int key = kb * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-            if (key < L) mx = fmaxf(mx, sc[kb][v]);
-        }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float scale = 0.125f;             // 1/sqrt(64)
-    float sum = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int key = kb * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-            const float pv = key < L ? __expf((sc[kb][v] - mx) * scale) : 0.f;
-            sc[kb][v] = pv;
-            sum += pv;
-        }
-    sum += __shfl_xor(sum, 32, 64);
-    const float inv = 1.f / sum;
+    for (int ks = 0; ks < 4; ++ks) kchunk[ks] = (unsigned)(((ks * 2 + lh) ^ (l32 & 7)) << 4);
+    // V: lane i of a group of 16 names keys 4 lh + (i >> 2), features 16 ((lane >> 4) & 1) + 4 (i & 3) .. + 3 of a 16-key step and a
+    // 32-feature half, and receives the step's keys 4 lh .. 4 lh + 3 of feature 16 ((lane >> 4) & 1) + i
+    const unsigned i16 = lane & 15, vr = lh * 4 + (i16 >> 2), vrev = ((vr & 1) << 2) | (vr & 2) | (vr >> 2);
+    const unsigned vbase = lds_v + vr * ATT_ROW + (i16 & 1) * 8, vchunk = (((lane >> 4) & 1) * 2 + ((i16 & 3) >> 1)) ^ vrev;
+    const unsigned vaddr[2] = {vbase + (vchunk << 4), vbase + ((vchunk ^ 4) << 4)};
+    auto vread = [](unsigned a) { return __builtin_amdgcn_ds_read_tr16_b64_v4f16((__attribute__((address_space(3))) fp16x4*)(uintptr_t)a); };
 
-    floatx16 oacc[2];
+    for (int qb = qb0 + wave; qb < qb1; qb += ATT_WAVES) {
+        const int q0 = qb * 32;
+        const bool row_ok = q0 + l32 < S;       // a ragged last block: rows at or beyond S are not written
+        half_t* orow = out + ((long long)b * S + q0 + l32) * hidden + h * ATT_D;
+        if (q0 >= L) {                          // whole query block is padding: defined output, no work
+            if (row_ok) {
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
-    const int nsteps = (L + 15) >> 4;       // 16-key steps with at least one valid key
-#pragma unroll
-    for (int st = 0; st < 2 * NKB; ++st) {
-        if (st < nsteps) {
-            half8 pf;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) pf[j] = (half_t)sc[st >> 1][(st & 1) * 8 + j];
-#pragma unroll
-            for (int db = 0; db < 2; ++db) {
-                const half_t* vrow = Vt + (db * 32 + l32) * ATT_LDV + st * 16 + 4 * lh;
-                const half4 lo = *(const half4*)vrow;
-                const half4 hi = *(const half4*)(vrow + 8);
-                half8 vf;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) { vf[j] = lo[j]; vf[4 + j] = hi[j]; }
-                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf, oacc[db], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) *(uintx4*)(orow + 16 * i + 8 * lh) = uintx4{0, 0, 0, 0};
             }
+            continue;
         }
+        if (qb != qb0 + wave) load_q(qb);
+        const float c = 0.125f * 1.44269504088896340736f;       // 1/sqrt(64), and log2(e): the probabilities are powers of two
+        floatx16 o[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[0][v] = o[1][v] = 0.f;
+        float mx = -INFINITY, sum = 0.f;        // running maximum of the row, and this lane's part of the sum
+        auto step = [&](int k0, auto masked) __attribute__((always_inline)) {
+            constexpr bool MASK = decltype(masked)::value;
+            floatx16 sc[ATT_KB];                // lane holds query q0 + l32 against keys k0 + kb*32 + 8g + 4*lh + j  (v = 4g + j)
+            float m = mx;
+#pragma unroll
+            for (int kb = 0; kb < ATT_KB; ++kb) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sc[kb][v] = 0.f;
+                if (!MASK || k0 + kb * 32 < L) {
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+                        sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(*(const half8*)(krow + (k0 + kb * 32) * ATT_ROW + kchunk[ks]), qf[ks], sc[kb], 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    if (MASK && k0 + kb * 32 + 8 * (v >> 2) + 4 * lh + (v & 3) >= L) sc[kb][v] = -INFINITY;
+                    m = fmaxf(m, sc[kb][v]);
+                }
+            }
+            const float2 mm = both_halves(m);
+            m = fmaxf(mm.x, mm.y);
+            const float mc = m * c;
+            if (k0 > 0) {
+                const float alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(mx, c, -mc));
+                sum *= alpha;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { o[0][v] *= alpha; o[1][v] *= alpha; }
+            }
+            mx = m;
+#pragma unroll
+            for (int st = 0; st < 2 * ATT_KB; ++st) {
+                if (MASK && k0 + st * 16 >= L) continue;
+                half8 pf;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[st >> 1][(st & 1) * 8 + j], c, -mc));
+                    sum += pv;
+                    pf[j] = (half_t)pv;
+                }
+#pragma unroll
+                for (int db = 0; db < 2; ++db) {
+                    const unsigned a = vaddr[db] + (unsigned)(k0 + st * 16) * ATT_ROW;
+                    const fp16x4 lo = vread(a), hi = vread(a + 8 * ATT_ROW);
+                    half8 vf;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) { vf[j] = (half_t)lo[j]; vf[4 + j] = (half_t)hi[j]; }
+                    o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf, o[db], 0, 0, 0);
+                }
+            }
+        };
+        int k0 = 0;
+        for (; k0 + 32 * ATT_KB <= L; k0 += 32 * ATT_KB) step(k0, std::false_type{});
+        if (k0 < L) step(k0, std::true_type{});
+        const float2 ss = both_halves(sum);
+        const float inv = 1.f / (ss.x + ss.y);
+        // lane holds out[q0+l32][db*32 + 8g + 4*lh + j]; after the exchange with lane ^ 32, 8 features of one g
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; g += 2) {
+                half4 e, f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { e[j] = (half_t)(o[db][4 * g + j] * inv); f[j] = (half_t)(o[db][4 * g + 4 + j] * inv); }
+                const uintx2 eu = __builtin_bit_cast(uintx2, e), fu = __builtin_bit_cast(uintx2, f);
+                const auto x = __builtin_amdgcn_permlane32_swap(eu[0], fu[0], false, false);
+                const auto y = __builtin_amdgcn_permlane32_swap(eu[1], fu[1], false, false);
+                if (row_ok) *(uintx4*)(orow + db * 32 + 8 * (g + lh)) = uintx4{x[0], y[0], x[1], y[1]};
+            }
     }
-    // lane holds out[q0+l32][db*32 + 8g + 4*lh + j]
-    if (!row_ok) return;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            half4 o;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = (half_t)(oacc[db][4 * g + j] * inv);
-            *(half4*)(orow + db * 32 + 8 * g + 4 * lh) = o;
-        }
 }
 
 int launch_attention(const half_t* qkv, const int32_t* valid_len, int B, int S, int heads, half_t* out, int hp,
                      hipStream_t stream) {
     if (!qkv || !valid_len || !out || B <= 0 || heads <= 0) { set_error("attention: invalid arguments"); return -1; }
     if (S <= 0 || S > 256) { set_error("attention: sequence length %d must be in 1..256", S); return -5; }
-    if ((long long)B * heads > 0x7fffffffLL) { set_error("attention: grid too large"); return -5; }
-    const dim3 grid((unsigned)(B * heads));
-    auto lds_bytes = [](int nkb) { return (size_t)(32 * nkb * ATT_LDK + ATT_D * (32 * nkb + 8)) * sizeof(half_t); };
-    if (S <= 128) {
-        hipLaunchKernelGGL(attention_kernel<4>, grid, dim3(256), lds_bytes(4), stream, qkv, valid_len, S, heads, out, hp);
-    } else {
-        static std::atomic<bool> configured{false};      // more than 64 KB of LDS has to be asked for once
-        if (!configured.load(std::memory_order_acquire)) {
-            hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<8>),
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(8));
-            if (ea != hipSuccess) { set_error("attention: hipFuncSetAttribute: %s", hipGetErrorString(ea)); return -2; }
-            configured.store(true, std::memory_order_release);
-        }
-        hipLaunchKernelGGL(attention_kernel<8>, grid, dim3(512), lds_bytes(8), stream, qkv, valid_len, S, heads, out, hp);
-    }
+    if ((long long)B * heads > 0x3fffffffLL || (long long)S * heads * (3 * ATT_D * 2) > 0x7fffffffLL) { set_error("attention: grid or row too large"); return -5; }
+    // More than 4 query blocks: two workgroups with one block per wavefront each as long as all of them are on the chip at once (3 of
+    // 197 keys per compute unit): 32 x 12 heads 12.7 us against 15.4 with two blocks per wavefront.  Beyond that K and V are better read
+    // once (64 x 12: 25.4 against 23.8).
+    const int seq_heads = B * heads, nq = (S + 31) / 32;
+    const int parts = nq > ATT_WAVES && 2LL * seq_heads <= 768 ? 2 : 1;
+    const size_t lds = (size_t)((S + 15) / 16 * 16) * 2 * ATT_ROW;      // at most 64 KB
+    hipLaunchKernelGGL(attention_kernel, dim3((unsigned)(seq_heads * parts)), dim3(64 * ATT_WAVES), lds, stream, qkv, valid_len, S, heads, seq_heads,
+                       (nq + parts - 1) / parts, out, hp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("attention launch: %s", hipGetErrorString(e)); return -2; }
     return 0;

@@ -387,6 +387,23 @@ def test_attention(S, B, Sq, heads, lens):
         assert np.array_equal(out2[b, :vl[b]], out[b, :vl[b]])
 
 
+@pytest.mark.parametrize("B,Sq,heads", [(64, 160, 6), (65, 160, 6), (1, 129, 1)])
+def test_attention_query_blocks_per_workgroup(S, B, Sq, heads):
+    """Sequences of more than 4 query blocks, on both sides of the line between one workgroup per head and two; lengths around
+    the 16-key steps, the 32-key blocks and the 64-key passes, one of them empty (all output rows zero)."""
+    hid = heads * 64
+    qkv = f16(R.standard_normal((B, Sq, 3 * hid)))
+    vl = np.resize(np.array([Sq, 1, 64, 65, 16, 0, 79, 127, 128, 97, Sq - 1], np.int32), B)
+    out = S.k_attention(dev(S, qkv), dev(S, vl), heads).float().cpu().numpy()
+    for b in range(min(B, 11)):
+        L = int(vl[b])
+        if L:
+            ref = ops.attention(qkv[b:b + 1, :, :hid], qkv[b:b + 1, :, hid:2 * hid], qkv[b:b + 1, :, 2 * hid:], vl[b:b + 1], heads)[0]
+            check_kernel(out[b, :L], ref[:L], f"attention length {L}", rel=2.0 ** -9, abs_rel=2e-3)
+        assert not out[b, -(-L // 32) * 32:].any()
+    assert np.isfinite(out).all()
+
+
 def stem_pool_weights(w_oihw):
     """[64,3,7,7] -> the fused stem kernel's [64][176] layout (strait.h, strait_k_stem_pool)."""
     wf = np.zeros((64, 22 * 8), np.float16)
