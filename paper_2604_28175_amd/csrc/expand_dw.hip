@@ -16,7 +16,11 @@
 //         from LDS, in the order the stand-alone depthwise kernels use, + bias, activation, and stores 16 bytes per
 //         position.
 // Every arithmetic step is the one the two stand-alone kernels take, in the same order: results are bit-identical.
-// Small images give few tiles, so the groups of a tile can be shared out over several workgroups (gridDim.y).
+// The groups of a tile can be shared out over several workgroups (gridDim.y), down to one group each (ONE): such a workgroup
+// requests nothing ahead and is done after one pass, which is the whole time of a small batch's launch.  5 images of 14 x 14 with 64
+// channels expanded to 384: tiles of 4 rows and one group each, 240 workgroups, 4.7 us; tiles of 14 rows, two groups
+// each, 30 workgroups, were 12.7.
+#include <algorithm>
 #include <atomic>
 
 #include "kernels.hpp"
@@ -45,8 +49,8 @@ __device__ __forceinline__ float edw_act(float v, int act) {
 }
 
 // KS: 16-channel steps of the expansion's reduction (Cin rounded up); STRIDE of the depthwise layer; the tile is
-// TP x TQ outputs with TP = 256 / (4 TQ) * TH.
-template <int KS, int STRIDE, int TQ, int TH>
+// TP x TQ outputs with TP = 256 / (4 TQ) * TH.  ONE: one tile and one group per workgroup.
+template <int KS, int STRIDE, int TQ, int TH, bool ONE>
 __global__ void __launch_bounds__(256) expand_dw_kernel(const ExpandDwParams p) {
     constexpr int STRIPS = 256 / (4 * TQ), TP = STRIPS * TH;
     constexpr int IR = (TP - 1) * STRIDE + 3, IC = (TQ - 1) * STRIDE + 3;      // input pixels under the tile and its rim
@@ -193,8 +197,10 @@ __global__ void __launch_bounds__(256) expand_dw_kernel(const ExpandDwParams p) 
             }
         }
         const int g_next = g + 1 < g_end ? g + 1 : g_begin;                   // after a tile's last group: the next tile's first
-        load_w1(g_next, wf_next, bv_next);                                    // requested while this group goes on
-        load_wd(g_next, wv_next, bdv_next);
+        if (!ONE) {
+            load_w1(g_next, wf_next, bv_next);                                // requested while this group goes on
+            load_wd(g_next, wv_next, bdv_next);
+        }
         lds_barrier();
         // ---- B2: depthwise 3x3 from the expanded tile --------------------------------------------------------------
         {
@@ -233,6 +239,7 @@ __global__ void __launch_bounds__(256) expand_dw_kernel(const ExpandDwParams p) 
                 }
             }
         }
+        if (ONE) return;
 #pragma unroll
         for (int k = 0; k < 9; ++k) wv[k] = wv_next[k];
 #pragma unroll
@@ -253,60 +260,109 @@ constexpr unsigned edw_lds_bytes(int ks, int stride, int tq, int th) {
     return (unsigned)(rows * (ks * 16 + 8 + EDW_HP) * 2);
 }
 
+// One way to cut a layer: the tile, and how many groups a workgroup takes.
+struct EdwCut {
+    int tp, npb, th, lds;                  // output rows, 32-pixel blocks of input, positions per thread, bytes of LDS
+    long long tiles;
+    int gpb;                               // groups per workgroup (1: the kernel without look-ahead)
+    double us;                             // estimate
+};
+constexpr int edw_pixel_blocks(int stride, int tq, int th) {
+    return ((256 / (4 * tq) * th - 1) * stride + 3) * ((tq - 1) * stride + 3) / 32 + ((((256 / (4 * tq) * th - 1) * stride + 3) * ((tq - 1) * stride + 3)) % 32 != 0);
+}
+constexpr bool edw_ahead(int ks, int stride, int tq, int th) { return edw_pixel_blocks(stride, tq, th) * 32 * ks * 2 <= 12 * 256; }
+
+// Estimated times, fitted to 15 layers of images of 160, 224 and 256 pixels at 1 to 128 images, every tile and split of them (mean
+// error 7 % with one group per workgroup, 18 % with several).  One group: a launch, a pass over the tile, and what the
+// workgroups that share a compute unit add, more where LDS does not hold them at once.  Several: every workgroup of a compute unit in turn.
 template <int KS, int STRIDE, int TQ, int TH>
-static int launch_edw_tile(const ExpandDwParams& q, hipStream_t stream) {
-    constexpr int STRIPS = 256 / (4 * TQ), TP = STRIPS * TH;
-    constexpr unsigned lds = edw_lds_bytes(KS, STRIDE, TQ, TH);
-    static_assert(lds <= 160 * 1024, "LDS limit");
+static EdwCut edw_cut(const ExpandDwParams& p, bool one) {
+    EdwCut c;
+    c.th = TH;
+    c.tp = 256 / (4 * TQ) * TH;
+    c.npb = edw_pixel_blocks(STRIDE, TQ, TH);
+    c.lds = (int)edw_lds_bytes(KS, STRIDE, TQ, TH);
+    c.tiles = (long long)p.N * ((p.P + c.tp - 1) / c.tp) * ((p.Q + TQ - 1) / TQ);
+    const int groups = (p.Chid + 31) / 32, resident = std::min(160 * 1024 / (c.lds + 512), 4);
+    c.gpb = 1;
+    if (!one) {
+        int split = 1;
+        while (c.tiles * split < 256 && split * 2 <= groups) split *= 2;
+        c.gpb = (groups + split - 1) / split;
+        // two full workgroups per compute unit, where they fit and the split comes out even: they hide each other's waits
+        const int g2 = (int)((c.tiles * groups + 511) / 512);
+        const long long n2 = g2 > 0 && g2 <= groups ? c.tiles * ((groups + g2 - 1) / g2) : 0;
+        if (resident >= 2 && n2 >= 448 && n2 <= 512) c.gpb = g2;
+    }
+    const long long n = c.tiles * ((groups + c.gpb - 1) / c.gpb);
+    const double per_cu = (double)((n + 255) / 256);
+    if (one) c.us = 3.6 + 0.36 * ((c.npb + 3) / 4) + 0.77 * TH + (per_cu - 1) * (0.044 * c.npb * KS + 0.25 * TH) + 2.2 * (double)((n + 256LL * resident - 1) / (256LL * resident) - 1);
+    else c.us = 4.6 + per_cu * (0.10 * c.npb * KS + c.gpb * (0.83 + 0.29 * TH));
+    return c;
+}
+
+template <int KS, int STRIDE, int TQ, int TH, bool ONE>
+static int launch_edw_tile(const ExpandDwParams& q, const EdwCut& c, hipStream_t stream) {
+    static_assert(edw_lds_bytes(KS, STRIDE, TQ, TH) <= 160 * 1024, "LDS limit");
     ExpandDwParams p = q;
-    p.tiles_p = (p.P + TP - 1) / TP;
+    p.tiles_p = (p.P + c.tp - 1) / c.tp;
     p.tiles_q = (p.Q + TQ - 1) / TQ;
-    const long long tiles = (long long)p.N * p.tiles_p * p.tiles_q;
-    if (tiles <= 0 || tiles > 0x7fffffffLL) { set_error("expand+depthwise: bad grid (%lld tiles)", tiles); return -5; }
-    // few tiles: share the channel groups of a tile out over several workgroups (each loads the input tile again)
+    if (c.tiles <= 0 || c.tiles > 0x7fffffffLL) { set_error("expand+depthwise: bad grid (%lld tiles)", c.tiles); return -5; }
     const int groups = (p.Chid + 31) / 32;
-    int split = 1;
-    while (tiles * split < 256 && split * 2 <= groups) split *= 2;
-    p.groups_per_block = (groups + split - 1) / split;
-    const unsigned gy = (unsigned)((groups + p.groups_per_block - 1) / p.groups_per_block);
-    auto kernel = expand_dw_kernel<KS, STRIDE, TQ, TH>;
+    p.groups_per_block = c.gpb;
+    const unsigned gy = (unsigned)((groups + c.gpb - 1) / c.gpb);
+    auto kernel = expand_dw_kernel<KS, STRIDE, TQ, TH, ONE>;
     static std::atomic<bool> configured{false};
-    if (!configured.load(std::memory_order_acquire) && lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) { set_error("expand+depthwise: cannot reserve %u bytes of LDS: %s", lds, hipGetErrorString(e)); return -2; }
+    if (!configured.load(std::memory_order_acquire) && c.lds > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, c.lds);
+        if (e != hipSuccess) { set_error("expand+depthwise: cannot reserve %d bytes of LDS: %s", c.lds, hipGetErrorString(e)); return -2; }
     }
     configured.store(true, std::memory_order_release);
     // where the kernel requests a tile's input one tile ahead, two workgroups per compute unit walk over the tiles
-    constexpr int IRr = (TP - 1) * STRIDE + 3, ICc = (TQ - 1) * STRIDE + 3, NITs = (((IRr * ICc + 31) / 32 * 32) * KS * 2 + 255) / 256;
-    const unsigned gx = (NITs <= 12 && tiles > 512) ? 512u : (unsigned)tiles;
-    hipLaunchKernelGGL(kernel, dim3(gx, gy), dim3(256), lds, stream, p);
+    const unsigned gx = (!ONE && edw_ahead(KS, STRIDE, TQ, TH) && c.tiles > 512) ? 512u : (unsigned)c.tiles;
+    hipLaunchKernelGGL(kernel, dim3(gx, gy), dim3(256), (unsigned)c.lds, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("expand+depthwise launch: %s", hipGetErrorString(e)); return -2; }
     return 0;
 }
 
+// The tile TQ x TH with several groups per workgroup, or with one, or one of the two smallest tiles with one: whichever is estimated to
+// be the fastest.
+template <int KS, int STRIDE, int TQ, int TH>
+static int launch_edw_best(const ExpandDwParams& p, hipStream_t stream) {
+    const EdwCut several = edw_cut<KS, STRIDE, TQ, TH>(p, false), one = edw_cut<KS, STRIDE, TQ, TH>(p, true), s8 = edw_cut<KS, STRIDE, 8, 1>(p, true);
+    double best = std::min(std::min(several.us, one.us), s8.us);
+    if constexpr (edw_lds_bytes(KS, STRIDE, 16, 1) <= 160 * 1024) {
+        const EdwCut s16 = edw_cut<KS, STRIDE, 16, 1>(p, true);
+        if (s16.us < best) return launch_edw_tile<KS, STRIDE, 16, 1, true>(p, s16, stream);
+    }
+    if (best == s8.us) return launch_edw_tile<KS, STRIDE, 8, 1, true>(p, s8, stream);
+    if (best == one.us) return launch_edw_tile<KS, STRIDE, TQ, TH, true>(p, one, stream);
+    return launch_edw_tile<KS, STRIDE, TQ, TH, false>(p, several, stream);
+}
+
 template <int KS>
 static int launch_edw_ks(const ExpandDwParams& p, int stride, hipStream_t stream) {
-    // tile by image width: 32 wide, 16 wide (14 x 14 maps as one tile), 8 wide (7 x 7)
+    // large tile by image width: 32 wide, 16 wide (14 x 14 maps as one tile), 8 wide (7 x 7)
     if (stride == 1) {
-        if (p.Q > 16) return launch_edw_tile<KS, 1, 32, 4>(p, stream);
-        if (p.Q > 8) return launch_edw_tile<KS, 1, 16, 4>(p, stream);
-        return launch_edw_tile<KS, 1, 8, 1>(p, stream);
+        if (p.Q > 16) return launch_edw_best<KS, 1, 32, 4>(p, stream);
+        if (p.Q > 8) return launch_edw_best<KS, 1, 16, 4>(p, stream);
+        return launch_edw_best<KS, 1, 8, 1>(p, stream);
     }
     // stride 2 puts four input pixels under an output: with many input channels only the smallest tile fits LDS
     // (two workgroups per compute unit matter more than a tile's ratio of rim to area: half the height where the taller tile
     // would take more than half of LDS)
     if constexpr (edw_lds_bytes(KS, 2, 32, 2) <= 80 * 1024) {
-        if (p.Q > 16) return launch_edw_tile<KS, 2, 32, 2>(p, stream);
+        if (p.Q > 16) return launch_edw_best<KS, 2, 32, 2>(p, stream);
     } else if constexpr (edw_lds_bytes(KS, 2, 32, 1) <= 160 * 1024) {
-        if (p.Q > 16) return launch_edw_tile<KS, 2, 32, 1>(p, stream);
+        if (p.Q > 16) return launch_edw_best<KS, 2, 32, 1>(p, stream);
     }
     if constexpr (edw_lds_bytes(KS, 2, 16, 2) <= 80 * 1024) {
-        if (p.Q > 8) return launch_edw_tile<KS, 2, 16, 2>(p, stream);
+        if (p.Q > 8) return launch_edw_best<KS, 2, 16, 2>(p, stream);
     } else if constexpr (edw_lds_bytes(KS, 2, 16, 1) <= 160 * 1024) {
-        if (p.Q > 8) return launch_edw_tile<KS, 2, 16, 1>(p, stream);
+        if (p.Q > 8) return launch_edw_best<KS, 2, 16, 1>(p, stream);
     }
-    return launch_edw_tile<KS, 2, 8, 1>(p, stream);
+    return launch_edw_best<KS, 2, 8, 1>(p, stream);
 }
 
 bool expand_dw_supported(int Cin, int Chid, int stride) {

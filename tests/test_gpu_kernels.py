@@ -517,6 +517,24 @@ def test_expand_dw(S, case):
     check_kernel(y.float().cpu().numpy(), ref, f"expand+dw {case}")
 
 
+@pytest.mark.parametrize("case", [(1, 28, 30, 32, 200, 1), (16, 56, 56, 24, 144, 1), (128, 55, 57, 24, 144, 1), (64, 28, 28, 32, 192, 1), (32, 13, 14, 96, 576, 1),
+                                  (96, 14, 14, 64, 384, 1), (48, 7, 6, 160, 968, 1), (17, 14, 14, 96, 576, 2), (64, 28, 27, 32, 192, 2), (32, 80, 82, 16, 96, 2)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_expand_dw_every_cut(S, case):
+    """Batches for which each way to cut a layer is chosen (smallest tiles, large tiles with one group of channels per workgroup, with
+    several, workgroups that walk over tiles): bit for bit what the two stand-alone kernels give."""
+    N, H, W, Cin, Chid, stride = case
+    x = dev(S, f16(R.standard_normal((N, H, W, Cin))))
+    w1 = dev(S, f16(R.standard_normal((Chid, Cin)) * (2.0 / Cin) ** 0.5))
+    b1 = dev(S, R.standard_normal(Chid).astype(np.float32))
+    wd = dev(S, f16(R.standard_normal((3, 3, Chid)) * 0.47))
+    bd = dev(S, R.standard_normal(Chid).astype(np.float32))
+    y = S.k_expand_dw(x, w1, b1, wd, bd, stride)
+    y2 = S.k_dwconv3x3(S.k_conv2d(x, w1.reshape(Chid, 1, 1, Cin), b1, 1, 0, 2), wd, bd, stride, 2)
+    S.torch.cuda.synchronize()
+    assert S.torch.equal(y, y2)
+
+
 def test_expand_dw_errors(S):
     x = dev(S, np.zeros((1, 8, 8, 12), np.float16))
     with pytest.raises(S.StraitError):       # Cin % 8 != 0
