@@ -73,13 +73,18 @@ __global__ void __launch_bounds__(64 * ATT_WAVES, 4) attention_kernel(const half
     const unsigned pieces = (unsigned)(L + 15) / 16 * 2;
     const unsigned lds0 = (unsigned)(uintptr_t)att_lds, lds_v = lds0 + pieces * 8 * ATT_ROW;
     if (qb0 * 32 < L) {
-        const unsigned long long a = (unsigned long long)seq;
-        const intx4 rsrc = {(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), L * pitch * 2, 0x00020000};   // raw buffer of L rows
+        // raw buffer of the rows below L among the 8 rows of a piece: a descriptor per piece, whose offsets fit 32 bits whatever the length
+        auto rows8 = [&](unsigned p) -> intx4 {
+            const unsigned long long a = (unsigned long long)(seq + (long long)p * 8 * pitch);
+            const int left = L - (int)p * 8;
+            return {__builtin_amdgcn_readfirstlane((int)(unsigned)a), __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xffffu)),
+                    __builtin_amdgcn_readfirstlane((left < 0 ? 0 : left < 8 ? left : 8) * pitch * 2), 0x00020000};
+        };
         const unsigned r = lane >> 3, c = lane & 7, rev = ((r & 1) << 2) | (r & 2) | (r >> 2);
-        const unsigned row = r * (unsigned)pitch * 2u + (unsigned)h * ATT_ROW, step = (unsigned)pitch * 16u;
+        const unsigned row = r * (unsigned)pitch * 2u + (unsigned)h * ATT_ROW;
         const unsigned koff = row + (unsigned)hidden * 2u + ((c ^ r) << 4), voff = row + (unsigned)hidden * 4u + ((c ^ rev) << 4);
-        for (unsigned p = wave; p < pieces; p += ATT_WAVES) att_dma16(rsrc, koff + p * step, lds0 + p * 8 * ATT_ROW);
-        for (unsigned p = wave; p < pieces; p += ATT_WAVES) att_dma16(rsrc, voff + p * step, lds_v + p * 8 * ATT_ROW);
+        for (unsigned p = wave; p < pieces; p += ATT_WAVES) att_dma16(rows8(p), koff, lds0 + p * 8 * ATT_ROW);
+        for (unsigned p = wave; p < pieces; p += ATT_WAVES) att_dma16(rows8(p), voff, lds_v + p * 8 * ATT_ROW);
     }
     half8 qf[4];
     auto load_q = [&](int qb) {
@@ -141,7 +146,7 @@ __global__ void __launch_bounds__(64 * ATT_WAVES, 4) attention_kernel(const half
             }
             const float2 mm = both_halves(m);
             m = fmaxf(mm.x, mm.y);
-            const float mc = m * c;
+            const float mc = m > -INFINITY ? m * c : 0.f;     // nothing but -inf so far: probabilities of 0, as if these keys were masked
             if (k0 > 0) {
                 const float alpha = __builtin_amdgcn_exp2f(__builtin_fmaf(mx, c, -mc));
                 sum *= alpha;
@@ -195,7 +200,7 @@ int launch_attention(const half_t* qkv, const int32_t* valid_len, int B, int S, 
                      hipStream_t stream) {
     if (!qkv || !valid_len || !out || B <= 0 || heads <= 0) { set_error("attention: invalid arguments"); return -1; }
     if (S <= 0 || S > 256) { set_error("attention: sequence length %d must be in 1..256", S); return -5; }
-    if ((long long)B * heads > 0x3fffffffLL || (long long)S * heads * (3 * ATT_D * 2) > 0x7fffffffLL) { set_error("attention: grid or row too large"); return -5; }
+    if ((long long)B * heads > 0x3fffffffLL || 8LL * heads * (3 * ATT_D * 2) > 0x7fffffffLL) { set_error("attention: grid or row too large"); return -5; }
     // More than 4 query blocks: two workgroups with one block per wavefront each as long as all of them are on the chip at once (3 of
     // 197 keys per compute unit): 32 x 12 heads 12.7 us against 15.4 with two blocks per wavefront.  Beyond that K and V are better read
     // once (64 x 12: 25.4 against 23.8).

@@ -404,6 +404,25 @@ def test_attention_query_blocks_per_workgroup(S, B, Sq, heads):
     assert np.isfinite(out).all()
 
 
+@pytest.mark.parametrize("dead", [1, 64, 70, 128])
+def test_attention_leading_scores_of_minus_infinity(S, dead):
+    """Keys whose scores are -inf have probability 0, also where they fill the first 64-key passes of the running maximum."""
+    qkv = f16(R.standard_normal((1, 150, 192)))
+    qkv[..., 0] = 1
+    ref = ops.attention(qkv[:, :, :64], qkv[:, dead:, 64:128], qkv[:, dead:, 128:], np.array([150 - dead], np.int32), 1)[0]
+    qkv[0, :dead, 64] = -np.inf
+    out = S.k_attention(dev(S, qkv), dev(S, np.array([150], np.int32)), 1).float().cpu().numpy()[0]
+    check_kernel(out, ref, f"{dead} keys at -inf", rel=2.0 ** -9, abs_rel=2e-3)
+
+
+def test_attention_rows_of_more_than_31_bits(S):
+    """One sequence whose rows span more than 2 GB: 23040 heads, every 64th group the same values."""
+    qkv = f16(R.standard_normal((1, 256, 3, 64 * 64)))
+    out = S.k_attention(dev(S, np.tile(qkv, 360).reshape(1, 256, -1)), dev(S, np.array([250], np.int32)), 360 * 64)[0]
+    one = S.k_attention(dev(S, qkv.reshape(1, 256, -1)), dev(S, np.array([250], np.int32)), 64)[0]
+    assert (out.reshape(256, 360, -1) == one[:, None, :]).all()
+
+
 def stem_pool_weights(w_oihw):
     """[64,3,7,7] -> the fused stem kernel's [64][176] layout (strait.h, strait_k_stem_pool)."""
     wf = np.zeros((64, 22 * 8), np.float16)
