@@ -52,7 +52,8 @@ static const size_t kOutOnCopyStream = 4u << 20;
 // Enqueues the result's way out behind the kernel sequence on `s`.
 static int enqueue_output(Model& m, Instance& in, Ticket* t, hipStream_t s) {
     const size_t bytes = m.out_bytes(t->batch);
-    t->chunks = (unsigned)((bytes + OUT_CHUNK - 1) / OUT_CHUNK);
+    t->chunk_bytes = out_chunk_bytes(bytes);
+    t->chunks = (unsigned)((bytes + t->chunk_bytes - 1) / t->chunk_bytes);
     t->out_pending = bytes >= kOutOnCopyStream;
     if (t->out_pending) return launch_stamp(in.ctl_dev, STAMP_K1, s, nullptr, nullptr, 0, t->seq);
     return launch_copy_out(in.dev_out, in.pinned_out_dev, bytes, in.ctl_dev, in.counters + 1, t->seq, false, t->hp, s);
@@ -113,11 +114,11 @@ static void copy_chunks(Ticket* t, Instance& in, hipStream_t s) {
     const size_t bytes = t->model->out_bytes(t->batch);
     const unsigned chunks = t->chunks;
     for (unsigned c; (c = t->chunk_next.fetch_add(1, std::memory_order_relaxed)) < chunks;) {
-        const size_t at = (size_t)c * OUT_CHUNK;
+        const size_t at = (size_t)c * t->chunk_bytes;
         const int rc = await_flag(&in.ctl->flag[c], t->seq, s);
         if (c + 1 == chunks) t->t_last.store(now_ns(), std::memory_order_relaxed);
         if (rc) t->copy_status.store(rc, std::memory_order_relaxed);
-        else memcpy((char*)t->host_out + at, (const char*)in.pinned_out + at, std::min<size_t>(OUT_CHUNK, bytes - at));
+        else memcpy((char*)t->host_out + at, (const char*)in.pinned_out + at, std::min<size_t>(t->chunk_bytes, bytes - at));
         t->chunk_done.fetch_add(1, std::memory_order_release);
     }
 }

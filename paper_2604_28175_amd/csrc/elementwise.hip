@@ -113,7 +113,7 @@ int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* sr
     return 0;
 }
 
-// Result, in chunks of OUT_CHUNK bytes, each in OUT_PARTS parts of which a workgroup takes every gridDim.x-th: when the last part of
+// Result, in chunks of out_chunk_bytes, each in OUT_PARTS parts of which a workgroup takes every gridDim.x-th: when the last part of
 // chunk c is written, flag[c] becomes `seq`, so that the host can move a chunk on while the next ones are on the link.  Stamps
 // STAMP_K1 (first workgroup starts; unless `k1_taken`) and STAMP_DONE.  counters[1 + c] count a chunk's parts, counters[0] the
 // chunks; both are left at zero.
@@ -125,13 +125,13 @@ __device__ __forceinline__ void store_through(void* p, uint4 v) {
     const uint4v r = {v.x, v.y, v.z, v.w};
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(r) : "memory");
 }
-__global__ void __launch_bounds__(256) copy_out_kernel(const char* __restrict__ src, char* __restrict__ dst, size_t bytes, unsigned parts, unsigned chunks,
+__global__ void __launch_bounds__(256) copy_out_kernel(const char* __restrict__ src, char* __restrict__ dst, size_t bytes, size_t part_bytes, unsigned parts, unsigned chunks,
                                                        HostControl* ctl, unsigned* counters, unsigned seq, int k1_taken, int hp) {
     if (hp) __builtin_amdgcn_s_setprio(3);
     if (blockIdx.x == 0 && threadIdx.x == 0 && !k1_taken)
         __hip_atomic_store(&ctl->stamp[STAMP_K1], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     for (unsigned part = blockIdx.x; part < parts; part += gridDim.x) {
-        const size_t at = (size_t)part * (OUT_CHUNK / OUT_PARTS), n = bytes - at < OUT_CHUNK / OUT_PARTS ? bytes - at : OUT_CHUNK / OUT_PARTS;
+        const size_t at = (size_t)part * part_bytes, n = bytes - at < part_bytes ? bytes - at : part_bytes;
         const size_t n16 = n >> 4;
         const uint4* s16 = (const uint4*)(src + at);
         uint4* d16 = (uint4*)(dst + at);
@@ -159,14 +159,15 @@ __global__ void __launch_bounds__(256) copy_out_kernel(const char* __restrict__ 
     }
 }
 int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, hipStream_t stream) {
-    if (!src || !dst || !ctl || !counters || bytes == 0 || (bytes & 3) || bytes > (size_t)OUT_CHUNK * OUT_MAX_CHUNKS ||
+    if (!src || !dst || !ctl || !counters || bytes == 0 || (bytes & 3) ||
         ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15)) {
-        set_error("copy out: 16-byte aligned buffers, a multiple of 4 bytes and at most %zu bytes required", (size_t)OUT_CHUNK * OUT_MAX_CHUNKS); return -1;
+        set_error("copy out: 16-byte aligned buffers and a multiple of 4 bytes required"); return -1;
     }
-    const unsigned chunks = (unsigned)((bytes + OUT_CHUNK - 1) / OUT_CHUNK);
-    const unsigned parts = (unsigned)((bytes + OUT_CHUNK / OUT_PARTS - 1) / (OUT_CHUNK / OUT_PARTS));
+    const size_t chunk = out_chunk_bytes(bytes), part = chunk / OUT_PARTS;
+    const unsigned chunks = (unsigned)((bytes + chunk - 1) / chunk);
+    const unsigned parts = (unsigned)((bytes + part - 1) / part);
     const unsigned blocks = std::min(parts, 16u);
-    hipLaunchKernelGGL(copy_out_kernel, dim3(blocks), dim3(256), 0, stream, (const char*)src, (char*)dst, bytes, parts, chunks, ctl, counters, seq,
+    hipLaunchKernelGGL(copy_out_kernel, dim3(blocks), dim3(256), 0, stream, (const char*)src, (char*)dst, bytes, part, parts, chunks, ctl, counters, seq,
                        k1_taken ? 1 : 0, hp);
     STRAIT_CHECK_LAUNCH("copy out");
     return 0;

@@ -118,7 +118,12 @@ int launch_argmax_f16(const half_t* x, int rows, int n, long long row_stride, in
 int launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 // ---- transfers by kernel, with the timestamps and the completion flags of a batch (elementwise.hip)
 enum { STAMP_H2D0 = 0, STAMP_H2D1 = 1, STAMP_K0 = 2, STAMP_K1 = 3, STAMP_DONE = 4, STAMP_COUNT = 8 };
-constexpr unsigned OUT_CHUNK = 256u << 10, OUT_PARTS = 8, OUT_MAX_CHUNKS = 4096;
+constexpr unsigned OUT_PARTS = 8, OUT_MAX_CHUNKS = 4096;
+inline size_t out_chunk_bytes(size_t bytes) {          // of a result: 256 KB, doubled while it has more chunks than there are flags (beyond 1 GiB)
+    size_t c = 256u << 10;
+    while ((bytes + c - 1) / c > OUT_MAX_CHUNKS) c *= 2;
+    return c;
+}
 struct HostControl {                     // in pinned host memory, written by the GPU
     uint64_t stamp[STAMP_COUNT];         // device clock (hipDeviceAttributeWallClockRate)
     uint32_t k1_seq, pad[7];             // sequence number of the last batch whose kernels are done (results that leave on a copy stream)

@@ -135,7 +135,8 @@ struct Ticket {
     unsigned seq = 0;
     size_t worker = 0;                 // index of its compute stream in Context::workers
     size_t copy = 0;                   // index of its copy stream in Context::copy
-    unsigned chunks = 0;               // of its result (OUT_CHUNK bytes each)
+    unsigned chunks = 0;               // of its result
+    size_t chunk_bytes = 0;
     std::atomic<unsigned> chunk_next{0}, chunk_done{0};   // handed out to a copying thread / copied to the caller's buffer
     std::atomic<bool> chunks_coming{false};               // the copy off the device is enqueued: another thread may lend a hand
     std::atomic<int64_t> t_last{0};    // host time at which the last chunk was seen to be there
