@@ -90,8 +90,9 @@ static int issue_in_segments(Context* ctx, StreamWorker* w, Ticket* t) {
 }
 
 // Polls until the GPU has written `seq`.  The wait ends: a kernel that is enqueued on `s` already writes it, and every few
-// milliseconds the stream is asked whether it has failed, or has run dry without.
-static int await_flag(const uint32_t* flag, unsigned seq, hipStream_t s) {
+// milliseconds the stream is asked whether it has failed, or has run dry without.  Not while a thread is submitting to it, that is holds
+// its mutex: the stream may be recording a graph, which a query would spoil, and would itself be refused.
+static int await_flag(const uint32_t* flag, unsigned seq, hipStream_t s, std::mutex& submitting) {
     int64_t asked = 0;
     for (unsigned n = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++n) {
         __builtin_ia32_pause();
@@ -100,6 +101,8 @@ static int await_flag(const uint32_t* flag, unsigned seq, hipStream_t s) {
         const int64_t now = now_ns();
         if (asked == 0) asked = now;
         if (now - asked < 5000000) continue;
+        std::unique_lock<std::mutex> lk(submitting, std::try_to_lock);
+        if (!lk.owns_lock()) continue;
         asked = now;
         const hipError_t e = hipStreamQuery(s);
         if (e == hipErrorNotReady) { (void)hipGetLastError(); continue; }
@@ -110,12 +113,12 @@ static int await_flag(const uint32_t* flag, unsigned seq, hipStream_t s) {
 
 // Takes chunks of the result and copies each to the caller's buffer as it arrives, until none is left to take.  Two threads can be at it:
 // one copies large results out of the pinned buffer at about 31 GB/s, the link brings 52.
-static void copy_chunks(Ticket* t, Instance& in, hipStream_t s) {
+static void copy_chunks(Ticket* t, Instance& in, hipStream_t s, std::mutex& submitting) {
     const size_t bytes = t->model->out_bytes(t->batch);
     const unsigned chunks = t->chunks;
     for (unsigned c; (c = t->chunk_next.fetch_add(1, std::memory_order_relaxed)) < chunks;) {
         const size_t at = (size_t)c * t->chunk_bytes;
-        const int rc = await_flag(&in.ctl->flag[c], t->seq, s);
+        const int rc = await_flag(&in.ctl->flag[c], t->seq, s, submitting);
         if (c + 1 == chunks) t->t_last.store(now_ns(), std::memory_order_relaxed);
         if (rc) t->copy_status.store(rc, std::memory_order_relaxed);
         else memcpy((char*)t->host_out + at, (const char*)in.pinned_out + at, std::min<size_t>(t->chunk_bytes, bytes - at));
@@ -124,13 +127,14 @@ static void copy_chunks(Ticket* t, Instance& in, hipStream_t s) {
 }
 
 static hipStream_t output_stream(Context* ctx, const Ticket* t) { return t->out_pending ? ctx->copy[t->copy] : ctx->workers[t->worker]->stream; }
+static std::mutex& output_mutex(Context* ctx, const Ticket* t) { return t->out_pending ? ctx->copy_mu[t->copy] : ctx->compute_mu[t->worker]; }
 
 // Sees the result into the caller's buffer.  *done: host time at which its last part was seen in host memory.
 static int await_result(Context* ctx, StreamWorker* w, Ticket* t, int64_t* done) {
     Instance& in = t->model->inst[t->instance];
     hipStream_t s = output_stream(ctx, t);
     if (t->out_pending) {
-        if (await_flag(&in.ctl->k1_seq, t->seq, w->stream)) return STRAIT_E_HIP;
+        if (await_flag(&in.ctl->k1_seq, t->seq, w->stream, ctx->compute_mu[t->worker])) return STRAIT_E_HIP;
         std::lock_guard<std::mutex> lk(ctx->copy_mu[t->copy]);
         if (launch_copy_out(in.dev_out, in.pinned_out_dev, t->model->out_bytes(t->batch), in.ctl_dev, in.counters + 1, t->seq, true, t->hp, s)) return STRAIT_E_HIP;
     }
@@ -139,7 +143,7 @@ static int await_result(Context* ctx, StreamWorker* w, Ticket* t, int64_t* done)
         t->chunks_coming.store(true, std::memory_order_release);
         ctx->cv_done.notify_all();
     }
-    copy_chunks(t, in, s);
+    copy_chunks(t, in, s, output_mutex(ctx, t));
     while (t->chunk_done.load(std::memory_order_acquire) < t->chunks) __builtin_ia32_pause();   // the other thread's last memcpy
     *done = t->t_last.load(std::memory_order_relaxed);
     return t->copy_status.load(std::memory_order_relaxed);
@@ -662,7 +666,7 @@ strait_status strait_wait(strait_ticket t, strait_record* rec) {
                 c->cv_done.wait(lk, [&] { return t->done.load(std::memory_order_acquire) || can_help(); });
                 done = t->done.load(std::memory_order_acquire);
             }
-            if (!done) copy_chunks(t, m->inst[t->instance], output_stream(c, t));
+            if (!done) copy_chunks(t, m->inst[t->instance], output_stream(c, t), output_mutex(c, t));
         }
     }
     if (rec) *rec = t->rec;

@@ -306,6 +306,42 @@ def test_graph_replay_equals_kernel_by_kernel(ctx, arch, batch):
         m.free()
 
 
+def test_graphs_recorded_while_an_earlier_batch_is_awaited(ctx):
+    """A batch of tens of milliseconds is being waited for, and its stream asked every few milliseconds whether it is well, while the batches
+    behind it record their graphs on the same stream, one after the other: neither disturbs the other."""
+    S = ctx.S
+    slow_md = synth.encoder(3, layers=6, hidden=768, heads=12, ffn=3072, seq=256)
+    slow_b, quick_n = 512, 48
+    x8, vl8 = synth.token_batch(slow_md, 8, 1, min_len=32)
+    rows = np.arange(slow_b) % 8
+    x, vl = x8[rows], vl8[rows]
+    md = synth.resnet50(9, hw=64)
+    xq = synth.default_image_batch(md, 1, 3)
+    slow = ctx.load(synth.pack(slow_md), max_batch=slow_b, n_instances=2)
+    quick = ctx.load(synth.pack(md), max_batch=1, n_instances=quick_n)
+    try:
+        ctx.set_graphs(True)
+        for i in range(quick_n):                  # the first use of an instance runs without a graph
+            buf = quick.staging(i, 1)
+            buf[:] = xq
+            ref, _ = quick.infer(buf, prio=S.PRIO_LOW)
+        out = [slow.new_output(slow_b) for _ in range(2)]
+        outq = [quick.new_output(1) for _ in range(quick_n)]
+        tickets = [slow.submit(S.PRIO_LOW, x, vl, o) for o in out]
+        tq = [quick.submit(S.PRIO_LOW, quick.staging(i, 1), None, outq[i]) for i in range(quick_n)]
+        for t in tickets:
+            slow.wait(t)
+        for t in tq:
+            quick.wait(t)
+        assert np.array_equal(out[0], out[1])
+        for o in outq:
+            assert np.array_equal(quick.decode(o, 1)["logits"], ref["logits"])
+    finally:
+        ctx.set_graphs(False)
+        slow.free()
+        quick.free()
+
+
 def test_small_batch_split_reduction_is_reproducible(ctx):
     """Small batches split long reductions over several workgroups per tile; the partial results are summed
     in a fixed order, so repeated runs must agree bit for bit, at either priority."""
