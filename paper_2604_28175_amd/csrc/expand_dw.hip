@@ -327,46 +327,78 @@ static int launch_edw_tile(const ExpandDwParams& q, const EdwCut& c, hipStream_t
 }
 
 // The tile TQ x TH with several groups per workgroup, or with one, or one of the two smallest tiles with one: whichever is estimated to
-// be the fastest.
+// be the fastest.  With `us`: only its estimate.
 template <int KS, int STRIDE, int TQ, int TH>
-static int launch_edw_best(const ExpandDwParams& p, hipStream_t stream) {
+static int launch_edw_best(const ExpandDwParams& p, hipStream_t stream, double* us) {
     const EdwCut several = edw_cut<KS, STRIDE, TQ, TH>(p, false), one = edw_cut<KS, STRIDE, TQ, TH>(p, true), s8 = edw_cut<KS, STRIDE, 8, 1>(p, true);
     double best = std::min(std::min(several.us, one.us), s8.us);
     if constexpr (edw_lds_bytes(KS, STRIDE, 16, 1) <= 160 * 1024) {
         const EdwCut s16 = edw_cut<KS, STRIDE, 16, 1>(p, true);
+        if (us) { *us = std::min(best, s16.us); return 0; }
         if (s16.us < best) return launch_edw_tile<KS, STRIDE, 16, 1, true>(p, s16, stream);
     }
+    if (us) { *us = best; return 0; }
     if (best == s8.us) return launch_edw_tile<KS, STRIDE, 8, 1, true>(p, s8, stream);
     if (best == one.us) return launch_edw_tile<KS, STRIDE, TQ, TH, true>(p, one, stream);
     return launch_edw_tile<KS, STRIDE, TQ, TH, false>(p, several, stream);
 }
 
 template <int KS>
-static int launch_edw_ks(const ExpandDwParams& p, int stride, hipStream_t stream) {
+static int launch_edw_ks(const ExpandDwParams& p, int stride, hipStream_t stream, double* us) {
     // large tile by image width: 32 wide, 16 wide (14 x 14 maps as one tile), 8 wide (7 x 7)
     if (stride == 1) {
-        if (p.Q > 16) return launch_edw_best<KS, 1, 32, 4>(p, stream);
-        if (p.Q > 8) return launch_edw_best<KS, 1, 16, 4>(p, stream);
-        return launch_edw_best<KS, 1, 8, 1>(p, stream);
+        if (p.Q > 16) return launch_edw_best<KS, 1, 32, 4>(p, stream, us);
+        if (p.Q > 8) return launch_edw_best<KS, 1, 16, 4>(p, stream, us);
+        return launch_edw_best<KS, 1, 8, 1>(p, stream, us);
     }
     // stride 2 puts four input pixels under an output: with many input channels only the smallest tile fits LDS
     // (two workgroups per compute unit matter more than a tile's ratio of rim to area: half the height where the taller tile
     // would take more than half of LDS)
     if constexpr (edw_lds_bytes(KS, 2, 32, 2) <= 80 * 1024) {
-        if (p.Q > 16) return launch_edw_best<KS, 2, 32, 2>(p, stream);
+        if (p.Q > 16) return launch_edw_best<KS, 2, 32, 2>(p, stream, us);
     } else if constexpr (edw_lds_bytes(KS, 2, 32, 1) <= 160 * 1024) {
-        if (p.Q > 16) return launch_edw_best<KS, 2, 32, 1>(p, stream);
+        if (p.Q > 16) return launch_edw_best<KS, 2, 32, 1>(p, stream, us);
     }
     if constexpr (edw_lds_bytes(KS, 2, 16, 2) <= 80 * 1024) {
-        if (p.Q > 8) return launch_edw_best<KS, 2, 16, 2>(p, stream);
+        if (p.Q > 8) return launch_edw_best<KS, 2, 16, 2>(p, stream, us);
     } else if constexpr (edw_lds_bytes(KS, 2, 16, 1) <= 160 * 1024) {
-        if (p.Q > 8) return launch_edw_best<KS, 2, 16, 1>(p, stream);
+        if (p.Q > 8) return launch_edw_best<KS, 2, 16, 1>(p, stream, us);
     }
-    return launch_edw_best<KS, 2, 8, 1>(p, stream);
+    return launch_edw_best<KS, 2, 8, 1>(p, stream, us);
+}
+
+static int launch_edw(const ExpandDwParams& p, int stride, hipStream_t stream, double* us) {
+    const int ks = (p.Cin + 15) / 16;
+    if (ks <= 1) return launch_edw_ks<1>(p, stride, stream, us);
+    if (ks <= 2) return launch_edw_ks<2>(p, stride, stream, us);
+    if (ks <= 4) return launch_edw_ks<4>(p, stride, stream, us);
+    if (ks <= 6) return launch_edw_ks<6>(p, stride, stream, us);
+    return launch_edw_ks<10>(p, stride, stream, us);
 }
 
 bool expand_dw_supported(int Cin, int Chid, int stride) {
     return Cin >= 8 && Cin % 8 == 0 && Cin <= 160 && Chid >= 8 && Chid % 8 == 0 && (stride == 1 || stride == 2);
+}
+
+// One launch or two: the estimate above against that of the 1x1 and the depthwise launch, 8.2 us for the pair and its bytes (the
+// expanded tensor written and read, the output written) at 5.6 TB/s, 2.6 TB/s past the 250 MB that stay in the memory-side cache.
+// Measured on the served network's nine layers at image sides 160 and 224 and 8 to 128 images, one launch / two in us:
+// 224, 16 images: 56x56x24>144 20.8 / 17.8, stride 2 11.6 / 13.3, 28x28x32>192 9.3 / 11.1, 14x14x64>384 7.8 / 10.6, 7x7x160>960 7.6 /
+// 10.0; 64 images: 54.5 / 41.2, 31.7 / 32.9, 20.3 / 19.7, 17.8 / 14.5, 27.0 / 14.4; 112x112x16>96 stride 2 18.1 / 24.8 at 16 images,
+// 94 / 191 at 128.  Over these 162 the two-launch estimate is 8 % off on average, the choice costs 0.4 % of the sum of the better times
+// (always two launches: 17 %).  The one-launch estimate knows nothing of memory's rate, so where two launches take more than
+// 25 us only the layer whose expanded tensor dwarfs its input, at stride 2 its output too, is computed in one.
+bool expand_dw_pays(int N, int H, int W, int Cin, int Chid, int stride) {
+    if (N <= 0 || H <= 0 || W <= 0 || !expand_dw_supported(Cin, Chid, stride)) return false;
+    ExpandDwParams p{};
+    p.N = N; p.H = H; p.W = W; p.Cin = Cin; p.Chid = Chid;
+    p.P = (H - 1) / stride + 1; p.Q = (W - 1) / stride + 1;
+    const double mb = 2e-6 * N * Chid * (2.0 * H * W + (double)p.P * p.Q);
+    const double two = 8.2 + mb / 5.6 + std::max(0.0, mb - 250) / 9;
+    if (two > 25 && !(stride == 2 && Cin <= 16)) return false;
+    double one = 0;
+    (void)launch_edw(p, stride, nullptr, &one);
+    return one < 0.95 * two;
 }
 
 int launch_expand_dw(const half_t* x, int N, int H, int W, int Cin, const half_t* w1, int ldw1, const float* b1, int Chid, int act1,
@@ -385,12 +417,7 @@ int launch_expand_dw(const half_t* x, int N, int H, int W, int Cin, const half_t
     p.w1 = w1; p.ldw1 = ldw1; p.b1 = b1; p.Chid = Chid; p.act1 = act1;
     p.wd = wd_rsc; p.bd = bd; p.act2 = act2; p.y = y; p.hp = hp;
     p.P = (H - 1) / stride + 1; p.Q = (W - 1) / stride + 1;      // 3x3, padding 1
-    const int ks = (Cin + 15) / 16;
-    if (ks <= 1) return launch_edw_ks<1>(p, stride, stream);
-    if (ks <= 2) return launch_edw_ks<2>(p, stride, stream);
-    if (ks <= 4) return launch_edw_ks<4>(p, stride, stream);
-    if (ks <= 6) return launch_edw_ks<6>(p, stride, stream);
-    return launch_edw_ks<10>(p, stride, stream);
+    return launch_edw(p, stride, stream, nullptr);
 }
 
 }  // namespace strait

@@ -94,8 +94,10 @@ int launch_stem3x3s2_dw(const half_t* x, const half_t* wf, const float* bias, in
                         int N, int H, int W, half_t* y, int hp, hipStream_t stream);
 // 1x1 convolution Cin -> Chid (+ b1, act1) and the depthwise 3x3 of stride 1 or 2, padding 1, behind it (+ bd, act2) in one
 // launch (expand_dw.hip): x [N,H,W,Cin] -> y [N,P,Q,Chid]; w1 [Chid][ldw1], wd_rsc [3][3][Chid].  Bit-identical to the two
-// launches.  expand_dw_supported: whether the kernel takes these channel counts and this stride.
+// launches.  expand_dw_supported: whether the kernel takes these channel counts and this stride;
+// expand_dw_pays: whether it does and is estimated to be faster than the two launches.
 bool expand_dw_supported(int Cin, int Chid, int stride);
+bool expand_dw_pays(int N, int H, int W, int Cin, int Chid, int stride);
 int launch_expand_dw(const half_t* x, int N, int H, int W, int Cin, const half_t* w1, int ldw1, const float* b1, int Chid, int act1,
                      const half_t* wd_rsc, const float* bd, int stride, int act2, half_t* y, int hp, hipStream_t stream);
 int launch_dwconv3x3(const half_t* x, int N, int H, int W, int C, const half_t* w_rsc, const float* bias,

@@ -1011,12 +1011,9 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
         switch (op.kind) {
             case OP_CONV: {
                 // An inverted residual block's expansion and depthwise layer as one launch, the expanded tensor staying in
-                // LDS.  It pays where launches are what a batch costs (MobileNetV2 up to batch 8: -3.5 to -7 % per batch) and
-                // on the one layer whose expanded tensor dwarfs its input and output while two workgroups still fit a compute
-                // unit (112 x 112 x 16 -> 96 at stride 2: -10 % per batch of 64 or 128); elsewhere the two launches, each
-                // with every lane busy, are as fast or faster (all blocks fused at batch 64: +3 %).
+                // LDS, where that is estimated to be the faster way (expand_dw_pays).
                 if (op.dw_next && i + 1 <= last_layer && m.ctx->pair_min_pixels > 0 &&
-                    (batch <= 8 || (m.ops[i + 1].stride == 2 && op.vC <= 16 && (long long)batch * op.P * op.Q * op.K >= 36000000LL))) {
+                    expand_dw_pays(batch, op.P, op.Q, op.vC, op.K, m.ops[i + 1].stride)) {
                     const Op& dw = m.ops[i + 1];
                     rc = launch_expand_dw((const half_t*)src, batch, op.P, op.Q, op.vC, op.w, op.ldw, op.bias, op.K, op.act, dw.w, dw.bias,
                                           dw.stride, dw.act, (half_t*)slot_ptr(m, in, dw.out, dw.out_ref, batch), hp, stream);

@@ -130,8 +130,7 @@ def test_mobilenet_v2(ctx, hw, batch):
 
 
 def test_mobilenet_v2_fused_expansions_equal_separate_launches(ctx):
-    """Up to batch 8 every inverted residual block runs its expansion and its depthwise layer as one launch (and the
-    112 x 112 one at any batch large enough); the kernel takes the same arithmetic steps, so the whole network's output
+    """At batch 6 every inverted residual block runs its expansion and its depthwise layer as one launch; the kernel takes the same arithmetic steps, so the whole network's output
     must be bit-identical with the fusion switched off, and the oracle's within tolerance."""
     md = synth.mobilenet_v2(synth.SEEDS[synth.ARCH_MOBILENETV2])
     x = synth.default_image_batch(md, 6, 99)
@@ -144,6 +143,24 @@ def test_mobilenet_v2_fused_expansions_equal_separate_launches(ctx):
         assert np.array_equal(sep["logits"], fused["logits"]) and np.array_equal(sep["top1"], fused["top1"])
         ref = omodels.mobilenet_v2_forward(md.tensors, x)
         check_logits(fused["logits"], ref.logits, fused["top1"], "MobileNetV2 b6, fused expansions")
+    finally:
+        ctx.set_pair_fusion(40000)
+        m.free()
+
+
+@pytest.mark.parametrize("batch,hw", [(12, 224), (33, 96), (40, 160)])
+def test_mobilenet_v2_some_expansions_fused(ctx, batch, hw):
+    """Sizes at which one launch is estimated to be faster for some of the blocks and two for the others: bit for bit what the
+    network gives with the fusion switched off."""
+    md = synth.mobilenet_v2(synth.SEEDS[synth.ARCH_MOBILENETV2], hw)
+    x = synth.default_image_batch(md, batch, 98)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    try:
+        ctx.set_pair_fusion(0)
+        sep, _ = m.infer(x, prio=ctx.S.PRIO_LOW)
+        ctx.set_pair_fusion(40000)
+        fused, _ = m.infer(x, prio=ctx.S.PRIO_LOW)
+        assert np.array_equal(sep["logits"], fused["logits"]) and np.array_equal(sep["top1"], fused["top1"])
     finally:
         ctx.set_pair_fusion(40000)
         m.free()
