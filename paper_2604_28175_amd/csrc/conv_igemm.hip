@@ -1484,6 +1484,9 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
                 p.W >= 14 && p.Q == p.W && p.PQ == p.H * p.W) {
                 long long mv;
                 const int id = patch_tile(p, &mv);
+                // three rounds of 512 workgroups and more are the 256 x 128 patch tile's, whose estimate is too high there (56 x 56, 256 -> 256,
+                // 64 images: 206 us at 1150 TFLOP/s, estimated 301; VGG-19 b96 with the estimates' choice 4973 us a batch, with this tile 4750)
+                if (id == T_PATCH256x128 && (mv + 255) / 256 * (p.Cout / 128) >= 1536) return launch_tile_id(p, T_PATCH256x128, mode, stream);
                 if (id >= 0) consider((TileId)id, mv);
             }
         }
