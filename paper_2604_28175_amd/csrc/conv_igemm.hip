@@ -346,9 +346,16 @@ constexpr int dma_tile_waves_per_simd() {
 // workgroup's), and at the end groups 1.. hand their partial sums to group 0 through LDS, which adds them in group
 // order and finishes the tile.  A split reduction without a second launch, for the small batches where one more
 // launch costs as much as the convolution.
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int STAGES, bool GELU, bool HOIST, bool DUAL = false, int KG = 1>
+//
+// RES: how a residual is added.  RES_LATE: to the rounded product, fetched as the tile is stored.  RES_EARLY: likewise, but requested right
+// after the reduction, before the staging barrier: that takes its latency off the path between the last MFMA and the stores.
+// RES_WIDE, for few outputs behind a long reduction: it goes through the staging tile first and is added in fp32, so that the
+// sum is rounded once, as in the second launch of a split reduction and in conv_skinny.hip.  (A 128-token sequence through twelve
+// encoder layers: relative error against 64-bit arithmetic 1.42e-3, with a rounding before the add 1.46e-3.)
+enum { RES_LATE = 0, RES_EARLY = 1, RES_WIDE = 2 };
+template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int STAGES, bool GELU, int RES, bool DUAL = false, int KG = 1>
 __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG / 4 : dma_tile_waves_per_simd<BM, BN, BK, WGM, WGN, STAGES>())) conv_igemm_dma_kernel(const ConvParams p) {
-    static_assert(!DUAL || (MODE == MODE_1X1 && !HOIST && !GELU), "a second source belongs to a plain pointwise convolution");
+    static_assert(!DUAL || (MODE == MODE_1X1 && RES == RES_LATE && !GELU), "a second source belongs to a plain pointwise convolution");
     static_assert(KG == 1 || (!GELU && !DUAL && KG * STAGES * (BM + BN) * BK * 2 + 1024 <= 160 * 1024 && WGM * WGN * KG <= 16), "groups: LDS or workgroup limit");
     constexpr int CPRW = BK / 8;                       // 16-byte chunks per LDS row
     constexpr int RPI = 64 / CPRW;                     // rows covered by one wave-wide transfer
@@ -659,12 +666,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     // clamping one against 0, 6 or an infinity, gives the same fp16 result whether it is done in fp16 or
     // in fp32 and then rounded, and it takes a quarter of the instructions (short-reduction layers spend
     // most of their instructions here).  Bias and residual are fetched where they are used: holding
-    // them across the reduction would cost a wave per SIMD in registers.  Layers that add a residual
-    // (HOIST) request it right after the reduction, before the staging barrier: that takes its latency
-    // off the path between the last MFMA and the stores.
+    // them across the reduction would cost a wave per SIMD in registers.
     constexpr int CPR = BN / 8, NCH = BM * CPR / NT;
     half_t* Cs = smem_all;
-    const bool fuse_act = (p.res == nullptr);
+    const bool fuse_act = RES == RES_WIDE || p.res == nullptr;
     const half_t lo = (p.act == ACT_RELU || p.act == ACT_RELU6) ? (half_t)0.f : (half_t)-INFINITY;
     const half_t hi = p.act == ACT_RELU6 ? (half_t)6.f : (half_t)INFINITY;
     const half_t lo1 = fuse_act ? lo : (half_t)-INFINITY, hi1 = fuse_act ? hi : (half_t)INFINITY;
@@ -685,10 +690,20 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
         const float4 b4 = *(const float4*)(bias_s + wn0 + a * 32 + 8 * g + 4 * lh);
         bv[0] = b4.x; bv[1] = b4.y; bv[2] = b4.z; bv[3] = b4.w;
     };
-    half8 rv[HOIST ? NCH : 1];
-    if (HOIST && !fuse_act && finisher) {
+    half8 rv[RES == RES_EARLY ? NCH : 1];
+    if (RES == RES_EARLY && !fuse_act && finisher) {
 #pragma unroll
         for (int i = 0; i < NCH; ++i) rv[i] = residual_chunk(i);
+    }
+    if (RES == RES_WIDE) {
+        if (finisher) {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                const int id = tid + i * NT, row = id / CPR, c8 = id - row * CPR;
+                *(half8*)(Cs + row * LDC + c8 * 8) = residual_chunk(i);
+            }
+        }
+        __syncthreads();
     }
     if (finisher)
 #pragma unroll
@@ -700,15 +715,17 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             bias4(a, g, bv);
 #pragma unroll
             for (int b = 0; b < TMB; ++b) {
-                half4 h;
+                half4* const at = (half4*)(Cs + (wm0 + b * 32 + l32) * LDC + cn);
+                half4 h, r;
+                if (RES == RES_WIDE) r = *at;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     float v = acc[a][b][4 * g + j] + bv[j];
+                    if (RES == RES_WIDE) v += (float)r[j];
                     if (GELU) v = gelu_f(v);
                     h[j] = (half_t)v;
                 }
-                h = __builtin_elementwise_min(__builtin_elementwise_max(h, lo4), hi4);
-                *(half4*)(Cs + (wm0 + b * 32 + l32) * LDC + cn) = h;
+                *at = __builtin_elementwise_min(__builtin_elementwise_max(h, lo4), hi4);
             }
         }
     __syncthreads();
@@ -721,7 +738,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
         if (m < p.M && n < p.Cout) {
             half8 v = *(const half8*)(Cs + row * LDC + c8 * 8);
             if (!fuse_act) {
-                const half8 r = HOIST ? rv[i] : residual_chunk(i);
+                const half8 r = RES == RES_EARLY ? rv[i] : residual_chunk(i);
                 v = __builtin_elementwise_min(__builtin_elementwise_max(v + r, lo8), hi8);
             }
             *(half8*)((half_t*)p.y + (long long)m * p.ldy + n) = v;
@@ -1330,16 +1347,21 @@ static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
         return 0;
     };
     int rc;
-    if constexpr (KG > 1) {
-        if (mode == MODE_1X1 && p.res) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, true, false, KG>);
-        else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false, false, KG>);
-        else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, false, false, KG>);
+    if (p.res_f32 && p.ksplit == 1) {
+        if constexpr (BM <= 64 && BN == 64) {
+            if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_WIDE, false, KG>);
+            else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_WIDE, false, KG>);
+        } else { set_error("conv: this tile does not add a residual in fp32"); return -5; }
+    } else if constexpr (KG > 1) {
+        if (mode == MODE_1X1 && p.res) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY, false, KG>);
+        else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, KG>);
+        else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE, false, KG>);
     } else {
-        if (mode == MODE_1X1 && p.act == ACT_GELU) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, false>);
-        else if (mode == MODE_1X1 && p.x2) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false, true>);
-        else if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, true>);
-        else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, false>);
-        else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, false>);
+        if (mode == MODE_1X1 && p.act == ACT_GELU) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, RES_LATE>);
+        else if (mode == MODE_1X1 && p.x2) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, true>);
+        else if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY>);
+        else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE>);
+        else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE>);
     }
     if (rc) return rc;
     if (p.ksplit > 1) {
@@ -1453,6 +1475,9 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
     const long long lead = (long long)p.pad_h * p.sH + (long long)p.pad_w * p.sW;
     const bool small = (p.x_elems + lead) * 2 <= 0x7fffffffLL && (long long)p.Cout * p.ldw * 2 <= 0x7fffffffLL;
     p.ksplit = 1;
+    // Up to 128 tiles of 64 x 64 the residual's pass through LDS is little beside a reduction of more than 1024 (128 x 768 x 3072: 8.6 us, 8.5 without); larger
+    // layers, which their stores bound, add it to the rounded product.
+    p.res_f32 = p.res && p.Kg > 1024 && tiles(64, 64) <= 128;
     // (GELU after a residual add is left to the first kernel: the LDS-direct one applies GELU before the staging)
     const bool regular = (mode == MODE_1X1 && !(p.act == ACT_GELU && p.res)) || (mode == MODE_GATHER8 && p.C % 32 == 0 && p.R * p.S <= 32 && p.act != ACT_GELU);
     if (regular && small) {
@@ -1475,9 +1500,10 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
             for (int i = 0; i < T_DMA; ++i) {
                 const TileInfo& t = tile_info[i];
                 if (t.bk == 64 && gather && p.C % 64 != 0) continue;
+                if (p.res_f32 && (t.bm > 64 || t.bn > 64)) continue;                        // (the larger ones leave most compute units idle)
                 if (t.kg > 1 && (p.Kg < 512 || p.x2 || p.act == ACT_GELU)) continue;        // too short to split
                 if (i == T256x128s && p.Kg >= 512) continue;                                // a tile for streaming layers
-                if (t.bm < 128 && mb > 250) continue;                                       // estimates are not good for so many small tiles
+                if (t.bm < 128 && mb > 250 && !p.res_f32) continue;                                       // estimates are not good for so many small tiles
                 consider((TileId)i, p.M);
             }
             if (gather && p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 1 && p.pad_w == 1 && !p.res &&

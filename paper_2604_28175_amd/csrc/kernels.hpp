@@ -40,6 +40,7 @@ struct ConvParams {
     float* ws;               // optional split-K workspace (16-byte aligned) and its size in bytes
     size_t ws_bytes;
     int ksplit;              // filled in by launch_conv
+    int res_f32;             // add the residual in fp32, before the rounding; filled in by launch_conv
     int tile_cw;             // tile columns of a group in the kernels' tile order; filled in by the launcher
     int strip_w;             // 3x3 patch kernel: width of the strips a row is cut into; filled in by the launcher
     // Optional second source of a 1x1 convolution with stride 1 (a block-closing convolution that absorbs the block's 1x1

@@ -660,6 +660,26 @@ def test_gemm_tiles_integer_data_is_bit_exact(S, M, N, K, use_res):
     assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)
 
 
+@pytest.mark.parametrize("N,H,C,K,Rk", [
+    (97, 1, 3072, 768, 1), (128, 1, 3072, 768, 1), (192, 1, 3072, 768, 1),    # a transformer block's second product, one or two short sequences
+    (33, 1, 3072, 768, 1), (640, 1, 4096, 768, 1), (500, 1, 3104, 520, 1),    # fewer rows, the largest output (120 tiles), ragged everywhere
+    (1, 7, 512, 512, 3), (8, 14, 128, 256, 3), (3, 9, 160, 72, 3)])           # gathered: three sizes of output
+def test_residual_is_added_before_the_only_rounding(S, N, H, C, K, Rk):
+    """Long reductions for few outputs: products between 2048 and 4096, of which fp16 holds the even ones, and a residual that
+    leaves 0 or 1 of them.  Exact only if the sum is formed in fp32 and rounded once."""
+    kg = C * Rk * Rk
+    x = R.integers(0, 3, (N, H, H, C)).astype(np.float16)
+    w = (np.floor(2900 / kg) + (R.random((K, C, Rk, Rk)) < 2900 / kg % 1)).astype(np.float16)      # 2900 on average away from the border
+    b = R.integers(0, 6, K).astype(np.float32)
+    full = ops.conv2d(x, w, b, 1, Rk // 2)
+    inside = (full > 2048) & (full < 4096)
+    assert inside.mean() > 0.4
+    res = np.where(inside, -2 * np.floor(full / 2), 0)
+    want = np.where(inside, full + res, 0)
+    y = S.k_conv2d(dev(S, x), dev(S, np.ascontiguousarray(np.transpose(w, (0, 2, 3, 1)))), dev(S, b), 1, Rk // 2, 0, dev(S, res.astype(np.float16)))
+    assert np.array_equal(np.where(inside, y.float().cpu().numpy().astype(np.float64), 0), want)
+
+
 @pytest.mark.parametrize("N,H,C,K,Rk,stride,pad,use_res,out_f32", [
     (1, 7, 512, 512, 3, 1, 1, False, False),     # 49 pixels: a ragged fourth tile; 72 super-slices over four wavefronts
     (1, 14, 192, 40, 3, 2, 1, True, False),      # stride 2, channels ragged in the tile; 27 super-slices: unequal parts
