@@ -507,7 +507,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             dma16(second ? xrsrc2 : xrsrc, v, live ? soff_x : 0u, sx + (unsigned)((j * NW + wave) * 1024));
         } else {
             const int jw = j - XI;
-            dma16(wrsrc, live ? woff[jw] : OOB_OFFSET, live ? (unsigned)ki * (BK * 2) : 0u, sw + (unsigned)((jw * NW + wave) * 1024));
+            unsigned v = woff[jw];                     // (a weight row's ragged end is followed by the next row, which may hold infinities)
+            if (MODE == MODE_1X1 && ragged_k) v = (ki * BK + cl * 8 < p.Kg) ? v : OOB_OFFSET;
+            dma16(wrsrc, live ? v : OOB_OFFSET, live ? (unsigned)ki * (BK * 2) : 0u, sw + (unsigned)((jw * NW + wave) * 1024));
         }
     };
     auto advance = [&]() __attribute__((always_inline)) {

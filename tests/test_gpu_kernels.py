@@ -660,6 +660,19 @@ def test_gemm_tiles_integer_data_is_bit_exact(S, M, N, K, use_res):
     assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)
 
 
+@pytest.mark.parametrize("M,N,K", [(300, 64, 96), (9000, 256, 96), (9000, 256, 160), (6455, 1184, 136), (1000, 264, 40), (77, 40, 72)])
+def test_gemm_infinite_weights_stay_in_their_channel(S, M, N, K):
+    """Reductions that end inside a slice: what lies behind a weight row's end is the next row, whose infinities must not
+    meet the zeros that fill up the slice of the input."""
+    x = R.integers(1, 3, (M, K)).astype(np.float16)
+    w = R.integers(-1, 2, (N, K)).astype(np.float16)
+    want = x.astype(np.float64) @ w.astype(np.float64).T
+    w[3::7] = np.inf
+    want[:, 3::7] = np.inf
+    y = S.k_gemm(dev(S, x), dev(S, w), None)
+    assert np.array_equal(y.float().cpu().numpy().astype(np.float64), want)
+
+
 @pytest.mark.parametrize("N,H,C,K,Rk", [
     (97, 1, 3072, 768, 1), (128, 1, 3072, 768, 1), (192, 1, 3072, 768, 1),    # a transformer block's second product, one or two short sequences
     (33, 1, 3072, 768, 1), (640, 1, 4096, 768, 1), (500, 1, 3104, 520, 1),    # fewer rows, the largest output (120 tiles), ragged everywhere
