@@ -239,6 +239,11 @@ strait_status strait_k_conv2d(void* stream, const void* x, int32_t N, int32_t H,
                               const void* w_krsc, const float* bias, int32_t K, int32_t R, int32_t S,
                               int32_t stride, int32_t pad, int32_t act, const void* res, void* y,
                               int32_t out_f32, int32_t hp);
+/* The kernel and tile that strait_k_conv2d would take for such a layer, e.g. "128x128x64" or "patch 256x128" (res: whether a
+ * residual is added); NULL where it would refuse it.  Launches nothing and needs no GPU: for tests and tuning.  A product of
+ * strait_k_gemm is the layer N = M, H = W = R = S = stride = 1, pad = 0, C = K, K = N. */
+const char* strait_k_conv2d_kernel(int32_t N, int32_t H, int32_t W, int32_t C, int32_t K, int32_t R, int32_t S, int32_t stride,
+                                   int32_t pad, int32_t act, int32_t res, int32_t out_f32);
 /* Y[M,N] = act(X[M,K] W[N,K]^T + bias (+ res)); same kernel as the 1x1 convolution. */
 strait_status strait_k_gemm(void* stream, const void* x, const void* w, const float* bias, int32_t M,
                             int32_t N, int32_t K, int32_t act, const void* res, void* y, int32_t out_f32,

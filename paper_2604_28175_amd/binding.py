@@ -89,6 +89,7 @@ _SIGS = {
     "strait_run_timed": (_i32, [_vp, _i32, _i32, _i32, _vp]),
     "strait_read_activation": (_i32, [_vp, _i32, _i32, _i32, _vp, _sz, C.POINTER(_sz)]),
     "strait_k_conv2d": (_i32, [_vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32]),
+    "strait_k_conv2d_kernel": (C.c_char_p, [_i32] * 12),
     "strait_k_gemm": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32]),
     "strait_k_gemm_noalloc": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32]),
     "strait_k_conv1x1_proj": (_i32, [_vp, _vp, _i32, _i32, _i32, _i32, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32, _vp, _i32]),
@@ -363,6 +364,12 @@ def k_conv2d(x, w_krsc, bias, stride, pad, act=ACT_NONE, res=None, out_f32=False
     _check(lib.strait_k_conv2d(_stream(stream), _dev(x), n, h, w, c, _dev(w_krsc), _dev(bias), k, r, s, stride, pad,
                                act, _dev(res), _dev(y), int(out_f32), hp))
     return y
+
+
+def k_conv2d_kernel(n, h, w, c, k, r, stride, pad, act=ACT_NONE, res=False, out_f32=False) -> Optional[str]:
+    """Name of the kernel and tile that k_conv2d takes for such a layer (None: refused); needs no GPU."""
+    name = lib.strait_k_conv2d_kernel(n, h, w, c, k, r, r, stride, pad, act, int(res), int(out_f32))
+    return None if name is None else name.decode()
 
 
 def k_gemm(x, w, bias, act=ACT_NONE, res=None, out_f32=False, hp=0, stream=None):

@@ -770,24 +770,39 @@ strait_status strait_read_activation(strait_model* m, int32_t instance, int32_t 
 
 // ---- kernel-level entry points -----------------------------------------------------------------
 
-strait_status strait_k_conv2d(void* stream, const void* x, int32_t N, int32_t H, int32_t W, int32_t C,
-                              const void* w_krsc, const float* bias, int32_t K, int32_t R, int32_t S, int32_t stride,
-                              int32_t pad, int32_t act, const void* res, void* y, int32_t out_f32, int32_t hp) {
+static int conv2d_params(ConvParams& p, int32_t N, int32_t H, int32_t W, int32_t C, int32_t K, int32_t R, int32_t S, int32_t stride, int32_t pad,
+                         int32_t act, int32_t out_f32) {
     if (N <= 0 || H <= 0 || W <= 0 || C <= 0 || K <= 0 || R <= 0 || S <= 0 || stride <= 0 || pad < 0 ||
         H + 2 * pad < R || W + 2 * pad < S) { set_error("conv2d: invalid shape"); return STRAIT_E_SHAPE; }
     const int P = (H + 2 * pad - R) / stride + 1, Q = (W + 2 * pad - S) / stride + 1;
     if ((long long)N * P * Q > 0x7fffffffLL || (long long)R * S * C > 0x7fffffffLL) { set_error("conv2d: too large"); return STRAIT_E_SHAPE; }
-    ConvParams p{};
-    p.x = (const half_t*)x; p.bias = bias; p.res = (const half_t*)res; p.y = y;
     p.M = N * P * Q; p.PQ = P * Q; p.Q = Q; p.H = H; p.W = W; p.C = C; p.R = R; p.S = S;
     p.stride_h = p.stride_w = stride; p.pad_h = p.pad_w = pad;
     p.sN = (long long)H * W * C; p.sH = W * C; p.sW = C;
-    p.Kg = R * S * C; p.Cout = K; p.ldy = K; p.act = act; p.out_f32 = out_f32; p.hp = hp;
+    p.Kg = R * S * C; p.ldw = (p.Kg + 7) / 8 * 8; p.Cout = K; p.ldy = K; p.act = act; p.out_f32 = out_f32;
+    return 0;
+}
+
+const char* strait_k_conv2d_kernel(int32_t N, int32_t H, int32_t W, int32_t C, int32_t K, int32_t R, int32_t S, int32_t stride, int32_t pad,
+                                   int32_t act, int32_t res, int32_t out_f32) {
+    ConvParams p{};
+    if (conv2d_params(p, N, H, W, C, K, R, S, stride, pad, act, out_f32)) return nullptr;
+    half_t* const some = reinterpret_cast<half_t*>(256);        // any aligned address: nothing is launched
+    p.x = p.w = some; p.y = some; p.res = res ? some : nullptr; p.ws = (float*)some; p.ws_bytes = SPLITK_WS_BYTES;
+    return conv_kernel_name(p);
+}
+
+strait_status strait_k_conv2d(void* stream, const void* x, int32_t N, int32_t H, int32_t W, int32_t C,
+                              const void* w_krsc, const float* bias, int32_t K, int32_t R, int32_t S, int32_t stride,
+                              int32_t pad, int32_t act, const void* res, void* y, int32_t out_f32, int32_t hp) {
+    ConvParams p{};
+    const int bad = conv2d_params(p, N, H, W, C, K, R, S, stride, pad, act, out_f32);
+    if (bad) return bad;
+    p.x = (const half_t*)x; p.bias = bias; p.res = (const half_t*)res; p.y = y; p.hp = hp;
     void* tmp = nullptr;
-    if (p.Kg % 8 == 0) { p.w = (const half_t*)w_krsc; p.ldw = p.Kg; }
+    if (p.Kg % 8 == 0) p.w = (const half_t*)w_krsc;
     else {
         // rows padded with zeros to a multiple of 8 elements, as the kernel's 16-byte weight loads need
-        p.ldw = (p.Kg + 7) / 8 * 8;
         HIP_TRY(hipMalloc(&tmp, (size_t)K * p.ldw * 2));
         hipError_t e = hipMemsetAsync(tmp, 0, (size_t)K * p.ldw * 2, (hipStream_t)stream);
         if (e == hipSuccess) e = hipMemcpy2DAsync(tmp, (size_t)p.ldw * 2, w_krsc, (size_t)p.Kg * 2, (size_t)p.Kg * 2, K, hipMemcpyDeviceToDevice, (hipStream_t)stream);

@@ -1243,9 +1243,10 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
 // Against the thresholds used before (and with the pipelined loop): ResNet-50's layers 7 % faster on the sum over batch 1
 // to 128 (22 % at batch 1, 5 % at 128), an encoder layer's products 8 to 19 % from 1000 rows on and 20 to 32 % below.
 enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
-              T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64, T_COUNT };
+              T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64, T_ESTIMATED,
+              T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_REG128x128, T_REG128x64, T_REG64x64, T_COUNT };   // (these have no estimate)
 struct TileInfo { int bm, bn, bk, kg; bool shared; float c[7]; };   // shared: two or more workgroups fit a compute unit
-static const TileInfo tile_info[T_COUNT] = {
+static const TileInfo tile_info[T_ESTIMATED] = {
     {256, 256, 64, 1, false, {2.047f, 4.619f, 1.152f, 0.199f, 10.088f, 0.100f, 0.086f}},
     {256, 192, 64, 1, false, {1.482f, 4.048f, 0.952f, 0.175f, 7.991f, 0.100f, 0.108f}},
     {192, 128, 64, 1, false, {0.722f, 3.601f, 0.550f, 0.134f, 3.747f, 0.080f, 0.051f}},
@@ -1268,6 +1269,12 @@ static const TileInfo tile_info[T_COUNT] = {
     {128, 128, 32, 1, true, {2.534f, 1.637f, 0.369f, 0.f, 0.f, 0.217f, 0.f}},
     {256, 64, 32, 1, true, {3.575f, 0.f, 0.485f, 0.f, 0.f, 0.122f, 0.f}},
 };
+
+static const char* const tile_name[T_COUNT] = {
+    "256x256x64", "256x192x64", "192x128x64", "128x256x64", "128x128x64, 8 wavefronts", "128x128x64", "96x128x64", "64x128x64", "256x128x32", "128x64x32, 2 slices",
+    "128x64x32, 3 slices", "64x64x64", "64x64x32", "32x64x64", "64x64x64, 2 groups", "32x64x64, 4 groups", "small outputs 16x16", "small outputs 16x32",
+    "patch 256x128", "patch 128x128", "patch 256x64", "slabs 64x64x64", "slabs 64x64x32", "through registers 128x128", "through registers 128x64",
+    "through registers 64x64"};
 
 // The patch kernel's view of a layer: strips, bordered pixels (mv) and which of its tiles takes the layer (a TileId), or -1.
 static int patch_geometry(const ConvParams& p, int* strip_w, int* slots, long long* mv) {
@@ -1403,7 +1410,7 @@ static float estimate_us(const ConvParams& p, TileId id, long long pixels, bool 
                    t.c[6] * std::max(0.0, mb - 250.0));
 }
 
-static int launch_tile_id(const ConvParams& p, TileId id, int mode, hipStream_t stream) {
+static int launch_tile_id(const ConvParams& p, TileId id, int mode, bool staged, hipStream_t stream) {
     switch (id) {
         case T256x256: return launch_dma_tile<256, 256, 64, 2, 4, 2>(p, mode, stream);
         case T256x192: return launch_dma_tile<256, 192, 64, 4, 2, 2>(p, mode, stream);
@@ -1423,6 +1430,11 @@ static int launch_tile_id(const ConvParams& p, TileId id, int mode, hipStream_t 
         case T32x64_g4: return launch_dma_tile<32, 64, 64, 1, 2, 3, 4>(p, mode, stream);
         case T_SK16: return launch_conv_skinny(p, 16, mode == MODE_GATHER8, stream);
         case T_SK32: return launch_conv_skinny(p, 32, mode == MODE_GATHER8, stream);
+        case T_SLABS64: return launch_dma_tile<64, 64, 64, 2, 2, 3>(p, mode, stream);
+        case T_SLABS64s: return launch_dma_tile<64, 64, 32, 2, 2, 3>(p, mode, stream);
+        case T_REG128x128: return launch_tile<128, 128>(p, mode, staged, stream);
+        case T_REG128x64: return launch_tile<128, 64>(p, mode, staged, stream);
+        case T_REG64x64: return launch_tile<64, 64>(p, mode, staged, stream);
         default: return launch_conv3x3_patch(p, stream);
     }
 }
@@ -1442,8 +1454,8 @@ size_t conv_workspace_bytes(const ConvParams& p, size_t limit) {
     return ks > 1 ? (size_t)ks * p.M * p.Cout * 4 : 0;
 }
 
-int launch_conv(const ConvParams& params, hipStream_t stream) {
-    ConvParams p = params;
+// Checks a layer, fills in what the launchers derive and chooses its kernel: >= 0 a TileId, < 0 an error.
+static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
     if (!p.x || !p.w || !p.y || p.M <= 0 || p.Cout <= 0 || p.Kg <= 0 || p.C <= 0 || p.R <= 0 || p.S <= 0 ||
         p.Q <= 0 || p.PQ <= 0 || p.stride_h <= 0 || p.stride_w <= 0) {
         set_error("conv: invalid parameters"); return -1;
@@ -1466,11 +1478,11 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
     if ((reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.w) | reinterpret_cast<uintptr_t>(p.y) |
          reinterpret_cast<uintptr_t>(p.res)) & 15) { set_error("conv: pointers must be 16-byte aligned"); return -1; }
     const bool vec_ok = (p.C % 8 == 0) && (p.sW % 8 == 0) && (p.sH % 8 == 0) && (p.sN % 8 == 0);
-    int mode;
+    int& mode = *mode_out;
     if (vec_ok && p.R == 1 && p.S == 1 && p.pad_h == 0 && p.pad_w == 0) mode = MODE_1X1;
     else if (vec_ok) mode = MODE_GATHER8;
     else mode = MODE_SCALAR;
-    const bool staged = !p.out_f32 && (p.Cout % 8 == 0) && (p.ldy % 8 == 0);
+    const bool staged = *staged_out = !p.out_f32 && (p.Cout % 8 == 0) && (p.ldy % 8 == 0);
     auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * ((p.Cout + bn - 1) / bn); };
     const bool dense = mode == MODE_1X1 && p.stride_h == 1;
     p.x_elems = dense ? (long long)p.M * p.sW : (long long)(p.M / p.PQ) * p.sN;
@@ -1486,8 +1498,7 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
         const int ks = p.ws && (reinterpret_cast<uintptr_t>(p.ws) & 15) == 0 ? slab_split(p, p.ws_bytes) : 1;
         if (ks > 1) {
             p.ksplit = ks;
-            return mode == MODE_1X1 && p.Kg % 64 == 0 ? launch_dma_tile<64, 64, 64, 2, 2, 3>(p, mode, stream)
-                                                      : launch_dma_tile<64, 64, 32, 2, 2, 3>(p, mode, stream);
+            return mode == MODE_1X1 && p.Kg % 64 == 0 ? T_SLABS64 : T_SLABS64s;
         }
         const bool whole64 = p.Kg % 64 == 0 && p.C % 64 == 0;                 // slices of 64 never straddle a tap or the end
         const bool gather = mode == MODE_GATHER8;
@@ -1514,7 +1525,7 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
                 const int id = patch_tile(p, &mv);
                 // three rounds of 512 workgroups and more are the 256 x 128 patch tile's, whose estimate is too high there (56 x 56, 256 -> 256,
                 // 64 images: 206 us at 1150 TFLOP/s, estimated 301; VGG-19 b96 with the estimates' choice 4973 us a batch, with this tile 4750)
-                if (id == T_PATCH256x128 && (mv + 255) / 256 * (p.Cout / 128) >= 1536) return launch_tile_id(p, T_PATCH256x128, mode, stream);
+                if (id == T_PATCH256x128 && (mv + 255) / 256 * (p.Cout / 128) >= 1536) return T_PATCH256x128;
                 if (id >= 0) consider((TileId)id, mv);
             }
         }
@@ -1523,12 +1534,27 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
             consider(T_SK16, p.M);
             consider(T_SK32, p.M);
         }
-        if (best != T_COUNT) return launch_tile_id(p, best, mode, stream);
+        if (best != T_COUNT) return best;
     }
     if (p.x2) { set_error("conv: a second source needs the LDS-direct kernels (sizes out of their range)"); return -5; }
-    if (p.Cout > 64 && tiles(128, 128) >= 512) return launch_tile<128, 128>(p, mode, staged, stream);
-    if (tiles(128, 64) >= 512) return launch_tile<128, 64>(p, mode, staged, stream);
-    return launch_tile<64, 64>(p, mode, staged, stream);
+    if (p.Cout > 64 && tiles(128, 128) >= 512) return T_REG128x128;
+    if (tiles(128, 64) >= 512) return T_REG128x64;
+    return T_REG64x64;
+}
+
+int launch_conv(const ConvParams& params, hipStream_t stream) {
+    ConvParams p = params;
+    int mode = 0;
+    bool staged = false;
+    const int id = choose_conv(p, &mode, &staged);
+    return id < 0 ? id : launch_tile_id(p, (TileId)id, mode, staged, stream);
+}
+const char* conv_kernel_name(const ConvParams& params) {
+    ConvParams p = params;
+    int mode = 0;
+    bool staged = false;
+    const int id = choose_conv(p, &mode, &staged);
+    return id < 0 ? nullptr : tile_name[id];
 }
 
 }  // namespace strait

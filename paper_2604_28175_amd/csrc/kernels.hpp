@@ -53,6 +53,7 @@ struct ConvParams {
 };
 
 int launch_conv(const ConvParams& p, hipStream_t stream);
+const char* conv_kernel_name(const ConvParams& p);     // of the kernel and tile that launch_conv takes; null where it refuses the layer
 // Bytes of workspace (ConvParams::ws), at most `limit`, with which launch_conv splits this layer's reduction into slabs; 0 = it uses none.
 size_t conv_workspace_bytes(const ConvParams& p, size_t limit);
 // Small outputs with a reduction worth sharing out (conv_skinny.hip): 16 pixels x tn (16 or 32) channels per workgroup.  Called by
