@@ -1240,6 +1240,9 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
 // operand traffic and MFMAs.  The coefficients are non-negative least-squares fits (relative error) to measured times, 826
 // layer shapes on MI355X: the served networks' layers at batch 1 to 128 and image sides 160 to 256, token products of 32
 // to 16384 rows; mean error 5 to 9 %, and the estimated best is on average within 2 % of the measured best candidate.
+// The patch kernel's rows and the gathered 256 x 128 x 32 tile's c3 are fits to 240 more 3x3 layers (14 to 224 pixels wide, 32 to 512
+// channels in, 40 to 4500 tiles; mean error 3 to 12 %); the choice is then on average 2 % off the best there, before 7 % and up
+// to 1.7 times: 16 x 112 x 112, 64 -> 128 53 -> 41 us; 118 x 40 x 40 at stride 2, 160 -> 512 132 -> 83 us.
 // Against the thresholds used before (and with the pipelined loop): ResNet-50's layers 7 % faster on the sum over batch 1
 // to 128 (22 % at batch 1, 5 % at 128), an encoder layer's products 8 to 19 % from 1000 rows on and 20 to 32 % below.
 enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
@@ -1255,7 +1258,7 @@ static const TileInfo tile_info[T_ESTIMATED] = {
     {128, 128, 64, 1, true, {2.649f, 2.689f, 0.759f, 0.240f, 3.708f, 0.084f, 0.113f}},
     {96, 128, 64, 1, false, {0.949f, 3.098f, 0.360f, 0.089f, 1.597f, 0.060f, 0.082f}},
     {64, 128, 64, 1, true, {2.205f, 2.481f, 0.490f, 0.086f, 2.066f, 0.050f, 0.144f}},
-    {256, 128, 32, 1, true, {2.271f, 3.506f, 0.583f, 0.059f, 10.612f, 0.106f, 0.085f}},
+    {256, 128, 32, 1, true, {2.271f, 3.506f, 0.583f, 0.110f, 10.612f, 0.106f, 0.085f}},
     {128, 64, 32, 1, true, {2.823f, 0.742f, 0.358f, 0.056f, 2.304f, 0.069f, 0.143f}},
     {128, 64, 32, 1, true, {2.525f, 1.151f, 0.308f, 0.071f, 2.345f, 0.070f, 0.103f}},
     {64, 64, 64, 1, true, {2.454f, 1.311f, 0.339f, 0.075f, 0.715f, 0.031f, 0.200f}},
@@ -1265,9 +1268,9 @@ static const TileInfo tile_info[T_ESTIMATED] = {
     {32, 64, 64, 4, false, {1.316f, 2.420f, 0.391f, 0.174f, 0.f, 0.085f, 0.f}},
     {16, 16, 64, 4, true, {2.610f, 0.434f, 0.394f, 0.113f, 0.f, 0.f, 0.f}},
     {16, 32, 64, 4, true, {2.783f, 0.392f, 0.603f, 0.126f, 0.f, 0.f, 0.f}},
-    {256, 128, 32, 1, true, {0.f, 8.0f, 1.05f, 0.f, 0.f, 0.f, 0.f}},
-    {128, 128, 32, 1, true, {2.534f, 1.637f, 0.369f, 0.f, 0.f, 0.217f, 0.f}},
-    {256, 64, 32, 1, true, {3.575f, 0.f, 0.485f, 0.f, 0.f, 0.122f, 0.f}},
+    {256, 128, 32, 1, true, {1.258f, 4.155f, 0.580f, 0.f, 0.f, 0.163f, 0.069f}},
+    {128, 128, 32, 1, true, {2.342f, 2.491f, 0.376f, 0.f, 0.f, 0.129f, 0.142f}},
+    {256, 64, 32, 1, true, {2.515f, 4.531f, 0.328f, 0.f, 0.f, 0.057f, 0.052f}},
 };
 
 static const char* const tile_name[T_COUNT] = {
@@ -1276,7 +1279,7 @@ static const char* const tile_name[T_COUNT] = {
     "patch 256x128", "patch 128x128", "patch 256x64", "slabs 64x64x64", "slabs 64x64x32", "through registers 128x128", "through registers 128x64",
     "through registers 64x64"};
 
-// The patch kernel's view of a layer: strips, bordered pixels (mv) and which of its tiles takes the layer (a TileId), or -1.
+// The patch kernel's view of a layer: strips and bordered pixels (mv); -1 = not a layer of its.
 static int patch_geometry(const ConvParams& p, int* strip_w, int* slots, long long* mv) {
     int sw = p.W;
     while (sw > 64 && sw % 2 == 0) sw /= 2;
@@ -1288,22 +1291,19 @@ static int patch_geometry(const ConvParams& p, int* strip_w, int* slots, long lo
     return *mv >= (1LL << 24) - 4096 ? -1 : 0;         // the kernel's index arithmetic is exact below 2^24
 }
 static int patch_transfers(int bm, int nw, int slots) { return ((bm + 2 * slots + 2 + 15) / 16 + nw - 1) / nw; }
-static int patch_tile(const ConvParams& p, long long* mv) {
+// Whether the patch kernel's tile `id` takes the layer; *mv as above.
+static bool patch_takes(const ConvParams& p, TileId id, long long* mv) {
     int sw, wp;
-    if (patch_geometry(p, &sw, &wp, mv)) return -1;
-    if (p.Cout % 128 == 0) {
-        // a round and a half of workgroups at least: 8 waves on 256 x 128
-        if (((*mv + 255) / 256) * (p.Cout / 128) >= 768 && patch_transfers(256, 8, wp) <= 4) return T_PATCH256x128;
-        return patch_transfers(128, 4, wp) <= 6 ? T_PATCH128x128 : -1;
-    }
-    return p.Cout % 64 == 0 && patch_transfers(256, 4, wp) <= 8 ? T_PATCH256x64 : -1;
+    if (patch_geometry(p, &sw, &wp, mv)) return false;
+    if (id == T_PATCH256x128) return p.Cout % 128 == 0 && patch_transfers(256, 8, wp) <= 4;
+    if (id == T_PATCH128x128) return p.Cout % 128 == 0 && patch_transfers(128, 4, wp) <= 6;
+    return id == T_PATCH256x64 && p.Cout % 64 == 0 && p.Cout % 128 != 0 && patch_transfers(256, 4, wp) <= 8;
 }
-static int launch_conv3x3_patch(const ConvParams& params, hipStream_t stream) {
+static int launch_conv3x3_patch(const ConvParams& params, TileId id, hipStream_t stream) {
     ConvParams p = params;
     int wp;
     long long mv;
-    const int id = patch_tile(p, &mv);
-    if (id < 0 || patch_geometry(p, &p.strip_w, &wp, &mv)) { set_error("conv: not a layer of the patch kernel"); return -5; }
+    if (!patch_takes(p, id, &mv) || patch_geometry(p, &p.strip_w, &wp, &mv)) { set_error("conv: not a layer of the patch kernel"); return -5; }
     if (id == T_PATCH256x128) {
         if (patch_transfers(256, 8, wp) <= 3) return launch_patch_tile<256, 128, 4, 2, 3, 3>(p, mv, stream);
         return launch_patch_tile<256, 128, 4, 2, 4, 3>(p, mv, stream);
@@ -1435,7 +1435,7 @@ static int launch_tile_id(const ConvParams& p, TileId id, int mode, bool staged,
         case T_REG128x128: return launch_tile<128, 128>(p, mode, staged, stream);
         case T_REG128x64: return launch_tile<128, 64>(p, mode, staged, stream);
         case T_REG64x64: return launch_tile<64, 64>(p, mode, staged, stream);
-        default: return launch_conv3x3_patch(p, stream);
+        default: return launch_conv3x3_patch(p, id, stream);
     }
 }
 
@@ -1515,18 +1515,16 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
                 if (t.bk == 64 && gather && p.C % 64 != 0) continue;
                 if (p.res_f32 && (t.bm > 64 || t.bn > 64)) continue;                        // (the larger ones leave most compute units idle)
                 if (t.kg > 1 && (p.Kg < 512 || p.x2 || p.act == ACT_GELU)) continue;        // too short to split
-                if (i == T256x128s && p.Kg >= 512) continue;                                // a tile for streaming layers
+                if (i == T256x128s && p.Kg >= 512 && !(gather && p.C % 64 != 0)) continue;  // a tile for streaming layers, and for channels in halves of a slice
                 if (t.bm < 128 && mb > 250 && !p.res_f32) continue;                                       // estimates are not good for so many small tiles
                 consider((TileId)i, p.M);
             }
             if (gather && p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 1 && p.pad_w == 1 && !p.res &&
                 p.W >= 14 && p.Q == p.W && p.PQ == p.H * p.W) {
-                long long mv;
-                const int id = patch_tile(p, &mv);
-                // three rounds of 512 workgroups and more are the 256 x 128 patch tile's, whose estimate is too high there (56 x 56, 256 -> 256,
-                // 64 images: 206 us at 1150 TFLOP/s, estimated 301; VGG-19 b96 with the estimates' choice 4973 us a batch, with this tile 4750)
-                if (id == T_PATCH256x128 && (mv + 255) / 256 * (p.Cout / 128) >= 1536) return T_PATCH256x128;
-                if (id >= 0) consider((TileId)id, mv);
+                for (int i = T_PATCH256x128; i <= T_PATCH256x64; ++i) {
+                    long long mv;
+                    if (patch_takes(p, (TileId)i, &mv)) consider((TileId)i, mv);
+                }
             }
         }
         // short reductions stay with the kernel that reads operands through LDS; fp32 output has no other kernel
