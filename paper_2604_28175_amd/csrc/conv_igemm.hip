@@ -1246,8 +1246,8 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
 // Against the thresholds used before (and with the pipelined loop): ResNet-50's layers 7 % faster on the sum over batch 1
 // to 128 (22 % at batch 1, 5 % at 128), an encoder layer's products 8 to 19 % from 1000 rows on and 20 to 32 % below.
 enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
-              T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64, T_ESTIMATED,
-              T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_REG128x128, T_REG128x64, T_REG64x64, T_COUNT };   // (these have no estimate)
+              T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64,
+              T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_COUNT };   // (slabs have no estimate)
 struct TileInfo { int bm, bn, bk, kg; bool shared; float c[7]; };   // shared: two or more workgroups fit a compute unit
 static const TileInfo tile_info[T_ESTIMATED] = {
     {256, 256, 64, 1, false, {2.047f, 4.619f, 1.152f, 0.199f, 10.088f, 0.100f, 0.086f}},
@@ -1271,13 +1271,16 @@ static const TileInfo tile_info[T_ESTIMATED] = {
     {256, 128, 32, 1, true, {1.258f, 4.155f, 0.580f, 0.f, 0.f, 0.163f, 0.069f}},
     {128, 128, 32, 1, true, {2.342f, 2.491f, 0.376f, 0.f, 0.f, 0.129f, 0.142f}},
     {256, 64, 32, 1, true, {2.515f, 4.531f, 0.328f, 0.f, 0.f, 0.057f, 0.052f}},
+    {128, 128, 32, 1, true, {0.f, 13.979f, 0.756f, 0.205f, 0.f, 0.230f, 0.f}},
+    {128, 64, 32, 1, true, {1.775f, 6.853f, 0.583f, 0.123f, 0.f, 0.218f, 0.f}},
+    {64, 64, 32, 1, true, {3.299f, 3.197f, 0.383f, 0.f, 0.f, 0.147f, 0.f}},
 };
 
 static const char* const tile_name[T_COUNT] = {
     "256x256x64", "256x192x64", "192x128x64", "128x256x64", "128x128x64, 8 wavefronts", "128x128x64", "96x128x64", "64x128x64", "256x128x32", "128x64x32, 2 slices",
     "128x64x32, 3 slices", "64x64x64", "64x64x32", "32x64x64", "64x64x64, 2 groups", "32x64x64, 4 groups", "small outputs 16x16", "small outputs 16x32",
-    "patch 256x128", "patch 128x128", "patch 256x64", "slabs 64x64x64", "slabs 64x64x32", "through registers 128x128", "through registers 128x64",
-    "through registers 64x64"};
+    "patch 256x128", "patch 128x128", "patch 256x64", "through registers 128x128", "through registers 128x64", "through registers 64x64",
+    "slabs 64x64x64", "slabs 64x64x32"};
 
 // The patch kernel's view of a layer: strips and bordered pixels (mv); -1 = not a layer of its.
 static int patch_geometry(const ConvParams& p, int* strip_w, int* slots, long long* mv) {
@@ -1397,13 +1400,13 @@ static int launch_tile(const ConvParams& p, int mode, bool staged, hipStream_t s
     return 0;
 }
 
-static float estimate_us(const ConvParams& p, TileId id, long long pixels, bool gather, double mb) {
+static float estimate_us(const ConvParams& p, TileId id, long long pixels, bool gather, bool staged, double mb) {
     const TileInfo& t = tile_info[id];
     const long long tiles = (pixels + t.bm - 1) / t.bm * ((p.Cout + t.bn - 1) / t.bn);
     const long long per_cu = (tiles + 255) / 256;
     const double nk = std::ceil((double)p.Kg / (t.bk * t.kg));
     double r;
-    if (id == T_SK16 || id == T_SK32) r = std::max(1.0, tiles / 256.0);
+    if (id == T_SK16 || id == T_SK32) r = staged ? std::max(1.0, tiles / 256.0) : (double)per_cu;     // (the better fit in each case)
     else if (!t.shared) r = (double)per_cu;
     else r = per_cu > 8 ? tiles / 512.0 : per_cu / 2 + (per_cu % 2 ? 0.6 : 0.0);
     return (float)(t.c[0] + r * (t.c[1] + nk * (t.c[2] + (gather ? t.c[3] : 0.f)) + (p.act == ACT_GELU ? t.c[4] : 0.f)) + t.c[5] * mb +
@@ -1439,19 +1442,24 @@ static int launch_tile_id(const ConvParams& p, TileId id, int mode, bool staged,
     }
 }
 
-// A reduction of 16384 or more for 16 rows or more and a handful of tiles (the first fully connected layer of a plain CNN): bound
-// by the bytes of weights in flight, it is split over up to 32 workgroups per tile with fp32 slabs and a second launch
-// (64 rows, 25088 -> 4096: 54 us against 91 us in one launch; below 16 rows the kernel of conv_skinny.hip is faster, 38 against
-// 45 us at 6 rows).  Returns the number of parts whose slabs fit in `limit` bytes; 1 = no split.
-static int slab_split(const ConvParams& p, size_t limit) {
-    if (p.Kg < 16384 || p.M < 16 || p.x2 || p.Cout % 8 != 0 || p.ldy % 8 != 0) return 1;
+// Up to 128 tiles of 64 x 64, split over up to 32 workgroups each that leave fp32 slabs, which a second launch adds: the number of parts
+// (at least four 64-wide slices each, slabs of at most `limit` bytes) with the smallest estimate, which *us receives; 1 = no split.
+// The estimate is a fit like the table's, to 200 layers of 8 to 4096 channels and reductions of 512 to 32768, each in 2 to 48 parts
+// (mean error 7 %; its number of parts is on average within 5 % of the best): the two launches, a round of workgroups, a slice,
+// the slabs' bytes, the finishing launch's chain of slabs, the operands' bytes; and no faster than 6.2 TB/s of operands.
+static int slab_split(const ConvParams& p, size_t limit, bool gather, float* us) {
+    int best = 1;
+    *us = 1e30f;
     const long long t = (long long)((p.M + 63) / 64) * ((p.Cout + 63) / 64);
-    if (t > 128) return 1;
-    return (int)std::max<long long>(1, std::min<long long>({32, (1280 + t - 1) / t, (long long)(limit / ((size_t)p.M * p.Cout * 4))}));
-}
-size_t conv_workspace_bytes(const ConvParams& p, size_t limit) {
-    const int ks = slab_split(p, limit);
-    return ks > 1 ? (size_t)ks * p.M * p.Cout * 4 : 0;
+    if (t > 128 || p.x2 || p.Cout % 8 != 0 || p.ldy % 8 != 0) return 1;
+    const double slab_mb = (double)p.M * p.Cout * 4e-6, operand_mb = ((double)p.x_elems + (double)p.Cout * p.Kg) * 2e-6;
+    for (int ks : {2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+        const double nk = std::ceil(p.Kg / 64.0 / ks), r = std::max(1.0, (double)(t * ks) / 512.0);
+        if (nk < 4 || (size_t)ks * p.M * p.Cout * 4 > limit) break;
+        const float e = (float)std::max(2.0 + operand_mb / 6.2, 5.093 + r * (0.586 + nk * (gather ? 0.287 : 0.181)) + 0.651 * ks * slab_mb + 0.111 * ks + 0.064 * operand_mb);
+        if (e < *us) { *us = e; best = ks; }
+    }
+    return best;
 }
 
 // Checks a layer, fills in what the launchers derive and chooses its kernel: >= 0 a TileId, < 0 an error.
@@ -1488,6 +1496,10 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
     p.x_elems = dense ? (long long)p.M * p.sW : (long long)(p.M / p.PQ) * p.sN;
     const long long lead = (long long)p.pad_h * p.sH + (long long)p.pad_w * p.sW;
     const bool small = (p.x_elems + lead) * 2 <= 0x7fffffffLL && (long long)p.Cout * p.ldw * 2 <= 0x7fffffffLL;
+    auto through_registers = [&]() {
+        if (p.Cout > 64 && tiles(128, 128) >= 512) return T_REG128x128;
+        return tiles(128, 64) >= 512 ? T_REG128x64 : T_REG64x64;
+    };
     p.ksplit = 1;
     // Up to 128 tiles of 64 x 64 the residual's pass through LDS is little beside a reduction of more than 1024 (128 x 768 x 3072: 8.6 us, 8.5 without); larger
     // layers, which their stores bound, add it to the rounded product.
@@ -1495,18 +1507,13 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
     // (GELU after a residual add is left to the first kernel: the LDS-direct one applies GELU before the staging)
     const bool regular = (mode == MODE_1X1 && !(p.act == ACT_GELU && p.res)) || (mode == MODE_GATHER8 && p.C % 32 == 0 && p.R * p.S <= 32 && p.act != ACT_GELU);
     if (regular && small) {
-        const int ks = p.ws && (reinterpret_cast<uintptr_t>(p.ws) & 15) == 0 ? slab_split(p, p.ws_bytes) : 1;
-        if (ks > 1) {
-            p.ksplit = ks;
-            return mode == MODE_1X1 && p.Kg % 64 == 0 ? T_SLABS64 : T_SLABS64s;
-        }
         const bool whole64 = p.Kg % 64 == 0 && p.C % 64 == 0;                 // slices of 64 never straddle a tap or the end
         const bool gather = mode == MODE_GATHER8;
-        const double mb = ((double)p.x_elems * 2 + (double)p.Cout * p.Kg * 2 + (double)p.M * p.Cout * 2 * (p.res ? 2 : 1)) * 1e-6;
+        const double mb = ((double)p.x_elems * 2 + (double)p.Cout * p.Kg * 2 + (double)p.M * p.Cout * ((p.out_f32 ? 4 : 2) + (p.res ? 2 : 0))) * 1e-6;
         TileId best = T_COUNT;
         float best_us = 1e30f;
         auto consider = [&](TileId id, long long pixels) {
-            const float us = estimate_us(p, id, pixels, gather, mb);
+            const float us = estimate_us(p, id, pixels, gather, staged, mb);
             if (us < best_us) { best_us = us; best = id; }
         };
         if (staged) {
@@ -1526,18 +1533,34 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
                     if (patch_takes(p, (TileId)i, &mv)) consider((TileId)i, mv);
                 }
             }
+        } else {
+            // fp32 outputs, and counts of channels that are no whole chunks: the register-staged kernel on the tile that fills the chip,
+            // against the small-output kernel further down.  With fp32 outputs 16384 x 768 x 4096 takes 168 us here and 1034 there, 2221 x
+            // 1000 x 768 22 and 47, 9 x 1000 x 2048, a classifier, 23 and 5.5.  230 layers: the choice is on average
+            // 2.6 % off the better of the two.
+            consider(through_registers(), p.M);
         }
-        // short reductions stay with the kernel that reads operands through LDS; fp32 output has no other kernel
-        if (whole64 && (p.out_f32 || p.Kg >= 192) && tiles(16, 16) <= 0x7fffffffLL && mb <= 250) {
+        // short reductions to whole fp16 chunks stay with the kernels that read operands through LDS
+        if (whole64 && (!staged || p.Kg >= 192) && tiles(16, 16) <= 0x7fffffffLL && mb <= 250) {
             consider(T_SK16, p.M);
             consider(T_SK32, p.M);
+        }
+        // A split reduction for few outputs, where the kernels above leave compute units idle behind a long chain; fp16 outputs of at most
+        // 4608 had none that gained.  385 x 1024 x 8192 with fp32 outputs: 20 us against 87 with small outputs; 399 x 768 x 8192: 19
+        // against 65; 13 x 1000 x 25088 in fp16: 16 against 41.  A fifth is asked of it against kernels that share the
+        // reduction out themselves: with that none of the 200 layers measured is slower for it.
+        if ((!staged || p.Kg > 4608) && p.ws && (reinterpret_cast<uintptr_t>(p.ws) & 15) == 0) {
+            float us;
+            const int ks = slab_split(p, p.ws_bytes, gather, &us);
+            if (ks > 1 && us < (best >= T_REG128x128 ? 1.f : 0.8f) * best_us) {
+                p.ksplit = ks;
+                return whole64 ? T_SLABS64 : T_SLABS64s;
+            }
         }
         if (best != T_COUNT) return best;
     }
     if (p.x2) { set_error("conv: a second source needs the LDS-direct kernels (sizes out of their range)"); return -5; }
-    if (p.Cout > 64 && tiles(128, 128) >= 512) return T_REG128x128;
-    if (tiles(128, 64) >= 512) return T_REG128x64;
-    return T_REG64x64;
+    return through_registers();
 }
 
 int launch_conv(const ConvParams& params, hipStream_t stream) {
@@ -1546,6 +1569,15 @@ int launch_conv(const ConvParams& params, hipStream_t stream) {
     bool staged = false;
     const int id = choose_conv(p, &mode, &staged);
     return id < 0 ? id : launch_tile_id(p, (TileId)id, mode, staged, stream);
+}
+size_t conv_workspace_bytes(const ConvParams& params, size_t limit) {
+    ConvParams p = params;
+    p.ws = (float*)256;                                // any aligned address: nothing is launched
+    p.ws_bytes = limit;
+    int mode = 0;
+    bool staged = false;
+    const int id = choose_conv(p, &mode, &staged);
+    return id == T_SLABS64 || id == T_SLABS64s ? (size_t)p.ksplit * p.M * p.Cout * 4 : 0;
 }
 const char* conv_kernel_name(const ConvParams& params) {
     ConvParams p = params;

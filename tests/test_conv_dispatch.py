@@ -14,3 +14,24 @@ def test_wide_3x3_layers_between_the_measured_networks():
                                      (588, 14, 512, 64, 1, "patch 256x64"), (64, 56, 256, 256, 1, "patch 256x128"),
                                      (118, 40, 160, 512, 2, "256x128x32"), (60, 10, 160, 2048, 1, "256x128x32")):
         assert S.k_conv2d_kernel(n, h, h, c, k, 3, stride, 1) == want, (n, h, c, k, stride)
+
+
+def test_outputs_that_are_no_whole_fp16_chunks():
+    """fp32 outputs and odd numbers of channels: large products go through registers, few outputs to the kernels that share the
+    reduction out (they had all been given the small-output kernel, up to six times slower)."""
+    def gemm(m, n, k, out_f32=True):
+        return S.k_conv2d_kernel(m, 1, 1, k, n, 1, 1, 0, out_f32=out_f32)
+    assert gemm(16384, 768, 4096) == gemm(8192, 1001, 1024, False) == "through registers 128x128"
+    assert gemm(4096, 1000, 2048) == gemm(4096, 1001, 2048, False) == "through registers 128x64"
+    assert gemm(600, 1001, 256) == gemm(2221, 1000, 768) == "through registers 64x64"
+    assert gemm(9, 1000, 2048) == gemm(3, 10, 64) == gemm(12, 1001, 2048, False) == "small outputs 16x16"
+    assert gemm(385, 1024, 8192) == gemm(270, 512, 4096) == "slabs 64x64x64"
+
+
+def test_long_reductions_are_split_again():
+    def gemm(m, n, k):
+        return S.k_conv2d_kernel(m, 1, 1, k, n, 1, 1, 0)
+    assert gemm(13, 1000, 25088) == gemm(20, 64, 16384) == gemm(533, 64, 16320) == "slabs 64x64x64"
+    assert gemm(9, 72, 16352) == "slabs 64x64x32"                       # no whole slices of 64
+    assert gemm(6, 4096, 25088) == "small outputs 16x16"                # bound by its weights: nothing to gain
+    assert gemm(64, 768, 4096).startswith(("32x64x64", "64x64x64", "small"))

@@ -727,3 +727,26 @@ def test_small_outputs_gelu_and_second_source(S):
     ref = np.concatenate([x1, x2[:, ::2, ::2]], -1).astype(np.float64) @ wp.astype(np.float64).T + bp
     y = S.k_conv1x1_proj(dev(S, x1), dev(S, x2), 2, dev(S, wp), dev(S, bp))
     assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("N,H,C,K,Rk,act,use_res,out_f32,kernel", [
+    (13, 1, 25088, 1000, 1, 0, False, False, "slabs 64x64x64"),      # ragged rows and channels, 392 slices over many parts
+    (9, 1, 16352, 72, 1, 1, True, False, "slabs 64x64x32"),          # a reduction of no whole 64-wide slices, residual and ReLU in the second launch
+    (385, 1, 8192, 1024, 1, 0, True, True, "slabs 64x64x64"),        # 112 tiles in a few parts, fp32 residual sums out
+    (270, 1, 4096, 512, 1, 2, False, True, "slabs 64x64x64"),        # ReLU6
+    (8, 7, 1024, 512, 3, 0, True, True, "slabs 64x64x64"),           # gathered: parts start in the middle of a filter
+    (2, 9, 544, 64, 3, 0, False, False, "slabs 64x64x32")])          # ... with channels in halves of a slice
+def test_split_reductions_integer_data_is_bit_exact(S, N, H, C, K, Rk, act, use_res, out_f32, kernel):
+    """Few outputs behind a long reduction: fp32 slabs of several workgroups per tile, added and finished by a second launch.
+    Small integers: exact in any order."""
+    assert S.k_conv2d_kernel(N, H, H, C, K, Rk, 1, Rk // 2, act, use_res, out_f32) == kernel
+    x = R.integers(-2, 3, (N, H, H, C)).astype(np.float16)
+    w = (R.integers(-1, 2, (K, C, Rk, Rk)) * (R.random((K, C, Rk, Rk)) < 0.1)).astype(np.float16)
+    b = R.integers(-5, 6, K).astype(np.float32)
+    ref = ops.conv2d(x, w, b, 1, Rk // 2)
+    res = R.integers(-9, 10, ref.shape).astype(np.float16) if use_res else None
+    ref = act_ref(ref + (0 if res is None else res.astype(np.float64)), act)
+    assert np.abs(ref).max() < 2048
+    y = S.k_conv2d(dev(S, x), dev(S, np.ascontiguousarray(np.transpose(w, (0, 2, 3, 1)))), dev(S, b), 1, Rk // 2, act,
+                   None if res is None else dev(S, res), out_f32)
+    assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)

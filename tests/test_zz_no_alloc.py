@@ -43,6 +43,22 @@ def test_gemm_noalloc_equals_gemm_two_calls_in_a_row():
         check_kernel(y.float().cpu().numpy(), ref, f"gemm_noalloc {M}x{N}x{K}")
 
 
+def test_gemm_noalloc_split_reductions_equal_gemm():
+    """Products whose reduction is split: the slabs in the static array give the bits of the slabs in allocated memory, also
+    where a smaller product follows a larger one."""
+    import torch
+    import paper_2604_28175_amd as S
+    for M, N, K, use_res, out_f32 in ((385, 1024, 8192, True, True), (13, 1000, 25088, False, False), (9, 72, 16352, True, False)):
+        assert S.k_conv2d_kernel(M, 1, 1, K, N, 1, 1, 0, res=use_res, out_f32=out_f32).startswith("slabs")
+        x, w, b, res, ref = operands(torch, M, N, K, use_res)
+        want = S.k_gemm(x, w, b, S.ACT_NONE, res, out_f32)
+        y = torch.full((M, N), float("nan"), dtype=torch.float32 if out_f32 else torch.float16, device="cuda")
+        S.k_gemm_noalloc(x, w, b, y, S.ACT_NONE, res, out_f32)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want), f"gemm_noalloc {M}x{N}x{K} differs from gemm"
+        check_kernel(y.float().cpu().numpy(), ref, f"gemm_noalloc {M}x{N}x{K}")
+
+
 def test_gemm_noalloc_rejects_sizes_beyond_its_workspace():
     import torch
     import paper_2604_28175_amd as S
