@@ -67,7 +67,9 @@ typedef struct strait_ticket_s* strait_ticket;
 /* Context: one GPU plus the streams the caller created for it (Section 3.1: the priority of a
  * model selects the stream its batches run on).  n_hp/n_lp >= 1, n_copy >= 1, each at most
  * STRAIT_MAX_STREAMS.  A batch of priority p is issued on compute stream p[i % n_p] and its
- * host-to-device copy on copy_streams[j % n_copy] (i, j: running counters). */
+ * host-to-device copy on copy_streams[j % n_copy] (i, j: running counters); a small input whose compute stream is idle goes
+ * in on that instead.  While a batch is in flight a thread of the
+ * library polls for its result, one per compute stream, and a thread in strait_wait polls for up to 0.5 ms before it sleeps. */
 typedef struct {
     int32_t device;
     int32_t n_hp, n_lp, n_copy;
@@ -100,9 +102,9 @@ typedef struct {
     int64_t t_enqueue_ns;      /* host time at entry of strait_submit                       */
     int64_t t_issued_ns;       /* host time when everything had been enqueued               */
     int64_t t_done_ns;         /* host time the result was seen to be in host memory        */
-    float h2d_ms;              /* input copy                                                */
+    float h2d_ms;              /* input copy: its own time on the link, without waits between the pieces it travels in */
     float kernel_ms;           /* first kernel start to last kernel end                     */
-    float d2h_ms;              /* output copy                                               */
+    float d2h_ms;              /* output copy (that of 4 MB or more starts some us after the kernels, which only total_ms holds) */
     float total_ms;            /* start of input copy to end of output copy                 */
 } strait_record;
 
@@ -167,8 +169,10 @@ strait_status strait_ctx_set_branch_streams(strait_ctx* ctx, int32_t enabled);
 /* How inputs travel from the instance's pinned buffer to the device (Section 2 of the paper: inputs are
  * "copied to the GPU's memory" before the kernels run; the first-in first-out link of Section 3.2).
  * Inputs of at most max_bytes are read over the host link by a copy kernel, on the compute stream if that is idle and on
- * a copy stream beside its work otherwise; larger ones go by hipMemcpyAsync on a copy stream.  Both sit between the
- * same two timestamps, so records and the link model see no difference.  Default 8 MiB (every serving-sized batch): under concurrent
+ * a copy stream beside its work otherwise; larger ones go by hipMemcpyAsync on a copy stream.  An input in ordinary memory
+ * travels in pieces (from 512 KB or 4 MB on), copied to pinned memory while the piece before is on the link; pieces of batches
+ * submitted from several threads may alternate on a copy stream.  A record's h2d_ms is the time its own pieces take on the link, found
+ * for those of hipMemcpyAsync from the whole transfer and the times at which the host handed them over.  Default 8 MiB (every serving-sized batch): under concurrent
  * serving the asynchronous copy call of such sizes was measured to block its caller for milliseconds
  * now and then, a kernel launch never.  0 = always hipMemcpyAsync. */
 strait_status strait_ctx_set_h2d_kernel_limit(strait_ctx* ctx, int64_t max_bytes);

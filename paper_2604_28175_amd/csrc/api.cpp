@@ -136,6 +136,7 @@ static int await_result(Context* ctx, StreamWorker* w, Ticket* t, int64_t* done)
     if (t->out_pending) {
         if (await_flag(&in.ctl->k1_seq, t->seq, w->stream, ctx->compute_mu[t->worker])) return STRAIT_E_HIP;
         std::lock_guard<std::mutex> lk(ctx->copy_mu[t->copy]);
+        ++ctx->copy_seq[t->copy];
         if (launch_copy_out(in.dev_out, in.pinned_out_dev, t->model->out_bytes(t->batch), in.ctl_dev, in.counters + 1, t->seq, true, t->hp, s)) return STRAIT_E_HIP;
     }
     if (t->chunks > 1) {
@@ -149,6 +150,23 @@ static int await_result(Context* ctx, StreamWorker* w, Ticket* t, int64_t* done)
     return t->copy_status.load(std::memory_order_relaxed);
 }
 
+// The time that the pieces of an input take on the link, `span` from `start` (host clock) to the end of the last, waits for the host's own
+// copying between them left out: that of a first-in first-out link which is handed the pieces when this one was and ends when this one
+// did, its rate found by bisection.  With `last`, the time of the last piece, its rate stands for all of them.
+static float link_ms(const InputTiming& it, int64_t start, float span, float last) {
+    double total = 0;
+    for (int i = 0; i < it.pieces; ++i) total += (double)it.bytes[i];
+    if (last > 0) return (float)(last * total / it.bytes[it.pieces - 1]);
+    double lo = 0, hi = span;                          // time for all bytes
+    for (int n = 0; it.pieces > 1 && n < 40; ++n) {
+        const double mid = 0.5 * (lo + hi);
+        double end = 0;
+        for (int i = 0; i < it.pieces; ++i) end = std::max(end, (double)(it.handed[i] - start) * 1e-6) + mid * it.bytes[i] / total;
+        if (end > span) hi = mid; else lo = mid;
+    }
+    return (float)hi;
+}
+
 // Sees a ticket that has left its stream's queue through to its end: result, record, completion.
 static void complete_ticket(Context* ctx, StreamWorker* w, Ticket* t) {
     Instance& in = t->model->inst[t->instance];
@@ -158,15 +176,24 @@ static void complete_ticket(Context* ctx, StreamWorker* w, Ticket* t) {
     if (!status) status = await_result(ctx, w, t, &done);
     if (!done) done = now_ns();
     w->outstanding.fetch_sub(1, std::memory_order_acq_rel);
+    if (t->by_copy_stream) ctx->copy_outstanding[t->copy].fetch_sub(1, std::memory_order_acq_rel);
     if (t->prio == STRAIT_PRIO_HIGH) ctx->hp_in_flight.fetch_sub(1, std::memory_order_acq_rel);
     if (!status) {
         const volatile uint64_t* st = in.ctl->stamp;
         auto ms = [&](uint64_t from, uint64_t to) { return (float)((double)(int64_t)(to - from) * ctx->ms_per_tick); };
-        const uint64_t k0 = t->k0_stamped ? st[STAMP_K0] : st[STAMP_H2D1];
-        t->rec.h2d_ms = ms(st[STAMP_H2D0], st[STAMP_H2D1]);
+        const volatile uint64_t* piece = st + STAMP_PIECES;
+        const InputTiming& it = t->input;
+        const uint64_t k0 = t->k0_stamped ? st[STAMP_K0] : piece[2 * it.pieces - 1];
+        if (it.by_kernel) for (int i = 0; i < it.pieces; ++i) t->rec.h2d_ms += ms(piece[2 * i], piece[2 * i + 1]);
+        else {
+            // the transfer's start on the host's clock: from when a small result was seen, else when its first piece was handed over (earlier
+            // than it started by the first launch's milliseconds, where it is the process's first)
+            const int64_t start = t->chunks == 1 ? done - (int64_t)(1e6 * ms(piece[0], st[STAMP_DONE])) : it.handed[0];
+            t->rec.h2d_ms = link_ms(it, start, ms(piece[0], piece[1]), it.last_timed ? ms(st[STAMP_LAST], piece[1]) : 0.f);
+        }
         t->rec.kernel_ms = ms(k0, st[STAMP_K1]);
-        t->rec.d2h_ms = ms(st[STAMP_K1], st[STAMP_DONE]);
-        t->rec.total_ms = ms(st[STAMP_H2D0], st[STAMP_DONE]);
+        t->rec.d2h_ms = ms(st[t->out_pending ? STAMP_D2H0 : STAMP_K1], st[STAMP_DONE]);
+        t->rec.total_ms = ms(piece[0], st[STAMP_DONE]);
     }
     {
         std::lock_guard<std::mutex> lk(ctx->mu);
@@ -225,6 +252,8 @@ strait_status strait_ctx_create(const strait_ctx_desc* d, strait_ctx** out) {
     }
     c->compute_mu.resize(c->workers.size());
     c->copy_mu.resize(c->copy.size());
+    c->copy_seq.resize(c->copy.size(), 0);
+    c->copy_outstanding.resize(c->copy.size());
     for (StreamWorker* w : c->workers) w->th = std::thread(worker_loop, (Context*)c, w);
     *out = c;
     return STRAIT_OK;
@@ -487,12 +516,18 @@ static bool input_by_kernel(const strait_model* m, int batch) {
     std::lock_guard<std::mutex> lk(m->ctx->mu);
     return m->in_bytes(batch) <= m->ctx->h2d_kernel_limit && (m->in_bytes(batch) & 3) == 0;
 }
-// The input (and the valid lengths) into the instance's pinned buffer and on to the device through `s`; mu: the stream's mutex, or null if
-// the caller holds it.  An input that is not in the pinned buffer yet goes piece by piece, so that the host's copy of one piece
-// and the link's of the one before go on together; the link (52 GB/s) is the slower of the two, so each piece can be half as
-// large again as the one before it.  A batch of 1.5 MB: 374 us from submission to result in one piece, 355 in three.
-static int send_input(const strait_model* m, Instance& in, int batch, const void* host_in, const int32_t* valid_len, bool by_kernel, hipStream_t s,
-                      std::mutex* mu) {
+// The input (and the valid lengths) into the instance's pinned buffer and on to the device: through copy stream `ci`, or, with ci < 0, by
+// kernel through `s`, whose mutex the caller holds.  An input that is not in the pinned buffer yet goes piece by piece, so that the
+// host's copy of one piece and the link's of the one before go on together.  The link brings 52 GB/s, the host copies 75 from its caches
+// and 31 from memory; each piece is half as large again as the one before it: few launches, and the first piece is soon on the way.  A batch of
+// 1.5 MB: 374 us from submission to result in one piece, 355 in three.
+// A piece by kernel takes its own stamps.  Between pieces that a copy engine brings, a stamp (or asking whether it has run dry) holds it
+// up: 64 images of 224 x 224 at 2.05 ms, 40 us.  There the whole input is timed, and what the host's copying adds is known from when
+// it handed the pieces over (link_ms).  That needs a stream with nothing else on it: an input that finds another batch's ahead goes in one
+// piece, as the link has work meanwhile (`alone`), and once another's has come between, the rest goes as one with a start of its own.
+static int send_input(const strait_model* m, Instance& in, int batch, const void* host_in, const int32_t* valid_len, bool by_kernel, bool alone, int ci, hipStream_t s,
+                      InputTiming* timing) {
+    Context* c = m->ctx;
     const size_t inb = m->in_bytes(batch), off = (m->in_bytes(m->max_batch) + 255) / 256 * 256;
     const size_t lens = m->arch == STRAIT_ARCH_ENCODER ? (size_t)batch * 4 : 0;
     if (lens) {
@@ -502,20 +537,38 @@ static int send_input(const strait_model* m, Instance& in, int batch, const void
     const void* lsrc = lens ? (const char*)in.pinned_in_dev + off : nullptr;
     void* ldst = lens ? in.dev_valid : nullptr;
     const bool staged = host_in == in.pinned_in;
-    size_t piece = staged ? inb : by_kernel ? 512u << 10 : 4u << 20;
-    for (size_t at = 0; at < inb;) {
-        const size_t n = inb - at <= piece + piece / 2 ? inb - at : piece;
-        const bool first = at == 0, last = at + n == inb;
+    size_t piece = staged ? inb : by_kernel ? 512u << 10 : alone ? 4u << 20 : inb;
+    timing->by_kernel = by_kernel;
+    timing->last_timed = false;
+    unsigned seq = 0;                                  // of this batch's previous piece
+    int k = 0;
+    for (size_t at = 0; at < inb; ++k) {
+        size_t n = inb - at <= piece + piece / 2 || k == MAX_PIECES - 1 ? inb - at : piece;
         if (!staged) memcpy((char*)in.pinned_in + at, (const char*)host_in + at, n);
         std::unique_lock<std::mutex> lk;
-        if (mu) lk = std::unique_lock<std::mutex>(*mu);
+        if (ci >= 0) lk = std::unique_lock<std::mutex>(c->copy_mu[ci]);
+        if (!by_kernel && k > 0 && c->copy_seq[ci] != seq) {
+            timing->last_timed = true;
+            if (at + n < inb) {
+                lk.unlock();
+                memcpy((char*)in.pinned_in + at + n, (const char*)host_in + at + n, inb - at - n);
+                n = inb - at;
+                lk.lock();
+            }
+        }
+        const bool last = at + n == inb;
+        timing->pieces = k + 1;
+        timing->handed[k] = now_ns();
+        timing->bytes[k] = n;
+        if (ci >= 0) seq = ++c->copy_seq[ci];
         if (by_kernel) {
-            if (launch_copy_in((const char*)in.pinned_in_dev + at, (char*)in.dev_in + at, n, lsrc, ldst, last ? lens : 0, in.ctl_dev, in.counters, first, last, s))
+            if (launch_copy_in((const char*)in.pinned_in_dev + at, (char*)in.dev_in + at, n, lsrc, ldst, last ? lens : 0, in.ctl_dev, in.counters, k, s))
                 return STRAIT_E_HIP;
         } else {
-            if (first && launch_stamp(in.ctl_dev, STAMP_H2D0, s)) return STRAIT_E_HIP;
+            if (k == 0 && launch_stamp(in.ctl_dev, STAMP_PIECES, s)) return STRAIT_E_HIP;
+            if (timing->last_timed && launch_stamp(in.ctl_dev, STAMP_LAST, s)) return STRAIT_E_HIP;
             HIP_TRY(hipMemcpyAsync((char*)in.dev_in + at, (const char*)in.pinned_in + at, n, hipMemcpyHostToDevice, s));
-            if (last && launch_stamp(in.ctl_dev, STAMP_H2D1, s, lsrc, ldst, lens)) return STRAIT_E_HIP;
+            if (last && launch_stamp(in.ctl_dev, STAMP_PIECES + 1, s, lsrc, ldst, lens)) return STRAIT_E_HIP;
         }
         at += n;
         piece += piece / 2 & ~(size_t)15;
@@ -576,7 +629,9 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
     t->hp = hp_flag(c, prio);
     if (prio == STRAIT_PRIO_HIGH) c->hp_in_flight.fetch_add(1, std::memory_order_acq_rel);
     auto h2d_on_copy_stream = [&]() {
-        int r = send_input(m, in, batch, host_in, valid_len, by_kernel, cs, &c->copy_mu[cidx]);
+        t->by_copy_stream = true;
+        const bool alone = c->copy_outstanding[cidx].fetch_add(1, std::memory_order_acq_rel) == 0;
+        int r = send_input(m, in, batch, host_in, valid_len, by_kernel, alone, (int)cidx, cs, &t->input);
         std::lock_guard<std::mutex> lk(c->copy_mu[cidx]);
         if (!r) r = hipEventRecord(in.ev_h2d, cs) == hipSuccess ? 0 : STRAIT_E_HIP;
         return r;
@@ -602,7 +657,7 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
             in_line = w->outstanding.load(std::memory_order_acquire) == 0;
         }
         if (in_line) {
-            if (!rc) rc = send_input(m, in, batch, host_in, valid_len, true, s, nullptr);
+            if (!rc) rc = send_input(m, in, batch, host_in, valid_len, true, true, -1, s, &t->input);
         } else {
             if (!rc) rc = h2d_on_copy_stream();
             if (!slk.owns_lock()) slk.lock();
@@ -621,6 +676,7 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
     }
     if (rc) {
         if (prio == STRAIT_PRIO_HIGH) c->hp_in_flight.fetch_sub(1, std::memory_order_acq_rel);
+        if (t->by_copy_stream) c->copy_outstanding[cidx].fetch_sub(1, std::memory_order_acq_rel);
         if (rc == STRAIT_E_HIP && !strait::last_error()[0]) set_error("submit: a HIP call failed");
         (void)hipStreamSynchronize(s);
         (void)hipStreamSynchronize(cs);
@@ -691,7 +747,8 @@ strait_status strait_copy_in(strait_model* m, int32_t instance, strait_priority 
     HIP_TRY(hipSetDevice(c->device));
     Instance& in = m->inst[instance];
     const size_t ci = (size_t)instance % c->copy.size();
-    if ((rc = send_input(m, in, batch, host_in, valid_len, input_by_kernel(m, batch), c->copy[ci], &c->copy_mu[ci]))) return rc;
+    InputTiming timing;
+    if ((rc = send_input(m, in, batch, host_in, valid_len, input_by_kernel(m, batch), true, (int)ci, c->copy[ci], &timing))) return rc;
     {
         std::lock_guard<std::mutex> lk(c->copy_mu[ci]);
         HIP_TRY(hipEventRecord(in.ev_h2d, c->copy[ci]));

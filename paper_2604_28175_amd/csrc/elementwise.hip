@@ -65,32 +65,30 @@ __device__ __forceinline__ void copy_range(const uint32_t* __restrict__ src, uin
     if (block == 0 && tail + threadIdx.x < n4) dst[tail + threadIdx.x] = src[tail + threadIdx.x];
 }
 
-// A piece of an input (and, for token models, the valid lengths behind it): dst <- src, dst2 <- src2.  The first piece stamps STAMP_H2D0,
-// the last STAMP_H2D1.
+// A piece of an input (and, for token models, the valid lengths behind it): dst <- src, dst2 <- src2, with a stamp at its start and end.
 __global__ void __launch_bounds__(256) copy_in_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, size_t n4,
                                                       const uint32_t* __restrict__ src2, uint32_t* __restrict__ dst2, unsigned n4b,
-                                                      HostControl* ctl, unsigned* counters, int first, int last) {
-    if (first && blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(&ctl->stamp[STAMP_H2D0], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                                                      HostControl* ctl, unsigned* counters, int piece) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(&ctl->stamp[STAMP_PIECES + 2 * piece], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     copy_range(src, dst, n4, blockIdx.x, gridDim.x);
     if (blockIdx.x == 0)
         for (unsigned i = threadIdx.x; i < n4b; i += 256) dst2[i] = src2[i];
-    if (!last) return;
     __syncthreads();
     if (threadIdx.x == 0 && atomicAdd(&counters[0], 1u) == gridDim.x - 1) {      // the last workgroup to arrive
         counters[0] = 0;
-        __hip_atomic_store(&ctl->stamp[STAMP_H2D1], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&ctl->stamp[STAMP_PIECES + 2 * piece + 1], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 int launch_copy_in(const void* src, void* dst, size_t bytes, const void* src2, void* dst2, size_t bytes2, HostControl* ctl, unsigned* counters,
-                   bool first, bool last, hipStream_t stream) {
-    if (!src || !dst || !ctl || !counters || bytes == 0 || (bytes & 3) || (bytes2 & 3) || bytes2 > (1u << 20) || (bytes2 && (!src2 || !dst2)) ||
+                   int piece, hipStream_t stream) {
+    if (!src || !dst || !ctl || !counters || piece < 0 || piece >= MAX_PIECES || bytes == 0 || (bytes & 3) || (bytes2 & 3) || bytes2 > (1u << 20) || (bytes2 && (!src2 || !dst2)) ||
         ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15)) {
         set_error("copy in: 16-byte aligned buffers and multiples of 4 bytes required"); return -1;
     }
     const size_t n4 = bytes / 4, n16 = n4 / 4;
     const unsigned blocks = (unsigned)std::min<size_t>(256, std::max<size_t>(1, (n16 + 255) / 256));
     hipLaunchKernelGGL(copy_in_kernel, dim3(blocks), dim3(256), 0, stream, (const uint32_t*)src, (uint32_t*)dst, n4, (const uint32_t*)src2,
-                       (uint32_t*)dst2, (unsigned)(bytes2 / 4), ctl, counters, first ? 1 : 0, last ? 1 : 0);
+                       (uint32_t*)dst2, (unsigned)(bytes2 / 4), ctl, counters, piece);
     STRAIT_CHECK_LAUNCH("copy in");
     return 0;
 }
@@ -107,7 +105,7 @@ __global__ void __launch_bounds__(256) stamp_kernel(HostControl* ctl, int which,
     if (seq) __hip_atomic_store(&ctl->k1_seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* src, void* dst, size_t bytes, unsigned seq) {
-    if (!ctl || which < 0 || which >= 8 || (bytes & 3) || bytes > (1u << 20) || (bytes && (!src || !dst))) { set_error("stamp: bad argument"); return -1; }
+    if (!ctl || which < 0 || which >= STAMP_COUNT || (bytes & 3) || bytes > (1u << 20) || (bytes && (!src || !dst))) { set_error("stamp: bad argument"); return -1; }
     hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(bytes ? 256 : 64), 0, stream, ctl, which, (const uint32_t*)src, (uint32_t*)dst, (unsigned)(bytes / 4), seq);
     STRAIT_CHECK_LAUNCH("stamp");
     return 0;
@@ -115,7 +113,7 @@ int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* sr
 
 // Result, in chunks of out_chunk_bytes, each in OUT_PARTS parts of which a workgroup takes every gridDim.x-th: when the last part of
 // chunk c is written, flag[c] becomes `seq`, so that the host can move a chunk on while the next ones are on the link.  Stamps
-// STAMP_K1 (first workgroup starts; unless `k1_taken`) and STAMP_DONE.  counters[1 + c] count a chunk's parts, counters[0] the
+// STAMP_K1 (first workgroup starts; if `k1_taken`, when the kernels were done, STAMP_D2H0 instead) and STAMP_DONE.  counters[1 + c] count a chunk's parts, counters[0] the
 // chunks; both are left at zero.
 // Few workgroups: 16 of them keep the link busy (12.6 MB in 0.24 ms), and other batches run beside this.  The stores go through the
 // caches (sc0 sc1) and each workgroup waits for its own to be acknowledged before it counts a part: a system-scope fence would
@@ -128,8 +126,8 @@ __device__ __forceinline__ void store_through(void* p, uint4 v) {
 __global__ void __launch_bounds__(256) copy_out_kernel(const char* __restrict__ src, char* __restrict__ dst, size_t bytes, size_t part_bytes, unsigned parts, unsigned chunks,
                                                        HostControl* ctl, unsigned* counters, unsigned seq, int k1_taken, int hp) {
     if (hp) __builtin_amdgcn_s_setprio(3);
-    if (blockIdx.x == 0 && threadIdx.x == 0 && !k1_taken)
-        __hip_atomic_store(&ctl->stamp[STAMP_K1], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(&ctl->stamp[k1_taken ? STAMP_D2H0 : STAMP_K1], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     for (unsigned part = blockIdx.x; part < parts; part += gridDim.x) {
         const size_t at = (size_t)part * part_bytes, n = bytes - at < part_bytes ? bytes - at : part_bytes;
         const size_t n16 = n >> 4;

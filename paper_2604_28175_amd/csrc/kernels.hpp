@@ -121,7 +121,9 @@ int launch_argmax_f16(const half_t* x, int rows, int n, long long row_stride, in
 // Weight preparation on the device (load time): BatchNorm fold + OIHW -> kernel layout.
 int launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 // ---- transfers by kernel, with the timestamps and the completion flags of a batch (elementwise.hip)
-enum { STAMP_H2D0 = 0, STAMP_H2D1 = 1, STAMP_K0 = 2, STAMP_K1 = 3, STAMP_DONE = 4, STAMP_COUNT = 8 };
+// STAMP_PIECES + 2 i, + 2 i + 1: start and end of the i-th piece of an input that goes in by kernel; of one that copy engines bring, the
+// first pair holds its start and end, STAMP_LAST the start of a last piece that follows another batch's
+enum { STAMP_K0 = 0, STAMP_K1 = 1, STAMP_D2H0 = 2, STAMP_DONE = 3, STAMP_LAST = 4, STAMP_PIECES = 8, MAX_PIECES = 32, STAMP_COUNT = STAMP_PIECES + 2 * MAX_PIECES };
 constexpr unsigned OUT_PARTS = 8, OUT_MAX_CHUNKS = 4096;
 inline size_t out_chunk_bytes(size_t bytes) {          // of a result: 256 KB, doubled while it has more chunks than there are flags (beyond 1 GiB)
     size_t c = 256u << 10;
@@ -135,7 +137,7 @@ struct HostControl {                     // in pinned host memory, written by th
 };
 // counters: one unsigned (copy in), 1 + OUT_MAX_CHUNKS of them (copy out), in device memory, zero before the first launch and after each
 int launch_copy_in(const void* src, void* dst, size_t bytes, const void* src2, void* dst2, size_t bytes2, HostControl* ctl, unsigned* counters,
-                   bool first, bool last, hipStream_t stream);
+                   int piece, hipStream_t stream);
 int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* src = nullptr, void* dst = nullptr, size_t bytes = 0, unsigned seq = 0);
 int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, hipStream_t stream);
 

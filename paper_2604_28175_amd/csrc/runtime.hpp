@@ -123,6 +123,15 @@ struct Model {
     size_t out_offset(int ref, int b) const;
 };
 
+// What the time on the link of one batch's input is found from, besides its stamps.
+struct InputTiming {
+    bool by_kernel = false;            // every piece has its start and end; else (copy engine) the whole has
+    int pieces = 0;
+    int64_t handed[MAX_PIECES];        // host time at which each was enqueued
+    size_t bytes[MAX_PIECES];
+    bool last_timed = false;           // STAMP_LAST is set: another batch's transfers came between these pieces
+};
+
 struct Ticket {
     Model* model = nullptr;
     int instance = 0, prio = 0, batch = 0;
@@ -133,6 +142,8 @@ struct Ticket {
     bool deferred = false;             // kernels not enqueued yet: the stream's worker issues them segment by segment
     bool k0_stamped = false;           // kernel start has a stamp of its own (else it is the end of the input copy)
     unsigned seq = 0;
+    InputTiming input;
+    bool by_copy_stream = false;       // counted in Context::copy_outstanding
     size_t worker = 0;                 // index of its compute stream in Context::workers
     size_t copy = 0;                   // index of its copy stream in Context::copy
     unsigned chunks = 0;               // of its result
@@ -156,10 +167,13 @@ struct Context {
     int device = 0;
     std::vector<hipStream_t> hp, lp, copy;
     std::vector<StreamWorker*> workers;     // one per compute stream: hp first, then lp
-    // A batch's operations on a stream (event, copy, event / event, kernels, event, copy, event) are enqueued
-    // under that stream's mutex, so that batches submitted from several threads do not interleave on it and
-    // every record times its own batch only.
+    // A batch's kernels and result copy are enqueued under their stream's mutex, so that batches submitted from several threads do
+    // not interleave there.  Inputs may, piece by piece (an input that is staged by the caller, or small, is one piece): a
+    // high-priority input then waits for the rest of a piece, not for the rest of a low-priority batch that its caller is still
+    // copying.  A record holds its own batch's time on the link only (InputTiming).
     std::deque<std::mutex> compute_mu, copy_mu;
+    std::vector<unsigned> copy_seq;         // per copy stream, under its mutex: transfers enqueued so far
+    std::deque<std::atomic<int>> copy_outstanding;   // per copy stream: batches whose input it brings and whose result has not arrived
     std::mutex mu;                          // guards worker queues, ticket completion, counters
     std::condition_variable cv_work, cv_done;
     bool stop = false;

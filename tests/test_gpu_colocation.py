@@ -1,6 +1,8 @@
 """Dual-priority dispatch on one GPU: records, ordering and the concurrent-copy behaviour the
 paper's transfer model rests on (Section 3.2: pinned host-to-device copies of concurrent batches
 are served first-in first-out by the link)."""
+import mmap
+
 import numpy as np
 import pytest
 
@@ -149,3 +151,22 @@ def test_yielding_low_priority_batches_give_the_same_results(env):
         assert np.array_equal(out["logits"], ref_hp_as_lp["logits"])
     finally:
         ctx.set_lp_yield(0)
+
+
+def test_transfer_time_leaves_out_the_hosts_own_copying(env):
+    """An input in ordinary memory travels in pieces, between which the host copies the next one to pinned memory.  Reading
+    untouched pages makes that slow; the recorded transfer is the link's time all the same."""
+    S, colocate, ctx, md_hp, hp, md_lp, lp = env
+    staged = lp.staging(0, 64)
+    staged[:] = 0
+    out = lp.new_output(64)
+    link = min(lp.wait(lp.submit(S.PRIO_LOW, staged, None, out)).h2d_ms for _ in range(5))
+
+    def from_untouched_pages():
+        pages = mmap.mmap(-1, staged.nbytes)
+        pages.madvise(mmap.MADV_NOHUGEPAGE)
+        return lp.infer(np.frombuffer(pages, np.float16).reshape(staged.shape), prio=S.PRIO_LOW)[1].h2d_ms
+
+    host = min(from_untouched_pages() for _ in range(5))
+    print(f"19 MB: {link:.3f} ms from pinned memory, {host:.3f} ms from untouched pages")
+    assert 0.8 * link < host < 1.5 * link        # three pieces instead of one; with the host's copying in it, several times as much
