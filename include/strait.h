@@ -67,8 +67,8 @@ typedef struct strait_ticket_s* strait_ticket;
 /* Context: one GPU plus the streams the caller created for it (Section 3.1: the priority of a
  * model selects the stream its batches run on).  n_hp/n_lp >= 1, n_copy >= 1, each at most
  * STRAIT_MAX_STREAMS.  A batch of priority p is issued on compute stream p[i % n_p] and its
- * host-to-device copy on copy_streams[j % n_copy] (i, j: running counters); a small input whose compute stream is idle goes
- * in on that instead.  While a batch is in flight a thread of the
+ * host-to-device copy on copy_streams[j % n_copy] (i, j: running counters); with n_copy > 1 a small input whose compute stream is
+ * idle goes in on that instead.  With n_copy == 1 all transfers are first-in first-out.  While a batch is in flight a thread of the
  * library polls for its result, one per compute stream, and a thread in strait_wait polls for up to 0.5 ms before it sleeps. */
 typedef struct {
     int32_t device;
@@ -168,8 +168,8 @@ strait_status strait_ctx_set_branch_streams(strait_ctx* ctx, int32_t enabled);
 
 /* How inputs travel from the instance's pinned buffer to the device (Section 2 of the paper: inputs are
  * "copied to the GPU's memory" before the kernels run; the first-in first-out link of Section 3.2).
- * Inputs of at most max_bytes are read over the host link by a copy kernel, on the compute stream if that is idle and on
- * a copy stream beside its work otherwise; larger ones go by hipMemcpyAsync on a copy stream.  An input in ordinary memory
+ * Inputs of at most max_bytes are read over the host link by a copy kernel, on the compute stream if that is idle (and n_copy > 1)
+ * and on a copy stream beside its work otherwise; larger ones go by hipMemcpyAsync on a copy stream.  An input in ordinary memory
  * travels in pieces (from 512 KB or 4 MB on), copied to pinned memory while the piece before is on the link; pieces of batches
  * submitted from several threads may alternate on a copy stream.  A record's h2d_ms is the time its own pieces take on the link, found
  * for those of hipMemcpyAsync from the whole transfer and the times at which the host handed them over.  Default 8 MiB (every serving-sized batch): under concurrent

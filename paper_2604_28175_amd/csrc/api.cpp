@@ -649,10 +649,11 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
         }
     } else {
         // A small input goes in on an idle compute stream itself; otherwise it travels beside the batches ahead of it (enqueued
-        // before this stream's mutex is taken, so that a batch that is being issued does not hold its transfer up).
+        // before this stream's mutex is taken, so that a batch that is being issued does not hold its transfer up).  With one copy
+        // stream every input goes through it, so that transfers stay first-in first-out.
         std::unique_lock<std::mutex> slk(c->compute_mu[widx], std::defer_lock);
         bool in_line = false;
-        if (by_kernel && w->outstanding.load(std::memory_order_acquire) == 0) {
+        if (by_kernel && c->copy.size() > 1 && w->outstanding.load(std::memory_order_acquire) == 0) {
             slk.lock();
             in_line = w->outstanding.load(std::memory_order_acquire) == 0;
         }

@@ -170,3 +170,26 @@ def test_transfer_time_leaves_out_the_hosts_own_copying(env):
     host = min(from_untouched_pages() for _ in range(5))
     print(f"19 MB: {link:.3f} ms from pinned memory, {host:.3f} ms from untouched pages")
     assert 0.8 * link < host < 1.5 * link        # three pieces instead of one; with the host's copying in it, several times as much
+
+
+def test_small_inputs_on_one_copy_stream_are_first_in_first_out(env):
+    """Two small batches for two idle compute streams, one right behind the other: with a single copy stream their transfers do
+    not share the link."""
+    S, colocate, ctx, md_hp, hp, md_lp, lp = env
+    md = synth.tiny_cnn(synth.SEEDS[synth.ARCH_TINY_CNN], hw=256)
+    one = S.Context(device=0, n_hp=1, n_lp=1, n_copy=1)
+    try:
+        m = one.load(synth.pack(md), max_batch=20, n_instances=2)
+        xs, outs = [m.staging(i, 20) for i in range(2)], [m.new_output(20) for _ in range(2)]
+        for x in xs:
+            x[:] = 0.5
+        solo, pair = [], []
+        for _ in range(20):
+            solo.append(m.wait(m.submit(S.PRIO_LOW, xs[1], None, outs[1])).h2d_ms)
+            t = [m.submit(p, x, None, o) for p, x, o in zip((S.PRIO_HIGH, S.PRIO_LOW), xs, outs)]
+            pair.append(max(m.wait(k).h2d_ms for k in t))
+        print(f"7.9 MB: {np.median(solo):.3f} ms alone, {np.median(pair):.3f} ms the slower of two")
+        assert np.median(pair) < 1.25 * np.median(solo)        # sharing the link: twice
+        m.free()
+    finally:
+        one.close()
