@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(256) copy_in_kernel(const uint32_t* __restrict
         for (unsigned i = threadIdx.x; i < n4b; i += 256) dst2[i] = src2[i];
     __syncthreads();
     if (threadIdx.x == 0 && atomicAdd(&counters[0], 1u) == gridDim.x - 1) {      // the last workgroup to arrive
-        counters[0] = 0;
+        __hip_atomic_store(&counters[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&ctl->stamp[STAMP_PIECES + 2 * piece + 1], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
@@ -114,7 +114,7 @@ int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* sr
 // Result, in chunks of out_chunk_bytes, each in OUT_PARTS parts of which a workgroup takes every gridDim.x-th: when the last part of
 // chunk c is written, flag[c] becomes `seq`, so that the host can move a chunk on while the next ones are on the link.  Stamps
 // STAMP_K1 (first workgroup starts; if `k1_taken`, when the kernels were done, STAMP_D2H0 instead) and STAMP_DONE.  counters[1 + c] count a chunk's parts, counters[0] the
-// chunks; both are left at zero.
+// chunks; both are back at zero, for every stream, before the last flag is set.
 // Few workgroups: 16 of them keep the link busy (12.6 MB in 0.24 ms), and other batches run beside this.  The stores go through the
 // caches (sc0 sc1) and each workgroup waits for its own to be acknowledged before it counts a part: a system-scope fence would
 // instead write back the L2s, which hold other batches' data.
@@ -146,12 +146,14 @@ __global__ void __launch_bounds__(256) copy_out_kernel(const char* __restrict__ 
         const unsigned c = part / OUT_PARTS;
         const unsigned mine = parts - c * OUT_PARTS < OUT_PARTS ? parts - c * OUT_PARTS : OUT_PARTS;     // parts of this chunk
         if (threadIdx.x == 0 && atomicAdd(&counters[1 + c], 1u) == mine - 1) {
-            counters[1 + c] = 0;
+            __hip_atomic_store(&counters[1 + c], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (atomicAdd(&counters[0], 1u) == chunks - 1) {
-                counters[0] = 0;
+                __hip_atomic_store(&counters[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&ctl->stamp[STAMP_DONE], (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
+            // The host may give the instance to another stream as soon as it has seen every flag, before this kernel has ended
+            // and its plain stores are written back: the zeros must be where every unit's atomics look before the flag is out.
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __hip_atomic_store(&ctl->flag[c], seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }

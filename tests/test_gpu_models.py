@@ -425,6 +425,56 @@ def test_transfers_in_pieces_bring_every_byte(ctx, batch):
         m.free()
 
 
+def test_one_instance_handed_from_stream_to_stream(ctx):
+    """Results of several chunks, one instance, the priority and so the compute stream changing from batch to batch without a pause:
+    the counters that tell the last part of a chunk are the instance's and have to be back at zero for the next stream."""
+    S = ctx.S
+    md = synth.encoder(3, layers=1, hidden=256, heads=4, ffn=256, seq=256)
+    m = ctx.load(synth.pack(md), max_batch=33, n_instances=1)
+    try:
+        want = {}
+        for i in range(120):
+            batch = (33, 6, 16)[i % 3]                    # 4.3 MB: leaves on a copy stream
+            x, vl = synth.token_batch(md, batch, batch, min_len=32) if batch not in want else want[batch][0]
+            out = m.new_output(batch)
+            m.wait(m.submit((S.PRIO_HIGH, S.PRIO_LOW)[i & 1], x, vl, out))
+            ref = want.setdefault(batch, ((x, vl), out))[1]
+            assert np.array_equal(out, ref), i
+    finally:
+        m.free()
+
+
+def test_large_inputs_in_pieces_from_two_threads(ctx):
+    """19 MB in ordinary memory by the copy engine, in pieces, from two threads and through one and two copy streams at once: whole,
+    in several pieces, or the rest in one after another batch's came between; always every byte."""
+    import threading
+    S = ctx.S
+    md = synth.tiny_cnn(synth.SEEDS[synth.ARCH_TINY_CNN], hw=224)
+    for n_copy in (1, 2):
+        c = S.Context(device=0, n_hp=1, n_lp=1, n_copy=n_copy)
+        m = c.load(synth.pack(md), max_batch=64, n_instances=2)
+        try:
+            xs = [synth.default_image_batch(md, 64, i) for i in range(2)]
+            want = [m.infer(x)[0]["logits"].copy() for x in xs]
+            bad = []
+
+            def client(i):
+                for _ in range(10):
+                    out, rec = m.infer(xs[i], prio=(S.PRIO_HIGH, S.PRIO_LOW)[i])
+                    if not np.array_equal(out["logits"], want[i]) or not 0 < rec.h2d_ms <= rec.total_ms:
+                        bad.append((i, rec.h2d_ms, rec.total_ms))
+
+            threads = [threading.Thread(target=client, args=(i,)) for i in range(2)]
+            for t in threads:
+                t.start()
+            for t in threads:
+                t.join()
+            assert not bad
+        finally:
+            m.free()
+            c.close()
+
+
 def test_result_of_more_than_a_gibibyte(ctx):
     """2900 sequences of 393 KB: more 256 KB chunks than there are flags, so the chunks are larger.  Every row is the answer to one of
     eight sequences; a product's sums do not depend on the row, so equal sequences give equal rows."""
