@@ -1,5 +1,6 @@
 """Which kernel and tile a layer is given: host code, checked without a GPU."""
 import paper_2604_28175_amd as S
+from conv_shapes import LAYERS
 
 
 def test_a_refused_layer_has_no_kernel():
@@ -35,3 +36,10 @@ def test_long_reductions_are_split_again():
     assert gemm(9, 72, 16352) == "slabs 64x64x32"                       # no whole slices of 64
     assert gemm(6, 4096, 25088) == "small outputs 16x16"                # bound by its weights: nothing to gain
     assert gemm(64, 768, 4096).startswith(("32x64x64", "64x64x64", "small"))
+
+
+def test_every_kernel_has_a_layer():
+    """What the bit-exactness test on the GPU relies on: its layers reach every kernel and tile, and the one they say."""
+    for kernel, (n, h, w, c, k, r, stride, pad), res in LAYERS:
+        assert S.k_conv2d_kernel(n, h, w, c, k, r, stride, pad, res=res) == kernel, (kernel, n, h, w, c, k, r, stride, res)
+    assert len({kernel for kernel, _, _ in LAYERS}) == 19

@@ -3,6 +3,7 @@ entry points on the oracle's own operands, against the oracle's operator."""
 import numpy as np
 import pytest
 
+from conv_shapes import LAYERS
 from oracle import ops
 from parity import check_kernel
 
@@ -48,26 +49,26 @@ CONV_CASES = [
     (1, 40, 40, 64, 64, 3, 1, 1, 1, False, False),      # several 128-pixel tiles and a ragged tail (M = 1600)
     (1, 7, 7, 512, 512, 3, 1, 1, 1, False, False),      # long reduction (K = 4608), small M
     (11, 56, 56, 64, 256, 1, 1, 0, 1, True, False),     # 64 -> 256 pointwise with residual, M = 34496: many tiles, ragged tail, residual requested early
-    # wide 3x3 stride-1 layers with enough output tiles not to split the reduction: the kernel that keeps an input patch in LDS
-    (3, 56, 56, 64, 64, 3, 1, 1, 1, False, False),      # 64 channels out: 256-pixel tiles, two input slices
-    (6, 28, 28, 32, 128, 3, 1, 1, 1, False, False),     # 128 channels out: 128-pixel tiles, a single input slice, smallest patch
-    (1, 37, 112, 64, 128, 3, 1, 1, 0, False, False),    # wider rows (larger patch), ragged height, no activation
-    (2, 24, 224, 32, 64, 3, 1, 1, 1, False, False),     # widest rows served: the largest patch
+    # wide 3x3 stride-1 layers (which kernel a layer is given: conv_shapes.py and test_every_kernel_..., which assert it)
+    (3, 56, 56, 64, 64, 3, 1, 1, 1, False, False),      # 64 channels out, two input slices
+    (6, 28, 28, 32, 128, 3, 1, 1, 1, False, False),     # 128 channels out, a single input slice
+    (1, 37, 112, 64, 128, 3, 1, 1, 0, False, False),    # wider rows, ragged height, no activation
+    (2, 24, 224, 32, 64, 3, 1, 1, 1, False, False),     # widest rows served
     (2, 40, 100, 96, 192, 3, 1, 1, 2, False, False),    # three channel tiles, three input slices, ReLU6
-    # enough 256 x 128 tiles (768 or more) for the eight-wave form of that kernel, in both of its patch sizes
-    (64, 56, 56, 32, 256, 3, 1, 1, 1, False, False),    # 1626 tiles, three patch transfers per wave, two channel tiles
-    (16, 112, 112, 64, 128, 3, 1, 1, 1, False, False),  # rows cut into two strips of 56; two input slices
-    (48, 64, 64, 32, 128, 3, 1, 1, 0, False, False),    # 64-pixel rows: four patch transfers per wave
-    (12, 128, 128, 32, 128, 3, 1, 1, 2, False, False),  # two strips of 64: four transfers per wave with real pixels on the strips' sides
+    # more than 768 tiles of 256 x 128
+    (64, 56, 56, 32, 256, 3, 1, 1, 1, False, False),    # 1626 tiles, two channel tiles
+    (16, 112, 112, 64, 128, 3, 1, 1, 1, False, False),  # patch kernel: rows cut into two strips of 56; two input slices
+    (48, 64, 64, 32, 128, 3, 1, 1, 0, False, False),    # 64-pixel rows
+    (12, 128, 128, 32, 128, 3, 1, 1, 2, False, False),  # 128-pixel rows
     # 64 channels out, at most 128 in and 1024 or more 256-pixel tiles: workgroups that walk over several tiles each
     (81, 56, 56, 64, 64, 3, 1, 1, 1, False, False),     # 1028 tiles, two input slices
     (24, 112, 112, 32, 64, 3, 1, 1, 2, False, False),   # one slice: every slice is a tile's last; rows in two strips
     (320, 28, 28, 128, 64, 3, 1, 1, 0, False, False),   # four slices
-    # few tiles and a reduction worth splitting two to eight ways: two groups of wavefronts in one workgroup, half the slices each
+    # few tiles and a reduction worth splitting: groups of wavefronts, or the kernel for small outputs
     (8, 14, 14, 1024, 256, 1, 1, 0, 1, False, False),   # pointwise, 64-wide slices, 16 of them
     (2, 14, 14, 512, 256, 1, 1, 0, 1, True, False),     # pointwise with residual
     (8, 14, 14, 256, 256, 3, 1, 1, 1, False, False),    # 3x3: 72 slices of 32
-    (1, 10, 10, 264, 64, 1, 1, 0, 0, False, False),     # nine 32-wide slices, the last one ragged: the second group's fifth slice is empty
+    (1, 10, 10, 264, 64, 1, 1, 0, 0, False, False),     # nine 32-wide slices, the last one ragged
     (3, 9, 9, 160, 96, 3, 2, 1, 2, False, False),       # stride 2, ragged tiles in both directions, 45 slices
 ]
 
@@ -90,8 +91,8 @@ def test_conv2d(S, case):
 
 
 def test_conv2d_split_in_the_workgroup_integer_data_is_bit_exact(S):
-    """The reduction split over two groups of wavefronts of one workgroup (few tiles, 9 to 32 slices), pointwise and 3x3:
-    exact on integer data, partial sums and their hand-over included."""
+    """Few tiles and 9 to 32 slices, pointwise and 3x3: exact on integer data, partial sums included.  (The kernels that split the
+    reduction over groups of wavefronts have their own shapes in test_every_kernel_integer_data_is_bit_exact.)"""
     for (N, H, W, C, K, Rk, stride, pad) in ((4, 14, 14, 512, 128, 1, 1, 0), (1, 10, 10, 264, 64, 1, 1, 0), (2, 14, 14, 96, 64, 3, 1, 1)):
         x = R.integers(-2, 3, (N, H, W, C)).astype(np.float16)
         w = (R.integers(-1, 2, (K, C, Rk, Rk)) * (R.random((K, C, Rk, Rk)) < 0.2)).astype(np.float16)
@@ -114,22 +115,16 @@ def test_conv2d_integer_data_is_bit_exact(S):
         assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)
 
 
-@pytest.mark.parametrize("N,H,W,C,K", [(4, 40, 60, 32, 64),      # 256-pixel tiles, one strip per row
-                                       (2, 36, 128, 32, 128),    # rows cut into two strips of 64: the strips' side borders are real pixels
-                                       (1, 29, 224, 64, 64),     # four strips of 56, two input slices
-                                       (40, 15, 14, 32, 64),     # the narrowest rows served, odd height: shared borders everywhere
-                                       (30, 19, 17, 32, 128),    # odd width and height
-                                       (2, 70, 65, 32, 64),      # an odd width above 64 stays one strip
-                                       (2, 40, 130, 32, 64),     # two strips of odd width 65
-                                       (3, 21, 200, 32, 64),     # four strips of 50
-                                       # the eight-wave 256 x 128 tile (768 tiles or more): three and four patch transfers per wave
+@pytest.mark.parametrize("N,H,W,C,K", [(4, 40, 60, 32, 64), (2, 36, 128, 32, 128), (1, 29, 224, 64, 64), (40, 15, 14, 32, 64), (30, 19, 17, 32, 128),
+                                       (2, 70, 65, 32, 64), (2, 40, 130, 32, 64), (3, 21, 200, 32, 64),
+                                       # 768 tiles of 256 x 128 or more, the last one in the patch kernel: two strips of 64
                                        (64, 56, 56, 32, 256), (16, 112, 112, 32, 128), (48, 64, 64, 32, 128), (12, 128, 128, 64, 128),
-                                       # workgroups that walk over tiles (64 channels out, 1024 tiles or more): two slices, one slice,
-                                       # three slices (the patch buffers swap roles from tile to tile), two strips of odd width 65
+                                       # 64 channels out, 1024 tiles of 256 or more; in the patch kernel (81, 300 and 6 images): workgroups that
+                                       # walk over tiles with two and three slices (the patch buffers swap roles from tile to tile)
                                        (81, 56, 56, 64, 64), (72, 60, 60, 32, 64), (300, 30, 30, 96, 64), (50, 40, 130, 32, 64),
                                        (6, 224, 224, 64, 64)])   # and four strips of 56
 def test_conv2d_wide_3x3_integer_data_is_bit_exact(S, N, H, W, C, K):
-    """The wide 3x3 stride-1 layers run from an input patch in LDS, addressed through the bordered image: with
+    """Wide 3x3 stride-1 layers, from an input patch in LDS addressed through the bordered image or gathered: with
     integer data every border, strip seam and tile seam must come out exactly."""
     x = R.integers(-3, 4, (N, H, W, C)).astype(np.float16)
     w = R.integers(-2, 3, (K, C, 3, 3)).astype(np.float16)
@@ -598,11 +593,12 @@ def test_launchers_reject_bad_shapes(S):
 
 
 SPLITK_CASES = [
-    # N, H, W, C, K, R, stride, pad, act, residual, out_f32   (few output tiles + long reduction: split-K path)
-    (1, 7, 7, 512, 512, 3, 1, 1, 1, True, False),       # 49 pixels, K = 4608, residual + ReLU in the finishing kernel
+    # N, H, W, C, K, R, stride, pad, act, residual, out_f32   (few output tiles + long reduction, shared out inside a workgroup;
+    # split over several: test_split_reductions_integer_data_is_bit_exact)
+    (1, 7, 7, 512, 512, 3, 1, 1, 1, True, False),       # 49 pixels, K = 4608, residual + ReLU
     (2, 14, 14, 256, 256, 3, 2, 1, 1, False, False),    # strided 3x3, slices start in the middle of the tap sequence
     (1, 7, 7, 1024, 512, 1, 1, 0, 2, False, False),     # 1x1, ReLU6
-    (8, 1, 1, 2048, 1000, 1, 1, 0, 0, False, True),     # classifier head: fp32 logits out of the finishing kernel
+    (8, 1, 1, 2048, 1000, 1, 1, 0, 0, False, True),     # classifier head: fp32 logits
     (3, 9, 11, 64, 72, 3, 1, 1, 0, False, False),       # ragged M and N tiles, uneven split of the 18 slices
 ]
 
@@ -622,7 +618,7 @@ def test_conv2d_split_k(S, case):
     args = (dev(S, x), dev(S, w_krsc), dev(S, b), stride, pad, act, None if res is None else dev(S, res), out_f32)
     y1 = S.k_conv2d(*args).float().cpu().numpy()
     check_kernel(y1, ref, f"split-K conv {case}")
-    # slabs are reduced in a fixed order: a second launch gives the same bits
+    # partial sums are added in a fixed order: a second launch gives the same bits
     y2 = S.k_conv2d(*args).float().cpu().numpy()
     assert np.array_equal(y1, y2)
 
@@ -640,11 +636,11 @@ def test_gemm_gelu_and_ragged_k(S):
 
 
 @pytest.mark.parametrize("M,N,K,use_res", [
-    # one shape per tile of the dispatch, ragged in pixels and (where the layer allows it) in channels and slices
+    # many sizes of output, ragged in pixels and (where the layer allows it) in channels and slices
     (6311, 2304, 512, False), (8617, 1160, 64, False), (8347, 456, 64, True), (6455, 1184, 136, False), (8298, 280, 192, True),
     (4881, 1584, 136, False), (8491, 208, 136, True), (8466, 72, 520, False), (8894, 648, 64, True), (8514, 200, 64, False),
     (8387, 72, 64, True), (8250, 16, 192, False), (77, 40, 64, False), (45, 72, 520, True),
-    # reductions split inside the workgroup: two groups of wavefronts, four groups
+    # longer reductions
     (2891, 136, 768, True), (661, 208, 512, False),
     # one slice, fewer slices than the ring holds, exactly as many, one more
     (300, 64, 32, False), (300, 64, 96, False), (300, 64, 128, True), (9000, 256, 192, False), (9000, 256, 256, False)])
@@ -750,3 +746,28 @@ def test_split_reductions_integer_data_is_bit_exact(S, N, H, C, K, Rk, act, use_
     y = S.k_conv2d(dev(S, x), dev(S, np.ascontiguousarray(np.transpose(w, (0, 2, 3, 1)))), dev(S, b), 1, Rk // 2, act,
                    None if res is None else dev(S, res), out_f32)
     assert np.array_equal(y.float().cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("kernel,shape,use_res", LAYERS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v).replace(" ", "_"))
+def test_every_kernel_integer_data_is_bit_exact(S, kernel, shape, use_res):
+    """Small integers are exact in fp16 and fp32, in any order of addition: every kernel, its ring of slices, its edges and its way
+    to add a residual against the taps' products in fp32."""
+    N, H, W, C, K, Rk, stride, pad = shape
+    assert S.k_conv2d_kernel(N, H, W, C, K, Rk, stride, pad, res=use_res) == kernel
+    g = S.torch.Generator(device="cuda").manual_seed(N * H + C * K)
+    ints = lambda lo, hi, size: S.torch.randint(lo, hi, size, generator=g, device="cuda").float()
+    x = ints(-2, 3, (N, H, W, C))
+    w = ints(-1, 2, (K, Rk, Rk, C)) * (ints(0, 10, (K, Rk, Rk, C)) < 3)
+    b = ints(-5, 6, (K,))
+    P, Q = (H + 2 * pad - Rk) // stride + 1, (W + 2 * pad - Rk) // stride + 1
+    xp = S.torch.nn.functional.pad(x, (0, 0, pad, pad, pad, pad))
+    ref = b.expand(N * P * Q, K).clone()
+    for r in range(Rk):
+        for s in range(Rk):
+            ref += xp[:, r:r + (P - 1) * stride + 1:stride, s:s + (Q - 1) * stride + 1:stride].reshape(-1, C) @ w[:, r, s].T.contiguous()
+    res = ints(-9, 10, (N, P, Q, K)) if use_res else None
+    if use_res:
+        ref += res.reshape(ref.shape)
+    assert ref.abs().max() < 2048
+    y = S.k_conv2d(x.half(), w.half(), b, stride, pad, 0, None if res is None else res.half())
+    assert S.torch.equal(y.float().reshape(ref.shape), ref)
