@@ -23,6 +23,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "activation.hpp"
 #include "kernels.hpp"
 
 namespace strait {
@@ -32,24 +33,6 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 enum { MODE_1X1 = 0, MODE_GATHER8 = 1, MODE_SCALAR = 2 };
-
-// erf by the rational approximation 7.1.26 of Abramowitz & Stegun (|error| <= 1.5e-7, far below
-// the 2^-11 resolution of the fp16 result): 1 - (a1 t + ... + a5 t^5) exp(-x^2), t = 1/(1 + p|x|).
-__device__ __forceinline__ float fast_erf(float x) {
-    const float ax = fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(1.f + 0.3275911f * ax);
-    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-    const float r = 1.f - poly * __expf(-ax * ax);
-    return copysignf(r, x);
-}
-__device__ __forceinline__ float gelu_f(float v) { return 0.5f * v * (1.f + fast_erf(v * 0.70710678118654752440f)); }
-
-__device__ __forceinline__ float apply_act(float v, int act) {
-    if (act == ACT_RELU) return fmaxf(v, 0.f);
-    if (act == ACT_RELU6) return fminf(fmaxf(v, 0.f), 6.f);
-    if (act == ACT_GELU) return gelu_f(v);
-    return v;
-}
 
 template <int BM, int BN, int MODE, bool STAGED>
 __global__ void __launch_bounds__(256) conv_igemm_kernel(const ConvParams p) {
@@ -1243,6 +1226,7 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
 // The patch kernel's rows and the gathered 256 x 128 x 32 tile's c3 are fits to 240 more 3x3 layers (14 to 224 pixels wide, 32 to 512
 // channels in, 40 to 4500 tiles; mean error 3 to 12 %); the choice is then on average 2 % off the best there, before 7 % and up
 // to 1.7 times: 16 x 112 x 112, 64 -> 128 53 -> 41 us; 118 x 40 x 40 at stride 2, 160 -> 512 132 -> 83 us.
+// The rows of the kernel through registers are fits to 230 layers with fp32 or odd outputs (mean error 17 to 20 %).
 // Against the thresholds used before (and with the pipelined loop): ResNet-50's layers 7 % faster on the sum over batch 1
 // to 128 (22 % at batch 1, 5 % at 128), an encoder layer's products 8 to 19 % from 1000 rows on and 20 to 32 % below.
 enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,

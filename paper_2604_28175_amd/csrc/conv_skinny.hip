@@ -18,6 +18,7 @@
 // wavefronts in one workgroup) -> after, us: 3x3 256 -> 256 at 14 x 14, one image 11.7 -> 7.5; 3x3 128 -> 128 at 28 x 28 9.9 -> 6.5;
 // 1x1 1024 -> 256 at 14 x 14 6.0 -> 4.4; 1x1 2048 -> 512 at 7 x 7 9.0 -> 6.1; 2048 -> 1000 classifier, 8 images 8.3 -> 5.5;
 // 25088 -> 4096 for 6 rows 44.6 -> 38.3 (5.4 TB/s of weights); 960 -> 160 at 7 x 7, 5 images 6.4 -> 4.4.
+#include "activation.hpp"
 #include "kernels.hpp"
 
 namespace strait {
@@ -28,19 +29,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr unsigned SK_OOB = 0x80000000u;               // beyond any buffer these kernels accept
-
-__device__ __forceinline__ float sk_erf(float x) {     // Abramowitz & Stegun 7.1.26, as in conv_igemm.hip
-    const float ax = fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(1.f + 0.3275911f * ax);
-    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-    return copysignf(1.f - poly * __expf(-ax * ax), x);
-}
-__device__ __forceinline__ float sk_act(float v, int act) {
-    if (act == ACT_RELU) return fmaxf(v, 0.f);
-    if (act == ACT_RELU6) return fminf(fmaxf(v, 0.f), 6.f);
-    if (act == ACT_GELU) return 0.5f * v * (1.f + sk_erf(v * 0.70710678118654752440f));
-    return v;
-}
 
 template <int TN, bool GATHER, bool DUAL>
 __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
@@ -190,7 +178,7 @@ __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
             for (int j = 0; j < 4; ++j) o[j] += (float)r[j];
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = sk_act(o[j], p.act);
+        for (int j = 0; j < 4; ++j) o[j] = apply_act(o[j], p.act);
         if (p.out_f32) *(float4*)((float*)p.y + at) = make_float4(o[0], o[1], o[2], o[3]);
         else {
             half4 h;
@@ -204,7 +192,7 @@ __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
             if (no + j >= p.Cout) break;
             float t = o[j] + (p.bias ? p.bias[no + j] : 0.f);
             if (p.res) t += (float)p.res[at + j];
-            t = sk_act(t, p.act);
+            t = apply_act(t, p.act);
             if (p.out_f32) ((float*)p.y)[at + j] = t;
             else ((half_t*)p.y)[at + j] = (half_t)t;
         }
