@@ -1231,7 +1231,7 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
 // to 128 (22 % at batch 1, 5 % at 128), an encoder layer's products 8 to 19 % from 1000 rows on and 20 to 32 % below.
 enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
               T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64,
-              T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_COUNT };   // (slabs have no estimate)
+              T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_COUNT };   // (slabs: slab_split)
 struct TileInfo { int bm, bn, bk, kg; bool shared; float c[7]; };   // shared: two or more workgroups fit a compute unit
 static const TileInfo tile_info[T_ESTIMATED] = {
     {256, 256, 64, 1, false, {2.047f, 4.619f, 1.152f, 0.199f, 10.088f, 0.100f, 0.086f}},
