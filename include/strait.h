@@ -248,7 +248,9 @@ strait_status strait_k_conv2d(void* stream, const void* x, int32_t N, int32_t H,
  * strait_k_gemm is the layer N = M, H = W = R = S = stride = 1, pad = 0, C = K, K = N. */
 const char* strait_k_conv2d_kernel(int32_t N, int32_t H, int32_t W, int32_t C, int32_t K, int32_t R, int32_t S, int32_t stride,
                                    int32_t pad, int32_t act, int32_t res, int32_t out_f32);
-/* Y[M,N] = act(X[M,K] W[N,K]^T + bias (+ res)); same kernel as the 1x1 convolution. */
+/* Y[M,N] = act(X[M,K] W[N,K]^T + bias (+ res)); same kernel as the 1x1 convolution.  Where the reduction of a small product is split, a
+ * workspace is allocated and freed around the launch (strait_k_conv2d likewise); not on a stream that records a graph, which gets
+ * a kernel that needs none. */
 strait_status strait_k_gemm(void* stream, const void* x, const void* w, const float* bias, int32_t M,
                             int32_t N, int32_t K, int32_t act, const void* res, void* y, int32_t out_f32,
                             int32_t hp);

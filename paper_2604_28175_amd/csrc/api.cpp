@@ -828,6 +828,14 @@ strait_status strait_read_activation(strait_model* m, int32_t instance, int32_t 
 
 // ---- kernel-level entry points -----------------------------------------------------------------
 
+// Not while the stream records a graph: the launch is then one that needs no workspace.
+static bool may_allocate(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 static int conv2d_params(ConvParams& p, int32_t N, int32_t H, int32_t W, int32_t C, int32_t K, int32_t R, int32_t S, int32_t stride, int32_t pad,
                          int32_t act, int32_t out_f32) {
     if (N <= 0 || H <= 0 || W <= 0 || C <= 0 || K <= 0 || R <= 0 || S <= 0 || stride <= 0 || pad < 0 ||
@@ -869,7 +877,7 @@ strait_status strait_k_conv2d(void* stream, const void* x, int32_t N, int32_t H,
     }
     // a long reduction for few outputs may be split into slabs, which needs an fp32 workspace
     void* ws = nullptr;
-    if (conv_workspace_bytes(p, SPLITK_WS_BYTES)) {
+    if (may_allocate((hipStream_t)stream) && conv_workspace_bytes(p, SPLITK_WS_BYTES)) {
         if (hipMalloc(&ws, SPLITK_WS_BYTES) != hipSuccess) { (void)hipGetLastError(); ws = nullptr; }
         p.ws = (float*)ws; p.ws_bytes = ws ? SPLITK_WS_BYTES : 0;
     }
@@ -905,7 +913,7 @@ strait_status strait_k_gemm(void* stream, const void* x, const void* w, const fl
     p.stride_h = p.stride_w = 1; p.pad_h = p.pad_w = 0;
     p.sN = K; p.sH = K; p.sW = K; p.Kg = K; p.ldw = K; p.Cout = N; p.ldy = N; p.act = act; p.out_f32 = out_f32; p.hp = hp;
     void* ws = nullptr;
-    if (conv_workspace_bytes(p, SPLITK_WS_BYTES)) {
+    if (may_allocate((hipStream_t)stream) && conv_workspace_bytes(p, SPLITK_WS_BYTES)) {
         if (hipMalloc(&ws, SPLITK_WS_BYTES) != hipSuccess) { (void)hipGetLastError(); ws = nullptr; }
         p.ws = (float*)ws; p.ws_bytes = ws ? SPLITK_WS_BYTES : 0;
     }

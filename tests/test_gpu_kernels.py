@@ -771,3 +771,25 @@ def test_every_kernel_integer_data_is_bit_exact(S, kernel, shape, use_res):
     assert ref.abs().max() < 2048
     y = S.k_conv2d(x.half(), w.half(), b, stride, pad, 0, None if res is None else res.half())
     assert S.torch.equal(y.float().reshape(ref.shape), ref)
+
+
+def test_split_reduction_under_capture(S):
+    """A product whose reduction is split allocates a workspace; on a stream that records a graph it takes a kernel that needs none."""
+    M, N, K = 270, 512, 4096
+    assert S.k_conv2d_kernel(M, 1, 1, K, N, 1, 1, 0, out_f32=True).startswith("slabs")
+    x = R.integers(-2, 3, (M, K)).astype(np.float16)
+    w = R.integers(-1, 2, (N, K)).astype(np.float16)
+    want = x.astype(np.float64) @ w.astype(np.float64).T
+    dx, dw = dev(S, x), dev(S, w)
+    eager = S.k_gemm(dx, dw, None, 0, None, True)
+    S.torch.cuda.synchronize()
+    graph = S.torch.cuda.CUDAGraph()
+    with S.torch.cuda.graph(graph):
+        y = S.k_gemm(dx, dw, None, 0, None, True)
+    for _ in range(3):
+        y.fill_(float("nan"))
+        graph.replay()
+        S.torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), want)
+        assert S.torch.equal(S.k_gemm(dx, dw, None, 0, None, True), eager)
+    assert np.array_equal(eager.cpu().numpy().astype(np.float64), want)
