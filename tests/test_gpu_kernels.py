@@ -634,6 +634,20 @@ def test_gemm_gelu_and_ragged_k(S):
         check_kernel(y.float().cpu().numpy(), ref, f"gemm {M}x{N}x{K} act {act}")
 
 
+def test_gelu_over_its_range(S):
+    """Every fp16 value from -9 to 9 and the specials through the activation alone (identity weights).  Per element: half a unit of
+    fp16's last place (6e-8 apart below 6.1e-5), and the 2.5e-7 that the polynomial may be off."""
+    v = np.arange(65536, dtype=np.uint16).view(np.float16)
+    v = np.concatenate([v[np.isfinite(v) & (np.abs(v.astype(np.float64)) <= 9)], np.zeros(7, np.float16)])
+    v = v[:v.size // 8 * 8].reshape(-1, 8)
+    y = S.k_gemm(dev(S, v), dev(S, np.eye(8, dtype=np.float16)), None, 3).float().cpu().numpy().astype(np.float64)
+    ref = ops.gelu(v.astype(np.float64))
+    ulp = np.maximum(2.0 ** (np.floor(np.log2(np.maximum(np.abs(ref), 1e-30))) - 10), 2.0 ** -24)
+    assert np.all(np.abs(y - ref) <= 0.5 * ulp * 1.001 + 2.5e-7)
+    bias = np.array([np.inf, -np.inf, np.nan, 6.5, -6.5, -30000, 30000, 0], np.float32)
+    y = S.k_gemm(dev(S, np.zeros((1, 8), np.float16)), dev(S, np.eye(8, dtype=np.float16)), dev(S, bias), 3).float().cpu().numpy()[0]
+    assert y[0] == np.inf and not np.isfinite(y[2]) and np.array_equal(y[[1, 3, 4, 5, 6, 7]], [0, 6.5, 0, 0, 30000, 0])
+
 
 @pytest.mark.parametrize("M,N,K,use_res", [
     # many sizes of output, ragged in pixels and (where the layer allows it) in channels and slices
