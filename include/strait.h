@@ -254,6 +254,17 @@ const char* strait_k_conv2d_kernel(int32_t N, int32_t H, int32_t W, int32_t C, i
 strait_status strait_k_gemm(void* stream, const void* x, const void* w, const float* bias, int32_t M,
                             int32_t N, int32_t K, int32_t act, const void* res, void* y, int32_t out_f32,
                             int32_t hp);
+/* A product with a LayerNorm folded into it (fp16 output, N and K multiples of 64).  Statistics of a tensor [M][n], n a multiple of 64 and at most
+ * 1024: for each row and 64 channels {sum, sum of squares about their own mean}, fp32 [M][n / 64][2].
+ * With ln_csum: Y = act(LN(X) W^T + b), ln_stats those of X, and w, ln_csum, bias what strait_k_fold_layernorm makes of W, b; act none or GELU, no res.
+ * With stats_out: Y = X W^T + bias + res, and stats_out receives Y's statistics; with ln_stats, ln_g and ln_b as well, those of res, it is LN(res) that
+ * is added.  ln_eps inside the root. */
+strait_status strait_k_gemm_ln(void* stream, const void* x, const void* w, const float* bias, const void* res, int32_t M, int32_t N, int32_t K,
+                               int32_t act, const float* ln_stats, const float* ln_csum, const float* ln_g, const float* ln_b, float ln_eps, void* y,
+                               float* stats_out, int32_t hp);
+/* w_out [N][K] = fp16(w gamma), csum [N] = the sums of its rows, b_out [N] = b + w beta. */
+strait_status strait_k_fold_layernorm(void* stream, const void* w, const float* b, const float* gamma, const float* beta, int32_t N, int32_t K,
+                                      void* w_out, float* csum, float* b_out);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): strait_k_gemm for products of at most 128 * 4096 outputs (M * N; E_SHAPE beyond -- larger products
  * use no workspace and strait_k_gemm allocates nothing for them), with the split-K workspace of 16 MiB taken from a

@@ -91,6 +91,8 @@ _SIGS = {
     "strait_k_conv2d": (_i32, [_vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32]),
     "strait_k_conv2d_kernel": (C.c_char_p, [_i32] * 12),
     "strait_k_gemm": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32]),
+    "strait_k_gemm_ln": (_i32, [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _vp, C.c_float, _vp, _vp, _i32]),
+    "strait_k_fold_layernorm": (_i32, [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _vp, _vp, _vp]),
     "strait_k_gemm_noalloc": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32]),
     "strait_k_conv1x1_proj": (_i32, [_vp, _vp, _i32, _i32, _i32, _i32, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32, _vp, _i32]),
     "strait_k_expand_dw": (_i32, [_vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp, _i32, _i32, _vp, _vp, _i32, _i32, _vp, _i32]),
@@ -379,6 +381,26 @@ def k_gemm(x, w, bias, act=ACT_NONE, res=None, out_f32=False, hp=0, stream=None)
     y = torch.empty((m, n), dtype=torch.float32 if out_f32 else torch.float16, device=x.device)
     _check(lib.strait_k_gemm(_stream(stream), _dev(x), _dev(w), _dev(bias), m, n, k, act, _dev(res), _dev(y), int(out_f32), hp))
     return y
+
+
+def k_gemm_ln(x, w, bias, act=ACT_NONE, res=None, ln_stats=None, ln_csum=None, ln_g=None, ln_b=None, ln_eps=1e-6, stats=False, hp=0, stream=None):
+    """strait_k_gemm_ln; returns (y, the statistics of y or None)."""
+    import torch
+    m, k = x.shape
+    n = w.shape[0]
+    y = torch.empty((m, n), dtype=torch.float16, device=x.device)
+    out = torch.empty((m, n // 64, 2), dtype=torch.float32, device=x.device) if stats else None
+    _check(lib.strait_k_gemm_ln(_stream(stream), _dev(x), _dev(w), _dev(bias), _dev(res), m, n, k, act, _dev(ln_stats), _dev(ln_csum), _dev(ln_g),
+                                _dev(ln_b), ln_eps, _dev(y), _dev(out), hp))
+    return y, out
+
+
+def k_fold_layernorm(w, b, gamma, beta, stream=None):
+    import torch
+    n, k = w.shape
+    w_out, csum, b_out = torch.empty_like(w), torch.empty(n, dtype=torch.float32, device=w.device), torch.empty(n, dtype=torch.float32, device=w.device)
+    _check(lib.strait_k_fold_layernorm(_stream(stream), _dev(w), _dev(b), _dev(gamma), _dev(beta), n, k, _dev(w_out), _dev(csum), _dev(b_out)))
+    return w_out, csum, b_out
 
 
 def k_gemm_noalloc(x, w, bias, y, act=ACT_NONE, res=None, out_f32=False, hp=0, stream=None):

@@ -358,6 +358,7 @@ static void free_instance(Instance& in) {
     if (in.dev_out) (void)hipFree(in.dev_out);
     if (in.dev_valid) (void)hipFree(in.dev_valid);
     if (in.splitk_ws) (void)hipFree(in.splitk_ws);
+    for (float2* s : in.ln_stats) if (s) (void)hipFree(s);
     for (void* b : in.bufs) if (b) (void)hipFree(b);
     if (in.side) { (void)hipStreamSynchronize(in.side); (void)hipStreamDestroy(in.side); }
     if (in.ctl) (void)hipHostFree(in.ctl);
@@ -372,6 +373,7 @@ static void free_instance(Instance& in) {
 static void free_model(strait_model* m) {
     for (Instance& in : m->inst) free_instance(in);
     for (void* d : m->dev_allocs) (void)hipFree(d);
+    if (m->fold_tmp) (void)hipFree(m->fold_tmp);
     delete m;
 }
 
@@ -399,6 +401,8 @@ strait_status strait_model_load(strait_ctx* c, const strait_model_desc* d, strai
                   hipMalloc(&in.dev_in, inb) == hipSuccess && hipMalloc(&in.dev_out, outb) == hipSuccess &&
                   hipMalloc((void**)&in.dev_valid, (size_t)d->max_batch * 4 + 256) == hipSuccess &&
                   hipMalloc((void**)&in.splitk_ws, SPLITK_WS_BYTES) == hipSuccess;
+        for (size_t i = 0; ok && i < 2 && m->ln_folds; ++i)
+            ok = hipMalloc((void**)&in.ln_stats[i], (size_t)d->max_batch * m->seq * (m->hidden / 64) * sizeof(float2)) == hipSuccess;
         for (size_t i = 0; ok && i < m->buf_elems.size(); ++i) {
             void* b = nullptr;
             const size_t bytes = (m->buf_elems[i] * 2 * (size_t)d->max_batch + 255) / 256 * 256;
@@ -434,6 +438,7 @@ strait_status strait_model_load(strait_ctx* c, const strait_model_desc* d, strai
             HIP_TRY(hipMemcpy(in.dev_valid, full.data(), full.size() * 4, hipMemcpyHostToDevice));
         }
     }
+    if ((rc = finish_plan(*m))) { free_model(m); return rc; }
     HIP_TRY(hipDeviceSynchronize());
     {
         std::lock_guard<std::mutex> lk(c->mu);
@@ -819,7 +824,7 @@ strait_status strait_read_activation(strait_model* m, int32_t instance, int32_t 
     Instance& in = m->inst[instance];
     hipStream_t s = compute_stream(m->ctx, STRAIT_PRIO_LOW, instance);
     HIP_TRY(hipSetDevice(m->ctx->device));
-    rc = run_plan(*m, in, batch, s, 0, layer, false);     // re-run the prefix: later layers reuse buffers
+    rc = run_plan(*m, in, batch, s, 0, layer, false, 0, true);     // re-run the prefix: later layers reuse buffers
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipMemcpy(host_out, in.bufs[op.out], need, hipMemcpyDeviceToHost));
@@ -920,6 +925,24 @@ strait_status strait_k_gemm(void* stream, const void* x, const void* w, const fl
     int rc = launch_conv(p, (hipStream_t)stream);
     if (ws) { (void)hipStreamSynchronize((hipStream_t)stream); (void)hipFree(ws); }
     return rc;
+}
+
+strait_status strait_k_gemm_ln(void* stream, const void* x, const void* w, const float* bias, const void* res, int32_t M, int32_t N, int32_t K,
+                               int32_t act, const float* ln_stats, const float* ln_csum, const float* ln_g, const float* ln_b, float ln_eps, void* y,
+                               float* stats_out, int32_t hp) {
+    if (M <= 0 || N <= 0 || K <= 0) { set_error("gemm_ln: needs positive sizes"); return STRAIT_E_SHAPE; }
+    ConvParams p{};
+    p.x = (const half_t*)x; p.w = (const half_t*)w; p.bias = bias; p.res = (const half_t*)res; p.y = y;
+    p.M = M; p.PQ = 1; p.Q = 1; p.H = 1; p.W = 1; p.C = K; p.R = 1; p.S = 1;
+    p.stride_h = p.stride_w = 1;
+    p.sN = K; p.sH = K; p.sW = K; p.Kg = K; p.ldw = K; p.Cout = N; p.ldy = N; p.act = act; p.hp = hp;
+    p.ln_stats = (const float2*)ln_stats; p.ln_csum = ln_csum; p.ln_g = ln_g; p.ln_b = ln_b; p.ln_eps = ln_eps; p.stats_out = (float2*)stats_out;
+    return launch_gemm_ln(p, (hipStream_t)stream);
+}
+
+strait_status strait_k_fold_layernorm(void* stream, const void* w, const float* b, const float* gamma, const float* beta, int32_t N, int32_t K,
+                                      void* w_out, float* csum, float* b_out) {
+    return launch_fold_layernorm((const half_t*)w, b, gamma, beta, N, K, (half_t*)w_out, csum, b_out, (hipStream_t)stream);
 }
 
 strait_status strait_k_pointwise_pair(void* stream, const void* x, const void* w3, const float* b3, const void* res, void* y,

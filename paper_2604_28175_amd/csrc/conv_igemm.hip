@@ -23,16 +23,10 @@
 #include <cmath>
 #include <type_traits>
 
-#include "activation.hpp"
-#include "kernels.hpp"
+#include "conv_dma.hpp"
 
 namespace strait {
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-enum { MODE_1X1 = 0, MODE_GATHER8 = 1, MODE_SCALAR = 2 };
 
 template <int BM, int BN, int MODE, bool STAGED>
 __global__ void __launch_bounds__(256) conv_igemm_kernel(const ConvParams p) {
@@ -256,480 +250,6 @@ __global__ void __launch_bounds__(256) conv_igemm_kernel(const ConvParams p) {
     }
 }
 
-
-// ------------------------------------------------------------------------------------------
-// Deep-pipelined variant for the regular cases: dense 1x1 / GEMM, and filters whose channel count
-// is a multiple of the 32-wide slice (so a slice never straddles two filter taps).
-//
-// The kernel above keeps one slice in flight per workgroup and spends most of its issue slots on
-// per-lane gather arithmetic.  Here
-//   - slices travel global -> LDS directly (buffer_load_dwordx4 ... lds: each lane names a 16-byte
-//     chunk, the wave's 64 chunks land in 1 KB of consecutive LDS) through a ring of STAGES
-//     buffers, one barrier per slice.  The operand fragments of a slice's first step are read right
-//     after the barrier that hands the slice over, ahead of the MFMAs of the slice before it, and the
-//     transfers that refill the freed buffer are issued between those MFMAs: a wavefront that is alone
-//     on its SIMD keeps the MFMA pipe fed across the barrier (8192 x 768 x 3072 on 128 x 192: 46 -> 41.5 us;
-//     what is left is LDS traffic, T per flop = 0.555 + 0.255 (LDS bytes per MFMA clock / 128) in 1 / PFLOP/s).
-//     The last STAGES slices run in a loop of their own that requests nothing;
-//   - the address of a chunk is split into a per-lane part fixed for the whole kernel (pixel or
-//     channel row, chunk within the slice) held in a VGPR, and a part that is the same for the
-//     whole workgroup (filter tap, channel base of the slice) kept in a scalar register and
-//     advanced by scalar instructions: a weight load costs no vector instruction at all, an input
-//     load one bit test and one select;
-//   - whether tap (r,s) of an output pixel falls inside the image is precomputed per lane as a bit
-//     mask over the taps; a tap outside, a row beyond M or a channel beyond Cout gets the offset
-//     0x80000000, which the buffer's range check turns into zeros in LDS (no stale data, no branch);
-//   - the hardware fixes the LDS position of lane i's chunk, so the bank-conflict-avoiding layout
-//     is obtained from the other side: rows are 64 bytes (4 chunks) and lane i fetches logical
-//     chunk (i & 3) ^ ((i >> 4) & 3) of its row, i.e. LDS holds chunk c of row r at position
-//     c ^ ((r >> 2) & 3); any 16 consecutive rows read at one logical chunk then touch 16
-//     distinct 16-byte bank groups;
-//   - the loads are issued from inline assembly so that the waits are ours: "all but the newest
-//     STAGES-2 slices have landed" before the barrier, rather than a wait for everything;
-//   - tiles are dealt to the XCDs as rectangles (tile_cw below): a batch of 8 sequences' Q/K/V product fetched its
-//     3.5 MB of weights into all eight L2s before, and fetches a quarter of them into each now (13.6 -> 9.8 us).
-typedef int intx4 __attribute__((ext_vector_type(4)));
-
-constexpr unsigned OOB_OFFSET = 0x80000000u;       // beyond any buffer this kernel accepts
-
-__device__ __forceinline__ intx4 make_rsrc(const void* base, unsigned bytes) {
-    const unsigned long long a = (unsigned long long)base;
-    intx4 r;
-    r[0] = (int)(unsigned)a;
-    r[1] = (int)((unsigned)(a >> 32) & 0xffffu);   // stride 0: raw buffer
-    r[2] = (int)bytes;                              // num_records in bytes
-    r[3] = 0x00020000;                              // 32-bit data format, offsets in bytes
-    return r;
-}
-
-// One wave-wide transfer of 64 x 16 bytes: lane i's chunk at rsrc.base + voff + soff goes to
-// LDS byte address lds_base + 16 i; lanes whose voff is out of range deposit zeros.
-__device__ __forceinline__ void dma16(intx4 rsrc, unsigned voff, unsigned soff, unsigned lds_base) {
-    const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m0v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_loads_then_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-// Waves per SIMD that the LDS footprint of a tile configuration allows (the register allocator is asked
-// for that many: left to itself it splits accumulators into AGPRs and loses waves for nothing).
-template <int BM, int BN, int BK, int WGM, int WGN, int STAGES>
-constexpr int dma_tile_waves_per_simd() {
-    constexpr int ring = STAGES * (BM + BN) * BK * 2, ctile = BM * (BN + 8) * 2;
-    constexpr int lds = (ring > ctile ? ring : ctile) + 1024;
-    constexpr int blocks = 160 * 1024 / lds;
-    constexpr int w = blocks * WGM * WGN / 4;
-    return w < 1 ? 1 : (w > 8 ? 8 : w);
-}
-
-// KG > 1: the workgroup holds KG groups of WGM x WGN wavefronts, all on the same output tile; group g reduces the g-th
-// part of the slices in a ring of its own, the groups step through their parts together (the barriers are the
-// workgroup's), and at the end groups 1.. hand their partial sums to group 0 through LDS, which adds them in group
-// order and finishes the tile.  A split reduction without a second launch, for the small batches where one more
-// launch costs as much as the convolution.
-//
-// RES: how a residual is added.  RES_LATE: to the rounded product, fetched as the tile is stored.  RES_EARLY: likewise, but requested right
-// after the reduction, before the staging barrier: that takes its latency off the path between the last MFMA and the stores.
-// RES_WIDE, for few outputs behind a long reduction: it goes through the staging tile first and is added in fp32, so that the
-// sum is rounded once, as in the second launch of a split reduction and in conv_skinny.hip.  (A 128-token sequence through twelve
-// encoder layers: relative error against 64-bit arithmetic 1.42e-3, with a rounding before the add 1.46e-3.)
-enum { RES_LATE = 0, RES_EARLY = 1, RES_WIDE = 2 };
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int STAGES, bool GELU, int RES, bool DUAL = false, int KG = 1>
-__global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG / 4 : dma_tile_waves_per_simd<BM, BN, BK, WGM, WGN, STAGES>())) conv_igemm_dma_kernel(const ConvParams p) {
-    static_assert(!DUAL || (MODE == MODE_1X1 && RES == RES_LATE && !GELU), "a second source belongs to a plain pointwise convolution");
-    static_assert(KG == 1 || (!GELU && !DUAL && KG * STAGES * (BM + BN) * BK * 2 + 1024 <= 160 * 1024 && WGM * WGN * KG <= 16), "groups: LDS or workgroup limit");
-    constexpr int CPRW = BK / 8;                       // 16-byte chunks per LDS row
-    constexpr int RPI = 64 / CPRW;                     // rows covered by one wave-wide transfer
-    constexpr int SWD = 16 / CPRW;                     // rows that share a bank window
-    constexpr int NW = WGM * WGN, NT = 64 * NW;        // the waves form a WGM x WGN grid over the tile
-    constexpr int TM = BM / WGM, TN = BN / WGN;
-    constexpr int TMB = TM / 32, TNB = TN / 32;
-    constexpr int XI = BM / (NW * RPI), WI = BN / (NW * RPI); // transfers per wave per slice
-    static_assert((BK == 32 || BK == 64) && TM % 32 == 0 && TN % 32 == 0 && BM % (NW * RPI) == 0 && BN % (NW * RPI) == 0, "unsupported tile");
-    static_assert((NW * RPI) % (SWD * CPRW) == 0, "the swizzle of a lane's row has to be the same in all of its transfers");
-    constexpr int STAGE = (BM + BN) * BK;              // halfs per stage
-    constexpr int LDC = BN + 8;
-    static_assert(MODE == MODE_1X1 || MODE == MODE_GATHER8, "vector modes only");
-    static_assert(STAGES >= 2 && STAGES * STAGE * 2 <= 160 * 1024 && BM * LDC * 2 <= 160 * 1024, "LDS limit");
-
-    extern __shared__ __attribute__((aligned(1024))) half_t smem_all[];    // max(KG * STAGES * STAGE, BM * LDC) halfs
-    const int group = KG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT) : 0;
-    half_t* const smem = smem_all + group * (STAGES * STAGE);          // this group's ring
-    const unsigned lds0 = (unsigned)(uintptr_t)smem;
-
-    if (p.hp) __builtin_amdgcn_s_setprio(3);
-
-    const int tid = (int)threadIdx.x - group * NT;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm0 = (wave % WGM) * TM, wn0 = (wave / WGM) * TN;
-    const int l32 = lane & 31, lh = lane >> 5;
-
-    const int tiles_n = (p.Cout + BN - 1) / BN;
-    int logical;
-    {
-        const int nb = gridDim.x, b = blockIdx.x;
-        const int per = nb >> 3, rem = nb & 7, xcd = b & 7, idx = b >> 3;
-        logical = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
-    }
-    // split-K: the grid holds ksplit copies of the tile grid; copy z reduces slices [k_begin, k_end)
-    int zsplit = 0, tile = logical;
-    if (KG > 1) zsplit = group;
-    else if (p.ksplit > 1) {
-        const int ntiles = gridDim.x / p.ksplit;
-        zsplit = logical / ntiles;
-        tile = logical - zsplit * ntiles;
-    }
-    // Tiles are numbered down groups of tile_cw tile columns (row-major inside a group), so that the contiguous range an XCD
-    // gets covers a rectangle of about equal extent in pixels and channels: its L2 then fetches the fewest operand rows.
-    int tm, tn;
-    {
-        const int tiles_m = (p.M + BM - 1) / BM;
-        const int gsz = tiles_m * p.tile_cw, g = tile / gsz, r = tile - g * gsz;
-        const int w = p.tile_cw < tiles_n - g * p.tile_cw ? p.tile_cw : tiles_n - g * p.tile_cw;
-        tm = r / w;
-        tn = g * p.tile_cw + (r - tm * w);
-    }
-    const int m0 = tm * BM;
-    const int n0 = tn * BN;
-
-    // The input buffer starts `lead` elements before x so that the per-lane offset of an output
-    // pixel (its window's top-left tap, which may lie in the padding) is never negative.
-    const long long lead = (long long)p.pad_h * p.sH + (long long)p.pad_w * p.sW;
-    const intx4 xrsrc = make_rsrc(p.x - lead, (unsigned)((p.x_elems + lead) * 2));
-    const intx4 wrsrc = make_rsrc(p.w, (unsigned)((long long)p.Cout * p.ldw * 2));
-
-    // ---- per-lane constants: row (lane >> 2) of each 16-row group, logical chunk cl ---------------
-    const int rsub = lane / CPRW;
-    const int cl = (lane % CPRW) ^ (((wave * RPI + rsub) / SWD) & (CPRW - 1));
-    unsigned xoff[XI], tapmask[XI];
-#pragma unroll
-    for (int j = 0; j < XI; ++j) {
-        const int m = m0 + (j * NW + wave) * RPI + rsub;
-        xoff[j] = OOB_OFFSET;
-        tapmask[j] = 0xffffffffu;
-        if (m < p.M) {
-            if (MODE == MODE_1X1 && p.stride_h == 1) {
-                xoff[j] = (unsigned)(((long long)m * p.sW + cl * 8) * 2);
-            } else {
-                const int n = m / p.PQ, rem = m - n * p.PQ;
-                const int pp = rem / p.Q, qq = rem - pp * p.Q;
-                const int ih0 = pp * p.stride_h - p.pad_h, iw0 = qq * p.stride_w - p.pad_w;
-                xoff[j] = (unsigned)(((long long)n * p.sN + (long long)(pp * p.stride_h) * p.sH +
-                                      (long long)(qq * p.stride_w) * p.sW + cl * 8) * 2);
-                if (MODE == MODE_GATHER8) {
-                    unsigned mask = 0;
-                    for (int rr = 0; rr < p.R; ++rr)
-                        for (int ss = 0; ss < p.S; ++ss)
-                            if ((unsigned)(ih0 + rr) < (unsigned)p.H && (unsigned)(iw0 + ss) < (unsigned)p.W)
-                                mask |= 1u << (rr * p.S + ss);
-                    tapmask[j] = mask;
-                }
-            }
-        }
-    }
-    // DUAL: the slices from p.C on come from the second tensor, addressed by output pixel with its own strides
-    const intx4 xrsrc2 = DUAL ? make_rsrc(p.x2, (unsigned)(p.x2_elems * 2)) : xrsrc;
-    unsigned xoff2[DUAL ? XI : 1];
-    if (DUAL) {
-#pragma unroll
-        for (int j = 0; j < XI; ++j) {
-            const int m = m0 + (j * NW + wave) * RPI + rsub;
-            xoff2[j] = OOB_OFFSET;
-            if (m < p.M) {
-                const int n = m / p.PQ, rem = m - n * p.PQ;
-                const int pp = rem / p.Q, qq = rem - pp * p.Q;
-                xoff2[j] = (unsigned)(((long long)n * p.sN2 + (long long)(pp * p.stride2) * p.sH2 +
-                                       (long long)(qq * p.stride2) * p.sW2 + cl * 8) * 2);
-            }
-        }
-    }
-    unsigned woff[WI];
-#pragma unroll
-    for (int j = 0; j < WI; ++j) {
-        const int n = n0 + (j * NW + wave) * RPI + rsub;
-        woff[j] = n < p.Cout ? (unsigned)(((long long)n * p.ldw + cl * 8) * 2) : OOB_OFFSET;
-    }
-
-    // ---- workgroup-uniform position of the slice being issued ---------------------------------
-    const int nk_all = (p.Kg + BK - 1) / BK;
-    const int kparts = KG > 1 ? KG : p.ksplit;
-    const int kchunk = (nk_all + kparts - 1) / kparts;
-    const int k_begin = zsplit * kchunk;
-    const int k_end = k_begin + kchunk < nk_all ? k_begin + kchunk : nk_all;
-    // (the groups of one workgroup share its barriers: all of them take kchunk steps, slices past a group's part arrive as zeros)
-    const int nk = KG > 1 ? kchunk : (k_end > k_begin ? k_end - k_begin : 0);
-    const bool ragged_k = (p.Kg & (BK - 1)) != 0;      // only possible for 1x1 / GEMM
-    int ki = k_begin;                                  // slice index
-    int tap = 0, ts = 0, cb = 0;                       // filter tap, its column, channel base
-    unsigned tap_off = 0;                              // byte offset of the tap: (r*sH + s*sW) * 2
-    if (MODE == MODE_GATHER8 && k_begin > 0) {
-        const int per_tap = p.C / BK;
-        tap = k_begin / per_tap;
-        cb = (k_begin - tap * per_tap) * BK;
-        const int r0 = tap / p.S;
-        ts = tap - r0 * p.S;
-        tap_off = (unsigned)(r0 * p.sH + ts * p.sW) * 2u;
-    }
-    const unsigned row_step = (unsigned)(p.sH - p.S * p.sW) * 2u;   // from the end of a filter row to the next
-
-    // one transfer (j-th of this wave's XI + WI) of the slice being issued
-    auto issue_one = [&](int stage, int j) __attribute__((always_inline)) {
-        const unsigned sx = lds0 + (unsigned)(stage * STAGE) * 2u;
-        const unsigned sw = sx + (unsigned)(BM * BK) * 2u;
-        const bool live = ki < k_end;                  // slices past the end deposit zeros
-        if (j < XI) {
-            const bool second = DUAL && ki * BK >= p.C;   // workgroup-uniform
-            const unsigned soff_x = MODE == MODE_1X1 ? (unsigned)(second ? ki * BK - p.C : ki * BK) * 2u : tap_off + (unsigned)cb * 2u;
-            unsigned v = xoff[j];
-            if (DUAL && second) v = xoff2[j];
-            if (MODE == MODE_GATHER8) v = ((tapmask[j] >> tap) & 1u) ? v : OOB_OFFSET;
-            if (MODE == MODE_1X1 && ragged_k) v = (ki * BK + cl * 8 < p.Kg) ? v : OOB_OFFSET;
-            if (!live) v = OOB_OFFSET;
-            dma16(second ? xrsrc2 : xrsrc, v, live ? soff_x : 0u, sx + (unsigned)((j * NW + wave) * 1024));
-        } else {
-            const int jw = j - XI;
-            unsigned v = woff[jw];                     // (a weight row's ragged end is followed by the next row, which may hold infinities)
-            if (MODE == MODE_1X1 && ragged_k) v = (ki * BK + cl * 8 < p.Kg) ? v : OOB_OFFSET;
-            dma16(wrsrc, live ? v : OOB_OFFSET, live ? (unsigned)ki * (BK * 2) : 0u, sw + (unsigned)((jw * NW + wave) * 1024));
-        }
-    };
-    auto advance = [&]() __attribute__((always_inline)) {
-        ++ki;
-        if (MODE == MODE_GATHER8) {
-            cb += BK;
-            if (cb >= p.C) {
-                cb = 0;
-                ++tap;
-                tap_off += (unsigned)p.sW * 2u;
-                if (++ts == p.S) { ts = 0; tap_off += row_step; }
-            }
-        }
-    };
-    auto issue = [&](int stage) {
-#pragma unroll
-        for (int j = 0; j < XI + WI; ++j) issue_one(stage, j);
-        advance();
-    };
-
-    floatx16 acc[TNB][TMB];
-#pragma unroll
-    for (int a = 0; a < TNB; ++a)
-#pragma unroll
-        for (int b = 0; b < TMB; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-
-    // The tile's bias row goes to LDS with the very first transfer (channels past Cout, or no bias at all,
-    // arrive as zeros), so that the epilogue does not start with a round trip to L2.
-    constexpr unsigned BIAS_LDS = (KG * STAGES * STAGE > BM * LDC ? KG * STAGES * STAGE : BM * LDC) * 2;   // byte offset
-    static_assert(BN <= 256, "bias row: one transfer carries 256 floats");
-    if (wave == 0) {                                   // (every group fetches it, so that the wavefronts' transfer counts agree)
-        const intx4 brsrc = make_rsrc(p.bias, p.bias ? (unsigned)p.Cout * 4u : 0u);
-        const int c = n0 + lane * 4;
-        dma16(brsrc, (p.bias && lane * 4 < BN && c + 3 < p.Cout) ? (unsigned)c * 4u : OOB_OFFSET, 0u, (unsigned)(uintptr_t)smem_all + BIAS_LDS);
-    }
-
-#pragma unroll
-    for (int i = 0; i < STAGES; ++i) if (i == 0 || i < nk) issue(i);
-
-    const int swz = (l32 / SWD) & (CPRW - 1);
-    constexpr int KS = BK / 16;
-    half8 wf[2][TNB], xf[2][TMB];
-    auto load_frags = [&](int buf, int stage, int ks) __attribute__((always_inline)) {
-        const half_t* Xs = smem + stage * STAGE;
-        const half_t* Ws = Xs + BM * BK;
-        const int pos = ((ks * 2 + lh) ^ swz) * 8;
-#pragma unroll
-        for (int a = 0; a < TNB; ++a) wf[buf][a] = *(const half8*)(Ws + (wn0 + a * 32 + l32) * BK + pos);
-#pragma unroll
-        for (int b = 0; b < TMB; ++b) xf[buf][b] = *(const half8*)(Xs + (wm0 + b * 32 + l32) * BK + pos);
-    };
-    constexpr int NX = XI + WI, NM = TMB * TNB, PER = (NX + NM - 1) / NM;   // transfers per slice, MFMAs per step, transfers per MFMA
-    int rd = 0;
-    if (nk >= STAGES) wait_loads_then_barrier<(STAGES - 1) * NX>(); else wait_loads_then_barrier<0>();
-    load_frags(0, 0, 0);
-    // main part: every step requests a further slice; tail: the last STAGES slices, nothing left to request
-    const int nmain = nk - STAGES;
-    for (int kt = 0; kt < nmain; ++kt) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int frd = rd;
-            if (ks + 1 < KS) load_frags((ks + 1) & 1, rd, ks + 1);
-            else {
-                wait_loads_then_barrier<(STAGES - 2) * NX>();   // slice kt + 1 has landed everywhere; slice kt's buffer is free
-                rd = rd + 1 == STAGES ? 0 : rd + 1;
-                load_frags((ks + 1) & 1, rd, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int q = 0; q < NM; ++q) {
-                const int a = q / TMB, b = q % TMB;
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[ks & 1][a], xf[ks & 1][b], acc[a][b], 0, 0, 0);
-                if (ks == KS - 1) {
-#pragma unroll
-                    for (int j = q * PER; j < (q + 1) * PER && j < NX; ++j) issue_one(frd, j);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (ks == KS - 1) advance();
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    for (int kt = nmain > 0 ? nmain : 0; kt < nk; ++kt) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            if (ks + 1 < KS) load_frags((ks + 1) & 1, rd, ks + 1);
-            else {
-                wait_loads_then_barrier<0>();
-                rd = rd + 1 == STAGES ? 0 : rd + 1;
-                load_frags((ks + 1) & 1, rd, 0);                 // (after the last slice: whatever the buffer holds, not used)
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int q = 0; q < NM; ++q) {
-                const int a = q / TMB, b = q % TMB;
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[ks & 1][a], xf[ks & 1][b], acc[a][b], 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    __syncthreads();                                   // LDS is free
-
-    // ---- groups: partial sums of groups 1.. to group 0 through LDS, added in group order ----------------------
-    if (KG > 1) {
-        float* xch = (float*)smem_all;                 // [KG - 1][NW][TNB * TMB * 16][64 lanes]
-        if (group > 0) {
-            float* dst = xch + ((group - 1) * NW + wave) * (TNB * TMB * 16 * 64) + lane;
-#pragma unroll
-            for (int a = 0; a < TNB; ++a)
-#pragma unroll
-                for (int b = 0; b < TMB; ++b)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) dst[((a * TMB + b) * 16 + v) * 64] = acc[a][b][v];
-        }
-        __syncthreads();
-        if (group == 0) {
-            for (int g = 1; g < KG; ++g) {
-                const float* src = xch + ((g - 1) * NW + wave) * (TNB * TMB * 16 * 64) + lane;
-#pragma unroll
-                for (int a = 0; a < TNB; ++a)
-#pragma unroll
-                    for (int b = 0; b < TMB; ++b)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) acc[a][b][v] += src[((a * TMB + b) * 16 + v) * 64];
-            }
-        }
-        __syncthreads();                               // before the epilogue parks the output tile in the same memory
-    }
-    const bool finisher = KG == 1 || group == 0;       // the other groups only keep the epilogue's barrier company
-
-    // ---- split-K: fp32 partial sums to this copy's slab; a second kernel reduces and finishes ------
-    if (p.ksplit > 1) {
-        float* slab = p.ws + (long long)zsplit * p.M * p.Cout;
-#pragma unroll
-        for (int a = 0; a < TNB; ++a)
-#pragma unroll
-            for (int b = 0; b < TMB; ++b) {
-                const int m = m0 + wm0 + b * 32 + l32;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int n = n0 + wn0 + a * 32 + 8 * g + 4 * lh;
-                    if (m < p.M && n < p.Cout) {
-                        float4 v = make_float4(acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]);
-                        *(float4*)(slab + (long long)m * p.Cout + n) = v;
-                    }
-                }
-            }
-        return;
-    }
-
-    // ---- epilogue (same as the first kernel's staged path) --------------------------------------
-    // ReLU / ReLU6 / none are one clamp with workgroup-uniform bounds; GELU is a separate instantiation
-    // The epilogue's arithmetic after the bias is done on packed fp16 pairs: adding two fp16 numbers, or
-    // clamping one against 0, 6 or an infinity, gives the same fp16 result whether it is done in fp16 or
-    // in fp32 and then rounded, and it takes a quarter of the instructions (short-reduction layers spend
-    // most of their instructions here).  Bias and residual are fetched where they are used: holding
-    // them across the reduction would cost a wave per SIMD in registers.
-    constexpr int CPR = BN / 8, NCH = BM * CPR / NT;
-    half_t* Cs = smem_all;
-    const bool fuse_act = RES == RES_WIDE || p.res == nullptr;
-    const half_t lo = (p.act == ACT_RELU || p.act == ACT_RELU6) ? (half_t)0.f : (half_t)-INFINITY;
-    const half_t hi = p.act == ACT_RELU6 ? (half_t)6.f : (half_t)INFINITY;
-    const half_t lo1 = fuse_act ? lo : (half_t)-INFINITY, hi1 = fuse_act ? hi : (half_t)INFINITY;
-    const half4 lo4 = {lo1, lo1, lo1, lo1}, hi4 = {hi1, hi1, hi1, hi1};
-    const half8 lo8 = {lo, lo, lo, lo, lo, lo, lo, lo}, hi8 = {hi, hi, hi, hi, hi, hi, hi, hi};
-    auto residual_chunk = [&](int i) {
-        const int id = tid + i * NT;
-        const int row = id / CPR, c8 = id - row * CPR;
-        const int m = m0 + row, n = n0 + c8 * 8;
-        half8 r;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) r[j] = (half_t)0.f;
-        if (m < p.M && n < p.Cout) r = *(const half8*)(p.res + (long long)m * p.ldy + n);
-        return r;
-    };
-    const float* bias_s = (const float*)((const char*)smem_all + BIAS_LDS);
-    auto bias4 = [&](int a, int g, float (&bv)[4]) {
-        const float4 b4 = *(const float4*)(bias_s + wn0 + a * 32 + 8 * g + 4 * lh);
-        bv[0] = b4.x; bv[1] = b4.y; bv[2] = b4.z; bv[3] = b4.w;
-    };
-    half8 rv[RES == RES_EARLY ? NCH : 1];
-    if (RES == RES_EARLY && !fuse_act && finisher) {
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) rv[i] = residual_chunk(i);
-    }
-    if (RES == RES_WIDE) {
-        if (finisher) {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int id = tid + i * NT, row = id / CPR, c8 = id - row * CPR;
-                *(half8*)(Cs + row * LDC + c8 * 8) = residual_chunk(i);
-            }
-        }
-        __syncthreads();
-    }
-    if (finisher)
-#pragma unroll
-    for (int a = 0; a < TNB; ++a)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int cn = wn0 + a * 32 + 8 * g + 4 * lh;
-            float bv[4];
-            bias4(a, g, bv);
-#pragma unroll
-            for (int b = 0; b < TMB; ++b) {
-                half4* const at = (half4*)(Cs + (wm0 + b * 32 + l32) * LDC + cn);
-                half4 h, r;
-                if (RES == RES_WIDE) r = *at;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float v = acc[a][b][4 * g + j] + bv[j];
-                    if (RES == RES_WIDE) v += (float)r[j];
-                    if (GELU) v = gelu_f(v);
-                    h[j] = (half_t)v;
-                }
-                *at = __builtin_elementwise_min(__builtin_elementwise_max(h, lo4), hi4);
-            }
-        }
-    __syncthreads();
-    if (!finisher) return;
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-        const int id = tid + i * NT;
-        const int row = id / CPR, c8 = id - row * CPR;
-        const int m = m0 + row, n = n0 + c8 * 8;
-        if (m < p.M && n < p.Cout) {
-            half8 v = *(const half8*)(Cs + row * LDC + c8 * 8);
-            if (!fuse_act) {
-                const half8 r = RES == RES_EARLY ? rv[i] : residual_chunk(i);
-                v = __builtin_elementwise_min(__builtin_elementwise_max(v + r, lo8), hi8);
-            }
-            *(half8*)((half_t*)p.y + (long long)m * p.ldy + n) = v;
-        }
-    }
-}
 
 // Second pass of a split-K launch: y = act(sum_z slab_z + bias (+ res)), 8 channels per thread,
 // slabs summed in a fixed order so that results do not depend on scheduling.
@@ -1229,9 +749,6 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
 // The rows of the kernel through registers are fits to 230 layers with fp32 or odd outputs (mean error 17 to 20 %).
 // Against the thresholds used before (and with the pipelined loop): ResNet-50's layers 7 % faster on the sum over batch 1
 // to 128 (22 % at batch 1, 5 % at 128), an encoder layer's products 8 to 19 % from 1000 rows on and 20 to 32 % below.
-enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
-              T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64,
-              T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_COUNT };   // (slabs: slab_split)
 struct TileInfo { int bm, bn, bk, kg; bool shared; float c[7]; };   // shared: two or more workgroups fit a compute unit
 static const TileInfo tile_info[T_ESTIMATED] = {
     {256, 256, 64, 1, false, {2.047f, 4.619f, 1.152f, 0.199f, 10.088f, 0.100f, 0.086f}},
@@ -1545,6 +1062,27 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
     }
     if (p.x2) { set_error("conv: a second source needs the LDS-direct kernels (sizes out of their range)"); return -5; }
     return through_registers();
+}
+
+// The same for a dense product with a LayerNorm folded in: the LDS-direct kernel only, on the tiles that gemm_ln.hip instantiates (slices of 64).
+int choose_gemm_ln(ConvParams& p) {
+    int mode = 0;
+    bool staged = false;
+    const int rc = choose_conv(p, &mode, &staged);     // checks the parameters and fills in what is derived
+    if (rc < 0) return rc;
+    if (mode != MODE_1X1 || !staged || p.stride_h != 1 || p.x2 || p.Kg % 64 != 0 || p.Cout % 64 != 0) { set_error("gemm with LayerNorm: not a dense product of whole 64-channel groups"); return -5; }
+    p.ksplit = 1;
+    const double mb = ((double)p.x_elems * 2 + (double)p.Cout * p.Kg * 2 + (double)p.M * p.Cout * (p.res ? 4 : 2)) * 1e-6;
+    int best = -5;
+    float best_us = 1e30f;
+    for (int i = 0; i < T_DMA; ++i) {
+        const TileInfo& t = tile_info[i];
+        if (p.ln_stats && t.bn == 256 && (p.ln_csum ? p.Kg : p.Cout) > 64 * LN_MAX_PARTS_256) continue;         // (LDS)
+        if (t.bk != 64 || (t.kg > 1 && (p.Kg < 512 || p.act == ACT_GELU)) || (t.bm < 128 && mb > 250)) continue;
+        const float us = estimate_us(p, (TileId)i, p.M, false, true, mb);
+        if (us < best_us) { best_us = us; best = i; }
+    }
+    return best;
 }
 
 int launch_conv(const ConvParams& params, hipStream_t stream) {

@@ -50,6 +50,17 @@ struct ConvParams {
     int K2, stride2, sH2, sW2;
     long long sN2;
     long long x2_elems;      // extent of x2 in elements; filled in by launch_conv
+    // A LayerNorm folded into the products on its two sides (launch_gemm_ln only).  Statistics of a tensor [M][n], n a multiple of 64: for each
+    // row and 64 channels {sum, sum of squares about their own mean}, [M][n / 64]; 16-byte aligned.
+    const float2* ln_stats;  // of the input (with ln_csum) or of the residual (with ln_g, ln_b), which is then normalised
+    const float* ln_csum;    // [Cout] sums of the rows of w, which holds gamma; bias holds w beta
+    const float* ln_g; const float* ln_b;    // [Cout]
+    float ln_eps, ln_inv_n;  // (ln_inv_n filled in by launch_gemm_ln)
+    float2* stats_out;       // of the output
+    // Between two such products a tensor [M][n] may lie in slices of 64 channels, [n / 64][M][64]: what a tile reads of a slice is then one piece of
+    // memory and not a row every 2 n bytes.
+    int x_sliced, y_sliced;
+    unsigned x_slice;        // bytes from one slice of the input to the next; filled in by launch_gemm_ln
 };
 
 int launch_conv(const ConvParams& p, hipStream_t stream);
@@ -60,6 +71,16 @@ size_t conv_workspace_bytes(const ConvParams& p, size_t limit);
 // launch_conv with x_elems filled in; C and Kg multiples of 64.
 int launch_conv_skinny(const ConvParams& p, int tn, bool gather, hipStream_t stream);
 int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn);
+
+// A dense product with a LayerNorm folded in (gemm_ln.hip): of its input (ln_stats, ln_csum; no residual), or its output's statistics for one that
+// follows (stats_out; with a residual, normalised where ln_stats, ln_g and ln_b are given).
+int launch_gemm_ln(const ConvParams& p, hipStream_t stream);
+// whether launch_gemm_ln takes M x N x K products whose normalised width is `width`
+bool gemm_ln_supported(long long M, long long N, long long K, int width);
+// w [N][K], b [N] and the LayerNorm's gamma, beta [K] -> fp16(gamma w), its row sums, b + w beta
+int launch_fold_layernorm(const half_t* w, const float* b, const float* gamma, const float* beta, int N, int K, half_t* w_out, float* csum, float* b_out,
+                          hipStream_t stream);
+int choose_gemm_ln(ConvParams& p);                     // >= 0 a tile (conv_dma.hpp: TileId); < 0 an error
 
 // Two chained pointwise convolutions in one launch (pointwise_pair.hip):
 //   y[m, 0:N1] = act1(x[m, 0:K1] w3^T + b3 (+ res[m, 0:N1]));   z[m, 0:N2] = act2(y[m, 0:N1] w1^T + b1)

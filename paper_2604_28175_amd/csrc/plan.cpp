@@ -79,19 +79,34 @@ static int parse_container(const void* blob, size_t bytes, Container& c) {
 
 // ------------------------------------------------------------------------------------------
 // weight preparation (host) + upload
+static int upload_weights(Model& m, const void* host, size_t bytes, void** dev) {
+    void* d = nullptr;
+    const size_t padded = (bytes + 255) / 256 * 256;
+    if (hipMalloc(&d, padded) != hipSuccess) { set_error("hipMalloc(%zu) for weights failed", padded); return STRAIT_E_NOMEM; }
+    m.dev_allocs.push_back(d);
+    HIP_TRY(hipMemset(d, 0, padded));
+    HIP_TRY(hipMemcpy(d, host, bytes, hipMemcpyHostToDevice));
+    *dev = d;
+    return 0;
+}
+
+int finish_plan(Model& m) {
+    if (m.fold_tmp) { (void)hipFree(m.fold_tmp); m.fold_tmp = nullptr; }
+    for (Model::Cold& c : m.cold) {
+        void *w = nullptr, *b = nullptr;
+        int rc;
+        if ((rc = upload_weights(m, c.w.data(), c.w.size() * 2, &w)) || (rc = upload_weights(m, c.b.data(), c.b.size() * 4, &b))) return rc;
+        m.ops[c.op].w = (const half_t*)w;
+        m.ops[c.op].bias = (const float*)b;
+    }
+    m.cold.clear();
+    return 0;
+}
+
 struct Loader {
     Model& m;
     const Container& c;
-    int upload(const void* host, size_t bytes, void** dev) {
-        void* d = nullptr;
-        const size_t padded = (bytes + 255) / 256 * 256;
-        if (hipMalloc(&d, padded) != hipSuccess) { set_error("hipMalloc(%zu) for weights failed", padded); return STRAIT_E_NOMEM; }
-        m.dev_allocs.push_back(d);
-        HIP_TRY(hipMemset(d, 0, padded));
-        HIP_TRY(hipMemcpy(d, host, bytes, hipMemcpyHostToDevice));
-        *dev = d;
-        return 0;
-    }
+    int upload(const void* host, size_t bytes, void** dev) { return upload_weights(m, host, bytes, dev); }
     static bool shape_is(const TensorView* v, std::initializer_list<unsigned> s) {
         if (!v || v->ndim != (int)s.size()) return false;
         int i = 0;
@@ -278,7 +293,8 @@ struct Loader {
         return 0;
     }
     // linear layers: rows of several [out_i, in] matrices stacked, biases concatenated
-    int linear_weights(std::initializer_list<std::string> names, unsigned in, Op& op, unsigned* total_out) {
+    // (cold: of the op about to be added; they stay on the host until finish_plan)
+    int linear_weights(std::initializer_list<std::string> names, unsigned in, Op& op, unsigned* total_out, bool cold = false) {
         std::vector<half_t> w;
         std::vector<float> b;
         for (const std::string& nm : names) {
@@ -289,15 +305,16 @@ struct Loader {
             for (unsigned i = 0; i < tb->count; ++i) b.push_back((float)tb->data[i]);
         }
         if (in % 8 != 0) { set_error("linear layer input width %u must be a multiple of 8", in); return STRAIT_E_SHAPE; }
+        op.ldw = (int)in;
+        *total_out = (unsigned)b.size();
+        op.info.weight_bytes = (int64_t)w.size() * 2 + (int64_t)b.size() * 4;
+        if (cold) { m.cold.push_back({m.ops.size(), std::move(w), std::move(b)}); return 0; }
         void *dw = nullptr, *db = nullptr;
         int rc;
         if ((rc = upload(w.data(), w.size() * 2, &dw))) return rc;
         if ((rc = upload(b.data(), b.size() * 4, &db))) return rc;
         op.w = (const half_t*)dw;
         op.bias = (const float*)db;
-        op.ldw = (int)in;
-        *total_out = (unsigned)b.size();
-        op.info.weight_bytes = (int64_t)w.size() * 2 + (int64_t)b.size() * 4;
         return 0;
     }
     int vector_f32(const std::string& name, unsigned n, const float** dev) {
@@ -505,7 +522,7 @@ struct Builder {
     // a linear layer applied to every row of a [rows][K] activation per sample (token-wise GEMM); several weight
     // matrices of the container may be stacked along the output axis (Q | K | V)
     int token_gemm(const std::string& name, std::initializer_list<std::string> ws, int rows, int in, int K, int N, int act,
-                   int res, int out) {
+                   int res, int out, bool cold = false) {
         Op op;
         name_op(op, name, 0);
         op.kind = OP_CONV;
@@ -514,7 +531,7 @@ struct Builder {
         op.C = K; op.K = N; op.vC = K; op.vR = op.vS = 1; op.vH = op.vW = 1;
         op.sN = K; op.sH = K; op.sW = K;
         unsigned nout = 0;
-        int rc = ld.linear_weights(ws, K, op, &nout);
+        int rc = ld.linear_weights(ws, K, op, &nout, cold);
         if (rc) return rc;
         if ((int)nout != N) { set_error("'%s': expected %d outputs, container has %u", name.c_str(), N, nout); return STRAIT_E_FORMAT; }
         op.info.macs_per_sample = (int64_t)rows * K * N;
@@ -536,6 +553,42 @@ struct Builder {
         op.info.bytes_per_sample = 4LL * rows * width;
         op.info.weight_bytes = 8LL * width;
         m.ops.push_back(op);
+        return 0;
+    }
+
+    // Marks the LayerNorm op `ln`, which normalises what the product right before it writes, as one that can be folded into that product, into op `in`,
+    // which multiplies its output, and into op `res`, if given, which adds it.  Nothing else may read its output.
+    int fold_layer_norm(int ln, int in, int res) {
+        Op &l = m.ops[ln], &c = m.ops[in];
+        if (l.K % 64 != 0 || l.K > 1024 || c.vC != l.K || c.ldw != l.K || c.K % 64 != 0 || m.ops[ln - 1].vC % 64 != 0) return 0;
+        const size_t n = (size_t)c.K * l.K;
+        void *w = nullptr, *v = nullptr;
+        if (hipMalloc(&w, n * 2) != hipSuccess) { set_error("hipMalloc(%zu) for weights failed", n * 2); return STRAIT_E_NOMEM; }
+        m.dev_allocs.push_back(w);
+        if (hipMalloc(&v, (size_t)c.K * 8) != hipSuccess) { set_error("hipMalloc(%zu) for weights failed", (size_t)c.K * 8); return STRAIT_E_NOMEM; }
+        m.dev_allocs.push_back(v);
+        c.w_ln = (const half_t*)w; c.csum_ln = (const float*)v; c.bias_ln = (const float*)v + c.K;
+        const Model::Cold* src = nullptr;
+        for (const Model::Cold& s : m.cold) if (s.op == (size_t)in) src = &s;
+        if (!src) { set_error("'%s': its weights are not on the host", c.name.c_str()); return STRAIT_E_INVALID; }
+        const size_t need = n * 2 + (size_t)c.K * 4;
+        if (m.fold_tmp_bytes < need) {
+            if (m.fold_tmp) { (void)hipFree(m.fold_tmp); m.fold_tmp = nullptr; }
+            m.fold_tmp_bytes = 0;
+            if (hipMalloc(&m.fold_tmp, need) != hipSuccess) { m.fold_tmp = nullptr; set_error("hipMalloc(%zu) for weights failed", need); return STRAIT_E_NOMEM; }
+            m.fold_tmp_bytes = need;
+        }
+        HIP_TRY(hipMemcpy(m.fold_tmp, src->w.data(), n * 2, hipMemcpyHostToDevice));
+        HIP_TRY(hipMemcpy((char*)m.fold_tmp + n * 2, src->b.data(), (size_t)c.K * 4, hipMemcpyHostToDevice));
+        const int rc = launch_fold_layernorm((const half_t*)m.fold_tmp, (const float*)((char*)m.fold_tmp + n * 2), l.bias, l.beta, c.K, l.K, (half_t*)w,
+                                             (float*)v, (float*)v + c.K, nullptr);
+        if (rc) return rc;
+        HIP_TRY(hipStreamSynchronize(nullptr));
+        l.fold_ops[0] = ln - 1; l.fold_ops[1] = in; l.fold_ops[2] = res;
+        l.ln_slot = m.ln_folds++ & 1;
+        m.ops[ln - 1].ln_out = ln;
+        c.ln_in = ln;
+        if (res >= 0) m.ops[res].ln_res = ln;
         return 0;
     }
 
@@ -784,8 +837,8 @@ static int plan_vit(Model& m, Builder& b) {
     if (seq > 256) { set_error("ViT: %d tokens, at most 256 are supported", seq); return STRAIT_E_SHAPE; }
     m.seq = seq; m.hidden = hidden;
     Loader& ld = b.ld;
-    auto gemm = [&](const std::string& name, std::initializer_list<std::string> ws, int in, int K, int N, int act, int res, int out) {
-        return b.token_gemm(name, ws, seq, in, K, N, act, res, out);
+    auto gemm = [&](const std::string& name, std::initializer_list<std::string> ws, int in, int K, int N, int act, int res, int out, bool cold = false) {
+        return b.token_gemm(name, ws, seq, in, K, N, act, res, out, cold);
     };
     auto lnorm = [&](const std::string& name, int in, int out, int rows, long long in_stride) {
         return b.layer_norm(name, in, out, 0, rows, hidden, 1e-6f, in_stride);
@@ -819,7 +872,8 @@ static int plan_vit(Model& m, Builder& b) {
         const int n1 = b.pl.get(tok);
         if ((rc = lnorm(p + ".ln1", z, n1, seq, 0))) return rc;
         const int qkv = b.pl.get(3 * tok);
-        if ((rc = gemm(p + ".qkv", {p + ".q", p + ".k", p + ".v"}, n1, hidden, 3 * hidden, ACT_NONE, SLOT_NONE, qkv))) return rc;
+        if ((rc = gemm(p + ".qkv", {p + ".q", p + ".k", p + ".v"}, n1, hidden, 3 * hidden, ACT_NONE, SLOT_NONE, qkv, i > 0))) return rc;
+        if (i > 0 && (rc = b.fold_layer_norm((int)m.ops.size() - 2, (int)m.ops.size() - 1, -1))) return rc;
         b.pl.put(n1);
         const int att = b.pl.get(tok);
         b.attention(p + ".attn", qkv, att, seq, heads, hidden);
@@ -831,7 +885,8 @@ static int plan_vit(Model& m, Builder& b) {
         const int n2 = b.pl.get(tok);
         if ((rc = lnorm(p + ".ln2", z1, n2, seq, 0))) return rc;
         const int f = b.pl.get((size_t)seq * ffn);
-        if ((rc = gemm(p + ".ffn1", {p + ".ffn1"}, n2, hidden, ffn, ACT_GELU, SLOT_NONE, f))) return rc;
+        if ((rc = gemm(p + ".ffn1", {p + ".ffn1"}, n2, hidden, ffn, ACT_GELU, SLOT_NONE, f, true))) return rc;
+        if ((rc = b.fold_layer_norm((int)m.ops.size() - 2, (int)m.ops.size() - 1, -1))) return rc;
         b.pl.put(n2);
         const int z2 = b.pl.get(tok);
         if ((rc = gemm(p + ".ffn2", {p + ".ffn2"}, f, ffn, hidden, ACT_NONE, z1, z2))) return rc;
@@ -851,41 +906,47 @@ static int plan_encoder(Model& m, Builder& b) {
     if (heads <= 0 || hidden != heads * 64) { set_error("encoder: head dimension must be 64 (hidden %d, heads %d)", hidden, heads); return STRAIT_E_SHAPE; }
     if (seq <= 0 || seq > 256) { set_error("encoder: sequence length %d must be in 1..256", seq); return STRAIT_E_SHAPE; }
     if (ffn % 8 != 0) { set_error("encoder: ffn width must be a multiple of 8"); return STRAIT_E_SHAPE; }
-    auto gemm = [&](const std::string& name, std::initializer_list<std::string> ws, int in, int K, int N, int act, int res, int out) {
-        return b.token_gemm(name, ws, seq, in, K, N, act, res, out);
+    auto gemm = [&](const std::string& name, std::initializer_list<std::string> ws, int in, int K, int N, int act, int res, int out, bool cold = false) {
+        return b.token_gemm(name, ws, seq, in, K, N, act, res, out, cold);
     };
     auto lnorm = [&](const std::string& name, int in, int out, int out_ref) {
         return b.layer_norm(name, in, out, out_ref, seq, hidden, 1e-12f, 0);
     };
-    int x = SLOT_INPUT, rc;
+    // (a tensor that a LayerNorm reads lives as long as that LayerNorm's output: where it is folded, the products read the tensor itself)
+    int x = SLOT_INPUT, x_raw = SLOT_NONE, rc;
     const size_t tok = (size_t)seq * hidden;
     for (int i = 0; i < layers; ++i) {
         char pre[16];
         snprintf(pre, sizeof(pre), "l%d", i);
         const std::string p(pre);
         const int qkv = b.pl.get(3 * tok);
-        if ((rc = gemm(p + ".qkv", {p + ".q", p + ".k", p + ".v"}, x, hidden, 3 * hidden, ACT_NONE, SLOT_NONE, qkv))) return rc;
+        if ((rc = gemm(p + ".qkv", {p + ".q", p + ".k", p + ".v"}, x, hidden, 3 * hidden, ACT_NONE, SLOT_NONE, qkv, i > 0))) return rc;
+        const int qkv_op = (int)m.ops.size() - 1;
         const int att = b.pl.get(tok);
         b.attention(p + ".attn", qkv, att, seq, heads, hidden);
         b.pl.put(qkv);
         const int t = b.pl.get(tok);
         if ((rc = gemm(p + ".o", {p + ".o"}, att, hidden, hidden, ACT_NONE, x, t))) return rc;
+        if (i > 0 && (rc = b.fold_layer_norm(qkv_op - 1, qkv_op, (int)m.ops.size() - 1))) return rc;
         b.pl.put(att);
         const int h = b.pl.get(tok);
         if ((rc = lnorm(p + ".ln1", t, h, 0))) return rc;
-        b.pl.put(t);
+        const int ln1_op = (int)m.ops.size() - 1;
+        b.pl.put(x_raw);
         b.pl.put(x);
         const int f = b.pl.get((size_t)seq * ffn);
-        if ((rc = gemm(p + ".ffn1", {p + ".ffn1"}, h, hidden, ffn, ACT_GELU, SLOT_NONE, f))) return rc;
+        if ((rc = gemm(p + ".ffn1", {p + ".ffn1"}, h, hidden, ffn, ACT_GELU, SLOT_NONE, f, true))) return rc;
         const int t2 = b.pl.get(tok);
         if ((rc = gemm(p + ".ffn2", {p + ".ffn2"}, f, ffn, hidden, ACT_NONE, h, t2))) return rc;
+        if ((rc = b.fold_layer_norm(ln1_op, ln1_op + 1, (int)m.ops.size() - 1))) return rc;
         b.pl.put(f);
+        b.pl.put(t);
         const bool last = i == layers - 1;
         const int y = last ? SLOT_OUT : b.pl.get(tok);
         if ((rc = lnorm(p + ".ln2", t2, y, 0))) return rc;
-        b.pl.put(t2);
         b.pl.put(h);
         x = y;
+        x_raw = t2;
     }
     Op am;
     name_op(am, "argmax", 2);
@@ -960,7 +1021,7 @@ static void* slot_ptr(Model& m, Instance& in, int slot, int ref, int batch) {
     return nullptr;
 }
 
-int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer) {
+int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer, bool read_last) {
     const int n = (int)m.ops.size();
     if (last_layer < 0 || last_layer >= n) last_layer = n - 1;
     // Per-layer timing and prefix runs keep everything on the one stream (their events bracket single launches).
@@ -984,9 +1045,22 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
         }
         return with_proj ? 3 : 0;                       // 3: no pair, but the convolution takes the projection as a second source
     };
+    // whether LayerNorm op `ln` is folded into the products on its two sides; every layer it concerns comes to the same answer, also where a batch
+    // is issued in segments
+    if (first_layer == 0) in.ln_fold = m.ctx->pair_min_pixels > 0;
+    auto folded = [&](int ln) {
+        if (ln < 0 || m.ops[ln].fold_ops[0] < 0 || !in.ln_fold) return false;
+        for (int o : m.ops[ln].fold_ops)
+            if (o >= 0 && !gemm_ln_supported((long long)batch * m.ops[ln].P, m.ops[o].K, m.ops[o].vC, m.ops[ln].K)) return false;
+        return true;
+    };
     for (int i = first_layer; i <= last_layer; ++i) {
         const Op& op = m.ops[i];
         stream = main_stream;
+        if (op.kind == OP_LAYERNORM && folded(i) && !(read_last && i == last_layer)) {
+            if (timed) { HIP_TRY(hipEventRecord(in.layer_ev[i], stream)); in.layer_skipped[i] = 1; }
+            continue;
+        }
         if (i == fused_away || i == stem_next_done || (op.proj_of >= 0 && pair_here(op.proj_of) >= 2)) {
             if (timed) { HIP_TRY(hipEventRecord(in.layer_ev[i], stream)); in.layer_skipped[i] = 1; }
             continue;
@@ -1056,6 +1130,29 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                     p.x2 = (const half_t*)slot_ptr(m, in, dn.in, 0, batch);
                     p.K2 = dn.vC; p.stride2 = dn.stride; p.sH2 = dn.sH; p.sW2 = dn.sW; p.sN2 = dn.sN;
                     p.Kg = op.vC + dn.vC; p.ldw = p.Kg;
+                }
+                const bool fold_in = folded(op.ln_in), fold_res = folded(op.ln_res), fold_out = folded(op.ln_out);
+                if (fold_in || fold_res || fold_out) {
+                    const Op* l = fold_in ? &m.ops[op.ln_in] : fold_res ? &m.ops[op.ln_res] : nullptr;
+                    if (l) { p.ln_stats = in.ln_stats[l->ln_slot]; p.ln_eps = l->eps; }
+                    if (fold_in) {
+                        p.x = (const half_t*)slot_ptr(m, in, l->in, 0, batch);
+                        p.w = op.w_ln; p.bias = op.bias_ln; p.ln_csum = op.csum_ln;
+                    } else if (fold_res) {
+                        p.res = (const half_t*)slot_ptr(m, in, l->in, 0, batch);
+                        p.ln_g = l->bias; p.ln_b = l->beta;
+                    }
+                    // (behind a folded residual the kernel always leaves statistics: where nobody reads them, in the other buffer)
+                    // a product that reads a folded product's output right behind it, and is one itself, has it in slices (8192 x 768 x 3072 and 12608 x
+                    // 768 x 3072: 1 to 7 % a launch, and 15 % where the two operands' places in memory clash)
+                    auto sliced = [&](int o) { return o + 1 < n && m.ops[o].kind == OP_CONV && m.ops[o + 1].kind == OP_CONV && folded(m.ops[o].ln_in) &&
+                                                      (folded(m.ops[o + 1].ln_out) || folded(m.ops[o + 1].ln_res)); };
+                    p.y_sliced = fold_in && sliced(i) && !(read_last && i == last_layer);
+                    p.x_sliced = !fold_in && i > 0 && sliced(i - 1);
+                    if (fold_out) p.stats_out = in.ln_stats[m.ops[op.ln_out].ln_slot];
+                    else if (fold_res) p.stats_out = in.ln_stats[1 - l->ln_slot];
+                    rc = launch_gemm_ln(p, stream);
+                    break;
                 }
                 // the split-K workspace belongs to the main stream's launches; a branch running beside them goes without
                 if (stream == main_stream) { p.ws = in.splitk_ws; p.ws_bytes = SPLITK_WS_BYTES; }

@@ -56,6 +56,13 @@ struct Op {
     bool dw_next = false;
     const half_t* w_proj = nullptr;
     const float* bias_proj = nullptr;
+    // A LayerNorm between token-wise products can be folded into them (gemm_ln.hip).  On the LayerNorm: fold_ops, the products concerned (before it;
+    // behind it, reading its output; reading it as a residual, or -1), and ln_slot, the instance's statistics buffer it takes.  On those products
+    // its index, as ln_out, ln_in, ln_res.  w_ln, bias_ln, csum_ln: the weights of an ln_in product with gamma, beta and the row sums in them.
+    int fold_ops[3] = {-1, -1, -1};
+    int ln_slot = 0, ln_out = -1, ln_in = -1, ln_res = -1;
+    const half_t* w_ln = nullptr;
+    const float *bias_ln = nullptr, *csum_ln = nullptr;
     // implicit-GEMM addressing (elements), see ConvParams
     long long sN = 0; int sH = 0, sW = 0, stride_w = 1, pad_h = 0, pad_w = 0, vC = 0, vR = 0, vS = 0, vH = 0, vW = 0;
     int ldw = 0;
@@ -80,6 +87,8 @@ struct Instance {
     void* dev_out = nullptr;
     int32_t* dev_valid = nullptr;
     float* splitk_ws = nullptr;        // fp32 slabs of split-K convolutions (small batches)
+    bool ln_fold = true;               // whether the batch in flight was begun with LayerNorms folded
+    float2* ln_stats[2] = {nullptr, nullptr};   // statistics of the tensors that a folded LayerNorm normalises; consecutive ones alternate
     std::vector<void*> bufs;
     HostControl* ctl = nullptr;        // pinned: timestamps and completion flags of the batch in flight, written by the GPU
     HostControl* ctl_dev = nullptr;    // the same memory as the GPU addresses it
@@ -112,7 +121,15 @@ struct Model {
     std::vector<size_t> buf_elems;     // per-sample elements of each activation buffer
     size_t in_elems = 0;               // per-sample fp16 input elements
     int classes = 0;                   // CNN
-    int seq = 0, hidden = 0;           // encoder
+    int seq = 0, hidden = 0;           // encoder, Vision Transformer
+    int ln_folds = 0;                  // LayerNorms that can be folded into products
+    // Weights of products that a folded LayerNorm replaces, on the host until everything that a batch does read has its place (finish_plan): what a
+    // batch reads then lies together and in the 256 MB memory-side cache.  (ViT batch 7, products of 3072 inputs: 23.6 us a launch, with
+    // 100 MB of such weights in between, against 19.6.)
+    struct Cold { size_t op; std::vector<half_t> w; std::vector<float> b; };
+    std::vector<Cold> cold;
+    void* fold_tmp = nullptr;          // device memory the fold reads them from
+    size_t fold_tmp_bytes = 0;
     std::vector<void*> dev_allocs;     // weights
     std::vector<Instance> inst;
     std::mutex mu;
@@ -191,7 +208,9 @@ struct Context {
 };
 
 int build_plan(Model& m, const void* blob, size_t bytes);
+int finish_plan(Model& m);             // after the instances' buffers
 // Enqueues layers first_layer..last_layer (last_layer < 0: up to the end) of the plan for `batch` samples on `stream`.
-int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer = 0);
+// read_last: the output of last_layer is going to be read by the caller (a layer folded or laid out for the next one is then computed as it is).
+int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer = 0, bool read_last = false);
 
 }  // namespace strait

@@ -649,6 +649,65 @@ def test_gelu_over_its_range(S):
     assert y[0] == np.inf and not np.isfinite(y[2]) and np.array_equal(y[[1, 3, 4, 5, 6, 7]], [0, 6.5, 0, 0, 30000, 0])
 
 
+@pytest.mark.parametrize("M,H,N,act,spread", [
+    # one row; a ragged last tile of each size; one to sixteen groups of 64 channels; GELU
+    (1, 64, 64, 0, 1.0), (37, 192, 576, 0, 1.0), (129, 768, 2304, 0, 1.0), (300, 768, 3072, 3, 1.0), (1025, 1024, 256, 0, 1.0), (1379, 768, 2304, 0, 1.0),
+    (2600, 768, 768, 3, 1.0), (5000, 512, 2304, 0, 1.0), (8200, 768, 768, 0, 1.0), (12608, 768, 3072, 3, 1.0),
+    # a row mean of 200 times the deviation
+    (260, 768, 768, 0, 0.005)])
+def test_gemm_with_folded_layernorm(S, M, H, N, act, spread):
+    """y1 = x0 w0^T + b0 + res with its statistics, then act(LN(y1) w1^T + b1), then LN(y1) as the residual of a third product."""
+    eps, rows = 1e-6, min(M, 400)
+    x0, w0, b0 = f16(R.standard_normal((M, 128)) * spread), f16(R.standard_normal((H, 128)) * 128 ** -0.5), np.zeros(H, np.float32)
+    res = f16(R.standard_normal((M, H)) * spread + 1.0)
+    g, be = R.uniform(0.8, 1.2, H).astype(np.float32), (R.standard_normal(H) * 0.1).astype(np.float32)
+    w1, b1 = f16(R.standard_normal((N, H)) * H ** -0.5), (R.standard_normal(N) * 0.1).astype(np.float32)
+    y1, st = S.k_gemm_ln(dev(S, x0), dev(S, w0), dev(S, b0), res=dev(S, res), stats=True)
+    plain = S.k_gemm(dev(S, x0), dev(S, w0), dev(S, b0), res=dev(S, res))
+    v = y1.cpu().numpy().astype(np.float64)
+    check_kernel(v, plain.cpu().numpy().astype(np.float64), "folded: first product")
+    q = v.reshape(M, H // 64, 64)
+    ref = np.stack([q.sum(-1), ((q - q.mean(-1, keepdims=True)) ** 2).sum(-1)], -1)
+    # 64 additions and 64 squares in 32 bits
+    assert np.all(np.abs(st.cpu().numpy() - ref) <= 1e-5 * np.stack([np.abs(q).sum(-1), ref[..., 1] + 1e-6 * (q ** 2).sum(-1)], -1))
+    wl, cs, bl = S.k_fold_layernorm(dev(S, w1), dev(S, b1), dev(S, g), dev(S, be))
+    wg = w1.astype(np.float64) * g                     # rounded to fp16 once, or to fp32 and then to fp16
+    assert np.all(np.abs(wl.cpu().numpy() - wg) <= np.abs(wg) * 2.0 ** -11 * 1.001 + 2.0 ** -25)
+    y2, _ = S.k_gemm_ln(y1, wl, bl, act, ln_stats=st, ln_csum=cs, ln_eps=eps)
+    at = np.linspace(0, M - 1, rows).astype(int)
+    norm = ops.layernorm(v[at], g, be, eps)
+    check_kernel(y2.float().cpu().numpy()[at], act_ref(ops.linear(norm, w1, b1), act), f"folded: {M}x{N}x{H} act {act}")
+    # the third product's residual is LN(y1); K of 1088 and few tiles: the residual goes through LDS, else it is fetched early
+    for K in (64, 1088):
+        x3, w3 = f16(R.standard_normal((M, K))), f16(R.standard_normal((H, K)) * K ** -0.5)
+        y3, s3 = S.k_gemm_ln(dev(S, x3), dev(S, w3), dev(S, b0), res=y1, ln_stats=st, ln_g=dev(S, g), ln_b=dev(S, be), ln_eps=eps, stats=True)
+        o = y3.cpu().numpy().astype(np.float64)
+        check_kernel(o[at], norm + ops.linear(x3[at], w3, b0), f"folded residual: {M}x{H}x{K}")
+        assert np.all(np.abs(s3.cpu().numpy()[..., 0] - o.reshape(M, H // 64, 64).sum(-1)) <= 1e-5 * np.abs(o).reshape(M, H // 64, 64).sum(-1))
+
+
+def test_gemm_with_folded_layernorm_of_equal_numbers_and_errors(S):
+    """A row of equal numbers normalises to beta alone; infinities stay in their row; what the kernel has no form for is refused."""
+    x = np.full((70, 128), 3.0, np.float16)
+    x[1], x[2, 5], x[3] = 0, np.inf, R.standard_normal(128)
+    w, b = f16(R.standard_normal((64, 128))), np.ones(64, np.float32)
+    g, be = np.full(128, 2, np.float32), R.standard_normal(128).astype(np.float32)
+    wl, cs, bl = S.k_fold_layernorm(dev(S, w), dev(S, b), dev(S, g), dev(S, be))
+    q = x.astype(np.float32).reshape(70, 2, 64)
+    with np.errstate(invalid="ignore"):
+        st = np.stack([q.sum(-1), ((q - q.mean(-1, keepdims=True)) ** 2).sum(-1)], -1)
+    y = S.k_gemm_ln(dev(S, x), wl, bl, ln_stats=dev(S, st), ln_csum=cs, ln_eps=1e-12)[0].float().cpu().numpy()
+    beta = ops.linear(be[None], w, b)[0]
+    ok = np.r_[0, 1, 4:70]
+    check_kernel(y[ok], np.broadcast_to(beta, (68, 64)), "equal rows")
+    check_kernel(y[3:4], ops.linear(ops.layernorm(x[3:4].astype(np.float64), g, be, 1e-12), w, b), "ordinary row")
+    x, st, r = dev(S, x), dev(S, st), dev(S, np.zeros((70, 64), np.float16))
+    for bad in (dict(w=wl), dict(w=wl, ln_stats=st), dict(w=wl, ln_stats=st, ln_csum=cs, res=r), dict(w=wl, stats=True), dict(w=wl, ln_stats=st, ln_csum=cs, act=1),
+                dict(w=wl, ln_stats=st, ln_csum=cs, stats=True, res=r), dict(w=wl, res=r, stats=True, ln_stats=st), dict(w=wl[:40], ln_stats=st, ln_csum=cs)):
+        with pytest.raises(S.StraitError):
+            S.k_gemm_ln(x, bias=bl, **bad)
+
+
 @pytest.mark.parametrize("M,N,K,use_res", [
     # many sizes of output, ragged in pixels and (where the layer allows it) in channels and slices
     (6311, 2304, 512, False), (8617, 1160, 64, False), (8347, 456, 64, True), (6455, 1184, 136, False), (8298, 280, 192, True),

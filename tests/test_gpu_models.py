@@ -208,6 +208,60 @@ def test_encoder(ctx, kw, batch):
     m.free()
 
 
+@pytest.mark.parametrize("arch,kw,batch", [("encoder", dict(layers=3, hidden=128, heads=2, ffn=256, seq=40), 5),
+                                           ("encoder", dict(layers=2, hidden=768, heads=12, ffn=3072, seq=128), 3),
+                                           ("encoder", dict(layers=2, hidden=1024, heads=16, ffn=512, seq=33), 2),     # sixteen statistics a row
+                                           ("encoder", dict(layers=2, hidden=1088, heads=17, ffn=256, seq=33), 2),     # one too many: not folded
+                                           ("encoder", dict(layers=2, hidden=128, heads=2, ffn=200, seq=40), 2),       # FFN1 cannot take it in
+                                           ("vit", dict(layers=3, hidden=192, heads=3, ffn=384), 3)])
+def test_folded_layernorms(ctx, arch, kw, batch):
+    """LayerNorms inside the products on their two sides against launches of their own; segments; every layer's own output; timing."""
+    if arch == "encoder":
+        md = synth.encoder(5, **kw)
+        x, vl = synth.token_batch(md, batch, 7, min_len=20)
+        ref = omodels.encoder_forward(md.tensors, x, vl, md.hyper, keep=True)
+    else:
+        md = synth.vit(5, hw=96, classes=50, **kw)
+        x, vl = synth.default_image_batch(md, batch, 7), None
+        ref = omodels.vit_forward(md.tensors, x, md.hyper, keep=True)
+    key = "hidden" if arch == "encoder" else "logits"
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    rows = [slice(0, int(n)) for n in vl] if arch == "encoder" else [slice(None)] * batch
+    try:
+        got = m.infer(x, vl, prio=ctx.S.PRIO_LOW)[0][key]
+        for b in range(batch):
+            check_kernel(got[b][rows[b]], ref.logits[b][rows[b]], f"{arch} sample {b}", rel=2.0 ** -8, abs_rel=1e-2)
+        ctx.set_lp_yield(1)                                  # every layer in a segment of its own
+        assert np.array_equal(m.infer(x, vl, prio=ctx.S.PRIO_LOW)[0][key], got)
+        ctx.set_lp_yield(3)
+        assert np.array_equal(m.infer(x, vl, prio=ctx.S.PRIO_LOW)[0][key], got)
+        ctx.set_lp_yield(0)
+        ctx.set_pair_fusion(0)
+        apart = m.infer(x, vl, prio=ctx.S.PRIO_LOW)[0][key]
+        for b in range(batch):
+            check_kernel(apart[b][rows[b]], got[b][rows[b]].astype(np.float64), f"{arch} sample {b} apart", rel=2.0 ** -8, abs_rel=1e-2)
+        ctx.set_pair_fusion(40000)
+        if vl is not None:
+            m.copy_in(0, ctx.S.PRIO_LOW, x, vl)
+        else:
+            m.copy_in(0, ctx.S.PRIO_LOW, x)
+        names = [li.name.decode() for li in m.layers()]
+        checked = 0
+        for i, nm in enumerate(names):
+            if nm not in ref.trace.acts or not nm.startswith("l") or nm == f"l{kw['layers'] - 1}.ln2":      # (the last one is the output)
+                continue
+            act = ref.trace.acts[nm]
+            a = m.read_activation(0, i, batch).astype(np.float64).reshape(act.shape)
+            for b in range(batch):
+                check_kernel(a[b][rows[b]], act[b][rows[b]], f"layer {nm}", rel=2.0 ** -8, abs_rel=1e-2)
+            checked += 1
+        assert checked >= 5 * kw["layers"] - 1
+    finally:
+        ctx.set_lp_yield(0)
+        ctx.set_pair_fusion(40000)
+        m.free()
+
+
 @pytest.mark.parametrize("hw,batch,fc", [(32, 5, 64), (64, 3, 256)])
 def test_vgg19(ctx, hw, batch, fc):
     md = synth.vgg19(synth.SEEDS[synth.ARCH_VGG19], hw=hw, classes=100, fc=fc)
