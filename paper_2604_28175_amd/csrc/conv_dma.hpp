@@ -62,6 +62,12 @@ __device__ __forceinline__ void dma16(intx4 rsrc, unsigned voff, unsigned soff, 
     const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m0v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
+__device__ __forceinline__ void divmod_f(int v, int d, float rcp, int& q, int& r) {   // exact for 0 <= v < 2^24
+    q = (int)((float)v * rcp);
+    r = v - q * d;
+    if (r < 0) { --q; r += d; }
+    if (r >= d) { ++q; r -= d; }
+}
 template <int N>
 __device__ __forceinline__ void wait_loads_then_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
@@ -630,6 +636,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
 // The tiles a layer is given to one of (conv_igemm.hip: choose_conv).
 enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
               T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64,
-              T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_COUNT };   // (slabs: slab_split)
+              T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_SMALL32x16, T_SMALL64x16, T_SMALL64x32, T_SMALL128x32,
+              T_COUNT };                               // (slabs: slab_split; small: small_us)
 
 }  // namespace strait

@@ -316,12 +316,6 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(const ConvParams p) 
 // fixed number of transfers, so the in-order load counter tells when a given stage has landed.  LDS rows of 64
 // bytes are swizzled as in the kernel above (16-byte chunk c of row i sits at c ^ ((i >> 2) & 3)), which keeps
 // the operand reads conflict free for any run of consecutive rows, i.e. for every tap offset.
-__device__ __forceinline__ void divmod_f(int v, int d, float rcp, int& q, int& r) {   // exact for 0 <= v < 2^24
-    q = (int)((float)v * rcp);
-    r = v - q * d;
-    if (r < 0) { --q; r += d; }
-    if (r >= d) { ++q; r -= d; }
-}
 constexpr int patch_share(int npw, int as, int t) { return npw - t * as < 0 ? 0 : (npw - t * as > as ? as : npw - t * as); }
 
 constexpr int patch_wait(int npw, int as, int wi, int pre, int t) {     // transfers a wave may have in flight when tap step t starts
@@ -781,7 +775,7 @@ static const char* const tile_name[T_COUNT] = {
     "256x256x64", "256x192x64", "192x128x64", "128x256x64", "128x128x64, 8 wavefronts", "128x128x64", "96x128x64", "64x128x64", "256x128x32", "128x64x32, 2 slices",
     "128x64x32, 3 slices", "64x64x64", "64x64x32", "32x64x64", "64x64x64, 2 groups", "32x64x64, 4 groups", "small outputs 16x16", "small outputs 16x32",
     "patch 256x128", "patch 128x128", "patch 256x64", "through registers 128x128", "through registers 128x64", "through registers 64x64",
-    "slabs 64x64x64", "slabs 64x64x32"};
+    "slabs 64x64x64", "slabs 64x64x32", "small 3x3 32x16", "small 3x3 64x16", "small 3x3 64x32", "small 3x3 128x32"};
 
 // The patch kernel's view of a layer: strips and bordered pixels (mv); -1 = not a layer of its.
 static int patch_geometry(const ConvParams& p, int* strip_w, int* slots, long long* mv) {
@@ -914,6 +908,18 @@ static float estimate_us(const ConvParams& p, TileId id, long long pixels, bool 
                    t.c[6] * std::max(0.0, mb - 250.0));
 }
 
+// The small 3x3 kernel's tiles (conv3x3_small.hip), T_SMALL32x16 on: their time is the launch, a round of tiles, a slice of 64 channels, its patch (in
+// transfers of 32 slots) and the operands' megabytes.  Fits to 152 to 188 layers each (1 to 32 images of 5 to 64 pixels, 64 to 512 channels; mean error 1.5 %,
+// largest 6.5 %; the choice among them was the best of them every time).
+struct SmallTile { int bm, bn; float c[5]; };
+static const SmallTile small_tile[4] = {{32, 16, {1.428f, 2.552f, 0.236f, 0.0627f, 0.021f}}, {64, 16, {1.494f, 2.644f, 0.550f, 0.0211f, 0.f}},
+                                        {64, 32, {1.348f, 2.764f, 0.605f, 0.0712f, 0.f}}, {128, 32, {1.259f, 2.766f, 0.913f, 0.0644f, 0.116f}}};
+static float small_us(const ConvParams& p, const SmallTile& t, double mb) {
+    const long long mv = (long long)(p.M / p.PQ) * (p.H + 1) * (p.W + 1);
+    const double r = std::ceil((double)((mv + t.bm - 1) / t.bm * (p.Cout / t.bn)) / 256.0), nk = p.C / 64;
+    return (float)(t.c[0] + r * (t.c[1] + nk * (t.c[2] + t.c[3] * ((t.bm + 2 * (p.W + 1) + 2 + 31) / 32))) + t.c[4] * mb);
+}
+
 static int launch_tile_id(const ConvParams& p, TileId id, int mode, bool staged, hipStream_t stream) {
     switch (id) {
         case T256x256: return launch_dma_tile<256, 256, 64, 2, 4, 2>(p, mode, stream);
@@ -939,6 +945,8 @@ static int launch_tile_id(const ConvParams& p, TileId id, int mode, bool staged,
         case T_REG128x128: return launch_tile<128, 128>(p, mode, staged, stream);
         case T_REG128x64: return launch_tile<128, 64>(p, mode, staged, stream);
         case T_REG64x64: return launch_tile<64, 64>(p, mode, staged, stream);
+        case T_SMALL32x16: case T_SMALL64x16: case T_SMALL64x32: case T_SMALL128x32:
+            return launch_conv3x3_small(p, small_tile[id - T_SMALL32x16].bm, small_tile[id - T_SMALL32x16].bn, stream);
         default: return launch_conv3x3_patch(p, id, stream);
     }
 }
@@ -1034,6 +1042,14 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
                     if (patch_takes(p, (TileId)i, &mv)) consider((TileId)i, mv);
                 }
             }
+            if (gather && p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 1 && p.pad_w == 1 && !p.res &&
+                p.Q == p.W && p.PQ == p.H * p.W) {
+                for (int i = 0; i < 4; ++i) {
+                    if (!conv3x3_small_takes(p, small_tile[i].bm, small_tile[i].bn)) continue;
+                    const float us = small_us(p, small_tile[i], mb);
+                    if (us < best_us) { best_us = us; best = (TileId)(T_SMALL32x16 + i); }
+                }
+            }
         } else {
             // fp32 outputs, and counts of channels that are no whole chunks: the register-staged kernel on the tile that fills the chip,
             // against the small-output kernel further down.  With fp32 outputs 16384 x 768 x 4096 takes 168 us here and 1034 there, 2221 x
@@ -1053,7 +1069,7 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
         if ((!staged || p.Kg > 4608) && p.ws && (reinterpret_cast<uintptr_t>(p.ws) & 15) == 0) {
             float us;
             const int ks = slab_split(p, p.ws_bytes, gather, &us);
-            if (ks > 1 && us < (best >= T_REG128x128 ? 1.f : 0.8f) * best_us) {
+            if (ks > 1 && us < (best >= T_REG128x128 && best < T_SMALL32x16 ? 1.f : 0.8f) * best_us) {
                 p.ksplit = ks;
                 return whole64 ? T_SLABS64 : T_SLABS64s;
             }

@@ -70,6 +70,10 @@ size_t conv_workspace_bytes(const ConvParams& p, size_t limit);
 // Small outputs with a reduction worth sharing out (conv_skinny.hip): 16 pixels x tn (16 or 32) channels per workgroup.  Called by
 // launch_conv with x_elems filled in; C and Kg multiples of 64.
 int launch_conv_skinny(const ConvParams& p, int tn, bool gather, hipStream_t stream);
+// 3x3 with stride 1 and padding 1 on small images (conv3x3_small.hip), bm bordered pixels x bn channels per workgroup; called by launch_conv with x_elems
+// filled in.  No residual; C a multiple of 64.
+bool conv3x3_small_takes(const ConvParams& p, int bm, int bn);
+int launch_conv3x3_small(const ConvParams& p, int bm, int bn, hipStream_t stream);
 int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn);
 
 // A dense product with a LayerNorm folded in (gemm_ln.hip): of its input (ln_stats, ln_csum; no residual), or its output's statistics for one that

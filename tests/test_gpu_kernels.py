@@ -846,6 +846,22 @@ def test_every_kernel_integer_data_is_bit_exact(S, kernel, shape, use_res):
     assert S.torch.equal(y.float().reshape(ref.shape), ref)
 
 
+@pytest.mark.parametrize("tile,shapes", [
+    # one slice, a few, more than the ring holds; short patches and, in the second half, the longest ones
+    ("32x16", [(9, 42, 4, 64, 16), (17, 52, 8, 128, 16), (40, 10, 6, 512, 16), (2, 59, 27, 64, 16), (3, 14, 24, 192, 96), (2, 4, 22, 320, 160)]),
+    ("64x16", [(17, 43, 4, 64, 64), (3, 52, 5, 192, 256), (9, 29, 6, 320, 80), (1, 25, 55, 64, 160), (2, 34, 17, 192, 160), (9, 3, 62, 320, 96)]),
+    ("64x32", [(40, 56, 6, 64, 32), (5, 34, 8, 128, 256), (17, 40, 8, 320, 64), (1, 33, 50, 64, 160), (9, 17, 45, 192, 64), (9, 56, 28, 512, 32)]),
+    ("128x32", [(9, 32, 19, 64, 160), (3, 43, 30, 192, 160), (9, 40, 30, 512, 64), (3, 46, 62, 64, 96), (3, 46, 62, 192, 96), (5, 43, 50, 704, 64)])])
+def test_small_3x3_integer_data_is_bit_exact(S, tile, shapes):
+    """The 3x3 kernel of small images, each tile: ragged last tiles, images of any height, rounds of workgroups."""
+    for N, H, W, C, K in shapes:
+        test_every_kernel_integer_data_is_bit_exact(S, "small 3x3 " + tile, (N, H, W, C, K, 3, 1, 1), False)
+        x, w = f16(R.standard_normal((N, H, W, C))), f16(R.standard_normal((K, 3, 3, C)) * (9 * C) ** -0.5)
+        y = S.k_conv2d(dev(S, x), dev(S, w), None, 1, 1, 2)                 # no bias, ReLU6
+        ref = S.torch.nn.functional.conv2d(dev(S, x).float().permute(0, 3, 1, 2), dev(S, w).float().permute(0, 3, 1, 2), padding=1).permute(0, 2, 3, 1)
+        check_kernel(y.float().cpu().numpy(), ref.clamp(0, 6).cpu().numpy(), f"small 3x3 {tile} {N}x{H}x{W}x{C}->{K}")
+
+
 def test_split_reduction_under_capture(S):
     """A product whose reduction is split allocates a workspace; on a stream that records a graph it takes a kernel that needs none."""
     M, N, K = 270, 512, 4096
