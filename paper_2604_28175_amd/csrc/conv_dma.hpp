@@ -123,7 +123,14 @@ __device__ __forceinline__ float sum_of_8_lanes(float v) {     // of the aligned
     return v;
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int STAGES, bool GELU, int RES, bool DUAL = false, int KG = 1, int LN = LN_NONE>
+// DEEP, for tiles of few MFMAs per wavefront and step: operands are read from LDS three steps ahead and not one, so that a step does not wait for
+// LDS, and reads are in flight across the barrier; a stage is filled again one slice later.  1024 x 3072 x 768 with GELU on 128 x 128 tiles of 8
+// wavefronts 11.7 -> 11.2 us, 2758 x 768 x 3072 on 96 x 128 22.7 -> 21.2, 1379 x 768 x 3072 on 128 x 64 17.6 -> 16.5 (on 64 x 128, as before, 18.2).  What is
+// left is the rate of the transfers, 60 to 75 B/ns per compute unit whatever the tile: rings of 6 or 8 stages change nothing.
+// Short reductions on the 128 x 128 tile are better off without (3136 x 1024 x 256 with a residual 7.3 and 7.6): there from 512 on.
+template <int BM, int BN, int BK, int WGM, int WGN>
+constexpr bool dma_deep() { return BK == 64 && ((BM == 96 && BN == 128) || (BM == 128 && (BN == 128 || BN == 64) && WGM * WGN == 8)); }
+template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int STAGES, bool GELU, int RES, bool DUAL = false, int KG = 1, int LN = LN_NONE, bool DEEP = dma_deep<BM, BN, BK, WGM, WGN>()>
 __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG / 4 : dma_tile_waves_per_simd<BM, BN, BK, WGM, WGN, STAGES>())) conv_igemm_dma_kernel(const ConvParams p) {
     static_assert(!DUAL || (MODE == MODE_1X1 && RES == RES_LATE && !GELU), "a second source belongs to a plain pointwise convolution");
     static_assert(LN == LN_NONE || (MODE == MODE_1X1 && !DUAL && (LN == LN_IN ? RES == RES_LATE : !GELU && RES == RES_F32)), "LayerNorm belongs to dense products");
@@ -318,7 +325,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     const int ln_parts = (LN == LN_IN ? p.Kg : p.Cout) >> 6;
     if (LN == LN_IN || LN == LN_RES) {
         // the tile's rows' statistics lie in one piece; rows past the end arrive as zeros
-        static_assert(BM * 8 % 256 == 0, "alignment");
+        static_assert(LN == LN_NONE || BM * 8 % 256 == 0, "alignment");
         const intx4 srsrc = make_rsrc(p.ln_stats, (unsigned)((long long)p.M * ln_parts * 8));
         const unsigned piece = (unsigned)(BM * ln_parts * 8), at = (unsigned)m0 * (unsigned)ln_parts * 8u;
         for (unsigned o = wave * 1024u; o < piece; o += NW * 1024u)
@@ -336,11 +343,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     }
 
 #pragma unroll
-    for (int i = 0; i < STAGES; ++i) if (i == 0 || i < nk) issue(i);
+    for (int i = 0; i < (DEEP ? STAGES - 1 : STAGES); ++i) if (i == 0 || i < nk) issue(i);
 
     const int swz = (l32 / SWD) & (CPRW - 1);
     constexpr int KS = BK / 16;
-    half8 wf[2][TNB], xf[2][TMB];
+    half8 wf[DEEP ? KS : 2][TNB], xf[DEEP ? KS : 2][TMB];
     auto load_frags = [&](int buf, int stage, int ks) __attribute__((always_inline)) {
         const half_t* Xs = smem + stage * STAGE;
         const half_t* Ws = Xs + BM * BK;
@@ -351,6 +358,78 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
         for (int b = 0; b < TMB; ++b) xf[buf][b] = *(const half8*)(Xs + (wm0 + b * 32 + l32) * BK + pos);
     };
     constexpr int NX = XI + WI, NM = TMB * TNB, PER = (NX + NM - 1) / NM;   // transfers per slice, MFMAs per step, transfers per MFMA
+    // LN_IN, LN_RES: in every wavefront once the first slice is there
+    auto ln_combine = [&]() __attribute__((always_inline)) {
+    if (LN == LN_IN || LN == LN_RES) {
+        // the row's mean and deviation from its parts (sum s, sum of squares q about the part's own mean): two threads a row, every other part each
+        static_assert(LN == LN_NONE || LN == LN_OUT || NT >= 2 * BM, "two threads per row");
+        const float2* parts = (const float2*)((const char*)smem_all + PARTS_LDS) + (tid >> 1) * ln_parts;
+        float2 pt[LN_MAX_PARTS / 2];
+        float s = 0.f, q = 0.f;
+#pragma unroll
+        for (int i = 0; i < LN_MAX_PARTS / 2; ++i) {
+            const int k = 2 * i + (tid & 1);
+            pt[i] = parts[k < ln_parts ? k : 0];
+            s += k < ln_parts ? pt[i].x : 0.f;
+        }
+        s += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0xB1, 0xf, 0xf, true));
+        const float mean = s * p.ln_inv_n;
+#pragma unroll
+        for (int i = 0; i < LN_MAX_PARTS / 2; ++i) {
+            const float d = pt[i].x * (1.f / 64.f) - mean;
+            q += 2 * i + (tid & 1) < ln_parts ? pt[i].y + 64.f * d * d : 0.f;
+        }
+        q += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, q), 0xB1, 0xf, 0xf, true));
+        const float rs = __builtin_amdgcn_rsqf(q * p.ln_inv_n + p.ln_eps);
+        // (a row of equal numbers is beta alone: nothing of the products' rounding may be scaled up)
+        if (tid < 2 * BM && (tid & 1) == 0 && (KG == 1 || group == 0))
+            *(float2*)((char*)smem_all + ROWS_LDS + (tid >> 1) * 8) = q == 0.f ? make_float2(0.f, 0.f) : make_float2(rs, -rs * mean);
+    }
+    };
+    if constexpr (DEEP) {
+        static_assert(KS == 4 && STAGES >= 4, "four steps a slice, and a stage that is being left");
+        if (nk >= STAGES - 1) wait_loads_then_barrier<(STAGES - 2) * NX>(); else wait_loads_then_barrier<0>();
+#pragma unroll
+        for (int k = 0; k < 3; ++k) load_frags(k, 0, k);
+        int rd = 0, fill = STAGES - 1;                 // stage in use, stage to fill (left by everyone at the barrier inside a slice)
+        auto slice = [&](auto refillc, auto nextc) __attribute__((always_inline)) {
+            constexpr bool REFILL = decltype(refillc)::value, NEXT = decltype(nextc)::value;
+            const int nrd = rd + 1 == STAGES ? 0 : rd + 1;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if (ks == 0) load_frags(KS - 1, rd, KS - 1);
+                else if (NEXT) {
+                    if (ks == 1) {
+                        // slice kt + 1 has landed everywhere, and everyone has multiplied with slice kt - 1
+                        if (REFILL) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 3) * NX) : "memory");
+                        else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+                    }
+                    load_frags(ks - 1, nrd, ks - 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < NM; ++q) {
+                    const int a = q / TMB, b = q % TMB;
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[ks][a], xf[ks][b], acc[a][b], 0, 0, 0);
+                    if (REFILL && ks > 0) {
+                        constexpr int SLOTS = (KS - 1) * NM, EACH = (NX + SLOTS - 1) / SLOTS;   // transfers between two MFMAs
+#pragma unroll
+                        for (int j = ((ks - 1) * NM + q) * EACH; j < ((ks - 1) * NM + q + 1) * EACH && j < NX; ++j) issue_one(fill, j);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (REFILL) { advance(); fill = fill + 1 == STAGES ? 0 : fill + 1; }
+            rd = nrd;
+        };
+        int kt = 0;
+        for (; kt + STAGES - 1 < nk; ++kt) slice(std::true_type{}, std::true_type{});
+        ln_combine();
+        for (; kt + 1 < nk; ++kt) slice(std::false_type{}, std::true_type{});
+        if (kt < nk) slice(std::false_type{}, std::false_type{});
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else {
     int rd = 0;
     if (nk >= STAGES) wait_loads_then_barrier<(STAGES - 1) * NX>(); else wait_loads_then_barrier<0>();
     load_frags(0, 0, 0);
@@ -381,31 +460,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    if (LN == LN_IN || LN == LN_RES) {
-        // the row's mean and deviation from its parts (sum s, sum of squares q about the part's own mean): two threads a row, every other part each
-        static_assert(NT >= 2 * BM, "two threads per row");
-        const float2* parts = (const float2*)((const char*)smem_all + PARTS_LDS) + (tid >> 1) * ln_parts;
-        float2 pt[LN_MAX_PARTS / 2];
-        float s = 0.f, q = 0.f;
-#pragma unroll
-        for (int i = 0; i < LN_MAX_PARTS / 2; ++i) {
-            const int k = 2 * i + (tid & 1);
-            pt[i] = parts[k < ln_parts ? k : 0];
-            s += k < ln_parts ? pt[i].x : 0.f;
-        }
-        s += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0xB1, 0xf, 0xf, true));
-        const float mean = s * p.ln_inv_n;
-#pragma unroll
-        for (int i = 0; i < LN_MAX_PARTS / 2; ++i) {
-            const float d = pt[i].x * (1.f / 64.f) - mean;
-            q += 2 * i + (tid & 1) < ln_parts ? pt[i].y + 64.f * d * d : 0.f;
-        }
-        q += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, q), 0xB1, 0xf, 0xf, true));
-        const float rs = __builtin_amdgcn_rsqf(q * p.ln_inv_n + p.ln_eps);
-        // (a row of equal numbers is beta alone: nothing of the products' rounding may be scaled up)
-        if (tid < 2 * BM && (tid & 1) == 0 && (KG == 1 || group == 0))
-            *(float2*)((char*)smem_all + ROWS_LDS + (tid >> 1) * 8) = q == 0.f ? make_float2(0.f, 0.f) : make_float2(rs, -rs * mean);
-    }
+    ln_combine();
     for (int kt = nmain > 0 ? nmain : 0; kt < nk; ++kt) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -423,6 +478,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+    }
     }
     __syncthreads();                                   // LDS is free
 
@@ -526,7 +582,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     }
     if (RES == RES_F32) {
         constexpr int SR = f32_stage_rows<BM, BN>(), PASSES = BM / SR, LDF = BN + 4;
-        static_assert(SR % TM == 0 && NCH % PASSES == 0, "a wavefront's rows are staged in one go");
+        static_assert(RES != RES_F32 || (SR % TM == 0 && NCH % PASSES == 0), "a wavefront's rows are staged in one go");
         float* Fs = (float*)smem_all;
         // gamma and beta of a thread's eight channels, which are the same in all of its rows unless the tile's rows are no divisor of the workgroup
         constexpr bool SAME_C = NT % CPR == 0;
@@ -635,7 +691,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
 
 // The tiles a layer is given to one of (conv_igemm.hip: choose_conv).
 enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
-              T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64,
+              T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T128x64, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64,
               T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_SMALL32x16, T_SMALL64x16, T_SMALL64x32, T_SMALL128x32,
               T_COUNT };                               // (slabs: slab_split; small: small_us)
 

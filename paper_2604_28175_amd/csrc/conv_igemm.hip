@@ -761,6 +761,7 @@ static const TileInfo tile_info[T_ESTIMATED] = {
     {32, 64, 64, 1, true, {2.712f, 0.950f, 0.272f, 0.069f, 0.342f, 0.032f, 1.280f}},
     {64, 64, 64, 2, false, {1.059f, 2.700f, 0.289f, 0.126f, 0.f, 0.065f, 0.f}},
     {32, 64, 64, 4, false, {1.316f, 2.420f, 0.391f, 0.174f, 0.f, 0.085f, 0.f}},
+    {128, 64, 64, 1, false, {1.100f, 2.750f, 0.253f, 0.085f, 0.800f, 0.050f, 0.144f}},
     {16, 16, 64, 4, true, {2.610f, 0.434f, 0.394f, 0.113f, 0.f, 0.f, 0.f}},
     {16, 32, 64, 4, true, {2.783f, 0.392f, 0.603f, 0.126f, 0.f, 0.f, 0.f}},
     {256, 128, 32, 1, true, {1.258f, 4.155f, 0.580f, 0.f, 0.f, 0.163f, 0.069f}},
@@ -773,7 +774,7 @@ static const TileInfo tile_info[T_ESTIMATED] = {
 
 static const char* const tile_name[T_COUNT] = {
     "256x256x64", "256x192x64", "192x128x64", "128x256x64", "128x128x64, 8 wavefronts", "128x128x64", "96x128x64", "64x128x64", "256x128x32", "128x64x32, 2 slices",
-    "128x64x32, 3 slices", "64x64x64", "64x64x32", "32x64x64", "64x64x64, 2 groups", "32x64x64, 4 groups", "small outputs 16x16", "small outputs 16x32",
+    "128x64x32, 3 slices", "64x64x64", "64x64x32", "32x64x64", "64x64x64, 2 groups", "32x64x64, 4 groups", "128x64x64", "small outputs 16x16", "small outputs 16x32",
     "patch 256x128", "patch 128x128", "patch 256x64", "through registers 128x128", "through registers 128x64", "through registers 64x64",
     "slabs 64x64x64", "slabs 64x64x32", "small 3x3 32x16", "small 3x3 64x16", "small 3x3 64x32", "small 3x3 128x32"};
 
@@ -853,6 +854,15 @@ static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
         hipLaunchKernelGGL(kernel, grid, block, lds, stream, q);
         return 0;
     };
+    auto after = [&]() -> int {                        // the second launch of a split reduction
+        if (p.ksplit > 1) {
+            const long long n8 = (long long)p.M * (p.Cout / 8);
+            hipLaunchKernelGGL(splitk_finish_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, stream, q);
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) { set_error("conv launch: %s", hipGetErrorString(e)); return -2; }
+        return 0;
+    };
     int rc;
     if (p.res_f32 && p.ksplit == 1) {
         if constexpr (BM <= 64 && BN == 64) {
@@ -864,20 +874,21 @@ static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
         else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, KG>);
         else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE, false, KG>);
     } else {
+        if constexpr (BM == 128 && BN == 128 && dma_deep<BM, BN, BK, WGM, WGN>()) {
+            if (p.Kg < 512 && p.act != ACT_GELU && !p.x2) {
+                if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY, false, 1, LN_NONE, false>);
+                else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, 1, LN_NONE, false>);
+                else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE, false, 1, LN_NONE, false>);
+                return rc ? rc : after();
+            }
+        }
         if (mode == MODE_1X1 && p.act == ACT_GELU) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, RES_LATE>);
         else if (mode == MODE_1X1 && p.x2) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, true>);
         else if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY>);
         else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE>);
         else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE>);
     }
-    if (rc) return rc;
-    if (p.ksplit > 1) {
-        const long long n8 = (long long)p.M * (p.Cout / 8);
-        hipLaunchKernelGGL(splitk_finish_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, stream, q);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) { set_error("conv launch: %s", hipGetErrorString(e)); return -2; }
-    return 0;
+    return rc ? rc : after();
 }
 
 template <int BM, int BN>
@@ -938,6 +949,7 @@ static int launch_tile_id(const ConvParams& p, TileId id, int mode, bool staged,
         case T32x64: return launch_dma_tile<32, 64, 64, 1, 2, 4>(p, mode, stream);
         case T64x64_g2: return launch_dma_tile<64, 64, 64, 2, 2, 3, 2>(p, mode, stream);
         case T32x64_g4: return launch_dma_tile<32, 64, 64, 1, 2, 3, 4>(p, mode, stream);
+        case T128x64: return launch_dma_tile<128, 64, 64, 4, 2, 5>(p, mode, stream);
         case T_SK16: return launch_conv_skinny(p, 16, mode == MODE_GATHER8, stream);
         case T_SK32: return launch_conv_skinny(p, 32, mode == MODE_GATHER8, stream);
         case T_SLABS64: return launch_dma_tile<64, 64, 64, 2, 2, 3>(p, mode, stream);
@@ -1032,6 +1044,7 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
                 if (p.res_f32 && (t.bm > 64 || t.bn > 64)) continue;                        // (the larger ones leave most compute units idle)
                 if (t.kg > 1 && (p.Kg < 512 || p.x2 || p.act == ACT_GELU)) continue;        // too short to split
                 if (i == T256x128s && p.Kg >= 512 && !(gather && p.C % 64 != 0)) continue;  // a tile for streaming layers, and for channels in halves of a slice
+                if (i == T128x64 && (p.Kg < 512 || p.Cout < 128)) continue;                 // fitted on reductions worth its ring
                 if (t.bm < 128 && mb > 250 && !p.res_f32) continue;                                       // estimates are not good for so many small tiles
                 consider((TileId)i, p.M);
             }

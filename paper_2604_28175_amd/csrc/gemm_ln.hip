@@ -82,6 +82,7 @@ int launch_gemm_ln(const ConvParams& params, hipStream_t stream) {
         case T128x128_2: return launch_ln_tile<128, 128, 2, 2, 2>(p, stream);
         case T96x128: return launch_ln_tile<96, 128, 1, 4, 4>(p, stream);
         case T64x128: return launch_ln_tile<64, 128, 2, 2, 3>(p, stream);
+        case T128x64: return launch_ln_tile<128, 64, 4, 2, 5>(p, stream);
         case T64x64: return launch_ln_tile<64, 64, 2, 2, 3>(p, stream);
         case T32x64: return launch_ln_tile<32, 64, 1, 2, 4>(p, stream);
         case T64x64_g2: return launch_ln_tile<64, 64, 2, 2, 3, 2>(p, stream);

@@ -862,6 +862,17 @@ def test_small_3x3_integer_data_is_bit_exact(S, tile, shapes):
         check_kernel(y.float().cpu().numpy(), ref.clamp(0, 6).cpu().numpy(), f"small 3x3 {tile} {N}x{H}x{W}x{C}->{K}")
 
 
+@pytest.mark.parametrize("kernel,shape,use_res", [
+    ("128x64x64", (1659, 1, 1, 2768, 904, 1, 1, 0), False), ("128x64x64", (5191, 1, 1, 1312, 368, 1, 1, 0), False), ("128x64x64", (1379, 1, 1, 768, 768, 1, 1, 0), True),
+    ("128x64x64", (8827, 1, 1, 1960, 144, 1, 1, 0), True), ("128x64x64", (35, 9, 33, 384, 344, 3, 2, 1), False), ("128x64x64", (25, 27, 41, 256, 144, 3, 2, 1), True),
+    # either side of the length from which the 128 x 128 tile of 8 wavefronts reads its operands three steps ahead
+    ("128x128x64, 8 wavefronts", (12877, 1, 1, 448, 144, 1, 1, 0), True), ("128x128x64, 8 wavefronts", (2740, 1, 1, 920, 1160, 1, 1, 0), True),
+    ("128x128x64, 8 wavefronts", (4975, 1, 1, 2376, 680, 1, 1, 0), True)])
+def test_operands_read_ahead_integer_data_is_bit_exact(S, kernel, shape, use_res):
+    """Tiles whose operands are read three steps ahead: ragged rows, channels and slices, few slices and many."""
+    test_every_kernel_integer_data_is_bit_exact(S, kernel, shape, use_res)
+
+
 def test_split_reduction_under_capture(S):
     """A product whose reduction is split allocates a workspace; on a stream that records a graph it takes a kernel that needs none."""
     M, N, K = 270, 512, 4096
