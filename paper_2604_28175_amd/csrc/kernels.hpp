@@ -164,6 +164,21 @@ struct HostControl {                     // in pinned host memory, written by th
 int launch_copy_in(const void* src, void* dst, size_t bytes, const void* src2, void* dst2, size_t bytes2, HostControl* ctl, unsigned* counters,
                    int piece, hipStream_t stream);
 int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* src = nullptr, void* dst = nullptr, size_t bytes = 0, unsigned seq = 0);
+// The end of a classifier's batch (classify_out.hip): softmax and top-1 of `rows` samples' logits, and logits, probabilities and indices both to their
+// places on the device and to host memory; stamps and flag as launch_copy_out.  With x, a feature map [rows][HW][C], first the logits: its mean over
+// the HW positions, rounded to fp16, times w [n][ldw], + bias.  Results of one chunk (classify_out_takes), small heads (classify_out_pools).
+struct ClassifyOut {
+    const half_t* x; int HW, C;
+    const half_t* w; int ldw; const float* bias;
+    float* logits; float* probs; int32_t* top1;
+    int rows, n;
+    char* host; HostControl* ctl; unsigned* counter;   // counter: as launch_copy_out's first
+    unsigned seq;
+    int hp;
+};
+bool classify_out_takes(long long rows, int n);
+bool classify_out_pools(int HW, int C, int n);
+int launch_classify_out(const ClassifyOut& p, hipStream_t stream);
 int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, hipStream_t stream);
 
 void set_error(const char* fmt, ...);

@@ -1026,7 +1026,8 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
     if (last_layer < 0 || last_layer >= n) last_layer = n - 1;
     // Per-layer timing and prefix runs keep everything on the one stream (their events bracket single launches).
     if (first_layer < 0 || first_layer > last_layer) first_layer = 0;
-    const bool branches = !timed && first_layer == 0 && last_layer == n - 1 && in.side != nullptr && m.ctx->branch_streams;
+    const bool whole = last_layer == n - 1 || (!read_last && last_layer == classify_out_first(m, batch) - 1);
+    const bool branches = !timed && first_layer == 0 && whole && in.side != nullptr && m.ctx->branch_streams;
     bool forked = false;
     hipStream_t main_stream = stream;
     if (timed) in.layer_skipped.assign(m.ops.size(), 0);
@@ -1219,6 +1220,35 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
     }
     if (timed) HIP_TRY(hipEventRecord(in.layer_ev[last_layer + 1], main_stream));
     return 0;
+}
+
+int classify_out_first(const Model& m, int batch) {
+    const int n = (int)m.ops.size();
+    if (n < 2 || m.ops[n - 1].kind != OP_SOFTMAX || !classify_out_takes(batch, m.ops[n - 1].K)) return n;
+    if (n >= 4) {
+        const Op &fc = m.ops[n - 2], &gap = m.ops[n - 3];
+        if (fc.kind == OP_CONV && gap.kind == OP_POOL && gap.sub == POOL_GLOBAL_AVG && classify_out_pools(gap.H * gap.W, gap.C, fc.K)) return n - 3;
+    }
+    return n - 1;
+}
+
+int enqueue_classify_out(Model& m, Instance& in, int batch, hipStream_t stream, int hp, unsigned seq) {
+    const int n = (int)m.ops.size(), first = classify_out_first(m, batch);
+    const Op& sm = m.ops[n - 1];
+    ClassifyOut p{};
+    if (first == n - 3) {
+        const Op &fc = m.ops[n - 2], &gap = m.ops[n - 3];
+        p.x = (const half_t*)slot_ptr(m, in, gap.in, 0, batch);
+        p.HW = gap.H * gap.W; p.C = gap.C;
+        p.w = fc.w; p.ldw = fc.ldw; p.bias = fc.bias;
+    }
+    p.logits = (float*)slot_ptr(m, in, sm.in, 0, batch);
+    p.probs = (float*)slot_ptr(m, in, sm.out, sm.out_ref, batch);
+    p.top1 = (int32_t*)slot_ptr(m, in, SLOT_OUT, sm.out_ref2, batch);
+    p.rows = batch; p.n = sm.K;
+    p.host = (char*)in.pinned_out_dev; p.ctl = in.ctl_dev; p.counter = in.counters + 1;
+    p.seq = seq; p.hp = hp;
+    return launch_classify_out(p, stream);
 }
 
 }  // namespace strait

@@ -100,7 +100,7 @@ struct Instance {
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     std::vector<hipEvent_t> layer_ev;
     std::vector<char> layer_skipped;    // by the last timed run: layers that were computed inside another layer's launch
-    // Captured kernel sequences, keyed by (batch, wave-priority flag); a key is captured on its second
+    // Captured kernel sequences, keyed by (batch, wave-priority flag + 2 where the last layers are left to the result's way out); a key is captured on its second
     // use, after one eager pass has set the kernels' attributes outside of any capture.
     std::map<std::pair<int, int>, hipGraphExec_t> graphs;
     std::set<std::pair<int, int>> warmed;
@@ -212,5 +212,9 @@ int finish_plan(Model& m);             // after the instances' buffers
 // Enqueues layers first_layer..last_layer (last_layer < 0: up to the end) of the plan for `batch` samples on `stream`.
 // read_last: the output of last_layer is going to be read by the caller (a layer folded or laid out for the next one is then computed as it is).
 int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer = 0, bool read_last = false);
+// The first op of those that enqueue_classify_out computes on the result's way out; the number of ops where it computes none.
+// Depends on the model and the batch size only, so that a captured sequence always ends where the launch behind it begins.
+int classify_out_first(const Model& m, int batch);
+int enqueue_classify_out(Model& m, Instance& in, int batch, hipStream_t stream, int hp, unsigned seq);
 
 }  // namespace strait

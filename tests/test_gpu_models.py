@@ -347,6 +347,46 @@ def test_submit_errors_and_pool(ctx):
     assert e.value.status == S.E_FORMAT
 
 
+@pytest.mark.parametrize("arch,hw,classes,batch", [("tiny_cnn", 32, 10, 4), ("tiny_cnn", 20, 2, 3), ("tiny_cnn", 33, 256, 31), ("tiny_cnn", 32, 7, 300),   # pooling, product, softmax
+                                                   ("tiny_cnn", 32, 257, 2), ("tiny_cnn", 32, 1023, 5), ("mobilenet_v2", 64, 1000, 32), ("mobilenet_v2", 64, 1024, 3),  # softmax
+                                                   ("mobilenet_v2", 64, 1000, 33), ("tiny_cnn", 32, 1025, 2)])                                 # launches of their own
+def test_classifier_results_that_leave_in_the_launch_that_computes_them(ctx, arch, hw, classes, batch):
+    """Every form of the classifier's end, eager and replayed: the oracle's result, the same bytes on the device and from replays, and what the layers
+    by themselves give (fp32 sums of up to 1024 terms in another order: 1024 * 2^-24 of the largest probability; a pooled feature may round the other
+    way, 2^-10 of it)."""
+    S = ctx.S
+    md = getattr(synth, arch)(7, hw=hw, classes=classes)
+    x = synth.default_image_batch(md, batch, 11)
+    ref = (omodels.tiny_cnn_forward if arch == "tiny_cnn" else omodels.mobilenet_v2_forward)(md.tensors, x, keep=True)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    try:
+        m.copy_in(0, S.PRIO_LOW, x)
+        m.run(0, S.PRIO_LOW, batch)
+        apart = m.decode(m.copy_out(0, S.PRIO_LOW, batch), batch)
+        first = None
+        for graphs in (False, True, True, True, True):
+            ctx.set_graphs(graphs)
+            out = m.new_output(batch)
+            rec = m.wait(m.submit(S.PRIO_HIGH, x, None, out))
+            assert rec.kernel_ms > 0 and rec.d2h_ms > 0 and rec.total_ms >= rec.kernel_ms
+            if first is None:
+                first = out
+            assert np.array_equal(first, out), "a pass differs from the first"
+            assert np.array_equal(m.copy_out(0, S.PRIO_HIGH, batch).view(np.uint8), out.view(np.uint8)), "the device's copy differs"
+        got = m.decode(first, batch)
+        check_logits(got["logits"], ref.logits, got["top1"], f"{arch} {classes} classes b{batch}")
+        assert np.abs(got["probs"] - ref.probs).max() <= 2e-2 and np.abs(got["probs"].sum(-1) - 1).max() < 1e-4
+        assert np.array_equal(got["top1"], got["logits"].argmax(-1))
+        if arch == "tiny_cnn" and classes <= 256:
+            assert np.abs(got["logits"] - apart["logits"]).max() <= 2.0 ** -10 * np.abs(md.tensors["fc.w"].astype(np.float64)).sum(1).max() * ref.trace.acts["gap"].max()
+        else:
+            assert np.array_equal(got["logits"], apart["logits"]) and np.array_equal(got["top1"], apart["top1"])
+            assert np.abs(got["probs"] - apart["probs"]).max() <= 2 * 1024 * 2.0 ** -24 * apart["probs"].max()
+    finally:
+        ctx.set_graphs(False)
+        m.free()
+
+
 @pytest.mark.parametrize("arch,batch", [("resnet50", 3), ("mobilenet_v2", 4), ("encoder", 2)])
 def test_graph_replay_equals_kernel_by_kernel(ctx, arch, batch):
     """The captured-graph path replays the very same launches: every replay, on fresh inputs and with
