@@ -332,6 +332,12 @@ strait_status strait_k_stem3x3s2(void* stream, const void* x, int32_t N, int32_t
  * bit-identical to strait_k_stem3x3s2 followed by strait_k_dwconv3x3. */
 strait_status strait_k_stem3x3s2_dw(void* stream, const void* x, int32_t N, int32_t H, int32_t W, const void* wf, const float* bias,
                                     int32_t act1, const void* wd_rsc, const float* bd, int32_t act2, void* y, int32_t hp);
+/* The first 3x3 layer of a network on a 3-channel image, stride 1, padding 1, read as it lies in memory: x [N,H,W,3] -> y [N,H,W,Kout], + bias,
+ * activation (NONE, RELU, RELU6).  W even; Kout 16, 32 or 64 (E_SHAPE otherwise).  wf fp16 [max(Kout, 32)][2][3][16]: of channel k, for even and
+ * for odd columns, three filter rows of w[k][r][s][c] (9 halfs) that start at half 1 (even) and 0 (odd); the rest, and rows from Kout on, zero.
+ * bias fp32 [Kout] or NULL.  x, wf and y 16-byte aligned. */
+strait_status strait_k_stem3x3s1(void* stream, const void* x, int32_t N, int32_t H, int32_t W, const void* wf, const float* bias,
+                                 int32_t Kout, int32_t act, void* y, int32_t hp);
 /* ResNet stem in one launch: 7x7 convolution, stride 2, pad 3, of x [N,H,W,3] to 64 channels, + bias, ReLU, then 3x3
  * max pooling, stride 2, pad 1 -> y [N,P2,Q2,64] (P = (H-1)/2+1, P2 = (P-1)/2+1, likewise Q).  W even.
  * wf fp16 [64][176]: row k is 22 fragments of 8 halfs; fragment 3r + j holds halfs 8j..8j+7 of the 24-half window

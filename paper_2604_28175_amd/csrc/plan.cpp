@@ -273,6 +273,28 @@ struct Loader {
         op.info.weight_bytes = (int64_t)K * C * R * S * 2 + K * 4;
         return 0;
     }
+    // Direct 3x3/1 stem (launch_stem3x3s1): the convolution's weights once more, in that kernel's layout
+    int stem3s1_weights(const std::string& name, bool bn, unsigned K, const half_t** dev) {
+        const TensorView* w = c.find(name + ".w");
+        if (!w) return STRAIT_E_FORMAT;
+        if (!shape_is(w, {K, 3, 3, 3})) { set_error("'%s.w': expected [%u,3,3,3]", name.c_str(), K); return STRAIT_E_FORMAT; }
+        std::vector<float> scale, bias;
+        int rc = scale_bias(name, bn, K, scale, bias);
+        if (rc) return rc;
+        std::vector<half_t> out((size_t)std::max(K, 32u) * 96, (half_t)0);
+        for (unsigned k = 0; k < K; ++k)
+            for (unsigned odd = 0; odd < 2; ++odd)
+                for (unsigned r = 0; r < 3; ++r)
+                    for (unsigned s = 0; s < 3; ++s)
+                        for (unsigned cc = 0; cc < 3; ++cc) {
+                            const float v = (float)w->data[((k * 3 + cc) * 3 + r) * 3 + s];
+                            out[((size_t)k * 6 + odd * 3 + r) * 16 + (1 - odd) + s * 3 + cc] = bn ? (half_t)(v * scale[k]) : (half_t)v;
+                        }
+        void* dw = nullptr;
+        if ((rc = upload(out.data(), out.size() * 2, &dw))) return rc;
+        *dev = (const half_t*)dw;
+        return 0;
+    }
     // depthwise [C][1][3][3] -> [3][3][C]
     int dw_weights(const std::string& name, unsigned C, Op& op) {
         const TensorView* w = c.find(name + ".w");
@@ -422,6 +444,11 @@ struct Builder {
         pack.H = H; pack.W = W; pack.C = C; pack.Hp = Hp; pack.Wp = Wp; pack.Cpad = Cpad; pack.pad = pad;
         pack.P = Hp; pack.Q = Wp; pack.K = Cpad;
         pack.info.bytes_per_sample = 2LL * ((int64_t)H * W * C + (int64_t)Hp * Wp * Cpad);
+        if (C == 3 && R == 3 && stride == 1 && pad == 1 && stem3x3s1_supported(W, K, act)) {
+            // its convolution can read the image as it is: one launch for the two, without the copy
+            const int rc = ld.stem3s1_weights(name, bn, (unsigned)K, &pack.w);
+            if (rc) return rc;
+        }
         m.ops.push_back(pack);
 
         Op op;
@@ -1182,6 +1209,13 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                 rc = launch_stem3x3s2((const half_t*)src, op.w, op.bias, batch, op.H, op.W, op.K, op.act, (half_t*)dst, hp, stream);
                 break;
             case OP_PACK:
+                if (op.w && i + 1 <= last_layer && m.ctx->pair_min_pixels > 0) {
+                    const Op& cv = m.ops[i + 1];
+                    rc = launch_stem3x3s1((const half_t*)src, op.w, cv.bias, batch, op.H, op.W, cv.K, cv.act,
+                                          (half_t*)slot_ptr(m, in, cv.out, cv.out_ref, batch), hp, stream);
+                    fused_away = i + 1;
+                    break;
+                }
                 rc = launch_pack_input((const half_t*)src, batch, op.H, op.W, op.C, (half_t*)dst, op.Hp, op.Wp, op.Cpad, op.pad, op.pad, hp, stream);
                 break;
             case OP_DWCONV:

@@ -72,7 +72,7 @@ struct Op {
     int seq = 0, heads = 0;
     float eps = 0.f;
     long long in_row_stride = 0;      // LayerNorm: elements between input rows (0 = contiguous)
-    const half_t* w = nullptr;
+    const half_t* w = nullptr;        // (OP_PACK: of the stem behind it, where that can read the image itself)
     const float* bias = nullptr;      // conv/gemm bias, LayerNorm gamma, class token (OP_TOKENS)
     const float* beta = nullptr;      // LayerNorm beta, position embeddings (OP_TOKENS)
     strait_layer_info info{};

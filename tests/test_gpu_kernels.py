@@ -475,6 +475,36 @@ def test_stem3x3s2_integer_data_and_errors(S):
         S.k_stem3x3s2(dev(S, x), dev(S, stem3_weights(wt)), dev(S, b), 12)
 
 
+@pytest.mark.parametrize("n,h,w,k,act", [(2, 32, 32, 16, 1), (1, 224, 224, 64, 1), (3, 51, 38, 32, 0), (2, 1, 2, 64, 0), (1, 5, 64, 16, 2), (2, 4, 66, 64, 1),
+                                         (1, 9, 130, 32, 1), (7, 3, 126, 64, 2), (30, 96, 96, 64, 1)])
+def test_stem3x3s1(S, n, h, w, k, act):
+    """One launch from the image: random data against the oracle, integers exactly, and non-finite pixels reach the outputs they are taps of alone."""
+    def layout(wt):
+        wf = np.zeros((max(k, 32), 2, 3, 16), np.float16)
+        rows = np.transpose(wt, (0, 2, 3, 1)).reshape(k, 3, 9)
+        wf[:k, 0, :, 1:10] = rows
+        wf[:k, 1, :, 0:9] = rows
+        return wf.reshape(-1)
+    wt = f16(R.standard_normal((k, 3, 3, 3)) * (2.0 / 27) ** 0.5)
+    b = (R.standard_normal(k) * 0.5).astype(np.float32)
+    x = f16(R.standard_normal((n, h, w, 3)))
+    y = S.k_stem3x3s1(dev(S, x), dev(S, layout(wt)), dev(S, b), k, act=act).float().cpu().numpy()
+    check_kernel(y, act_ref(ops.conv2d(x, wt, b, 1, 1), act), f"stem 3x3/1 {n}x{h}x{w}->{k}")
+    xi, wi, bi = R.integers(-3, 4, x.shape).astype(np.float16), R.integers(-2, 3, wt.shape).astype(np.float16), R.integers(-4, 5, k).astype(np.float32)
+    yi = S.k_stem3x3s1(dev(S, xi), dev(S, layout(wi)), dev(S, bi), k, act=0).float().cpu().numpy()
+    assert np.array_equal(yi, ops.conv2d(xi, wi, bi, 1, 1))
+    py, px = h // 2, w // 2
+    xi[0, py, px, 1] = np.nan
+    yn = S.k_stem3x3s1(dev(S, xi), dev(S, layout(wi)), dev(S, bi), k, act=0).float().cpu().numpy()
+    touched = np.zeros(yn.shape[:3], bool)
+    touched[0, max(py - 1, 0):py + 2, max(px - 1, 0):px + 2] = True
+    assert not np.isfinite(yn[touched]).any() and np.array_equal(yn[~touched], yi[~touched])
+    with pytest.raises(S.StraitError):       # odd width
+        S.k_stem3x3s1(dev(S, x[:, :, :w - 1]), dev(S, layout(wt)), dev(S, b), k)
+    with pytest.raises(S.StraitError):       # a channel count the kernel does not take
+        S.k_stem3x3s1(dev(S, x), dev(S, layout(wt)), dev(S, b), 48)
+
+
 @pytest.mark.parametrize("n,h,w", [(2, 64, 64), (1, 224, 224), (3, 51, 38), (2, 7, 8), (2, 1, 2), (1, 130, 226), (5, 18, 122), (40, 96, 96)])
 def test_stem3x3s2_dw(S, n, h, w):
     """Stem 3x3/2 (3 -> 32) + depthwise 3x3 as one launch: against the oracle's two operators, and bit for bit against the
