@@ -73,6 +73,16 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// The kernels that hold a patch of the input in LDS, the next slice's on its way while nine tap steps run, and stream weights through a ring: transfers of
+// the patch (npw per wavefront and slice, as per step) in step t
+constexpr int patch_share(int npw, int as, int t) { return npw - t * as < 0 ? 0 : (npw - t * as > as ? as : npw - t * as); }
+
+constexpr int patch_wait(int npw, int as, int wi, int pre, int t) {     // transfers a wave may have in flight when tap step t starts
+    int n = patch_share(npw, as, (t + 9 - pre) % 9);
+    for (int k = 1; k < pre; ++k) n += wi + patch_share(npw, as, (t + 9 - k) % 9);
+    return n;
+}
+
 // Waves per SIMD that the LDS footprint of a tile configuration allows (the register allocator is asked
 // for that many: left to itself it splits accumulators into AGPRs and loses waves for nothing).
 template <int BM, int BN, int BK, int WGM, int WGN, int STAGES>
@@ -692,7 +702,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
 // The tiles a layer is given to one of (conv_igemm.hip: choose_conv).
 enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x128, T64x128, T256x128s, T128x64_2, T128x64_3,
               T64x64, T64x64s, T32x64, T64x64_g2, T32x64_g4, T128x64, T_DMA, T_SK16 = T_DMA, T_SK32, T_PATCH256x128, T_PATCH128x128, T_PATCH256x64,
-              T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_SMALL32x16, T_SMALL64x16, T_SMALL64x32, T_SMALL128x32,
-              T_COUNT };                               // (slabs: slab_split; small: small_us)
+              T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_SMALL32x16, T_SMALL64x16, T_SMALL64x32, T_SMALL128x32, T_MID96x128, T_MID192x128,
+              T_COUNT };                               // (slabs: slab_split; small, mid: small_us, mid_us)
 
 }  // namespace strait

@@ -316,14 +316,6 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(const ConvParams p) 
 // fixed number of transfers, so the in-order load counter tells when a given stage has landed.  LDS rows of 64
 // bytes are swizzled as in the kernel above (16-byte chunk c of row i sits at c ^ ((i >> 2) & 3)), which keeps
 // the operand reads conflict free for any run of consecutive rows, i.e. for every tap offset.
-constexpr int patch_share(int npw, int as, int t) { return npw - t * as < 0 ? 0 : (npw - t * as > as ? as : npw - t * as); }
-
-constexpr int patch_wait(int npw, int as, int wi, int pre, int t) {     // transfers a wave may have in flight when tap step t starts
-    int n = patch_share(npw, as, (t + 9 - pre) % 9);
-    for (int k = 1; k < pre; ++k) n += wi + patch_share(npw, as, (t + 9 - k) % 9);
-    return n;
-}
-
 template <int BM, int BN, int WGM, int WGN, int NPW, int NBS>
 __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 2) conv3x3_patch_kernel(const ConvParams p) {
     constexpr int NW = WGM * WGN, NT = 64 * NW;
@@ -776,7 +768,7 @@ static const char* const tile_name[T_COUNT] = {
     "256x256x64", "256x192x64", "192x128x64", "128x256x64", "128x128x64, 8 wavefronts", "128x128x64", "96x128x64", "64x128x64", "256x128x32", "128x64x32, 2 slices",
     "128x64x32, 3 slices", "64x64x64", "64x64x32", "32x64x64", "64x64x64, 2 groups", "32x64x64, 4 groups", "128x64x64", "small outputs 16x16", "small outputs 16x32",
     "patch 256x128", "patch 128x128", "patch 256x64", "through registers 128x128", "through registers 128x64", "through registers 64x64",
-    "slabs 64x64x64", "slabs 64x64x32", "small 3x3 32x16", "small 3x3 64x16", "small 3x3 64x32", "small 3x3 128x32"};
+    "slabs 64x64x64", "slabs 64x64x32", "small 3x3 32x16", "small 3x3 64x16", "small 3x3 64x32", "small 3x3 128x32", "mid 3x3 96x128", "mid 3x3 192x128"};
 
 // The patch kernel's view of a layer: strips and bordered pixels (mv); -1 = not a layer of its.
 static int patch_geometry(const ConvParams& p, int* strip_w, int* slots, long long* mv) {
@@ -931,6 +923,16 @@ static float small_us(const ConvParams& p, const SmallTile& t, double mb) {
     return (float)(t.c[0] + r * (t.c[1] + nk * (t.c[2] + t.c[3] * ((t.bm + 2 * (p.W + 1) + 2 + 31) / 32))) + t.c[4] * mb);
 }
 
+// The mid-size 3x3 kernel's (conv3x3_mid.hip): the launch, a round of tiles, a tap of 64 channels, the operands' megabytes.
+// Fits to 80 layers (3 to 32 images of 14 to 64 pixels, 64 to 512 channels): at most 11 % off, and that where half of the units are idle and they are too high.
+struct MidTile { int bm; float c[4]; };
+static const MidTile mid_tile[2] = {{96, {2.4f, 4.4f, 0.29f, 0.04f}}, {192, {1.2f, 6.9f, 0.54f, 0.03f}}};
+static float mid_us(const ConvParams& p, const MidTile& t, double mb) {
+    const long long mv = (long long)(p.M / p.PQ) * (p.H + 1) * (p.W + 1);
+    const double r = std::ceil((double)((mv + t.bm - 1) / t.bm * (p.Cout / 128)) / 256.0);
+    return (float)(t.c[0] + r * (t.c[1] + 9 * (p.C / 64) * t.c[2]) + t.c[3] * mb);
+}
+
 static int launch_tile_id(const ConvParams& p, TileId id, int mode, bool staged, hipStream_t stream) {
     switch (id) {
         case T256x256: return launch_dma_tile<256, 256, 64, 2, 4, 2>(p, mode, stream);
@@ -959,6 +961,7 @@ static int launch_tile_id(const ConvParams& p, TileId id, int mode, bool staged,
         case T_REG64x64: return launch_tile<64, 64>(p, mode, staged, stream);
         case T_SMALL32x16: case T_SMALL64x16: case T_SMALL64x32: case T_SMALL128x32:
             return launch_conv3x3_small(p, small_tile[id - T_SMALL32x16].bm, small_tile[id - T_SMALL32x16].bn, stream);
+        case T_MID96x128: case T_MID192x128: return launch_conv3x3_mid(p, mid_tile[id - T_MID96x128].bm, stream);
         default: return launch_conv3x3_patch(p, id, stream);
     }
 }
@@ -1061,6 +1064,11 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
                     if (!conv3x3_small_takes(p, small_tile[i].bm, small_tile[i].bn)) continue;
                     const float us = small_us(p, small_tile[i], mb);
                     if (us < best_us) { best_us = us; best = (TileId)(T_SMALL32x16 + i); }
+                }
+                for (int i = 0; i < 2; ++i) {
+                    if (!conv3x3_mid_takes(p, mid_tile[i].bm)) continue;
+                    const float us = mid_us(p, mid_tile[i], mb);
+                    if (us < best_us) { best_us = us; best = (TileId)(T_MID96x128 + i); }
                 }
             }
         } else {

@@ -74,6 +74,9 @@ int launch_conv_skinny(const ConvParams& p, int tn, bool gather, hipStream_t str
 // filled in.  No residual; C a multiple of 64.
 bool conv3x3_small_takes(const ConvParams& p, int bm, int bn);
 int launch_conv3x3_small(const ConvParams& p, int bm, int bn, hipStream_t stream);
+// Larger ones, bm (96 or 192) bordered pixels x 128 channels per workgroup (conv3x3_mid.hip); likewise.
+bool conv3x3_mid_takes(const ConvParams& p, int bm);
+int launch_conv3x3_mid(const ConvParams& p, int bm, hipStream_t stream);
 int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn);
 
 // A dense product with a LayerNorm folded in (gemm_ln.hip): of its input (ln_stats, ln_csum; no residual), or its output's statistics for one that

@@ -903,6 +903,20 @@ def test_operands_read_ahead_integer_data_is_bit_exact(S, kernel, shape, use_res
     test_every_kernel_integer_data_is_bit_exact(S, kernel, shape, use_res)
 
 
+@pytest.mark.parametrize("tile,shapes", [
+    # each length of the patch, odd and even numbers of slices, the narrowest and the widest images
+    ("96x128", [(17, 7, 46, 128, 384), (32, 44, 4, 192, 384), (10, 13, 42, 192, 384), (2, 58, 47, 128, 384), (33, 3, 55, 192, 384), (3, 29, 63, 192, 384), (2, 41, 62, 512, 256)]),
+    ("192x128", [(24, 64, 30, 128, 128), (40, 64, 5, 192, 384), (4, 58, 47, 192, 384), (25, 59, 31, 128, 128), (22, 33, 63, 128, 128), (27, 19, 64, 192, 128)])])
+def test_mid_3x3_integer_data_is_bit_exact(S, tile, shapes):
+    """The 3x3 kernel of mid-size layers, each tile: ragged last tiles, images of any height, two rounds of workgroups."""
+    for N, H, W, C, K in shapes:
+        test_every_kernel_integer_data_is_bit_exact(S, "mid 3x3 " + tile, (N, H, W, C, K, 3, 1, 1), False)
+        x, w = f16(R.standard_normal((N, H, W, C))), f16(R.standard_normal((K, 3, 3, C)) * (9 * C) ** -0.5)
+        y = S.k_conv2d(dev(S, x), dev(S, w), None, 1, 1, 2)                 # no bias, ReLU6
+        ref = S.torch.nn.functional.conv2d(dev(S, x).float().permute(0, 3, 1, 2), dev(S, w).float().permute(0, 3, 1, 2), padding=1).permute(0, 2, 3, 1)
+        check_kernel(y.float().cpu().numpy(), ref.clamp(0, 6).cpu().numpy(), f"mid 3x3 {tile} {N}x{H}x{W}x{C}->{K}")
+
+
 def test_split_reduction_under_capture(S):
     """A product whose reduction is split allocates a workspace; on a stream that records a graph it takes a kernel that needs none."""
     M, N, K = 270, 512, 4096
