@@ -946,7 +946,7 @@ strait_status strait_k_gemm_ln(void* stream, const void* x, const void* w, const
 
 strait_status strait_k_fold_layernorm(void* stream, const void* w, const float* b, const float* gamma, const float* beta, int32_t N, int32_t K,
                                       void* w_out, float* csum, float* b_out) {
-    return launch_fold_layernorm((const half_t*)w, b, gamma, beta, N, K, (half_t*)w_out, csum, b_out, (hipStream_t)stream);
+    return launch_fold_layernorm((const half_t*)w, b, gamma, beta, N, K, (half_t*)w_out, csum, b_out, nullptr, (hipStream_t)stream);
 }
 
 strait_status strait_k_pointwise_pair(void* stream, const void* x, const void* w3, const float* b3, const void* res, void* y,

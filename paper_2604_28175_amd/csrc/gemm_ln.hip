@@ -91,29 +91,40 @@ int launch_gemm_ln(const ConvParams& params, hipStream_t stream) {
     }
 }
 
-// One wavefront per row of w.
+// One wavefront per row of w.  `bad` becomes 1 where a row of w gamma has lost more to its rounding than fp16 takes from ordinary numbers, 2^-11 of each: a
+// row that mostly lies below fp16's normal range (6e-5), or a product beyond its largest number.
 __global__ void __launch_bounds__(256) fold_layernorm_kernel(const half_t* __restrict__ w, const float* __restrict__ b, const float* __restrict__ gamma,
                                                              const float* __restrict__ beta, int N, int K, half_t* __restrict__ w_out,
-                                                             float* __restrict__ csum, float* __restrict__ b_out) {
+                                                             float* __restrict__ csum, float* __restrict__ b_out, int* __restrict__ bad) {
     const int n = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (n >= N) return;
-    float s = 0.f, t = 0.f;
+    float s = 0.f, t = 0.f, lost = 0.f, all = 0.f;
     for (int k = lane; k < K; k += 64) {
         const float v = (float)w[(long long)n * K + k];
-        const half_t h = (half_t)(v * gamma[k]);
+        const float vg = v * gamma[k];
+        const half_t h = (half_t)vg;
+        const float d = ((float)h - vg) * 2048.f;
         w_out[(long long)n * K + k] = h;
         s += (float)h;
         t += v * beta[k];
+        lost += d * d;
+        all += vg * vg;
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { s += __shfl_xor(s, o, 64); t += __shfl_xor(t, o, 64); }
-    if (lane == 0) { csum[n] = s; b_out[n] = b[n] + t; }
+    for (int o = 32; o > 0; o >>= 1) {
+        s += __shfl_xor(s, o, 64); t += __shfl_xor(t, o, 64);
+        lost += __shfl_xor(lost, o, 64); all += __shfl_xor(all, o, 64);
+    }
+    if (lane == 0) {
+        csum[n] = s; b_out[n] = b[n] + t;
+        if (bad && !(lost <= all)) *bad = 1;           // (also where one of them is not a number)
+    }
 }
 
 int launch_fold_layernorm(const half_t* w, const float* b, const float* gamma, const float* beta, int N, int K, half_t* w_out, float* csum, float* b_out,
-                          hipStream_t stream) {
+                          int* bad, hipStream_t stream) {
     if (!w || !b || !gamma || !beta || !w_out || !csum || !b_out || N <= 0 || K <= 0) { set_error("fold_layernorm: invalid arguments"); return -1; }
-    hipLaunchKernelGGL(fold_layernorm_kernel, dim3((N + 3) / 4), dim3(256), 0, stream, w, b, gamma, beta, N, K, w_out, csum, b_out);
+    hipLaunchKernelGGL(fold_layernorm_kernel, dim3((N + 3) / 4), dim3(256), 0, stream, w, b, gamma, beta, N, K, w_out, csum, b_out, bad);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("fold_layernorm launch: %s", hipGetErrorString(e)); return -2; }
     return 0;

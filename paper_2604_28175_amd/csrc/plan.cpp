@@ -585,6 +585,7 @@ struct Builder {
 
     // Marks the LayerNorm op `ln`, which normalises what the product right before it writes, as one that can be folded into that product, into op `in`,
     // which multiplies its output, and into op `res`, if given, which adds it.  Nothing else may read its output.
+    // Weights that gamma takes out of fp16's normal range lose precision that the normalised activation keeps: there the LayerNorm stays a launch of its own.
     int fold_layer_norm(int ln, int in, int res) {
         Op &l = m.ops[ln], &c = m.ops[in];
         if (l.K % 64 != 0 || l.K > 1024 || c.vC != l.K || c.ldw != l.K || c.K % 64 != 0 || m.ops[ln - 1].vC % 64 != 0) return 0;
@@ -594,11 +595,11 @@ struct Builder {
         m.dev_allocs.push_back(w);
         if (hipMalloc(&v, (size_t)c.K * 8) != hipSuccess) { set_error("hipMalloc(%zu) for weights failed", (size_t)c.K * 8); return STRAIT_E_NOMEM; }
         m.dev_allocs.push_back(v);
-        c.w_ln = (const half_t*)w; c.csum_ln = (const float*)v; c.bias_ln = (const float*)v + c.K;
         const Model::Cold* src = nullptr;
         for (const Model::Cold& s : m.cold) if (s.op == (size_t)in) src = &s;
         if (!src) { set_error("'%s': its weights are not on the host", c.name.c_str()); return STRAIT_E_INVALID; }
-        const size_t need = n * 2 + (size_t)c.K * 4;
+        const size_t need = n * 2 + (size_t)c.K * 4 + 4;
+        int bad = 0;
         if (m.fold_tmp_bytes < need) {
             if (m.fold_tmp) { (void)hipFree(m.fold_tmp); m.fold_tmp = nullptr; }
             m.fold_tmp_bytes = 0;
@@ -607,10 +608,19 @@ struct Builder {
         }
         HIP_TRY(hipMemcpy(m.fold_tmp, src->w.data(), n * 2, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy((char*)m.fold_tmp + n * 2, src->b.data(), (size_t)c.K * 4, hipMemcpyHostToDevice));
+        int* const bad_dev = (int*)((char*)m.fold_tmp + need - 4);
+        HIP_TRY(hipMemcpy(bad_dev, &bad, 4, hipMemcpyHostToDevice));
         const int rc = launch_fold_layernorm((const half_t*)m.fold_tmp, (const float*)((char*)m.fold_tmp + n * 2), l.bias, l.beta, c.K, l.K, (half_t*)w,
-                                             (float*)v, (float*)v + c.K, nullptr);
+                                             (float*)v, (float*)v + c.K, bad_dev, nullptr);
         if (rc) return rc;
-        HIP_TRY(hipStreamSynchronize(nullptr));
+        HIP_TRY(hipMemcpy(&bad, bad_dev, 4, hipMemcpyDeviceToHost));
+        if (bad) {
+            m.dev_allocs.resize(m.dev_allocs.size() - 2);
+            (void)hipFree(w);
+            (void)hipFree(v);
+            return 0;
+        }
+        c.w_ln = (const half_t*)w; c.csum_ln = (const float*)v; c.bias_ln = (const float*)v + c.K;
         l.fold_ops[0] = ln - 1; l.fold_ops[1] = in; l.fold_ops[2] = res;
         l.ln_slot = m.ln_folds++ & 1;
         m.ops[ln - 1].ln_out = ln;

@@ -262,6 +262,30 @@ def test_folded_layernorms(ctx, arch, kw, batch):
         m.free()
 
 
+@pytest.mark.parametrize("norms", [("l0.ln1", "l0.ln2", "l1.ln1", "l1.ln2", "l2.ln1"), ("l0.ln1", "l1.ln2"), ("l0.ln2",)])
+def test_layernorms_whose_folded_weights_leave_the_normal_range(ctx, norms):
+    """gamma of 2^-14 takes fp16 weights below the normal range: such a LayerNorm stays apart, beside folded ones."""
+    md = synth.encoder(5, layers=3, hidden=128, heads=2, ffn=256, seq=40)
+    for k in norms:
+        md.tensors[k + ".g"] = np.full_like(md.tensors[k + ".g"], 2.0 ** -14)
+    x, vl = synth.token_batch(md, 3, 7, min_len=20)
+    ref = omodels.encoder_forward(md.tensors, x, vl, md.hyper).logits
+    m = ctx.load(synth.pack(md), max_batch=3, n_instances=1)
+    try:
+        got = m.infer(x, vl, prio=ctx.S.PRIO_LOW)[0]["hidden"]
+        ctx.set_pair_fusion(0)
+        apart = m.infer(x, vl, prio=ctx.S.PRIO_LOW)[0]["hidden"]
+        if len(norms) == 5:                              # every LayerNorm that could be folded
+            assert np.array_equal(got, apart)
+        for b in range(3):
+            n = int(vl[b])
+            check_kernel(got[b][:n], ref[b][:n], f"sample {b}", rel=2.0 ** -8, abs_rel=1e-2)
+            check_kernel(apart[b][:n], ref[b][:n], f"sample {b} apart", rel=2.0 ** -8, abs_rel=1e-2)
+    finally:
+        ctx.set_pair_fusion(40000)
+        m.free()
+
+
 @pytest.mark.parametrize("hw,batch,fc", [(32, 5, 64), (64, 3, 256)])
 def test_vgg19(ctx, hw, batch, fc):
     md = synth.vgg19(synth.SEEDS[synth.ARCH_VGG19], hw=hw, classes=100, fc=fc)
