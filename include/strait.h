@@ -141,7 +141,9 @@ strait_status strait_ctx_set_graphs(strait_ctx* ctx, int32_t enabled);
  * (strait_k_pointwise_pair).  Default 40000 (ResNet-50 at batch 16 and above: batch 128 2.29 -> 2.20 ms, batch 64 1.233 ->
  * 1.210 ms, batch 16 0.552 -> 0.543 ms; at batch 8 and below the two launches, which may split their reductions, are 1 %
  * faster); 0 = always two launches, and every other fusion of launches off as well (projection shortcuts, the first
- * block's opening convolution inside the stem launch): the layer-by-layer plan.  Results are the same bit for bit.  A graph that strait_ctx_set_graphs has
+ * block's opening convolution inside the stem launch, LayerNorms inside the products on their two sides, a 3x3/1 first layer that reads the image
+ * itself): the layer-by-layer plan.  A pair's results are those of its two launches, bit for bit; those of a projection shortcut or a folded LayerNorm
+ * are not, since a tensor between two launches is rounded to fp16 and the sums inside one launch are not.  A graph that strait_ctx_set_graphs has
  * already captured keeps the launches it was captured with: set this before the first batch. */
 strait_status strait_ctx_set_pair_fusion(strait_ctx* ctx, int64_t min_pixels);
 /* From how many output pixels on the closing 1x1 convolution of a residual stage's first block absorbs the block's 1x1
@@ -262,7 +264,8 @@ strait_status strait_k_gemm(void* stream, const void* x, const void* w, const fl
 strait_status strait_k_gemm_ln(void* stream, const void* x, const void* w, const float* bias, const void* res, int32_t M, int32_t N, int32_t K,
                                int32_t act, const float* ln_stats, const float* ln_csum, const float* ln_g, const float* ln_b, float ln_eps, void* y,
                                float* stats_out, int32_t hp);
-/* w_out [N][K] = fp16(w gamma), csum [N] = the sums of its rows, b_out [N] = b + w beta. */
+/* w_out [N][K] = fp16(w gamma), csum [N] = the sums of its rows, b_out [N] = b + w beta.  Where w gamma leaves fp16's normal range (6e-5 to 65504) its
+ * precision goes with it: a model whose gamma does that keeps the LayerNorm as a launch of its own. */
 strait_status strait_k_fold_layernorm(void* stream, const void* w, const float* b, const float* gamma, const float* beta, int32_t N, int32_t K,
                                       void* w_out, float* csum, float* b_out);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
