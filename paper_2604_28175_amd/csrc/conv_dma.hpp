@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             s += k < ln_parts ? pt[i].x : 0.f;
         }
         s += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0xB1, 0xf, 0xf, true));
-        const float mean = s * p.ln_inv_n;
+        const float mean = s / (float)(64 * ln_parts);       // (not times the reciprocal, which misses the number that a row of equal ones consists of: 7, 13 and 15 parts)
 #pragma unroll
         for (int i = 0; i < LN_MAX_PARTS / 2; ++i) {
             const float d = pt[i].x * (1.f / 64.f) - mean;

@@ -738,6 +738,26 @@ def test_gemm_with_folded_layernorm_of_equal_numbers_and_errors(S):
             S.k_gemm_ln(x, bias=bl, **bad)
 
 
+@pytest.mark.parametrize("H", [448, 832, 896, 960, 768, 1024])      # of the first four, 1 / H is no fp32 number whose product with a sum gives the mean
+@pytest.mark.parametrize("M", [70, 2600])
+def test_folded_layernorm_of_equal_numbers_at_every_kind_of_width(S, H, M):
+    """A row of equal numbers, any finite one, is beta alone: as a residual to the last bit, as an input to the product's rounding."""
+    rng = np.random.default_rng(H + M)
+    v = rng.integers(0, 65536, 4 * M, dtype=np.uint16).view(np.float16)
+    v = v[np.isfinite(v)][:M]
+    v[:2] = 1.75, 100
+    g, be = rng.uniform(0.8, 1.2, H).astype(np.float32), (rng.standard_normal(H) * 0.1).astype(np.float32)
+    zero, wz, bz = np.zeros((M, 64), np.float16), np.ones((H, 64), np.float16), np.zeros(H, np.float32)
+    y1, st = S.k_gemm_ln(dev(S, zero), dev(S, wz), dev(S, bz), res=dev(S, np.repeat(v[:, None], H, 1)), stats=True)
+    assert np.array_equal(y1.cpu().numpy(), np.repeat(v[:, None], H, 1))
+    y, _ = S.k_gemm_ln(dev(S, zero), dev(S, wz), dev(S, bz), res=y1, ln_stats=st, ln_g=dev(S, g), ln_b=dev(S, be), ln_eps=1e-12, stats=True)
+    assert np.array_equal(y.cpu().numpy(), np.broadcast_to(be.astype(np.float16), (M, H)))
+    w, b = f16(rng.standard_normal((192, H)) * H ** -0.5), (rng.standard_normal(192) * 0.1).astype(np.float32)
+    wl, cs, bl = S.k_fold_layernorm(dev(S, w), dev(S, b), dev(S, g), dev(S, be))
+    y, _ = S.k_gemm_ln(y1, wl, bl, ln_stats=st, ln_csum=cs, ln_eps=1e-12)
+    check_kernel(y.float().cpu().numpy(), np.broadcast_to(ops.linear(be[None], w, b), (M, 192)), f"equal rows of {H}")
+
+
 @pytest.mark.parametrize("M,N,K,use_res", [
     # many sizes of output, ragged in pixels and (where the layer allows it) in channels and slices
     (6311, 2304, 512, False), (8617, 1160, 64, False), (8347, 456, 64, True), (6455, 1184, 136, False), (8298, 280, 192, True),
