@@ -80,11 +80,14 @@ __global__ void __launch_bounds__(256) conv3x3_small_kernel(const ConvParams p) 
     auto issue = [&](int stage, int cs) __attribute__((always_inline)) {
         const bool live = cs < ncs;
         const unsigned base = lds0 + (unsigned)stage * STAGE, so = live ? (unsigned)cs * 128u : 0u;
+        // (opaque per slice: keeps the nine taps' offsets from being hoisted out of the loop, where they would not fit in the scalar registers)
+        unsigned step = live ? (BN == 16 ? 4u : 2u) * (unsigned)p.C : 0u;
+        asm volatile("" : "+s"(step));
+        unsigned at = so + (BN == 16 && (wave >> 1) ? step / 2 : 0u);
 #pragma unroll
-        for (int j = 0; j < WI; ++j) {
-            const int tap = BN == 16 ? 2 * j + (wave >> 1) : j;
-            const bool ok = live && (BN != 16 || tap < 9);
-            dma16(wrsrc, ok ? woff : OOB_OFFSET, ok ? so + (unsigned)(tap * p.C) * 2u : 0u, base + PATCH + (unsigned)(j * NW + wave) * 1024u);
+        for (int j = 0; j < WI; ++j, at += step) {
+            const bool ok = live && (BN != 16 || 2 * j + (wave >> 1) < 9);
+            dma16(wrsrc, ok ? woff : OOB_OFFSET, ok ? at : 0u, base + PATCH + (unsigned)(j * NW + wave) * 1024u);
         }
 #pragma unroll
         for (int j = 0; j < NPW; ++j) dma16(xrsrc, live ? aoff[j] : OOB_OFFSET, so, base + (unsigned)(j * NW + wave) * 1024u);

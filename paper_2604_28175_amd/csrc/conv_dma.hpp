@@ -58,9 +58,12 @@ __device__ __forceinline__ intx4 make_rsrc(const void* base, unsigned bytes) {
 
 // One wave-wide transfer of 64 x 16 bytes: lane i's chunk at rsrc.base + voff + soff goes to
 // LDS byte address lds_base + 16 i; lanes whose voff is out of range deposit zeros.
+// (The offset is copied by a scalar instruction first: the compiler may have it from a vector one, v_readlane of a spilled register, after which a
+// transfer may not read it for five wait states, and it does not count them for inline assembly.  The copy is also the wait that m0 needs.)
 __device__ __forceinline__ void dma16(intx4 rsrc, unsigned voff, unsigned soff, unsigned lds_base) {
     const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m0v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    unsigned so;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b32 %0, %4\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds" : "=&s"(so) : "s"(m0v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 __device__ __forceinline__ void divmod_f(int v, int d, float rcp, int& q, int& r) {   // exact for 0 <= v < 2^24
     q = (int)((float)v * rcp);
