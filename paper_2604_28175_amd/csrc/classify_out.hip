@@ -21,7 +21,7 @@ typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 // Host memory: through the caches, acknowledged when it is there.
 __device__ __forceinline__ void out_store(char* p, float4 v) {
     const uintx4 r = __builtin_bit_cast(uintx4, v);
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(r) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(r) : "memory");   // (s_nop: see store_through in elementwise.hip)
 }
 __device__ __forceinline__ void out_store(char* p, float v) { __hip_atomic_store((float*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
 

@@ -117,11 +117,12 @@ int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* sr
 // chunks; both are back at zero, for every stream, before the last flag is set.
 // Few workgroups: 16 of them keep the link busy (12.6 MB in 0.24 ms), and other batches run beside this.  The stores go through the
 // caches (sc0 sc1) and each workgroup waits for its own to be acknowledged before it counts a part: a system-scope fence would
-// instead write back the L2s, which hold other batches' data.
+// instead write back the L2s, which hold other batches' data.  A store of 16 bytes still reads its registers for two wait states after it was issued, which
+// the compiler does not count for inline assembly: an instruction that reused them right behind it would be stored in their place.
 __device__ __forceinline__ void store_through(void* p, uint4 v) {
     typedef unsigned uint4v __attribute__((ext_vector_type(4)));
     const uint4v r = {v.x, v.y, v.z, v.w};
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(r) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(r) : "memory");
 }
 __global__ void __launch_bounds__(256) copy_out_kernel(const char* __restrict__ src, char* __restrict__ dst, size_t bytes, size_t part_bytes, unsigned parts, unsigned chunks,
                                                        HostControl* ctl, unsigned* counters, unsigned seq, int k1_taken, int hp) {

@@ -39,3 +39,26 @@ def test_scalar_operands_of_transfers_into_lds(kernels):
                 states += assembly.wait_states(before)
     assert transfers > 1000
     assert not early, (len(early), early[:5])
+
+
+def test_data_of_wide_stores_is_not_overwritten(kernels):
+    """A store of more than eight bytes reads its data for two wait states after it was issued.  Those that are inline assembly bring the wait along,
+    since what the compiler places behind them changes with every change of the kernel."""
+    through, overwritten = 0, []
+    for name, code in kernels.items():
+        for i, ins in enumerate(code):
+            if not ins.startswith(("global_store_dwordx4", "global_store_dwordx3", "flat_store_dwordx4", "flat_store_dwordx3", "buffer_store_dwordx4", "buffer_store_dwordx3")):
+                continue
+            if ins.endswith("sc0 sc1"):
+                through += 1
+                assert code[i + 1] == "s_nop 1", (name, code[i:i + 3])
+            data = assembly.registers(assembly.operands(ins)[0 if ins.startswith("buffer") else 1])
+            states = 0
+            for behind in code[i + 1:i + 3]:
+                if behind.startswith(("s_branch", "s_endpgm", "s_setpc")):
+                    break
+                if states < 2 and behind.startswith("v_") and data & assembly.registers(assembly.operands(behind)[0]):
+                    overwritten.append((name, ins, behind, states))
+                states += assembly.wait_states(behind)
+    assert through >= 8                                    # copy out, and four forms of the classifier's end
+    assert not overwritten, (len(overwritten), overwritten[:5])
