@@ -4,7 +4,7 @@
 // Nothing here is bound by memory or arithmetic: a launch whose input comes from the launch before it takes 4 to 6 us for a round trip to memory and the
 // hand-over, whatever it computes.  So a workgroup takes one sample from its logits (or its feature map) to the host's buffer, a thread holding four
 // classes in registers, and the last workgroup to finish sets the flag that the host polls.  Results of one chunk only: a larger one leaves in
-// pieces beside the kernels that follow.  The device's copy of the result is written too.
+// pieces beside the kernels that follow.  The device's copy of the result is written too, and is there before the flag.
 // Measured on MI355X, one launch for two, us a pass: ResNet-50 one image 353 -> 325, eight 528 -> 500, MobileNetV2 five
 // images 290 -> 282 (two runs differ by up to 2 %).
 // The pooled head reads its weights once per sample through one compute unit, so it is for small ones: up to 16384 weights, 256 channels and 256
@@ -18,7 +18,9 @@ namespace strait {
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-// Host memory: through the caches, acknowledged when it is there.
+// Through the caches, acknowledged when it is there.  Not for host memory alone: the host may give the instance to another stream once it has seen the
+// flag, before this kernel has ended and its plain stores are written back (see copy_out_kernel in elementwise.hip), and the next
+// batch's logits may lie where this one's probabilities do.
 __device__ __forceinline__ void out_store(char* p, float4 v) {
     const uintx4 r = __builtin_bit_cast(uintx4, v);
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(r) : "memory");   // (s_nop: see store_through in elementwise.hip)
@@ -133,8 +135,8 @@ __global__ void __launch_bounds__(256) classify_out_kernel(const ClassifyOut p) 
             const float4 l = make_float4(v[0], v[1], v[2], v[3]), r = make_float4(e[0] * inv, e[1] * inv, e[2] * inv, e[3] * inv);
             out_store(host_logits + at[0] * 4, l);
             out_store(host_probs + at[0] * 4, r);
-            if (POOL) *(float4*)(p.logits + base + at[0]) = l;
-            *(float4*)(p.probs + base + at[0]) = r;
+            if (POOL) out_store((char*)(p.logits + base + at[0]), l);
+            out_store((char*)(p.probs + base + at[0]), r);
         }
     } else {
 #pragma unroll
@@ -142,13 +144,13 @@ __global__ void __launch_bounds__(256) classify_out_kernel(const ClassifyOut p) 
             if (at[k] >= n) continue;
             out_store(host_logits + at[k] * 4, v[k]);
             out_store(host_probs + at[k] * 4, e[k] * inv);
-            if (POOL) p.logits[base + at[k]] = v[k];
-            p.probs[base + at[k]] = e[k] * inv;
+            if (POOL) out_store((char*)(p.logits + base + at[k]), v[k]);
+            out_store((char*)(p.probs + base + at[k]), e[k] * inv);
         }
     }
     if (tid == 0) {
         __hip_atomic_store((int32_t*)(p.host + (size_t)p.rows * n * 8) + row, mi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        p.top1[row] = mi;
+        __hip_atomic_store(p.top1 + row, mi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     // each wavefront waits for its own stores to be acknowledged before the workgroup counts its row (see copy_out_kernel in elementwise.hip,
     // also for the order of the last stores)

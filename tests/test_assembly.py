@@ -62,3 +62,14 @@ def test_data_of_wide_stores_is_not_overwritten(kernels):
                 states += assembly.wait_states(behind)
     assert through >= 8                                    # copy out, and four forms of the classifier's end
     assert not overwritten, (len(overwritten), overwritten[:5])
+
+
+def test_the_end_of_a_classifier_writes_everything_through(kernels):
+    """The launch that raises the host's flag itself: the host may then give the instance, and with it the device's copy of the result, to another stream
+    before that launch has ended.  None of its stores may stay in a compute unit's or a chiplet's cache until then."""
+    ends = {name: [i for i in code if "_store_" in i and not i.startswith("ds_")] for name, code in kernels.items() if "classify_out_kernel" in name}
+    assert len(ends) == 4
+    for name, stores in ends.items():
+        assert len(stores) >= 6                            # logits, probabilities, index, stamps, flag
+        cached = [i for i in stores if not i.endswith("sc1")]
+        assert not cached, (name, cached)

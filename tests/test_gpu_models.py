@@ -411,6 +411,27 @@ def test_classifier_results_that_leave_in_the_launch_that_computes_them(ctx, arc
         m.free()
 
 
+def test_small_results_on_alternating_streams(ctx):
+    """One instance, its batches by turns on two compute streams and of two sizes, so that one batch's probabilities lie where the next one's logits do:
+    each result, and the device's copy read through the other stream as soon as the host has the result, is what it was the first time."""
+    S = ctx.S
+    md = synth.tiny_cnn(7, hw=32, classes=256)
+    m = ctx.load(synth.pack(md), max_batch=31, n_instances=1)
+    jobs = [(b, synth.default_image_batch(md, b, 11 + b), prio, other) for b, prio, other in
+            ((3, S.PRIO_HIGH, S.PRIO_LOW), (31, S.PRIO_LOW, S.PRIO_HIGH), (1, S.PRIO_HIGH, S.PRIO_LOW), (30, S.PRIO_LOW, S.PRIO_HIGH))]
+    first = {}
+    try:
+        for k in range(50):
+            for b, x, prio, other in jobs:
+                out = m.new_output(b)
+                m.wait(m.submit(prio, x, None, out))
+                if k % 5 == 0:                             # otherwise the next batch follows at once
+                    assert np.array_equal(m.copy_out(0, other, b).view(np.uint8), out.view(np.uint8)), f"pass {k}, batch {b}: the device's copy differs"
+                assert np.array_equal(first.setdefault(b, out), out), f"pass {k}, batch {b}: differs from the first"
+    finally:
+        m.free()
+
+
 @pytest.mark.parametrize("arch,batch", [("resnet50", 3), ("mobilenet_v2", 4), ("encoder", 2)])
 def test_graph_replay_equals_kernel_by_kernel(ctx, arch, batch):
     """The captured-graph path replays the very same launches: every replay, on fresh inputs and with
