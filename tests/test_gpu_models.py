@@ -411,6 +411,22 @@ def test_classifier_results_that_leave_in_the_launch_that_computes_them(ctx, arc
         m.free()
 
 
+def test_kernel_time_covers_every_row(ctx):
+    """3000 rows whose pooling, product and softmax share a launch with the result's way out, more than the GPU computes at a time: the computation does
+    not end with the first row (35 us before the last one).  What is left is the last row's 84 bytes on the link, 1 to 2 us of a median of eight."""
+    S = ctx.S
+    md = synth.tiny_cnn(7, hw=32, classes=10)
+    x = np.random.default_rng(1).random((3000, 32, 32, 3), dtype=np.float32).astype(np.float16)
+    m = ctx.load(synth.pack(md), max_batch=3000, n_instances=1)
+    try:
+        out = m.new_output(3000)
+        recs = [m.wait(m.submit(S.PRIO_HIGH, x, None, out)) for _ in range(9)][1:]
+        assert 0 < np.median([r.d2h_ms for r in recs]) < 0.015
+        assert all(r.kernel_ms > 0 and r.total_ms >= r.kernel_ms + r.d2h_ms for r in recs)
+    finally:
+        m.free()
+
+
 def test_small_results_on_alternating_streams(ctx):
     """One instance, its batches by turns on two compute streams and of two sizes, so that one batch's probabilities lie where the next one's logits do:
     each result, and the device's copy read through the other stream as soon as the host has the result, is what it was the first time."""
