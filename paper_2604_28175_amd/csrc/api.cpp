@@ -56,7 +56,7 @@ static int enqueue_output(Model& m, Instance& in, Ticket* t, hipStream_t s) {
     t->chunks = (unsigned)((bytes + t->chunk_bytes - 1) / t->chunk_bytes);
     t->out_pending = bytes >= kOutOnCopyStream;
     if (t->out_pending) return launch_stamp(in.ctl_dev, STAMP_K1, s, nullptr, nullptr, 0, t->seq);
-    if (classify_out_first(m, t->batch) < (int)m.ops.size()) return enqueue_classify_out(m, in, t->batch, s, t->hp, t->seq);
+    if (t->out_first < (int)m.ops.size()) return enqueue_classify_out(m, in, t->batch, t->out_first, s, t->hp, t->seq);
     return launch_copy_out(in.dev_out, in.pinned_out_dev, bytes, in.ctl_dev, in.counters + 1, t->seq, false, t->hp, s);
 }
 
@@ -69,7 +69,7 @@ static int issue_in_segments(Context* ctx, StreamWorker* w, Ticket* t) {
     Model& m = *t->model;
     Instance& in = m.inst[t->instance];
     hipStream_t s = w->stream;
-    const int n = classify_out_first(m, t->batch);
+    const int n = t->out_first;
     int seg;
     { std::lock_guard<std::mutex> lk(ctx->mu); seg = ctx->lp_yield_layers > 0 ? ctx->lp_yield_layers : n; }
     if (hipStreamWaitEvent(s, in.ev_h2d, 0) != hipSuccess || launch_stamp(in.ctl_dev, STAMP_K0, s)) return STRAIT_E_HIP;
@@ -326,11 +326,11 @@ static int hp_flag(const Context* c, int prio) { return prio == STRAIT_PRIO_HIGH
 
 // The kernel sequence of one batch on `s`: launched kernel by kernel, or, when the context asks for
 // graphs, as one replay of the sequence captured for this (instance, batch, wave-priority) key.
-// Only kernel launches are captured (no copies, events or memsets).  out_follows: only up to the
-// layers that the launch behind it computes (enqueue_output).
-static int run_batch(Model& m, Instance& in, int batch, hipStream_t s, int hp, bool out_follows) {
-    const bool cut = out_follows && classify_out_first(m, batch) < (int)m.ops.size();
-    const int last = cut ? classify_out_first(m, batch) - 1 : -1;
+// Only kernel launches are captured (no copies, events or memsets).  Only up to layer out_first, from
+// which on the launch behind it computes them (enqueue_output).
+static int run_batch(Model& m, Instance& in, int batch, hipStream_t s, int hp, int out_first) {
+    const bool cut = out_first < (int)m.ops.size();
+    const int last = cut ? out_first - 1 : -1;
     if (!m.ctx->use_graphs) return run_plan(m, in, batch, s, hp, last, false);
     const std::pair<int, int> key(batch, hp | (cut ? 2 : 0));
     auto it = in.graphs.find(key);
@@ -636,6 +636,7 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
     bool yielding;
     { std::lock_guard<std::mutex> lk(c->mu); yielding = prio == STRAIT_PRIO_LOW && c->lp_yield_layers > 0; }
     t->hp = hp_flag(c, prio);
+    t->out_first = classify_out_first(*m, batch);
     if (prio == STRAIT_PRIO_HIGH) c->hp_in_flight.fetch_add(1, std::memory_order_acq_rel);
     auto h2d_on_copy_stream = [&]() {
         t->by_copy_stream = true;
@@ -675,7 +676,7 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
             if (!rc) rc = launch_stamp(in.ctl_dev, STAMP_K0, s) ? STRAIT_E_HIP : 0;
             t->k0_stamped = true;
         }
-        if (!rc) rc = run_batch(*m, in, batch, s, t->hp, true);
+        if (!rc) rc = run_batch(*m, in, batch, s, t->hp, t->out_first);
         if (!rc) rc = enqueue_output(*m, in, t, s);
         if (!rc) {
             t->rec.t_issued_ns = now_ns();
@@ -773,7 +774,7 @@ strait_status strait_run(strait_model* m, int32_t instance, strait_priority prio
     if (rc) return rc;
     HIP_TRY(hipSetDevice(m->ctx->device));
     std::lock_guard<std::mutex> slk(m->ctx->compute_mu[compute_index(m->ctx, prio, (unsigned)instance)]);
-    return run_batch(*m, m->inst[instance], batch, compute_stream(m->ctx, prio, instance), hp_flag(m->ctx, prio), false);
+    return run_batch(*m, m->inst[instance], batch, compute_stream(m->ctx, prio, instance), hp_flag(m->ctx, prio), (int)m->ops.size());
 }
 
 strait_status strait_copy_out(strait_model* m, int32_t instance, strait_priority prio, int32_t batch, void* host_out) {

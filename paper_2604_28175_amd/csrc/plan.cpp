@@ -1271,7 +1271,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
 
 int classify_out_first(const Model& m, int batch) {
     const int n = (int)m.ops.size();
-    if (n < 2 || m.ops[n - 1].kind != OP_SOFTMAX || !classify_out_takes(batch, m.ops[n - 1].K)) return n;
+    if (n < 2 || m.ctx->pair_min_pixels <= 0 || m.ops[n - 1].kind != OP_SOFTMAX || !classify_out_takes(batch, m.ops[n - 1].K)) return n;
     if (n >= 4) {
         const Op &fc = m.ops[n - 2], &gap = m.ops[n - 3];
         if (fc.kind == OP_CONV && gap.kind == OP_POOL && gap.sub == POOL_GLOBAL_AVG && classify_out_pools(gap.H * gap.W, gap.C, fc.K)) return n - 3;
@@ -1279,8 +1279,8 @@ int classify_out_first(const Model& m, int batch) {
     return n - 1;
 }
 
-int enqueue_classify_out(Model& m, Instance& in, int batch, hipStream_t stream, int hp, unsigned seq) {
-    const int n = (int)m.ops.size(), first = classify_out_first(m, batch);
+int enqueue_classify_out(Model& m, Instance& in, int batch, int first, hipStream_t stream, int hp, unsigned seq) {
+    const int n = (int)m.ops.size();
     const Op& sm = m.ops[n - 1];
     ClassifyOut p{};
     if (first == n - 3) {

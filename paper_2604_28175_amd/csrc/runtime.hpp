@@ -169,6 +169,7 @@ struct Ticket {
     std::atomic<bool> chunks_coming{false};               // the copy off the device is enqueued: another thread may lend a hand
     std::atomic<int64_t> t_last{0};    // host time at which the last chunk was seen to be there
     std::atomic<int> copy_status{0};
+    int out_first = 0;                 // first op that the launch behind its kernel sequence computes; the number of ops: none
     bool out_pending = false;          // large result: its copy is enqueued when the kernels are seen done
     int hp = 0;                        // wave-priority flag its kernels are launched with
 };
@@ -212,9 +213,10 @@ int finish_plan(Model& m);             // after the instances' buffers
 // Enqueues layers first_layer..last_layer (last_layer < 0: up to the end) of the plan for `batch` samples on `stream`.
 // read_last: the output of last_layer is going to be read by the caller (a layer folded or laid out for the next one is then computed as it is).
 int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer = 0, bool read_last = false);
-// The first op of those that enqueue_classify_out computes on the result's way out; the number of ops where it computes none.
-// Depends on the model and the batch size only, so that a captured sequence always ends where the launch behind it begins.
+// The first op of those that enqueue_classify_out computes on the result's way out; the number of ops where it computes none, as in
+// the layer-by-layer plan (strait_ctx_set_pair_fusion).  Asked once per batch (Ticket::out_first), so that its sequence, also one in segments or a captured
+// one, ends where the launch behind it begins.
 int classify_out_first(const Model& m, int batch);
-int enqueue_classify_out(Model& m, Instance& in, int batch, hipStream_t stream, int hp, unsigned seq);
+int enqueue_classify_out(Model& m, Instance& in, int batch, int first, hipStream_t stream, int hp, unsigned seq);
 
 }  // namespace strait

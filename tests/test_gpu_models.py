@@ -411,6 +411,31 @@ def test_classifier_results_that_leave_in_the_launch_that_computes_them(ctx, arc
         m.free()
 
 
+@pytest.mark.parametrize("arch,hw,classes,batch", [("tiny_cnn", 33, 256, 31), ("mobilenet_v2", 64, 1000, 4)])
+def test_the_layer_by_layer_plan_ends_in_its_own_launches(ctx, arch, hw, classes, batch):
+    """set_pair_fusion(0): a submitted batch, eager, replayed or in segments, is what its layers by themselves give, to the last bit."""
+    S = ctx.S
+    md = getattr(synth, arch)(7, hw=hw, classes=classes)
+    x = synth.default_image_batch(md, batch, 11)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    ctx.set_pair_fusion(0)
+    try:
+        m.copy_in(0, S.PRIO_LOW, x)
+        m.run(0, S.PRIO_LOW, batch)
+        apart = m.copy_out(0, S.PRIO_LOW, batch)
+        for graphs, segment in ((False, 0), (True, 0), (True, 0), (True, 0), (False, 2)):
+            ctx.set_graphs(graphs)
+            ctx.set_lp_yield(segment)
+            out = m.new_output(batch)
+            m.wait(m.submit(S.PRIO_LOW, x, None, out))
+            assert np.array_equal(out.view(np.uint8), apart.view(np.uint8)), (graphs, segment)
+    finally:
+        ctx.set_graphs(False)
+        ctx.set_lp_yield(0)
+        ctx.set_pair_fusion(40000)
+        m.free()
+
+
 def test_kernel_time_covers_every_row(ctx):
     """3000 rows whose pooling, product and softmax share a launch with the result's way out, more than the GPU computes at a time: the computation does
     not end with the first row (35 us before the last one).  What is left is the last row's 84 bytes on the link, 1 to 2 us of a median of eight."""
