@@ -383,16 +383,12 @@ static void free_model(strait_model* m) {
 
 static const size_t COUNTER_BYTES = (2 + OUT_MAX_CHUNKS + 2) / 4 * 16;   // one for the input, one for the chunks, one per chunk; whole 16 bytes
 
-strait_status strait_model_load(strait_ctx* c, const strait_model_desc* d, strait_model** out) {
-    if (!c || !d || !out || !d->weights) { set_error("model_load: null argument"); return STRAIT_E_INVALID; }
-    if (d->max_batch < 1 || d->max_batch > 4096 || d->n_instances < 1 || d->n_instances > 64) {
-        set_error("model_load: max_batch must be in 1..4096 and n_instances in 1..64"); return STRAIT_E_INVALID;
-    }
-    HIP_TRY(hipSetDevice(c->device));
+static strait_status load_model(strait_ctx* c, const strait_model_desc* d, bool fold_layernorms, strait_model** out) {
     strait_model* m = new (std::nothrow) strait_model();
     if (!m) { set_error("out of host memory"); return STRAIT_E_NOMEM; }
     m->ctx = c;
     m->max_batch = d->max_batch;
+    m->fold_layernorms = fold_layernorms;
     int rc = build_plan(*m, d->weights, d->weights_bytes);
     if (rc) { free_model(m); return rc; }
     m->inst.resize(d->n_instances);
@@ -451,6 +447,23 @@ strait_status strait_model_load(strait_ctx* c, const strait_model_desc* d, strai
     }
     *out = m;
     return STRAIT_OK;
+}
+
+strait_status strait_model_load(strait_ctx* c, const strait_model_desc* d, strait_model** out) {
+    if (!c || !d || !out || !d->weights) { set_error("model_load: null argument"); return STRAIT_E_INVALID; }
+    if (d->max_batch < 1 || d->max_batch > 4096 || d->n_instances < 1 || d->n_instances > 64) {
+        set_error("model_load: max_batch must be in 1..4096 and n_instances in 1..64"); return STRAIT_E_INVALID;
+    }
+    HIP_TRY(hipSetDevice(c->device));
+    // Folded LayerNorms need a second set of weights for the products behind them (half of a transformer's) and memory for statistics: a model that
+    // fits without them only is loaded without them.
+    strait_status rc = load_model(c, d, true, out);
+    if (rc == STRAIT_E_NOMEM) {
+        (void)hipGetLastError();
+        rc = load_model(c, d, false, out);
+    }
+    if (rc) (void)hipGetLastError();      // reported here: the thread's next launch shall not find it
+    return rc;
 }
 
 strait_status strait_model_free(strait_model* m) {

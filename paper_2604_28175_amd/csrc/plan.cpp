@@ -330,7 +330,7 @@ struct Loader {
         op.ldw = (int)in;
         *total_out = (unsigned)b.size();
         op.info.weight_bytes = (int64_t)w.size() * 2 + (int64_t)b.size() * 4;
-        if (cold) { m.cold.push_back({m.ops.size(), std::move(w), std::move(b)}); return 0; }
+        if (cold && m.fold_layernorms) { m.cold.push_back({m.ops.size(), std::move(w), std::move(b)}); return 0; }
         void *dw = nullptr, *db = nullptr;
         int rc;
         if ((rc = upload(w.data(), w.size() * 2, &dw))) return rc;
@@ -588,7 +588,7 @@ struct Builder {
     // Weights that gamma takes out of fp16's normal range lose precision that the normalised activation keeps: there the LayerNorm stays a launch of its own.
     int fold_layer_norm(int ln, int in, int res) {
         Op &l = m.ops[ln], &c = m.ops[in];
-        if (l.K % 64 != 0 || l.K > 1024 || c.vC != l.K || c.ldw != l.K || c.K % 64 != 0 || m.ops[ln - 1].vC % 64 != 0) return 0;
+        if (!m.fold_layernorms || l.K % 64 != 0 || l.K > 1024 || c.vC != l.K || c.ldw != l.K || c.K % 64 != 0 || m.ops[ln - 1].vC % 64 != 0) return 0;
         const size_t n = (size_t)c.K * l.K;
         void *w = nullptr, *v = nullptr;
         if (hipMalloc(&w, n * 2) != hipSuccess) { set_error("hipMalloc(%zu) for weights failed", n * 2); return STRAIT_E_NOMEM; }

@@ -122,6 +122,7 @@ struct Model {
     size_t in_elems = 0;               // per-sample fp16 input elements
     int classes = 0;                   // CNN
     int seq = 0, hidden = 0;           // encoder, Vision Transformer
+    bool fold_layernorms = true;       // false: no LayerNorm is to be folded, for want of the memory that a second set of weights takes
     int ln_folds = 0;                  // LayerNorms that can be folded into products
     // Weights of products that a folded LayerNorm replaces, on the host until everything that a batch does read has its place (finish_plan): what a
     // batch reads then lies together and in the 256 MB memory-side cache.  (ViT batch 7, products of 3072 inputs: 23.6 us a launch, with

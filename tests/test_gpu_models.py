@@ -286,6 +286,57 @@ def test_layernorms_whose_folded_weights_leave_the_normal_range(ctx, norms):
         m.free()
 
 
+def test_a_model_that_fits_without_folded_layernorms_only(ctx):
+    """With memory left for one set of weights and half of the second: loaded, and its results are those of the layer-by-layer plan, bit for bit; with
+    less than one set it is refused, and with all memory back it is loaded as ever."""
+    import torch
+    S = ctx.S
+    layers, hidden, ffn = 8, 1024, 4096
+    md = synth.encoder(5, layers=layers, hidden=hidden, heads=16, ffn=ffn, seq=32)
+    blob = synth.pack(md)
+    second = layers * (3 * hidden + ffn) * hidden * 2      # Q, K, V and the first feed-forward product once more
+    x, vl = synth.token_batch(md, 2, 7, min_len=20)
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+    before = free()
+    m = ctx.load(blob, max_batch=2, n_instances=1)
+    both = before - free()
+    assert both > len(blob) + second // 2                  # (it is folded)
+    folded = m.infer(x, vl)[0]["hidden"]
+    ctx.set_pair_fusion(0)
+    apart = m.infer(x, vl)[0]["hidden"]
+    ctx.set_pair_fusion(40000)
+    m.free()
+    assert not np.array_equal(folded, apart)
+    filler = []
+    try:
+        for left, fits in ((both - second // 2, True), (len(blob) // 2, False)):
+            for _ in range(8):                             # (what the driver calls free can grow with the first large allocation)
+                if free() - left >= 4 << 20:
+                    filler.append(torch.empty(free() - left, dtype=torch.uint8, device="cuda"))
+            if abs(free() - left) >= 16 << 20:
+                pytest.skip("something else takes or gives back the GPU's memory")
+            if fits:
+                m = ctx.load(blob, max_batch=2, n_instances=1)
+                got = m.infer(x, vl)[0]["hidden"]
+                m.free()
+                assert np.array_equal(got, apart), (free(), left)
+            else:
+                with pytest.raises(S.StraitError) as e:
+                    ctx.load(blob, max_batch=2, n_instances=1)
+                assert e.value.status == S.E_NOMEM
+    finally:
+        filler.clear()
+        torch.cuda.empty_cache()
+    m = ctx.load(blob, max_batch=2, n_instances=1)
+    try:
+        assert np.array_equal(m.infer(x, vl)[0]["hidden"], folded)
+    finally:
+        m.free()
+
+
 @pytest.mark.parametrize("hw,batch,fc", [(32, 5, 64), (64, 3, 256)])
 def test_vgg19(ctx, hw, batch, fc):
     md = synth.vgg19(synth.SEEDS[synth.ARCH_VGG19], hw=hw, classes=100, fc=fc)
