@@ -1,5 +1,7 @@
 // The LDS-direct implicit-GEMM kernel, included by the files that instantiate it (conv_igemm.hip, gemm_ln.hip).
 #pragma once
+#include <atomic>
+
 #include "activation.hpp"
 #include "kernels.hpp"
 
@@ -700,6 +702,20 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             else *(half8*)((half_t*)p.y + (long long)m * p.ldy + n) = v;
         }
     }
+}
+
+// One launch of a kernel that takes ConvParams and `lds` bytes of dynamic LDS, of which `reserve`, the same in every call for a kernel, are asked for before
+// its first.  (The kernel is a template argument, so that each has a flag of its own: variants of a tile all have the same type.)
+template <void (*KERNEL)(ConvParams)>
+static int launch_with_lds(const ConvParams& p, dim3 grid, dim3 block, unsigned lds, unsigned reserve, hipStream_t stream) {
+    static std::atomic<bool> configured{false};            // (setting the attribute twice is harmless)
+    if (!configured.load(std::memory_order_acquire) && reserve > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, (int)reserve);
+        if (e != hipSuccess) { set_error("conv: cannot reserve %u bytes of LDS: %s", reserve, hipGetErrorString(e)); return -2; }
+    }
+    configured.store(true, std::memory_order_release);
+    hipLaunchKernelGGL(KERNEL, grid, block, lds, stream, p);
+    return 0;
 }
 
 // The tiles a layer is given to one of (conv_igemm.hip: choose_conv).

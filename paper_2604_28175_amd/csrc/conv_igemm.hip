@@ -836,16 +836,7 @@ static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
     dim3 grid((unsigned)tiles), block(64 * WGM * WGN * KG);
     ConvParams q = p;
     q.tile_cw = pick_tile_cw(tiles_m, tiles_n, BM, BN);
-    auto go = [&](auto kernel) -> int {
-        static std::atomic<bool> configured{false};     // one flag per instantiation; setting the attribute twice is harmless
-        if (!configured.load(std::memory_order_acquire) && lds > 48 * 1024) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) { set_error("conv: cannot reserve %u bytes of LDS: %s", lds, hipGetErrorString(e)); return -2; }
-        }
-        configured.store(true, std::memory_order_release);
-        hipLaunchKernelGGL(kernel, grid, block, lds, stream, q);
-        return 0;
-    };
+#define STRAIT_GO(...) launch_with_lds<conv_igemm_dma_kernel<__VA_ARGS__>>(q, grid, block, lds, lds, stream)
     auto after = [&]() -> int {                        // the second launch of a split reduction
         if (p.ksplit > 1) {
             const long long n8 = (long long)p.M * (p.Cout / 8);
@@ -858,28 +849,29 @@ static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
     int rc;
     if (p.res_f32 && p.ksplit == 1) {
         if constexpr (BM <= 64 && BN == 64) {
-            if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_WIDE, false, KG>);
-            else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_WIDE, false, KG>);
+            if (mode == MODE_1X1) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_WIDE, false, KG);
+            else rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_WIDE, false, KG);
         } else { set_error("conv: this tile does not add a residual in fp32"); return -5; }
     } else if constexpr (KG > 1) {
-        if (mode == MODE_1X1 && p.res) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY, false, KG>);
-        else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, KG>);
-        else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE, false, KG>);
+        if (mode == MODE_1X1 && p.res) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY, false, KG);
+        else if (mode == MODE_1X1) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, KG);
+        else rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE, false, KG);
     } else {
         if constexpr (BM == 128 && BN == 128 && dma_deep<BM, BN, BK, WGM, WGN>()) {
             if (p.Kg < 512 && p.act != ACT_GELU && !p.x2) {
-                if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY, false, 1, LN_NONE, false>);
-                else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, 1, LN_NONE, false>);
-                else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE, false, 1, LN_NONE, false>);
+                if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY, false, 1, LN_NONE, false);
+                else if (mode == MODE_1X1) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, 1, LN_NONE, false);
+                else rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE, false, 1, LN_NONE, false);
                 return rc ? rc : after();
             }
         }
-        if (mode == MODE_1X1 && p.act == ACT_GELU) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, RES_LATE>);
-        else if (mode == MODE_1X1 && p.x2) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, true>);
-        else if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY>);
-        else if (mode == MODE_1X1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE>);
-        else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE>);
+        if (mode == MODE_1X1 && p.act == ACT_GELU) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, RES_LATE);
+        else if (mode == MODE_1X1 && p.x2) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, true);
+        else if (mode == MODE_1X1 && p.res && p.ksplit == 1) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_EARLY);
+        else if (mode == MODE_1X1) rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE);
+        else rc = STRAIT_GO(BM, BN, BK, WGM, WGN, MODE_GATHER8, STAGES, false, RES_LATE);
     }
+#undef STRAIT_GO
     return rc ? rc : after();
 }
 

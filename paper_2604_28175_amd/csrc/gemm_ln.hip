@@ -7,7 +7,6 @@
 // 12.9 -> 13.8; 8192 rows 40 -> 42.8, 55 -> 59, 17.2 -> 19.7, 45 -> 49.  Encoder batch 8 836 -> 730 us, ViT batch 7 1001 -> 918; 2 x batch 64
 // 5257 -> 5105, ViT batch 64 3769 -> 3612 (1 % of each the GELU).
 #include <algorithm>
-#include <atomic>
 
 #include "conv_dma.hpp"
 
@@ -27,28 +26,20 @@ static int launch_ln_tile(const ConvParams& p, hipStream_t stream) {
     const unsigned in = base_in + ln_lds_bytes<BM, LN_IN>(p.Kg / 64), res = out + ln_lds_bytes<BM, LN_RES>(p.Cout / 64);
     ConvParams q = p;
     q.tile_cw = pick_tile_cw(tiles_m, tiles_n, BM, BN);
-    auto go = [&](auto kernel, unsigned lds) -> int {
-        static std::atomic<bool> configured{false};
-        if (!configured.load(std::memory_order_acquire)) {
-            // (once for all widths of a LayerNorm)
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) { set_error("gemm with LayerNorm: cannot reserve 160 KB of LDS: %s", hipGetErrorString(e)); return -2; }
-        }
-        configured.store(true, std::memory_order_release);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * WGM * WGN * KG), lds, stream, q);
-        return 0;
-    };
+    // (160 KB are asked for once, for all widths of a LayerNorm)
+#define STRAIT_GO(lds, ...) launch_with_lds<conv_igemm_dma_kernel<__VA_ARGS__>>(q, dim3((unsigned)tiles), dim3(64 * WGM * WGN * KG), lds, 160 * 1024, stream)
     int rc;
     if (!p.stats_out) {
         if (p.act == ACT_GELU) {
-            if constexpr (KG == 1) rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, RES_LATE, false, 1, LN_IN>, in);
+            if constexpr (KG == 1) rc = STRAIT_GO(in, BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, true, RES_LATE, false, 1, LN_IN);
             else { set_error("gemm with LayerNorm: no GELU on this tile"); return -5; }
-        } else rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, KG, LN_IN>, in);
+        } else rc = STRAIT_GO(in, BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_LATE, false, KG, LN_IN);
     } else if (p.ln_stats) {
-        rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_F32, false, KG, LN_RES>, res);
+        rc = STRAIT_GO(res, BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_F32, false, KG, LN_RES);
     } else {
-        rc = go(conv_igemm_dma_kernel<BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_F32, false, KG, LN_OUT>, out);
+        rc = STRAIT_GO(out, BM, BN, BK, WGM, WGN, MODE_1X1, STAGES, false, RES_F32, false, KG, LN_OUT);
     }
+#undef STRAIT_GO
     if (rc) return rc;
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("gemm with LayerNorm launch: %s", hipGetErrorString(e)); return -2; }
