@@ -5,10 +5,10 @@
 // hand-over, whatever it computes.  So a workgroup takes one sample from its logits (or its feature map) to the host's buffer, a thread holding four
 // classes in registers, and the last workgroup to finish sets the flag that the host polls.  Results of one chunk only: a larger one leaves in
 // pieces beside the kernels that follow.  The device's copy of the result is written too, and is there before the flag.
-// Measured on MI355X, one launch for two, us a pass: ResNet-50 one image 353 -> 325, eight 528 -> 500, MobileNetV2 five
-// images 290 -> 282 (two runs differ by up to 2 %).
+// Measured on MI355X against launches of their own, timed in turn, us a pass: with pooling and product (four 32 x 32 images, ten classes) 46.1 -> 37.5; softmax
+// and copy alone are worth no more than two runs of one side differ by, 1 to 4 %: ResNet-50 eight images 519 -> 510, one 324 -> 330, MobileNetV2 five 283 -> 285.
 // The pooled head reads its weights once per sample through one compute unit, so it is for small ones: up to 16384 weights, 256 channels and 256
-// classes (a hundred kilobytes would take longer than the two launches saved); with it, a 32 x 32 image's three layers and ten classes take 40.7 us a pass instead of 48.9.
+// classes (a hundred kilobytes would take longer than the two launches saved).
 #include <algorithm>
 
 #include "kernels.hpp"

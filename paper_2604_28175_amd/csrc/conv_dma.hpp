@@ -17,7 +17,7 @@ enum { MODE_1X1 = 0, MODE_GATHER8 = 1, MODE_SCALAR = 2 };
 // Deep-pipelined variant for the regular cases: dense 1x1 / GEMM, and filters whose channel count
 // is a multiple of the 32-wide slice (so a slice never straddles two filter taps).
 //
-// The kernel above keeps one slice in flight per workgroup and spends most of its issue slots on
+// conv_igemm_kernel (conv_igemm.hip) keeps one slice in flight per workgroup and spends most of its issue slots on
 // per-lane gather arithmetic.  Here
 //   - slices travel global -> LDS directly (buffer_load_dwordx4 ... lds: each lane names a 16-byte
 //     chunk, the wave's 64 chunks land in 1 KB of consecutive LDS) through a ring of STAGES
@@ -140,7 +140,7 @@ __device__ __forceinline__ float sum_of_8_lanes(float v) {     // of the aligned
 
 // DEEP, for tiles of few MFMAs per wavefront and step: operands are read from LDS three steps ahead and not one, so that a step does not wait for
 // LDS, and reads are in flight across the barrier; a stage is filled again one slice later.  1024 x 3072 x 768 with GELU on 128 x 128 tiles of 8
-// wavefronts 11.7 -> 11.2 us, 2758 x 768 x 3072 on 96 x 128 22.7 -> 21.2, 1379 x 768 x 3072 on 128 x 64 17.6 -> 16.5 (on 64 x 128, as before, 18.2).  What is
+// wavefronts 11.7 -> 11.2 us, 2758 x 768 x 3072 on 96 x 128 22.7 -> 21.2, 1379 x 768 x 3072 on 128 x 64 17.6 -> 16.5 (on the 64 x 128 tile that it had before, 18.2; all without a LayerNorm).  What is
 // left is the rate of the transfers, 60 to 75 B/ns per compute unit whatever the tile: rings of 6 or 8 stages change nothing.
 // Short reductions on the 128 x 128 tile are better off without (3136 x 1024 x 256 with a residual 7.3 and 7.6): there from 512 on.
 template <int BM, int BN, int BK, int WGM, int WGN>
@@ -388,7 +388,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             s += k < ln_parts ? pt[i].x : 0.f;
         }
         s += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0xB1, 0xf, 0xf, true));
-        const float mean = s / (float)(64 * ln_parts);       // (not times the reciprocal, which misses the number that a row of equal ones consists of: 7, 13 and 15 parts)
+        const float mean = s / (float)(64 * ln_parts);       // (not times the reciprocal, which misses the number that a row of equal ones consists of: 7, 13, 14 and 15 parts)
 #pragma unroll
         for (int i = 0; i < LN_MAX_PARTS / 2; ++i) {
             const float d = pt[i].x * (1.f / 64.f) - mean;
@@ -545,7 +545,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
         return;
     }
 
-    // ---- epilogue (same as the first kernel's staged path) --------------------------------------
+    // ---- epilogue (as the staged path of conv_igemm_kernel in conv_igemm.hip) --------------------------------------
     // ReLU / ReLU6 / none are one clamp with workgroup-uniform bounds; GELU is a separate instantiation
     // The epilogue's arithmetic after the bias is done on packed fp16 pairs: adding two fp16 numbers, or
     // clamping one against 0, 6 or an infinity, gives the same fp16 result whether it is done in fp16 or

@@ -301,7 +301,7 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(const ConvParams p) 
 // ------------------------------------------------------------------------------------------
 // 3x3, stride 1, padding 1, from an input patch held in LDS.
 //
-// The kernel above fetches every input pixel nine times, once per filter tap; on the wide early layers that
+// conv_igemm_dma_kernel (conv_dma.hpp) fetches every input pixel nine times, once per filter tap; on the wide early layers that
 // traffic between L2 and LDS, not the MFMAs, sets the pace.  Here pixels are numbered in a bordered space: every
 // image row is preceded by one border slot and every image by one border row, v = (n (H+1) + y) (W+1) + x for
 // output (n, y, x), and the slot with number u holds input pixel (u's row - 1, u's column - 1) or, in the border,
@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(256) splitk_finish_kernel(const ConvParams p) 
 // 32-channel slice of one tap at a time, stream through a three-stage ring.  The patch of the next slice arrives
 // in a second buffer during the first seven tap steps of the current one.  Per tap step every wave issues a
 // fixed number of transfers, so the in-order load counter tells when a given stage has landed.  LDS rows of 64
-// bytes are swizzled as in the kernel above (16-byte chunk c of row i sits at c ^ ((i >> 2) & 3)), which keeps
+// bytes are swizzled as there (16-byte chunk c of row i sits at c ^ ((i >> 2) & 3)), which keeps
 // the operand reads conflict free for any run of consecutive rows, i.e. for every tap offset.
 template <int BM, int BN, int WGM, int WGN, int NPW, int NBS>
 __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 2) conv3x3_patch_kernel(const ConvParams p) {
@@ -733,6 +733,8 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
 // channels in, 40 to 4500 tiles; mean error 3 to 12 %); the choice is then on average 2 % off the best there, before 7 % and up
 // to 1.7 times: 16 x 112 x 112, 64 -> 128 53 -> 41 us; 118 x 40 x 40 at stride 2, 160 -> 512 132 -> 83 us.
 // The rows of the kernel through registers are fits to 230 layers with fp32 or odd outputs (mean error 17 to 20 %).
+// The rows are older than the GELU of activation.hpp and than the operands read ahead on the 96 x 128 and 8-wavefront 128 x 128 tiles: c4 is about a
+// quarter too high on tiles that fill a unit, and those two tiles are up to 7 % faster than estimated.
 // Against the thresholds used before (and with the pipelined loop): ResNet-50's layers 7 % faster on the sum over batch 1
 // to 128 (22 % at batch 1, 5 % at 128), an encoder layer's products 8 to 19 % from 1000 rows on and 20 to 32 % below.
 struct TileInfo { int bm, bn, bk, kg; bool shared; float c[7]; };   // shared: two or more workgroups fit a compute unit
@@ -1093,7 +1095,9 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
     return through_registers();
 }
 
-// The same for a dense product with a LayerNorm folded in: the LDS-direct kernel only, on the tiles that gemm_ln.hip instantiates (slices of 64).
+// The same for a dense product with a LayerNorm folded in: the LDS-direct kernel only, on the tiles that gemm_ln.hip instantiates (slices of 64).  The
+// estimates are the plain products', whose epilogues are shorter by 0.6 to 1 us a round (gemm_ln.hip); among tiles that they put within a few per
+// cent of each other the choice is not better founded than that.
 int choose_gemm_ln(ConvParams& p) {
     int mode = 0;
     bool staged = false;

@@ -1079,8 +1079,8 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
         const bool with_proj = op.w_proj && pixels >= m.ctx->proj_min_pixels;
         if (op.pair && i + op.pair <= last_layer) {
             // (a pair with its projection is one tile per wavefront up to 65536 pixels, whatever their number; below about 20000 its two products take
-            // less as launches of their own.  With an event pair around each launch, some 2 us of it: 3136 pixels 16.1 us / 7.5 + 6.8, 12544 17.0 /
-            // 9.9 + 7.4, 18816 17.4 / 11.4 + 8.2)
+            // less as launches of their own, or the same: timed with an event pair around each launch, 2 us taken off each, 3136 pixels 14.1 us / 5.5 +
+            // 4.8, 12544 15.0 / 7.9 + 5.4, 18816 15.4 / 9.4 + 6.2: the two ways cross shortly before the last)
             if (with_proj && pixels >= std::min(m.ctx->pair_min_pixels, 20000LL) && pointwise_pair_proj_supported(op.vC, m.ops[op.proj_down].vC, op.K, m.ops[i + op.pair].K)) return 2;
             if (pixels >= m.ctx->pair_min_pixels) return 1;
         }
