@@ -181,7 +181,7 @@ struct ClassifyOut {
     const half_t* w; int ldw; const float* bias;
     float* logits; float* probs; int32_t* top1;
     int rows, n;
-    char* host; HostControl* ctl; unsigned* counter;   // counter: as launch_copy_out's first
+    char* host; HostControl* ctl; unsigned* counter;   // counter: launch_copy_out's, 33 lines of 32 from the first
     unsigned seq;
     int hp;
 };
