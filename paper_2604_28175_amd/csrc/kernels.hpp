@@ -122,6 +122,7 @@ int launch_stem3x3s2(const half_t* x, const half_t* wf, const float* bias, int N
 // 3x3 stride-1 pad-1 convolution of a 3-channel image to 16, 32 or 64 channels + bias + activation (stem3x3.hip), W even.  wf: [Kout rounded up to 32]
 // [2][3][16]: per channel, for even and for odd columns, three filter rows of 9 halfs {w[k][r][s][c]}, at 1 .. 9 and at 0 .. 8; the rest zero.
 bool stem3x3s1_supported(int W, int Kout, int act);
+bool stem3x3s1_pays(int N, int H, int W);              // whether it is estimated to be no slower than the packing launch and the product
 int launch_stem3x3s1(const half_t* x, const half_t* wf, const float* bias, int N, int H, int W, int Kout, int act, half_t* y, int hp,
                      hipStream_t stream);
 // The stride-2 stem (32 output channels) with a stride-1 depthwise 3x3 behind it (wd_rsc [3][3][32], + bd, act2) in one launch;

@@ -1222,7 +1222,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                 rc = launch_stem3x3s2((const half_t*)src, op.w, op.bias, batch, op.H, op.W, op.K, op.act, (half_t*)dst, hp, stream);
                 break;
             case OP_PACK:
-                if (op.w && i + 1 <= last_layer && m.ctx->pair_min_pixels > 0) {
+                if (op.w && i + 1 <= last_layer && m.ctx->pair_min_pixels > 0 && stem3x3s1_pays(batch, op.H, op.W)) {
                     const Op& cv = m.ops[i + 1];
                     rc = launch_stem3x3s1((const half_t*)src, op.w, cv.bias, batch, op.H, op.W, cv.K, cv.act,
                                           (half_t*)slot_ptr(m, in, cv.out, cv.out_ref, batch), hp, stream);

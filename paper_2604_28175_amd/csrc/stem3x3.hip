@@ -454,6 +454,14 @@ stem3x3s1_kernel(const half_t* __restrict__ x, const half_t* __restrict__ wf, co
     }
 }
 
+// Images that leave more than three quarters of a tile empty are worth it while they are few: a tile takes 2.5 ns whatever it holds, the two launches 10 ns for a
+// full one's pixels, and 4 us more.  Kernels in us, the copy and the product / this, 16 channels: 8 x 8 images, 1000 (2000 tiles) 4.2 + 6.4 / 8.6, 2000
+// 4.9 + 8.4 / 14.0, 3000 5.9 + 10.0 / 18.9; 10 x 10, 2000 (6000 tiles) 5.4 + 11.5 / 20.4; 16 x 16, a quarter full, 3000 (12000 tiles) 11.1 + 28.1 / 31.1.
+bool stem3x3s1_pays(int N, int H, int W) {
+    const long long tiles = (long long)N * ((H + S1_TP - 1) / S1_TP) * ((W + S1_TQ - 1) / S1_TQ);
+    return tiles * (S1_TP * S1_TQ / 4) - (long long)N * H * W <= 380 * (S1_TP * S1_TQ);      // positions short of a quarter
+}
+
 bool stem3x3s1_supported(int W, int Kout, int act) { return W >= 2 && W % 2 == 0 && (Kout == 16 || Kout == 32 || Kout == 64) && act != ACT_GELU; }
 
 int launch_stem3x3s1(const half_t* x, const half_t* wf, const float* bias, int N, int H, int W, int Kout, int act, half_t* y, int hp, hipStream_t stream) {

@@ -513,6 +513,26 @@ def test_more_rows_than_the_gpu_takes_at_a_time_end_in_launches_of_their_own(ctx
         m.free()
 
 
+@pytest.mark.parametrize("hw,batch", [(8, 1521), (10, 1058)])
+def test_many_small_images_are_packed_for_the_first_layer(ctx, hw, batch):
+    """Images that leave most of the direct first layer's tiles empty, one more of them than it takes: the layer-by-layer plan's bytes."""
+    S = ctx.S
+    md = synth.tiny_cnn(7, hw=hw, classes=10)
+    x = synth.default_image_batch(md, batch, 11)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    try:
+        got = []
+        for fusion in (40000, 0):
+            ctx.set_pair_fusion(fusion)
+            out = m.new_output(batch)
+            m.wait(m.submit(S.PRIO_LOW, x, None, out))
+            got.append(out.view(np.uint8).copy())
+        assert np.array_equal(*got)
+    finally:
+        ctx.set_pair_fusion(40000)
+        m.free()
+
+
 def test_kernel_time_covers_every_row(ctx):
     """1024 rows whose pooling, product and softmax share a launch with the result's way out: the computation does not end with the first row.  What is left
     then is the way of the rows' 84 bytes to the host, 4.5 us in a median of eight (12 with the first row's end and one counter for all rows)."""
