@@ -724,4 +724,6 @@ enum TileId { T256x256, T256x192, T192x128, T128x256, T128x128, T128x128_2, T96x
               T_REG128x128, T_REG128x64, T_REG64x64, T_ESTIMATED, T_SLABS64 = T_ESTIMATED, T_SLABS64s, T_SMALL32x16, T_SMALL64x16, T_SMALL64x32, T_SMALL128x32, T_MID96x128, T_MID192x128,
               T_COUNT };                               // (slabs: slab_split; small, mid: small_us, mid_us)
 
+bool gemm_ln_two_fit(int id, const ConvParams& p);     // whether two workgroups of a folded product's tile fit a compute unit (gemm_ln.hip)
+
 }  // namespace strait

@@ -1112,6 +1112,7 @@ int choose_gemm_ln(ConvParams& p) {
         const TileInfo& t = tile_info[i];
         if (p.ln_stats && t.bn == 256 && (p.ln_csum ? p.Kg : p.Cout) > 64 * LN_MAX_PARTS_256) continue;         // (LDS)
         if (t.bk != 64 || (t.kg > 1 && (p.Kg < 512 || p.act == ACT_GELU)) || (t.bm < 128 && mb > 250)) continue;
+        if (t.shared && !gemm_ln_two_fit(i, p)) continue;   // (the rows' statistics lie in LDS too: those of more than 768 channels leave no room for a second tile)
         const float us = estimate_us(p, (TileId)i, p.M, false, true, mb);
         if (us < best_us) { best_us = us; best = i; }
     }

@@ -12,6 +12,14 @@
 
 namespace strait {
 
+// LDS of a workgroup on a tile; parts: the groups of 64 channels that a row's statistics come in
+template <int BM, int BN, int STAGES, int KG>
+constexpr unsigned ln_tile_lds(int ln, int parts) {
+    constexpr unsigned ring = KG * STAGES * (BM + BN) * 64 * 2, ctile = BM * (BN + 8) * 2, ftile = f32_stage_rows<BM, BN>() * (BN + 4) * 4;
+    const unsigned park = ln == LN_IN ? ctile : ftile;
+    return (ring > park ? ring : park) + 1024 + (ln == LN_IN ? ln_lds_bytes<BM, LN_IN>(parts) : ln == LN_RES ? ln_lds_bytes<BM, LN_RES>(parts) : 0u);
+}
+
 template <int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1>
 static int launch_ln_tile(const ConvParams& p, hipStream_t stream) {
     constexpr int BK = 64;
@@ -19,11 +27,9 @@ static int launch_ln_tile(const ConvParams& p, hipStream_t stream) {
     const int tiles_n = (p.Cout + BN - 1) / BN;
     const long long tiles = tiles_m * tiles_n;
     if (tiles <= 0 || tiles > 0x7fffffffLL) { set_error("gemm with LayerNorm: bad grid (%lld tiles)", tiles); return -5; }
-    constexpr unsigned ring = KG * STAGES * (BM + BN) * BK * 2, ctile = BM * (BN + 8) * 2, ftile = f32_stage_rows<BM, BN>() * (BN + 4) * 4;
-    constexpr unsigned base_in = (ring > ctile ? ring : ctile) + 1024, out = (ring > ftile ? ring : ftile) + 1024;
     constexpr int most = BN == 256 ? LN_MAX_PARTS_256 : LN_MAX_PARTS;
-    static_assert(base_in + ln_lds_bytes<BM, LN_IN>(most) <= 160 * 1024 && out + ln_lds_bytes<BM, LN_RES>(most) <= 160 * 1024, "LDS limit");
-    const unsigned in = base_in + ln_lds_bytes<BM, LN_IN>(p.Kg / 64), res = out + ln_lds_bytes<BM, LN_RES>(p.Cout / 64);
+    static_assert(ln_tile_lds<BM, BN, STAGES, KG>(LN_IN, most) <= 160 * 1024 && ln_tile_lds<BM, BN, STAGES, KG>(LN_RES, most) <= 160 * 1024, "LDS limit");
+    const unsigned in = ln_tile_lds<BM, BN, STAGES, KG>(LN_IN, p.Kg / 64), res = ln_tile_lds<BM, BN, STAGES, KG>(LN_RES, p.Cout / 64), out = ln_tile_lds<BM, BN, STAGES, KG>(LN_OUT, 0);
     ConvParams q = p;
     q.tile_cw = pick_tile_cw(tiles_m, tiles_n, BM, BN);
     // (160 KB are asked for once, for all widths of a LayerNorm)
@@ -79,6 +85,17 @@ int launch_gemm_ln(const ConvParams& params, hipStream_t stream) {
         case T64x64_g2: return launch_ln_tile<64, 64, 2, 2, 3, 2>(p, stream);
         case T32x64_g4: return launch_ln_tile<32, 64, 1, 2, 3, 4>(p, stream);
         default: set_error("gemm with LayerNorm: no such tile"); return -5;
+    }
+}
+
+bool gemm_ln_two_fit(int id, const ConvParams& p) {
+    const int ln = !p.stats_out ? LN_IN : p.ln_stats ? LN_RES : LN_OUT, parts = (ln == LN_IN ? p.Kg : p.Cout) / 64;
+    switch (id) {
+        case T128x128_2: return 2 * ln_tile_lds<128, 128, 2, 1>(ln, parts) <= 160 * 1024;
+        case T64x128: return 2 * ln_tile_lds<64, 128, 3, 1>(ln, parts) <= 160 * 1024;
+        case T64x64: return 2 * ln_tile_lds<64, 64, 3, 1>(ln, parts) <= 160 * 1024;
+        case T32x64: return 2 * ln_tile_lds<32, 64, 4, 1>(ln, parts) <= 160 * 1024;
+        default: return false;
     }
 }
 

@@ -11,6 +11,7 @@ static size_t asked[KERNELS];
 static int kernels;
 static struct { dim3 grid, block; size_t lds; void* stream; } call;
 int recorded_launches, recorded_wide, recorded_unasked;
+int recorded_last_grid, recorded_last_block, recorded_last_lds;
 
 static size_t* of(const void* f) {
     int i = 0;
@@ -31,8 +32,9 @@ int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** strea
     return 0;
 }
 int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, void* stream) {
-    (void)grid; (void)block; (void)args; (void)stream;
+    (void)args; (void)stream;
     ++recorded_launches;
+    recorded_last_grid = (int)grid.x; recorded_last_block = (int)block.x; recorded_last_lds = (int)lds;
     if (lds > 64 * 1024) {
         ++recorded_wide;
         if (*of(f) < lds) {
