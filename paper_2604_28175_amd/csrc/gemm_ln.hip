@@ -57,6 +57,14 @@ bool gemm_ln_supported(long long M, long long N, long long K, int width) {
            N * K * 2 <= 0x7fffffffLL && M * width / 8 <= 0x7fffffffLL;
 }
 
+// Whole passes of three encoder layers, folded against LayerNorm launches of their own.  Above 768 channels the statistics leave no room for the largest tiles and for
+// pairs of 128 x 128: 832 to 1024 channels 0.88 to 0.97 of the time at 512 to 2048 rows, 0.94 to 0.98 at 3072, at 4096 0.96 with 832 and 0.98 to 1.03 above, 0.98 to
+// 1.07 at 5000 to 6400, 1.05 to 1.09 at 16384; up to 768 channels 0.84 to 1.00 everywhere.  Up to 64 rows the products go to kernels that take no LayerNorm in, and a row of whole
+// chunks for 64 lanes is the LayerNorm kernel's fastest form: 512 channels 1.02 to 1.06, 1024 0.98 to 1.02; others 0.89 to 1.02.
+bool gemm_ln_pays(long long rows, int width) {
+    return rows <= 64 ? width % 512 != 0 : width <= 64 * LN_MAX_PARTS_256 || rows <= (width <= 832 ? 4096 : 3072);
+}
+
 int launch_gemm_ln(const ConvParams& params, hipStream_t stream) {
     ConvParams p = params;
     const bool in = p.ln_stats && p.ln_csum, res = p.ln_stats && p.ln_g && p.ln_b;

@@ -84,6 +84,7 @@ int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn);
 int launch_gemm_ln(const ConvParams& p, hipStream_t stream);
 // whether launch_gemm_ln takes M x N x K products whose normalised width is `width`
 bool gemm_ln_supported(long long M, long long N, long long K, int width);
+bool gemm_ln_pays(long long rows, int width);          // whether folding is no slower than a LayerNorm launch between the products
 // w [N][K], b [N] and the LayerNorm's gamma, beta [K] -> fp16(gamma w), its row sums, b + w beta; *bad, if given, becomes 1 where
 // gamma w does not keep fp16's precision (gemm_ln.hip), and is left alone otherwise
 int launch_fold_layernorm(const half_t* w, const float* b, const float* gamma, const float* beta, int N, int K, half_t* w_out, float* csum, float* b_out,

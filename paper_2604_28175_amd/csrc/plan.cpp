@@ -1090,7 +1090,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
     // is issued in segments
     if (first_layer == 0) in.ln_fold = m.ctx->pair_min_pixels > 0;
     auto folded = [&](int ln) {
-        if (ln < 0 || m.ops[ln].fold_ops[0] < 0 || !in.ln_fold) return false;
+        if (ln < 0 || m.ops[ln].fold_ops[0] < 0 || !in.ln_fold || !gemm_ln_pays((long long)batch * m.ops[ln].P, m.ops[ln].K)) return false;
         for (int o : m.ops[ln].fold_ops)
             if (o >= 0 && !gemm_ln_supported((long long)batch * m.ops[ln].P, m.ops[o].K, m.ops[o].vC, m.ops[ln].K)) return false;
         return true;

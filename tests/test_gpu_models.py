@@ -262,6 +262,24 @@ def test_folded_layernorms(ctx, arch, kw, batch):
         m.free()
 
 
+@pytest.mark.parametrize("hidden,seq,batch,folds", [(1024, 35, 88, False), (1024, 32, 96, True), (832, 33, 125, False), (832, 32, 128, True), (768, 33, 125, True),   # one side and the other of 3072, 4096 rows
+                                                    (512, 32, 2, False), (512, 65, 1, True), (1024, 64, 1, False), (448, 32, 2, True)])            # 64 and 65
+def test_layernorms_are_folded_where_that_is_no_slower(ctx, hidden, seq, batch, folds):
+    """The layer-by-layer plan's bytes where they are not."""
+    md = synth.encoder(5, layers=2, hidden=hidden, heads=hidden // 64, ffn=256, seq=seq)
+    x, vl = synth.token_batch(md, batch, 7, min_len=20)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    try:
+        got = m.infer(x, vl, prio=ctx.S.PRIO_LOW)[0]["hidden"]
+        ctx.set_pair_fusion(0)
+        apart = m.infer(x, vl, prio=ctx.S.PRIO_LOW)[0]["hidden"]
+        assert np.array_equal(got, apart) != folds
+        check_kernel(got[0][:int(vl[0])], apart[0][:int(vl[0])].astype(np.float64), "folded and apart", rel=2.0 ** -8, abs_rel=1e-2)
+    finally:
+        ctx.set_pair_fusion(40000)
+        m.free()
+
+
 @pytest.mark.parametrize("norms", [("l0.ln1", "l0.ln2", "l1.ln1", "l1.ln2", "l2.ln1"), ("l0.ln1", "l1.ln2"), ("l0.ln2",)])
 def test_layernorms_whose_folded_weights_leave_the_normal_range(ctx, norms):
     """gamma of 2^-14 takes fp16 weights below the normal range: such a LayerNorm stays apart, beside folded ones."""
@@ -292,7 +310,7 @@ def test_a_model_that_fits_without_folded_layernorms_only(ctx):
     import torch
     S = ctx.S
     layers, hidden, ffn = 8, 1024, 4096
-    md = synth.encoder(5, layers=layers, hidden=hidden, heads=16, ffn=ffn, seq=32)
+    md = synth.encoder(5, layers=layers, hidden=hidden, heads=16, ffn=ffn, seq=64)
     blob = synth.pack(md)
     second = layers * (3 * hidden + ffn) * hidden * 2      # Q, K, V and the first feed-forward product once more
     x, vl = synth.token_batch(md, 2, 7, min_len=20)
