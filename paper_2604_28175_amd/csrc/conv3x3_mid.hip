@@ -40,17 +40,13 @@ __global__ void __launch_bounds__(512, 2) conv3x3_mid_kernel(const ConvParams p)
     const int l32 = lane & 31, lh = lane >> 5;
     const int wn0 = wave % WGN * (TNB * 32), wm0 = wave / WGN % WGM * TM, kh = wave / (WGM * WGN);
 
-    const int Wp = p.W + 1, HpWp = (p.H + 1) * Wp, NI = p.M / p.PQ;
-    const float rcp_w = 1.f / (float)Wp, rcp_i = 1.f / (float)HpWp;
+    const int Wp = p.W + 1, NI = divide(p.M, p.by_pq);
     int m0, n0;
     {
-        const int nb = gridDim.x, b = blockIdx.x;
-        const int per = nb >> 3, rem = nb & 7, xcd = b & 7, idx = b >> 3;
-        const int tile = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
-        const int tiles_n = p.Cout / BN, tiles_m = nb / tiles_n, gsz = tiles_m * p.tile_cw, g = tile / gsz, r = tile - g * gsz;
-        const int w = p.tile_cw < tiles_n - g * p.tile_cw ? p.tile_cw : tiles_n - g * p.tile_cw;
-        m0 = r / w * BM;
-        n0 = (g * p.tile_cw + r % w) * BN;
+        int tm, tn;
+        place_tile(p.order, xcd_range(p.order.tiles, blockIdx.x), tm, tn);
+        m0 = tm * BM;
+        n0 = tn * BN;
     }
     const intx4 xrsrc = make_rsrc(p.x, (unsigned)(p.x_elems * 2));
     const intx4 wrsrc = make_rsrc(p.w, (unsigned)((long long)p.Cout * p.ldw * 2));
@@ -60,9 +56,8 @@ __global__ void __launch_bounds__(512, 2) conv3x3_mid_kernel(const ConvParams p)
 #pragma unroll
     for (int j = 0; j < NPW; ++j) {
         const int s = (j * NW + wave) * 8 + (lane >> 3);
-        int img, rem, yp, xp;
-        divmod_f(m0 + s, HpWp, rcp_i, img, rem);
-        divmod_f(rem, Wp, rcp_w, yp, xp);
+        int img, yp, xp;
+        bordered_place(p, m0 + s, Wp, img, yp, xp);
         const int lc = (lane & 7) ^ ((s >> 1) & 7);
         aoff[j] = img < NI && yp >= 1 && xp >= 1 ? (unsigned)(((long long)img * p.sN + (long long)(yp - 1) * p.sH + (long long)(xp - 1) * p.sW + lc * 8) * 2) : OOB_OFFSET;
     }
@@ -209,9 +204,8 @@ __global__ void __launch_bounds__(512, 2) conv3x3_mid_kernel(const ConvParams p)
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
         const int id = tid + i * NT, row = id / CPR, c8 = id - row * CPR;
-        int img, rem, yy, xx;
-        divmod_f(m0 + row, HpWp, rcp_i, img, rem);
-        divmod_f(rem, Wp, rcp_w, yy, xx);
+        int img, yy, xx;
+        bordered_place(p, m0 + row, Wp, img, yy, xx);
         if (img < NI && yy < p.H && xx < p.W)
             *(half8*)((half_t*)p.y + ((long long)(img * p.H + yy) * p.W + xx) * p.ldy + n0 + c8 * 8) = *(const half8*)(Cs + row * LDC + c8 * 8);
     }
@@ -225,7 +219,7 @@ static int launch_mid_tile(const ConvParams& params, hipStream_t stream) {
     ConvParams p = params;
     const long long mv = (long long)(p.M / p.PQ) * (p.H + 1) * (p.W + 1), tiles_m = (mv + BM - 1) / BM;
     const int tiles_n = p.Cout / 128;
-    p.tile_cw = pick_tile_cw(tiles_m, tiles_n, BM + 2 * (p.W + 1) + 2, 9 * 128);
+    set_tile_order(p, tiles_m, tiles_n, BM + 2 * (p.W + 1) + 2, 9 * 128, 64, 1);
     constexpr unsigned lds = 2 * NPW * 8 * 1024 + NBS * 128 * 128 + 1024;
     auto kernel = conv3x3_mid_kernel<BM, WGM, WGN, KSPLIT, NPW, NBS>;
     static std::atomic<bool> configured{false};

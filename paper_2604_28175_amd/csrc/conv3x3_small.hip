@@ -44,17 +44,13 @@ __global__ void __launch_bounds__(256) conv3x3_small_kernel(const ConvParams p) 
     const int kh = wave % KSPLIT, pb = wave / KSPLIT * TMB;
     const int lr = lane & (MF - 1), lk = lane / MF;    // row of a block, chunk of a step
 
-    const int Wp = p.W + 1, HpWp = (p.H + 1) * Wp, NI = p.M / p.PQ;
-    const float rcp_w = 1.f / (float)Wp, rcp_i = 1.f / (float)HpWp;
+    const int Wp = p.W + 1, NI = divide(p.M, p.by_pq);
     int m0, n0;
     {
-        const int nb = gridDim.x, b = blockIdx.x;
-        const int per = nb >> 3, rem = nb & 7, xcd = b & 7, idx = b >> 3;
-        const int tile = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
-        const int tiles_n = p.Cout / BN, tiles_m = nb / tiles_n, gsz = tiles_m * p.tile_cw, g = tile / gsz, r = tile - g * gsz;
-        const int w = p.tile_cw < tiles_n - g * p.tile_cw ? p.tile_cw : tiles_n - g * p.tile_cw;
-        m0 = r / w * BM;
-        n0 = (g * p.tile_cw + r % w) * BN;
+        int tm, tn;
+        place_tile(p.order, xcd_range(p.order.tiles, blockIdx.x), tm, tn);
+        m0 = tm * BM;
+        n0 = tn * BN;
     }
     const intx4 xrsrc = make_rsrc(p.x, (unsigned)(p.x_elems * 2));
     const intx4 wrsrc = make_rsrc(p.w, (unsigned)((long long)p.Cout * p.ldw * 2));
@@ -64,9 +60,8 @@ __global__ void __launch_bounds__(256) conv3x3_small_kernel(const ConvParams p) 
 #pragma unroll
     for (int j = 0; j < NPW; ++j) {
         const int s = (j * NW + wave) * 8 + (lane >> 3);
-        int img, rem, yp, xp;
-        divmod_f(m0 + s, HpWp, rcp_i, img, rem);
-        divmod_f(rem, Wp, rcp_w, yp, xp);
+        int img, yp, xp;
+        bordered_place(p, m0 + s, Wp, img, yp, xp);
         const int lc = (lane & 7) ^ ((s >> 1) & 7);
         aoff[j] = img < NI && yp >= 1 && xp >= 1 ? (unsigned)(((long long)img * p.sN + (long long)(yp - 1) * p.sH + (long long)(xp - 1) * p.sW + lc * 8) * 2) : OOB_OFFSET;
     }
@@ -180,9 +175,8 @@ __global__ void __launch_bounds__(256) conv3x3_small_kernel(const ConvParams p) 
                 for (int h = 1; h < KSPLIT; ++h) t += h == b % KSPLIT ? acc[a][b][v] : part(b, a, h)[v * 64];
                 acc[a][b][v] = t;
             }
-        int img, rem, yy, xx;
-        divmod_f(m0 + (pb + b) * MF + lr, HpWp, rcp_i, img, rem);
-        divmod_f(rem, Wp, rcp_w, yy, xx);
+        int img, yy, xx;
+        bordered_place(p, m0 + (pb + b) * MF + lr, Wp, img, yy, xx);
         const bool ok = img < NI && yy < p.H && xx < p.W;
         half_t* row = (half_t*)p.y + ((long long)(img * p.H + yy) * p.W + xx) * p.ldy + n0;
 #pragma unroll
@@ -214,7 +208,7 @@ static int launch_small_tile(const ConvParams& params, hipStream_t stream) {
     ConvParams p = params;
     const long long mv = (long long)(p.M / p.PQ) * (p.H + 1) * (p.W + 1), tiles_m = (mv + BM - 1) / BM;
     const int tiles_n = p.Cout / BN;
-    p.tile_cw = pick_tile_cw(tiles_m, tiles_n, small_slots(BM, p.W), 9 * BN);
+    set_tile_order(p, tiles_m, tiles_n, small_slots(BM, p.W), 9 * BN, 64, 1);
     constexpr unsigned lds = NST * (NPW + (9 * BN + 31) / 32) * 4 * 1024;
     auto kernel = conv3x3_small_kernel<BM, BN, NST, NPW, KSPLIT>;
     static std::atomic<bool> configured{false};

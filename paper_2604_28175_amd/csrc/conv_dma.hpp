@@ -3,7 +3,7 @@
 #include <atomic>
 
 #include "activation.hpp"
-#include "kernels.hpp"
+#include "tiles.hpp"
 
 namespace strait {
 
@@ -42,7 +42,7 @@ enum { MODE_1X1 = 0, MODE_GATHER8 = 1, MODE_SCALAR = 2 };
 //     distinct 16-byte bank groups;
 //   - the loads are issued from inline assembly so that the waits are ours: "all but the newest
 //     STAGES-2 slices have landed" before the barrier, rather than a wait for everything;
-//   - tiles are dealt to the XCDs as rectangles (tile_cw below): a batch of 8 sequences' Q/K/V product fetched its
+//   - tiles are dealt to the XCDs as rectangles (TileOrder): a batch of 8 sequences' Q/K/V product fetched its
 //     3.5 MB of weights into all eight L2s before, and fetches a quarter of them into each now (13.6 -> 9.8 us).
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
@@ -66,12 +66,6 @@ __device__ __forceinline__ void dma16(intx4 rsrc, unsigned voff, unsigned soff, 
     const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base);
     unsigned so;
     asm volatile("s_mov_b32 m0, %1\n\ts_mov_b32 %0, %4\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds" : "=&s"(so) : "s"(m0v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-}
-__device__ __forceinline__ void divmod_f(int v, int d, float rcp, int& q, int& r) {   // exact for 0 <= v < 2^24
-    q = (int)((float)v * rcp);
-    r = v - q * d;
-    if (r < 0) { --q; r += d; }
-    if (r >= d) { ++q; r -= d; }
 }
 template <int N>
 __device__ __forceinline__ void wait_loads_then_barrier() {
@@ -176,31 +170,16 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     const int wm0 = (wave % WGM) * TM, wn0 = (wave / WGM) * TN;
     const int l32 = lane & 31, lh = lane >> 5;
 
-    const int tiles_n = (p.Cout + BN - 1) / BN;
-    int logical;
-    {
-        const int nb = gridDim.x, b = blockIdx.x;
-        const int per = nb >> 3, rem = nb & 7, xcd = b & 7, idx = b >> 3;
-        logical = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
-    }
+    const int logical = xcd_range(p.order.tiles * (KG > 1 ? 1 : p.ksplit), blockIdx.x);
     // split-K: the grid holds ksplit copies of the tile grid; copy z reduces slices [k_begin, k_end)
     int zsplit = 0, tile = logical;
     if (KG > 1) zsplit = group;
     else if (p.ksplit > 1) {
-        const int ntiles = gridDim.x / p.ksplit;
-        zsplit = logical / ntiles;
-        tile = logical - zsplit * ntiles;
+        zsplit = divide(logical, p.order.by_tiles);
+        tile = logical - zsplit * p.order.tiles;
     }
-    // Tiles are numbered down groups of tile_cw tile columns (row-major inside a group), so that the contiguous range an XCD
-    // gets covers a rectangle of about equal extent in pixels and channels: its L2 then fetches the fewest operand rows.
     int tm, tn;
-    {
-        const int tiles_m = (p.M + BM - 1) / BM;
-        const int gsz = tiles_m * p.tile_cw, g = tile / gsz, r = tile - g * gsz;
-        const int w = p.tile_cw < tiles_n - g * p.tile_cw ? p.tile_cw : tiles_n - g * p.tile_cw;
-        tm = r / w;
-        tn = g * p.tile_cw + (r - tm * w);
-    }
+    place_tile(p.order, tile, tm, tn);
     const int m0 = tm * BM;
     const int n0 = tn * BN;
 
@@ -223,18 +202,13 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             if (MODE == MODE_1X1 && p.stride_h == 1) {
                 xoff[j] = (unsigned)(((long long)m * p.sW + cl * 8) * 2);
             } else {
-                const int n = m / p.PQ, rem = m - n * p.PQ;
-                const int pp = rem / p.Q, qq = rem - pp * p.Q;
+                const int n = divide(m, p.by_pq), rem = m - n * p.PQ;
+                const int pp = divide(rem, p.by_q), qq = rem - pp * p.Q;
                 const int ih0 = pp * p.stride_h - p.pad_h, iw0 = qq * p.stride_w - p.pad_w;
                 xoff[j] = (unsigned)(((long long)n * p.sN + (long long)(pp * p.stride_h) * p.sH +
                                       (long long)(qq * p.stride_w) * p.sW + cl * 8) * 2);
                 if (MODE == MODE_GATHER8) {
-                    unsigned mask = 0;
-                    for (int rr = 0; rr < p.R; ++rr)
-                        for (int ss = 0; ss < p.S; ++ss)
-                            if ((unsigned)(ih0 + rr) < (unsigned)p.H && (unsigned)(iw0 + ss) < (unsigned)p.W)
-                                mask |= 1u << (rr * p.S + ss);
-                    tapmask[j] = mask;
+                    tapmask[j] = taps_inside(p, ih0, iw0);
                 }
             }
         }
@@ -248,8 +222,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
             const int m = m0 + (j * NW + wave) * RPI + rsub;
             xoff2[j] = OOB_OFFSET;
             if (m < p.M) {
-                const int n = m / p.PQ, rem = m - n * p.PQ;
-                const int pp = rem / p.Q, qq = rem - pp * p.Q;
+                const int n = divide(m, p.by_pq), rem = m - n * p.PQ;
+                const int pp = divide(rem, p.by_q), qq = rem - pp * p.Q;
                 xoff2[j] = (unsigned)(((long long)n * p.sN2 + (long long)(pp * p.stride2) * p.sH2 +
                                        (long long)(qq * p.stride2) * p.sW2 + cl * 8) * 2);
             }
@@ -264,8 +238,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
 
     // ---- workgroup-uniform position of the slice being issued ---------------------------------
     const int nk_all = (p.Kg + BK - 1) / BK;
-    const int kparts = KG > 1 ? KG : p.ksplit;
-    const int kchunk = (nk_all + kparts - 1) / kparts;
+    const int kchunk = p.kchunk;
     const int k_begin = zsplit * kchunk;
     const int k_end = k_begin + kchunk < nk_all ? k_begin + kchunk : nk_all;
     // (the groups of one workgroup share its barriers: all of them take kchunk steps, slices past a group's part arrive as zeros)
@@ -275,10 +248,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG, (KG > 1 ? WGM * WGN * KG 
     int tap = 0, ts = 0, cb = 0;                       // filter tap, its column, channel base
     unsigned tap_off = 0;                              // byte offset of the tap: (r*sH + s*sW) * 2
     if (MODE == MODE_GATHER8 && k_begin > 0) {
-        const int per_tap = p.C / BK;
-        tap = k_begin / per_tap;
-        cb = (k_begin - tap * per_tap) * BK;
-        const int r0 = tap / p.S;
+        tap = divide(k_begin * BK, p.by_c);
+        cb = k_begin * BK - tap * p.C;
+        const int r0 = divide(tap, p.by_s);
         ts = tap - r0 * p.S;
         tap_off = (unsigned)(r0 * p.sH + ts * p.sW) * 2u;
     }

@@ -342,21 +342,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 2) conv3x3_patch_k
     const int wm0 = (wave % WGM) * TM, wn0 = (wave / WGM) * TN;
     const int l32 = lane & 31, lh = lane >> 5;
 
-    const int tiles_n = p.Cout / BN;
-    int tile;
-    {
-        const int nb = gridDim.x, b = blockIdx.x;
-        const int per = nb >> 3, rem = nb & 7, xcd = b & 7, idx = b >> 3;
-        tile = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
-    }
-    const int tm = tile / tiles_n;
-    const int m0 = tm * BM, n0 = (tile - tm * tiles_n) * BN;
+    const int tile = xcd_range(p.order.tiles, blockIdx.x), tm = divide(tile, p.order.by_cw);
+    const int m0 = tm * BM, n0 = (tile - tm * p.order.cw) * BN;
 
     // rows wider than 64 pixels are cut into strips, each numbered as an image of its own with a border slot on
     // either side that holds the neighbouring strip's pixel (zero only at the true edges), so those are not shared
-    const int SW = p.strip_w, NS = __builtin_amdgcn_readfirstlane(p.W / SW);
-    const int Wp = SW + (NS == 1 ? 1 : 2), HpWp = (p.H + 1) * Wp, NI = (p.M / p.PQ) * NS;   // borders shared between neighbours
-    const float rcp_w = 1.f / (float)Wp, rcp_i = 1.f / (float)HpWp, rcp_s = 1.f / (float)NS;
+    const int SW = p.strip_w, NS = p.strips, Wp = SW + (NS == 1 ? 1 : 2), NI = divide(p.M, p.by_pq) * NS;   // borders shared between neighbours
     const intx4 xrsrc = make_rsrc(p.x, (unsigned)(p.x_elems * 2));
     const intx4 wrsrc = make_rsrc(p.w, (unsigned)((long long)p.Cout * p.ldw * 2));
 
@@ -365,10 +356,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 2) conv3x3_patch_k
 #pragma unroll
     for (int j = 0; j < NPW; ++j) {
         const int pp = (j * NW + wave) * 16 + (lane >> 2);
-        int img, rem, yp, xp, n, st;
-        divmod_f(m0 + pp, HpWp, rcp_i, img, rem);
-        divmod_f(rem, Wp, rcp_w, yp, xp);
-        divmod_f(img, NS, rcp_s, n, st);
+        int img, yp, xp;
+        bordered_place(p, m0 + pp, Wp, img, yp, xp);
+        const int n = divide(img, p.by_strips), st = img - n * NS;
         const int xr = st * SW + xp - 1;
         const int lc = (lane & 3) ^ ((pp >> 2) & 3);
         const bool inside = img < NI && yp >= 1 && yp <= p.H && xr >= 0 && xr < p.W;
@@ -480,10 +470,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 2) conv3x3_patch_k
     for (int i = 0; i < NCH; ++i) {
         const int id = tid + i * NT;
         const int row = id / CPR, c8 = id - row * CPR;
-        int img, rem, yy, xx, n, st;
-        divmod_f(m0 + row, HpWp, rcp_i, img, rem);
-        divmod_f(rem, Wp, rcp_w, yy, xx);
-        divmod_f(img, NS, rcp_s, n, st);
+        int img, yy, xx;
+        bordered_place(p, m0 + row, Wp, img, yy, xx);
+        const int n = divide(img, p.by_strips), st = img - n * NS;
         if (img < NI && yy < p.H && xx < SW) {
             const half8 v = *(const half8*)(Cs + row * LDC + c8 * 8);
             *(half8*)((half_t*)p.y + ((long long)(n * p.H + yy) * p.W + st * SW + xx) * p.ldy + n0 + c8 * 8) = v;
@@ -523,9 +512,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 2) conv3x3_patch_w
     const int wm0 = (wave % WGM) * TM, wn0 = (wave / WGM) * TN;
     const int l32 = lane & 31, lh = lane >> 5;
 
-    const int SW = p.strip_w, NS = __builtin_amdgcn_readfirstlane(p.W / SW);
-    const int Wp = SW + (NS == 1 ? 1 : 2), HpWp = (p.H + 1) * Wp, NI = (p.M / p.PQ) * NS;
-    const float rcp_w = 1.f / (float)Wp, rcp_i = 1.f / (float)HpWp, rcp_s = 1.f / (float)NS;
+    const int SW = p.strip_w, NS = p.strips, Wp = SW + (NS == 1 ? 1 : 2), NI = divide(p.M, p.by_pq) * NS;
     const intx4 xrsrc = make_rsrc(p.x, (unsigned)(p.x_elems * 2));
     const intx4 wrsrc = make_rsrc(p.w, (unsigned)((long long)p.Cout * p.ldw * 2));
 
@@ -539,10 +526,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 2) conv3x3_patch_w
 #pragma unroll
         for (int j = 0; j < NPW; ++j) {
             const int pp = (j * NW + wave) * 16 + (lane >> 2);
-            int img, rem, yp, xp, n, st;
-            divmod_f(m0 + pp, HpWp, rcp_i, img, rem);
-            divmod_f(rem, Wp, rcp_w, yp, xp);
-            divmod_f(img, NS, rcp_s, n, st);
+            int img, yp, xp;
+            bordered_place(p, m0 + pp, Wp, img, yp, xp);
+            const int n = divide(img, p.by_strips), st = img - n * NS;
             const int xr = st * SW + xp - 1;
             const int lc = (lane & 3) ^ ((pp >> 2) & 3);
             const bool inside = live && img < NI && yp >= 1 && yp <= p.H && xr >= 0 && xr < p.W;
@@ -646,10 +632,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN, WGM * WGN / 2) conv3x3_patch_w
         long long ybase[TMB];                          // this lane's pixel in y, in elements; -1: a border slot, nothing to store
 #pragma unroll
         for (int b = 0; b < TMB; ++b) {
-            int img, rem, yy, xx, n, st;
-            divmod_f(m0 + wm0 + b * 32 + l32, HpWp, rcp_i, img, rem);
-            divmod_f(rem, Wp, rcp_w, yy, xx);
-            divmod_f(img, NS, rcp_s, n, st);
+            int img, yy, xx;
+            bordered_place(p, m0 + wm0 + b * 32 + l32, Wp, img, yy, xx);
+            const int n = divide(img, p.by_strips), st = img - n * NS;
             ybase[b] = (img < NI && yy < p.H && xx < SW) ? ((long long)(n * p.H + yy) * p.W + st * SW + xx) * p.ldy : -1;
         }
 #pragma unroll
@@ -711,7 +696,9 @@ static int launch_patch_tile(const ConvParams& p, long long mv, hipStream_t stre
         if (e != hipSuccess) { set_error("conv: cannot reserve %u bytes of LDS: %s", lds, hipGetErrorString(e)); return -2; }
     }
     configured.store(true, std::memory_order_release);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * NW), lds, stream, p);
+    ConvParams q = p;
+    q.order.tiles = (int)tiles; q.order.cw = p.Cout / BN; q.order.by_cw = divisor(q.order.cw);        // (pixel tile by pixel tile)
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * NW), lds, stream, q);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("conv launch: %s", hipGetErrorString(e)); return -2; }
     return 0;
@@ -781,7 +768,7 @@ static int patch_geometry(const ConvParams& p, int* strip_w, int* slots, long lo
     *strip_w = sw;
     *slots = wp;
     *mv = (long long)(p.M / p.PQ) * (p.W / sw) * (p.H + 1) * wp;
-    return *mv >= (1LL << 24) - 4096 ? -1 : 0;         // the kernel's index arithmetic is exact below 2^24
+    return *mv >= (1LL << 24) - 4096 ? -1 : 0;         // slots in whole rows of tiles: far below 2^31
 }
 static int patch_transfers(int bm, int nw, int slots) { return ((bm + 2 * slots + 2 + 15) / 16 + nw - 1) / nw; }
 // Whether the patch kernel's tile `id` takes the layer; *mv as above.
@@ -797,6 +784,8 @@ static int launch_conv3x3_patch(const ConvParams& params, TileId id, hipStream_t
     int wp;
     long long mv;
     if (!patch_takes(p, id, &mv) || patch_geometry(p, &p.strip_w, &wp, &mv)) { set_error("conv: not a layer of the patch kernel"); return -5; }
+    p.strips = p.W / p.strip_w;
+    p.by_pq = divisor(p.PQ); p.by_strips = divisor(p.strips); p.by_row = divisor(wp); p.by_image = divisor((p.H + 1LL) * wp);
     if (id == T_PATCH256x128) {
         if (patch_transfers(256, 8, wp) <= 3) return launch_patch_tile<256, 128, 4, 2, 3, 3>(p, mv, stream);
         return launch_patch_tile<256, 128, 4, 2, 4, 3>(p, mv, stream);
@@ -811,9 +800,9 @@ static int launch_conv3x3_patch(const ConvParams& params, TileId id, hipStream_t
     return walk ? launch_patch_walk<256, 64, 4, 1, 8, 3>(p, mv, stream) : launch_patch_tile<256, 64, 4, 1, 8, 3>(p, mv, stream);
 }
 
-// Tile columns of a group (see the kernel's tile order): the contiguous range of about tiles / 8 tiles that an XCD gets should
-// touch as few operand rows as possible, tile_cw * BN weight rows and (range / tile_cw) * BM input rows.
-int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn) {
+// Tile columns of a group (TileOrder): the contiguous range of about tiles / 8 tiles that an XCD gets should
+// touch as few operand rows as possible, cw * BN weight rows and (range / cw) * BM input rows.
+static int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn) {
     const double per = std::max(1.0, (double)(tiles_m * tiles_n) / 8.0);
     int best = 1;
     double best_rows = 1e30;
@@ -822,6 +811,19 @@ int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn) {
         if (rows < best_rows) { best_rows = rows; best = c; }
     }
     return best;
+}
+
+void set_tile_order(ConvParams& p, long long tiles_m, int tiles_n, int bm, int bn, int bk, int parts) {
+    TileOrder& o = p.order;
+    o.cw = pick_tile_cw(tiles_m, tiles_n, bm, bn);
+    o.tiles = (int)(tiles_m * tiles_n);
+    o.group = (int)(tiles_m * o.cw);
+    o.full = tiles_n / o.cw;
+    o.last = tiles_n - o.full * o.cw;
+    o.by_tiles = divisor(o.tiles); o.by_group = divisor(o.group); o.by_cw = divisor(o.cw); o.by_last = divisor(o.last);
+    p.by_pq = divisor(p.PQ); p.by_q = divisor(p.Q); p.by_c = divisor(p.C); p.by_s = divisor(p.S);
+    p.by_row = divisor(p.W + 1LL); p.by_image = divisor((p.H + 1LL) * (p.W + 1LL));
+    p.kchunk = ((p.Kg + bk - 1) / bk + parts - 1) / parts;
 }
 
 // One launch of conv_igemm_dma_kernel on a BM x BN tile.  KG > 1: the reduction split over KG groups of wavefronts inside the
@@ -837,7 +839,7 @@ static int launch_dma_tile(const ConvParams& p, int mode, hipStream_t stream) {
     static_assert(lds <= 160 * 1024, "LDS limit");
     dim3 grid((unsigned)tiles), block(64 * WGM * WGN * KG);
     ConvParams q = p;
-    q.tile_cw = pick_tile_cw(tiles_m, tiles_n, BM, BN);
+    set_tile_order(q, tiles_m, tiles_n, BM, BN, BK, KG > 1 ? KG : p.ksplit);
 #define STRAIT_GO(...) launch_with_lds<conv_igemm_dma_kernel<__VA_ARGS__>>(q, grid, block, lds, lds, stream)
     auto after = [&]() -> int {                        // the second launch of a split reduction
         if (p.ksplit > 1) {

@@ -19,7 +19,7 @@
 // 1x1 1024 -> 256 at 14 x 14 6.0 -> 4.4; 1x1 2048 -> 512 at 7 x 7 9.0 -> 6.1; 2048 -> 1000 classifier, 8 images 8.3 -> 5.5;
 // 25088 -> 4096 for 6 rows 44.6 -> 38.3 (5.4 TB/s of weights); 960 -> 160 at 7 x 7, 5 images 6.4 -> 4.4.
 #include "activation.hpp"
-#include "kernels.hpp"
+#include "tiles.hpp"
 
 namespace strait {
 
@@ -40,18 +40,12 @@ __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
 
-    // tile order: an XCD (hardware id mod 8) gets a contiguous range, numbered down groups of tile_cw tile columns
-    const int tiles_n = (p.Cout + TN - 1) / TN;
     int m0, n0;
     {
-        const int nb = gridDim.x, b = blockIdx.x;
-        const int per = nb >> 3, rem = nb & 7, xcd = b & 7, idx = b >> 3;
-        const int tile = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
-        const int gsz = ((p.M + TM - 1) / TM) * p.tile_cw, g = tile / gsz, r = tile - g * gsz;
-        const int w = p.tile_cw < tiles_n - g * p.tile_cw ? p.tile_cw : tiles_n - g * p.tile_cw;
-        const int tm = r / w;
+        int tm, tn;
+        place_tile(p.order, xcd_range(p.order.tiles, blockIdx.x), tm, tn);
         m0 = tm * TM;
-        n0 = (g * p.tile_cw + (r - tm * w)) * TN;
+        n0 = tn * TN;
     }
 
     // the buffer starts `lead` elements before x, so that the offset of a window's top-left tap is never negative
@@ -66,16 +60,13 @@ __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
     if (m < p.M) {
         if (!GATHER && p.stride_h == 1) xoff = (unsigned)(((long long)m * p.sW + lg * 8) * 2);
         if (GATHER || p.stride_h != 1 || DUAL) {
-            const int n = m / p.PQ, rem = m - n * p.PQ, pp = rem / p.Q, qq = rem - pp * p.Q;
+            const int n = divide(m, p.by_pq), rem = m - n * p.PQ, pp = divide(rem, p.by_q), qq = rem - pp * p.Q;
             if (GATHER || p.stride_h != 1)
                 xoff = (unsigned)(((long long)n * p.sN + (long long)(pp * p.stride_h) * p.sH + (long long)(qq * p.stride_w) * p.sW + lg * 8) * 2);
             if (DUAL) xoff2 = (unsigned)(((long long)n * p.sN2 + (long long)(pp * p.stride2) * p.sH2 + (long long)(qq * p.stride2) * p.sW2 + lg * 8) * 2);
             if (GATHER) {
                 const int ih0 = pp * p.stride_h - p.pad_h, iw0 = qq * p.stride_w - p.pad_w;
-                taps = 0;
-                for (int rr = 0; rr < p.R; ++rr)
-                    for (int ss = 0; ss < p.S; ++ss)
-                        if ((unsigned)(ih0 + rr) < (unsigned)p.H && (unsigned)(iw0 + ss) < (unsigned)p.W) taps |= 1u << (rr * p.S + ss);
+                taps = taps_inside(p, ih0, iw0);
             }
         }
     }
@@ -93,9 +84,9 @@ __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
     unsigned tap_off = 0;
     const unsigned row_step = (unsigned)(p.sH - p.S * p.sW) * 2u;   // from the end of a filter row to the next
     if (GATHER) {
-        tap = cb / p.C;
+        tap = divide(cb, p.by_c);
         cb -= tap * p.C;
-        const int r0 = tap / p.S;
+        const int r0 = divide(tap, p.by_s);
         ts = tap - r0 * p.S;
         tap_off = (unsigned)(r0 * p.sH + ts * p.sW) * 2u;
     }
@@ -205,7 +196,7 @@ int launch_conv_skinny(const ConvParams& params, int tn, bool gather, hipStream_
     const long long tiles_m = (p.M + 15) / 16;
     const int tiles_n = (p.Cout + tn - 1) / tn;
     if (tiles_m * tiles_n > 0x7fffffffLL) { set_error("conv: bad grid (%lld tiles)", tiles_m * tiles_n); return -5; }
-    p.tile_cw = pick_tile_cw(tiles_m, tiles_n, 16, tn);
+    set_tile_order(p, tiles_m, tiles_n, 16, tn, 64, 1);
     const dim3 grid((unsigned)(tiles_m * tiles_n)), block(256);
 #define STRAIT_SK(TN)                                                                                                    \
     do {                                                                                                                \

@@ -31,7 +31,7 @@ static int launch_ln_tile(const ConvParams& p, hipStream_t stream) {
     static_assert(ln_tile_lds<BM, BN, STAGES, KG>(LN_IN, most) <= 160 * 1024 && ln_tile_lds<BM, BN, STAGES, KG>(LN_RES, most) <= 160 * 1024, "LDS limit");
     const unsigned in = ln_tile_lds<BM, BN, STAGES, KG>(LN_IN, p.Kg / 64), res = ln_tile_lds<BM, BN, STAGES, KG>(LN_RES, p.Cout / 64), out = ln_tile_lds<BM, BN, STAGES, KG>(LN_OUT, 0);
     ConvParams q = p;
-    q.tile_cw = pick_tile_cw(tiles_m, tiles_n, BM, BN);
+    set_tile_order(q, tiles_m, tiles_n, BM, BN, BK, KG);
     // (160 KB are asked for once, for all widths of a LayerNorm)
 #define STRAIT_GO(lds, ...) launch_with_lds<conv_igemm_dma_kernel<__VA_ARGS__>>(q, dim3((unsigned)tiles), dim3(64 * WGM * WGN * KG), lds, 160 * 1024, stream)
     int rc;

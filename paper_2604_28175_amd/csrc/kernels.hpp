@@ -12,6 +12,25 @@ typedef _Float16 half_t;
 
 enum Act { ACT_NONE = 0, ACT_RELU = 1, ACT_RELU6 = 2, ACT_GELU = 3 };
 
+// Division by a number that is the same for a whole launch, prepared on the host: n / d = floor(2 n mul / 2^32) >> shift, exact for 0 <= n < 2^31 and
+// 1 <= d < 2^31 (shift = ceil(log2 d), mul = floor(2^(31 + shift) / d) + 1: the error, less than 2 n d / 2^(32 + shift) <= n / 2^31 of one, reaches no next
+// quotient).  A division by an unknown number is 30 to 40 instructions that depend on each other, at one wavefront per SIMD 100 ns; a launch of a
+// small batch, 4 to 6 us long, began with four to eleven of them.
+struct Divisor { unsigned mul, shift; };
+inline Divisor divisor(long long d) {
+    Divisor r{1u, 0u};
+    if (d < 1) return r;
+    while ((1LL << r.shift) < d) ++r.shift;
+    r.mul = (unsigned)((1ULL << (31 + r.shift)) / (unsigned long long)d + 1);
+    return r;
+}
+#ifdef __HIPCC__
+__host__ __device__ inline int divide(int n, Divisor d) { return (int)((unsigned)(((unsigned long long)((unsigned)n << 1) * d.mul) >> 32) >> d.shift); }
+#endif
+// Tiles are numbered down groups of cw tile columns (row-major inside a group), so that the contiguous range an XCD gets covers a rectangle of about equal
+// extent in pixels and channels: its L2 then fetches the fewest operand rows.  Of `full` whole groups and one of the `last` columns.
+struct TileOrder { int tiles, cw, full, last, group; Divisor by_tiles, by_group, by_cw, by_last; };   // group: tiles of a whole one
+
 // One implicit-GEMM convolution (or plain GEMM) launch.
 //   y[m, k] = act(bias[k] + sum_{r,s,c} x[addr(m) + r*sH + s*sW + c] * w[k*ldw + (r*S + s)*C + c] (+ res[m*ldy + k]))
 // with m = (n, p, q), addr(m) = n*sN + (p*stride - pad)*sH + (q*stride_w - pad_w)*sW, taps outside
@@ -41,8 +60,11 @@ struct ConvParams {
     size_t ws_bytes;
     int ksplit;              // filled in by launch_conv
     int res_f32;             // add the residual in fp32, before the rounding; filled in by launch_conv
-    int tile_cw;             // tile columns of a group in the kernels' tile order; filled in by the launcher
-    int strip_w;             // 3x3 patch kernel: width of the strips a row is cut into; filled in by the launcher
+    TileOrder order;         // filled in by the launcher (set_tile_order), like the divisors and kchunk
+    Divisor by_pq, by_q, by_c, by_s, by_row, by_image;   // PQ, Q, C, S; W + 1 and (H + 1)(W + 1), the pixels of a bordered row and image
+    int kchunk;              // slices of a part of the reduction
+    int strip_w, strips;     // 3x3 patch kernel: width and number of the strips a row is cut into; filled in by the launcher
+    Divisor by_strips;
     // Optional second source of a 1x1 convolution with stride 1 (a block-closing convolution that absorbs the block's 1x1
     // projection shortcut): reduction elements [C, C + K2) are x2[n*sN2 + p*stride2*sH2 + q*stride2*sW2 + (k - C)], and
     // w is [Cout][C + K2].  Kg = C + K2; no res.
@@ -77,7 +99,8 @@ int launch_conv3x3_small(const ConvParams& p, int bm, int bn, hipStream_t stream
 // Larger ones, bm (96 or 192) bordered pixels x 128 channels per workgroup (conv3x3_mid.hip); likewise.
 bool conv3x3_mid_takes(const ConvParams& p, int bm);
 int launch_conv3x3_mid(const ConvParams& p, int bm, hipStream_t stream);
-int pick_tile_cw(long long tiles_m, int tiles_n, int bm, int bn);
+// The order of tiles_m x tiles_n tiles, whose operands are bm input rows and bn weight rows, and the divisors; bk: elements of a slice, parts: of the reduction
+void set_tile_order(ConvParams& p, long long tiles_m, int tiles_n, int bm, int bn, int bk, int parts);
 
 // A dense product with a LayerNorm folded in (gemm_ln.hip): of its input (ln_stats, ln_csum; no residual), or its output's statistics for one that
 // follows (stats_out; with a residual, normalised where ln_stats, ln_g and ln_b are given).
