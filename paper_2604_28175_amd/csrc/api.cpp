@@ -329,6 +329,7 @@ static int hp_flag(const Context* c, int prio) { return prio == STRAIT_PRIO_HIGH
 // Only kernel launches are captured (no copies, events or memsets).  Only up to layer out_first, from
 // which on the launch behind it computes them (enqueue_output).
 static int run_batch(Model& m, Instance& in, int batch, hipStream_t s, int hp, int out_first) {
+    if (out_first == 0) return 0;
     const bool cut = out_first < (int)m.ops.size();
     const int last = cut ? out_first - 1 : -1;
     if (!m.ctx->use_graphs) return run_plan(m, in, batch, s, hp, last, false);

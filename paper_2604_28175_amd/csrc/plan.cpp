@@ -12,6 +12,7 @@
 #include <cstring>
 
 #include "runtime.hpp"
+#include "small_net.hpp"
 
 namespace strait {
 
@@ -1272,6 +1273,8 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
 int classify_out_first(const Model& m, int batch) {
     const int n = (int)m.ops.size();
     if (n < 2 || m.ctx->pair_min_pixels <= 0 || m.ops[n - 1].kind != OP_SOFTMAX || !classify_out_takes(batch, m.ops[n - 1].K)) return n;
+    if (m.arch == STRAIT_ARCH_TINY_CNN && n == 7 && m.ops[0].kind == OP_PACK && m.ops[0].Cpad == 8 && m.ops[1].ldw == 96 &&
+        small_net_takes(m.ops[0].H, m.ops[0].W, m.ops[0].C, batch, m.ops[n - 1].K)) return 0;
     if (n >= 4) {
         const Op &fc = m.ops[n - 2], &gap = m.ops[n - 3];
         if (fc.kind == OP_CONV && gap.kind == OP_POOL && gap.sub == POOL_GLOBAL_AVG && classify_out_pools(gap.H * gap.W, gap.C, fc.K)) return n - 3;
@@ -1283,7 +1286,9 @@ int enqueue_classify_out(Model& m, Instance& in, int batch, int first, hipStream
     const int n = (int)m.ops.size();
     const Op& sm = m.ops[n - 1];
     ClassifyOut p{};
-    if (first == n - 3) {
+    if (first == 0) {
+        p.w = m.ops[5].w; p.ldw = m.ops[5].ldw; p.bias = m.ops[5].bias;
+    } else if (first == n - 3) {
         const Op &fc = m.ops[n - 2], &gap = m.ops[n - 3];
         p.x = (const half_t*)slot_ptr(m, in, gap.in, 0, batch);
         p.HW = gap.H * gap.W; p.C = gap.C;
@@ -1295,6 +1300,15 @@ int enqueue_classify_out(Model& m, Instance& in, int batch, int first, hipStream
     p.rows = batch; p.n = sm.K;
     p.host = (char*)in.pinned_out_dev; p.ctl = in.ctl_dev; p.counter = in.counters + 1;
     p.seq = seq; p.hp = hp;
+    if (first == 0) {
+        SmallNet s{};
+        s.x = (const half_t*)in.dev_in;
+        s.w0 = m.ops[1].w; s.w1 = m.ops[2].w; s.w2 = m.ops[3].w;
+        s.b0 = m.ops[1].bias; s.b1 = m.ops[2].bias; s.b2 = m.ops[3].bias;
+        s.H = m.ops[0].H; s.W = m.ops[0].W; s.C = m.ops[0].C;
+        s.out = p;
+        return launch_small_net(s, stream);
+    }
     return launch_classify_out(p, stream);
 }
 

@@ -531,6 +531,34 @@ def test_more_rows_than_the_gpu_takes_at_a_time_end_in_launches_of_their_own(ctx
         m.free()
 
 
+@pytest.mark.parametrize("h,w,classes,batch", [(1, 1, 4, 1), (2, 3, 10, 5), (7, 40, 255, 3), (31, 33, 12, 33), (32, 32, 256, 2), (45, 46, 10, 2), (48, 47, 10, 2)])
+def test_a_small_network_in_one_launch(ctx, h, w, classes, batch):
+    """Images of one pixel, odd and oblong ones, about the largest and one too large, the largest head: the oracle's result, with infinities and a NaN among the pixels too, where it has to be
+    infinite, zero or no number in the same places as layer by layer."""
+    S = ctx.S
+    md = synth.tiny_cnn(7, hw=32, classes=classes)
+    md = synth.ModelData(md.arch, (h, w, 3, classes), md.tensors)
+    x = np.random.default_rng(3).random((batch, h, w, 3), dtype=np.float32).astype(np.float16)
+    ref = omodels.tiny_cnn_forward(md.tensors, x)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    try:
+        got, _ = m.infer(x)
+        check_logits(got["logits"], ref.logits, got["top1"], f"tiny CNN {h} x {w}, {classes} classes, b{batch}")
+        assert np.abs(got["probs"] - ref.probs).max() <= 2e-2
+        x[0, h // 2, w // 2] = (np.inf, 0, 0)
+        x[batch - 1, h - 1, 0] = (0, -np.inf, np.nan)
+        odd = []
+        for fusion in (40000, 0):
+            ctx.set_pair_fusion(fusion)
+            odd.append(m.infer(x)[0])
+        assert np.array_equal(np.isnan(odd[0]["logits"]), np.isnan(odd[1]["logits"])) and np.array_equal(np.isinf(odd[0]["logits"]), np.isinf(odd[1]["logits"]))
+        fine = np.isfinite(odd[1]["logits"])
+        assert np.allclose(odd[0]["logits"][fine], odd[1]["logits"][fine], rtol=0, atol=2e-2 * max(1.0, np.abs(odd[1]["logits"][fine]).max(initial=0)))
+    finally:
+        ctx.set_pair_fusion(40000)
+        m.free()
+
+
 @pytest.mark.parametrize("hw,batch", [(8, 1521), (10, 1058)])
 def test_many_small_images_are_packed_for_the_first_layer(ctx, hw, batch):
     """Images that leave most of the direct first layer's tiles empty, one more of them than it takes: the layer-by-layer plan's bytes."""
