@@ -23,13 +23,15 @@
 #include <algorithm>
 #include <atomic>
 
-#include "kernels.hpp"
+#include "tiles.hpp"
 
 namespace strait {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int EDW_HP = 40;                                // halfs between pixels of the expanded tile: 32 channels + 8
 
@@ -38,10 +40,18 @@ struct ExpandDwParams {
     const half_t* w1; int ldw1; const float* b1; int Chid, act1;
     const half_t* wd; const float* bd; int act2;
     half_t* y; int P, Q, tiles_p, tiles_q, groups_per_block, hp;
+    Divisor by_tiles_p, by_tiles_q;
 };
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// px / IC for 0 <= px < LIMIT, by a 24-bit product (exact: px (IC - 65536 mod IC) stays below 65536)
+template <int IC, int LIMIT>
+__device__ __forceinline__ int edw_tile_row(int px) {
+    constexpr unsigned INV = 65536u / IC + 1;
+    static_assert((unsigned)LIMIT * (INV * IC - 65536u) < 65536u && (unsigned)LIMIT * INV < (1u << 24), "exact quotients");
+    return (int)(((unsigned)px & 0xffffffu) * INV >> 16);
+}
 __device__ __forceinline__ float edw_act(float v, int act) {
     if (act == ACT_RELU) return fmaxf(v, 0.f);
     if (act == ACT_RELU6) return fminf(fmaxf(v, 0.f), 6.f);
@@ -67,48 +77,44 @@ __global__ void __launch_bounds__(256) expand_dw_kernel(const ExpandDwParams p) 
     // a grid smaller than the number of tiles is a multiple of eight.
     const int ntiles = p.N * p.tiles_p * p.tiles_q;
     auto tile_of = [&](int v, int& n, int& P0, int& Q0) __attribute__((always_inline)) {
-        const unsigned per = (unsigned)ntiles >> 3, rem = (unsigned)ntiles & 7, xcd = (unsigned)v & 7, idx = (unsigned)v >> 3;
-        const int tile = (int)((xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx);
-        const int tq = tile % p.tiles_q, rest = tile / p.tiles_q;
-        Q0 = tq * TQ; P0 = (rest % p.tiles_p) * TP; n = rest / p.tiles_p;
+        const int tile = xcd_range(ntiles, v), rest = divide(tile, p.by_tiles_q);
+        n = divide(rest, p.by_tiles_p);
+        Q0 = (tile - rest * p.tiles_q) * TQ; P0 = (rest - n * p.tiles_p) * TP;
     };
     const int groups = (p.Chid + 31) >> 5;
     const int g_begin = (int)blockIdx.y * p.groups_per_block;
     const int g_end = g_begin + p.groups_per_block < groups ? g_begin + p.groups_per_block : groups;
 
+    // Weights and biases come through buffers: channels past the end have an offset beyond them and read as zero.
+    constexpr unsigned OOB = 0x80000000u;
+    const auto w1r = __builtin_amdgcn_make_buffer_rsrc((void*)p.w1, 0, p.Chid * p.ldw1 * 2, 0x00020000);
+    const auto wdr = __builtin_amdgcn_make_buffer_rsrc((void*)p.wd, 0, 9 * p.Chid * 2, 0x00020000);
+    const auto b1r = __builtin_amdgcn_make_buffer_rsrc((void*)p.b1, 0, p.b1 ? p.Chid * 4 : 0, 0x00020000);
+    const auto bdr = __builtin_amdgcn_make_buffer_rsrc((void*)p.bd, 0, p.bd ? p.Chid * 4 : 0, 0x00020000);
     // fragments of the expansion's weights and its bias for group g: output channel 32 g + l32, input channels 16 ks + 8 lh ..
     auto load_w1 = [&](int g, half8 (&wf)[KS], float (&bv)[4][4]) __attribute__((always_inline)) {
         const int row = 32 * g + l32;
+        const unsigned at = row < p.Chid ? (unsigned)(row * p.ldw1 + 8 * lh) * 2u : OOB;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            half8 v;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = (half_t)0.f;
-            if (g < groups && row < p.Chid && 16 * ks + 8 * lh < p.Cin) v = *(const half8*)(p.w1 + (long long)row * p.ldw1 + 16 * ks + 8 * lh);
-            wf[ks] = v;
-        }
+        for (int ks = 0; ks < KS; ++ks)
+            wf[ks] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(w1r, 16 * ks + 8 * lh < p.Cin ? at + 32u * ks : OOB, 0, 0));
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
-            const int c = 32 * g + 8 * g4 + 4 * lh;
-            float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (g < groups && p.b1 && c < p.Chid) b = *(const float4*)(p.b1 + c);
-            bv[g4][0] = b.x; bv[g4][1] = b.y; bv[g4][2] = b.z; bv[g4][3] = b.w;
+            const floatx4 b = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(b1r, (unsigned)(32 * g + 8 * g4 + 4 * lh) * 4u, 0, 0));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bv[g4][e] = b[e];
         }
     };
     // the depthwise layer's weights and bias of group g for this thread's 8 channels (c8)
     const int c8 = tid & 3, col = (tid >> 2) % TQ, strip = (tid >> 2) / TQ;
     auto load_wd = [&](int g, half8 (&wv)[9], float (&bdv)[8]) __attribute__((always_inline)) {
-        const int cd = 32 * g + 8 * c8;
-        const bool ok = g < groups && cd < p.Chid;
+        const unsigned cd = (unsigned)(32 * g + 8 * c8), at = (int)cd < p.Chid ? cd * 2u : OOB;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
+        for (int k = 0; k < 9; ++k) wv[k] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(wdr, at, (unsigned)(k * p.Chid) * 2u, 0));
+        const floatx4 b0 = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(bdr, cd * 4u, 0, 0));
+        const floatx4 b1 = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(bdr, cd * 4u + 16u, 0, 0));
 #pragma unroll
-            for (int j = 0; j < 8; ++j) wv[k][j] = (half_t)0.f;
-            if (ok) wv[k] = *(const half8*)(p.wd + (long long)k * p.Chid + cd);
-        }
-        float4 b0 = make_float4(0.f, 0.f, 0.f, 0.f), b1 = b0;
-        if (ok && p.bd) { b0 = *(const float4*)(p.bd + cd); b1 = *(const float4*)(p.bd + cd + 4); }
-        bdv[0] = b0.x; bdv[1] = b0.y; bdv[2] = b0.z; bdv[3] = b0.w; bdv[4] = b1.x; bdv[5] = b1.y; bdv[6] = b1.z; bdv[7] = b1.w;
+        for (int e = 0; e < 4; ++e) { bdv[e] = b0[e]; bdv[4 + e] = b1[e]; }
     };
     // both layers' weights are requested a whole group ahead: a group is short, and a wait for them would be most of it
     half8 wf[KS], wf_next[KS], wv[9], wv_next[9];
@@ -116,41 +122,37 @@ __global__ void __launch_bounds__(256) expand_dw_kernel(const ExpandDwParams p) 
     load_w1(g_begin, wf, bv);
     load_wd(g_begin, wv, bdv);
 
-    // ---- A: the input tile: its 16-byte pieces are requested into registers (every request from an address inside the
-    // image, several before the first is waited for) and deposited in LDS, zeros where the piece lies outside the image.
-    // Where a thread holds few enough of them, the next tile's are requested while this tile is computed.
+    // ---- A: the input tile: its 16-byte pieces are requested into registers (several before the first is waited for; a piece outside the image has an offset
+    // beyond the buffer and reads as zero) and deposited in LDS.  Where a thread holds few enough of them, the next tile's are requested while this
+    // tile is computed.  Threads take the same piece of every PSTEP-th pixel, so that nothing but the pixel's row and column is worked out per piece.
     constexpr int CH = KS * 2;                                                 // 16-byte pieces per pixel, zero-padded
-    constexpr int TOTAL = ROWS * CH, NIT = (TOTAL + 255) / 256;
+    constexpr int PSTEP = 256 / CH, NIT = (ROWS + PSTEP - 1) / PSTEP;
     constexpr bool AHEAD = NIT <= 12;
     constexpr int BATCH = AHEAD ? NIT : 8;
-    half8 xv[BATCH];
-    bool xok[BATCH];
+    const int px0 = tid / CH, ch = tid - px0 * CH;                             // (256 is no multiple of 12 or 20 pieces: the last threads take none)
+    const bool takes = px0 < PSTEP, whole = ch * 8 < p.Cin;
+    const unsigned row_bytes = (unsigned)(p.W * p.Cin) * 2u, pixel_bytes = (unsigned)p.Cin * 2u;
+    uintx4 xv[BATCH];
     auto request_tile = [&](int v, int it0) __attribute__((always_inline)) {
         int n, P0, Q0;
         tile_of(v, n, P0, Q0);
-        const int ih0 = P0 * STRIDE - 1, iw0 = Q0 * STRIDE - 1;
-        const half_t* img = p.x + (long long)n * p.H * p.W * p.Cin;
+        const int ih0 = P0 * STRIDE - 1, iw0 = Q0 * STRIDE - 1, top = ih0 < 0 ? 0 : ih0;
+        // the rows under the tile, from the first that there is
+        const int rows = p.H - top < IR ? p.H - top : IR;
+        const auto xr = __builtin_amdgcn_make_buffer_rsrc((void*)(p.x + ((long long)n * p.H + top) * p.W * p.Cin), 0, (int)((unsigned)rows * row_bytes), 0x00020000);
 #pragma unroll
         for (int b = 0; b < BATCH; ++b) {
-            const int id = tid + (it0 + b) * 256;
-            const int px = id / CH, ch = id - px * CH;
-            const int ir = px / IC, ic = px - ir * IC;
+            const int px = px0 + (it0 + b) * PSTEP, ir = edw_tile_row<IC, ROWS + BATCH * PSTEP>(px), ic = px - ir * IC;
             const int ih = ih0 + ir, iw = iw0 + ic;
-            xok[b] = id < TOTAL && px < NPX && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W && ch * 8 < p.Cin;
-            const long long off = xok[b] ? ((long long)ih * p.W + iw) * p.Cin + ch * 8 : 0;
-            xv[b] = *(const half8*)(img + off);
+            const bool ok = px < NPX && ih >= 0 && (unsigned)iw < (unsigned)p.W && whole;      // (rows past the last end the buffer)
+            xv[b] = __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? (unsigned)(ih - top) * row_bytes + (unsigned)iw * pixel_bytes + 16u * ch : OOB, 0, 0);
         }
     };
+    half_t* const xdst = xs + px0 * XP + ch * 8;
     auto deposit_tile = [&](int it0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int b = 0; b < BATCH; ++b) {
-            const int id = tid + (it0 + b) * 256;
-            const int px = id / CH, ch = id - px * CH;
-            half8 z;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) z[j] = xok[b] ? xv[b][j] : (half_t)0.f;
-            if (id < TOTAL) *(half8*)(xs + px * XP + ch * 8) = z;
-        }
+        for (int b = 0; b < BATCH; ++b)
+            if (takes && px0 + (it0 + b) * PSTEP < ROWS) *(uintx4*)(xdst + (it0 + b) * PSTEP * XP) = xv[b];
     };
     const half_t lo1 = (p.act1 == ACT_RELU || p.act1 == ACT_RELU6) ? (half_t)0.f : (half_t)-INFINITY;
     const half_t hi1 = p.act1 == ACT_RELU6 ? (half_t)6.f : (half_t)INFINITY;
@@ -270,7 +272,7 @@ struct EdwCut {
 constexpr int edw_pixel_blocks(int stride, int tq, int th) {
     return ((256 / (4 * tq) * th - 1) * stride + 3) * ((tq - 1) * stride + 3) / 32 + ((((256 / (4 * tq) * th - 1) * stride + 3) * ((tq - 1) * stride + 3)) % 32 != 0);
 }
-constexpr bool edw_ahead(int ks, int stride, int tq, int th) { return edw_pixel_blocks(stride, tq, th) * 32 * ks * 2 <= 12 * 256; }
+constexpr bool edw_ahead(int ks, int stride, int tq, int th) { return (edw_pixel_blocks(stride, tq, th) * 32 + 256 / (2 * ks) - 1) / (256 / (2 * ks)) <= 12; }
 
 // Estimated times, fitted to 15 layers of images of 160, 224 and 256 pixels at 1 to 128 images, every tile and split of them (mean
 // error 7 % with one group per workgroup, 18 % with several).  One group: a launch, a pass over the tile, and what the
@@ -307,6 +309,7 @@ static int launch_edw_tile(const ExpandDwParams& q, const EdwCut& c, hipStream_t
     ExpandDwParams p = q;
     p.tiles_p = (p.P + c.tp - 1) / c.tp;
     p.tiles_q = (p.Q + TQ - 1) / TQ;
+    p.by_tiles_p = divisor(p.tiles_p); p.by_tiles_q = divisor(p.tiles_q);
     if (c.tiles <= 0 || c.tiles > 0x7fffffffLL) { set_error("expand+depthwise: bad grid (%lld tiles)", c.tiles); return -5; }
     const int groups = (p.Chid + 31) / 32;
     p.groups_per_block = c.gpb;
