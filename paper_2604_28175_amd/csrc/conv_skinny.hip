@@ -76,6 +76,19 @@ __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
         woff[a] = n < p.Cout ? (unsigned)(((long long)n * p.ldw + lg * 8) * 2) : SK_OOB;
     }
 
+    // ---- what this thread needs for the four channels of one pixel that it will finish: requested now, so that no further
+    // round trip follows the reduction (one image, 2048 -> 512 channels 6.28 -> 6.24 us, 512 -> 2048 with its residual 4.63 -> 4.48, 1024 -> 256 4.04 -> 3.99)
+    constexpr int NQ = TN / 4;                         // channel quads of a pixel
+    const int cq = tid % NQ, px = tid / NQ;
+    const int mo = m0 + px, no = n0 + cq * 4;
+    const bool finishes = tid < TM * NQ && mo < p.M && no < p.Cout, whole = no + 4 <= p.Cout && ((p.Cout | p.ldy) & 3) == 0;
+    const long long at = (long long)mo * p.ldy + no;
+    float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+    half4 res = {(half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f};
+    if (finishes && whole) {
+        if (p.bias) bias = *(const float4*)(p.bias + no);
+        if (p.res) res = *(const half4*)(p.res + at);
+    }
     // ---- this wavefront's part of the reduction: super-slices sl .. s1 - 1
     const int ns = p.Kg >> 6;
     const int q = ns / NW, rq = ns - q * NW;
@@ -148,11 +161,7 @@ __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
 #pragma unroll
     for (int a = 0; a < NB; ++a) part[wave][a][lane] = make_float4(acc[a][0], acc[a][1], acc[a][2], acc[a][3]);
     __syncthreads();
-    constexpr int NQ = TN / 4;                         // channel quads of a pixel
-    if (tid >= TM * NQ) return;
-    const int cq = tid % NQ, px = tid / NQ;
-    const int mo = m0 + px, no = n0 + cq * 4;
-    if (mo >= p.M || no >= p.Cout) return;
+    if (!finishes) return;
     float4 v = part[0][cq >> 2][(cq & 3) * 16 + px];
 #pragma unroll
     for (int w = 1; w < NW; ++w) {
@@ -160,13 +169,11 @@ __global__ void __launch_bounds__(256) conv_skinny_kernel(const ConvParams p) {
         v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
     }
     float o[4] = {v.x, v.y, v.z, v.w};
-    const long long at = (long long)mo * p.ldy + no;
-    if (no + 4 <= p.Cout && ((p.Cout | p.ldy) & 3) == 0) {
-        if (p.bias) { const float4 b = *(const float4*)(p.bias + no); o[0] += b.x; o[1] += b.y; o[2] += b.z; o[3] += b.w; }
+    if (whole) {
+        if (p.bias) { o[0] += bias.x; o[1] += bias.y; o[2] += bias.z; o[3] += bias.w; }
         if (p.res) {
-            const half4 r = *(const half4*)(p.res + at);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] += (float)r[j];
+            for (int j = 0; j < 4; ++j) o[j] += (float)res[j];
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) o[j] = apply_act(o[j], p.act);
