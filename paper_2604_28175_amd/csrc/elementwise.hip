@@ -51,16 +51,19 @@ int launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {
 // timestamps of a batch's record (the device's constant-rate clock, written to the instance's pinned control block) and
 // the outgoing one tells the host that the result is there.  An event record costs about 3.6 us between two dependent launches and
 // a wait on one 12 us from the last kernel to the waiting thread; the stamps cost nothing and the flag 7 us.
+//
+// What bounds them is the link, 53 GB/s; what they cost others is the requests they have under way.  A kernel of another stream that begins or ends waits until every
+// cache has answered what it was asked, and an answer from host memory takes 1.5 us and the time of all that queues before it.  With 256 workgroups and four loads a
+// thread a chain of 2.3 us kernels beside a copy of 2.4 MB took 22 us a kernel, that is, stood still, and the copy 48.5 us; 80 KB under way still fill the link:
+//   workgroups of 256, one load a thread    32         24         20         16         12
+//   copy us, chain us a kernel              45.1 10.1  45.3 8.1   46.0 7.0   49.1 6.6   63.6 6.4
+// and on the way out, four stores a thread  16: 44.7 5.5   8: 45.3 3.7   4: 53.4 2.9.  128 requests served by two models side by side 4.55 -> 4.25 ms, eight images
+// of ResNet-50 alone 485 -> 477 us.
+constexpr unsigned COPY_IN_BLOCKS = 20, COPY_OUT_BLOCKS = 8;
 __device__ __forceinline__ void copy_range(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, size_t n4, unsigned block, unsigned blocks) {
-    // four independent 16-byte loads per thread and round keep enough requests in flight to fill the host link on the way in
     const size_t n16 = n4 >> 2;
     const size_t step = (size_t)blocks * 256;
-    size_t i = (size_t)block * 256 + threadIdx.x;
-    for (; i + 3 * step < n16; i += 4 * step) {
-        const uint4 a = ((const uint4*)src)[i], b = ((const uint4*)src)[i + step], c = ((const uint4*)src)[i + 2 * step], d = ((const uint4*)src)[i + 3 * step];
-        ((uint4*)dst)[i] = a; ((uint4*)dst)[i + step] = b; ((uint4*)dst)[i + 2 * step] = c; ((uint4*)dst)[i + 3 * step] = d;
-    }
-    for (; i < n16; i += step) ((uint4*)dst)[i] = ((const uint4*)src)[i];
+    for (size_t i = (size_t)block * 256 + threadIdx.x; i < n16; i += step) ((uint4*)dst)[i] = ((const uint4*)src)[i];
     const size_t tail = n16 << 2;
     if (block == 0 && tail + threadIdx.x < n4) dst[tail + threadIdx.x] = src[tail + threadIdx.x];
 }
@@ -86,7 +89,7 @@ int launch_copy_in(const void* src, void* dst, size_t bytes, const void* src2, v
         set_error("copy in: 16-byte aligned buffers and multiples of 4 bytes required"); return -1;
     }
     const size_t n4 = bytes / 4, n16 = n4 / 4;
-    const unsigned blocks = (unsigned)std::min<size_t>(256, std::max<size_t>(1, (n16 + 255) / 256));
+    const unsigned blocks = (unsigned)std::min<size_t>(COPY_IN_BLOCKS, std::max<size_t>(1, (n16 + 255) / 256));
     hipLaunchKernelGGL(copy_in_kernel, dim3(blocks), dim3(256), 0, stream, (const uint32_t*)src, (uint32_t*)dst, n4, (const uint32_t*)src2,
                        (uint32_t*)dst2, (unsigned)(bytes2 / 4), ctl, counters, piece);
     STRAIT_CHECK_LAUNCH("copy in");
@@ -115,7 +118,7 @@ int launch_stamp(HostControl* ctl, int which, hipStream_t stream, const void* sr
 // chunk c is written, flag[c] becomes `seq`, so that the host can move a chunk on while the next ones are on the link.  Stamps
 // STAMP_K1 (first workgroup starts; if `k1_taken`, when the kernels were done, STAMP_D2H0 instead) and STAMP_DONE.  counters[1 + c] count a chunk's parts, counters[0] the
 // chunks; both are back at zero, for every stream, before the last flag is set.
-// Few workgroups: 16 of them keep the link busy (12.6 MB in 0.24 ms), and other batches run beside this.  The stores go through the
+// Few workgroups (above).  The stores go through the
 // caches (sc0 sc1) and each workgroup waits for its own to be acknowledged before it counts a part: a system-scope fence would
 // instead write back the L2s, which hold other batches' data.  A store of 16 bytes still reads its registers for two wait states after it was issued, which
 // the compiler does not count for inline assembly: an instruction that reused them right behind it would be stored in their place.
@@ -167,7 +170,7 @@ int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, 
     const size_t chunk = out_chunk_bytes(bytes), part = chunk / OUT_PARTS;
     const unsigned chunks = (unsigned)((bytes + chunk - 1) / chunk);
     const unsigned parts = (unsigned)((bytes + part - 1) / part);
-    const unsigned blocks = std::min(parts, 16u);
+    const unsigned blocks = std::min(parts, COPY_OUT_BLOCKS);
     hipLaunchKernelGGL(copy_out_kernel, dim3(blocks), dim3(256), 0, stream, (const char*)src, (char*)dst, bytes, part, parts, chunks, ctl, counters, seq,
                        k1_taken ? 1 : 0, hp);
     STRAIT_CHECK_LAUNCH("copy out");
