@@ -91,6 +91,8 @@ static int upload_weights(Model& m, const void* host, size_t bytes, void** dev) 
     return 0;
 }
 
+static bool can_cut(const Model& m, int cut);
+
 int finish_plan(Model& m) {
     if (m.fold_tmp) { (void)hipFree(m.fold_tmp); m.fold_tmp = nullptr; }
     for (Model::Cold& c : m.cold) {
@@ -101,6 +103,8 @@ int finish_plan(Model& m) {
         m.ops[c.op].bias = (const float*)b;
     }
     m.cold.clear();
+    m.cuts.assign(m.ops.size() + 1, 0);
+    for (int i = 1; i < (int)m.ops.size(); ++i) m.cuts[i] = can_cut(m, i);
     return 0;
 }
 
@@ -1059,13 +1063,30 @@ static void* slot_ptr(Model& m, Instance& in, int slot, int ref, int batch) {
     return nullptr;
 }
 
-int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer, bool read_last) {
+// Elements per sample of what lies in `slot` when `op` reads it: those of the last op before it that wrote the slot.
+static size_t sample_elems(const Model& m, const Op& op, int slot) {
+    for (const Op* w = &op - 1; w >= m.ops.data(); --w)
+        if (w->out == slot) return (size_t)w->P * w->Q * w->K;
+    return 0;
+}
+
+int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer, bool read_last, int base, int whole_batch) {
     const int n = (int)m.ops.size();
+    const bool begun = whole_batch != 0 && first_layer > 0;       // the rest of a batch whose first layers were computed in parts
+    if (whole_batch == 0) whole_batch = batch;
+    // of a part of a batch: the place of its first sample, in a tensor that op `i` has written (-1: in the input)
+    auto at = [&](int slot, int ref, size_t elems) -> void* {
+        void* p = slot_ptr(m, in, slot, ref, batch);
+        return p && base ? (char*)p + base * elems * 2 : p;
+    };
+    auto src_of = [&](const Op& op, int slot) { return at(slot, 0, slot == SLOT_INPUT ? m.in_elems : sample_elems(m, op, slot)); };
+    auto dst_of = [&](const Op& op) { return at(op.out, op.out_ref, (size_t)op.P * op.Q * op.K); };
+    auto stats_of = [&](const Op& ln, int slot) { return in.ln_stats[slot] + (size_t)base * ln.P * (ln.K / 64); };
     if (last_layer < 0 || last_layer >= n) last_layer = n - 1;
     // Per-layer timing and prefix runs keep everything on the one stream (their events bracket single launches).
     if (first_layer < 0 || first_layer > last_layer) first_layer = 0;
     const bool whole = last_layer == n - 1 || (!read_last && last_layer == classify_out_first(m, batch) - 1);
-    const bool branches = !timed && first_layer == 0 && whole && in.side != nullptr && m.ctx->branch_streams;
+    const bool branches = !timed && (first_layer == 0 || begun) && whole && in.side != nullptr && m.ctx->branch_streams;
     bool forked = false;
     hipStream_t main_stream = stream;
     if (timed) in.layer_skipped.assign(m.ops.size(), 0);
@@ -1088,12 +1109,12 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
         return with_proj ? 3 : 0;                       // 3: no pair, but the convolution takes the projection as a second source
     };
     // whether LayerNorm op `ln` is folded into the products on its two sides; every layer it concerns comes to the same answer, also where a batch
-    // is issued in segments
-    if (first_layer == 0) in.ln_fold = m.ctx->pair_min_pixels > 0;
+    // is issued in segments or begun in parts
+    if (first_layer == 0 && base == 0) in.ln_fold = m.ctx->pair_min_pixels > 0;
     auto folded = [&](int ln) {
-        if (ln < 0 || m.ops[ln].fold_ops[0] < 0 || !in.ln_fold || !gemm_ln_pays((long long)batch * m.ops[ln].P, m.ops[ln].K)) return false;
+        if (ln < 0 || m.ops[ln].fold_ops[0] < 0 || !in.ln_fold || !gemm_ln_pays((long long)whole_batch * m.ops[ln].P, m.ops[ln].K)) return false;
         for (int o : m.ops[ln].fold_ops)
-            if (o >= 0 && !gemm_ln_supported((long long)batch * m.ops[ln].P, m.ops[o].K, m.ops[o].vC, m.ops[ln].K)) return false;
+            if (o >= 0 && !gemm_ln_supported((long long)whole_batch * m.ops[ln].P, m.ops[o].K, m.ops[o].vC, m.ops[ln].K)) return false;
         return true;
     };
     for (int i = first_layer; i <= last_layer; ++i) {
@@ -1121,8 +1142,8 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
             forked = false;
         }
         if (timed) HIP_TRY(hipEventRecord(in.layer_ev[i], stream));
-        const void* src = slot_ptr(m, in, op.in, 0, batch);
-        void* dst = slot_ptr(m, in, op.out, op.out_ref, batch);
+        const void* src = src_of(op, op.in);
+        void* dst = dst_of(op);
         int rc = 0;
         switch (op.kind) {
             case OP_CONV: {
@@ -1132,7 +1153,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                     expand_dw_pays(batch, op.P, op.Q, op.vC, op.K, m.ops[i + 1].stride)) {
                     const Op& dw = m.ops[i + 1];
                     rc = launch_expand_dw((const half_t*)src, batch, op.P, op.Q, op.vC, op.w, op.ldw, op.bias, op.K, op.act, dw.w, dw.bias,
-                                          dw.stride, dw.act, (half_t*)slot_ptr(m, in, dw.out, dw.out_ref, batch), hp, stream);
+                                          dw.stride, dw.act, (half_t*)dst_of(dw), hp, stream);
                     fused_away = i + 1;
                     break;
                 }
@@ -1142,15 +1163,15 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                     PairParams q{};
                     q.x = (const half_t*)src;
                     if (how == 2) {
-                        q.x2 = (const half_t*)slot_ptr(m, in, m.ops[op.proj_down].in, 0, batch);
+                        q.x2 = (const half_t*)src_of(m.ops[op.proj_down], m.ops[op.proj_down].in);
                         q.K2 = m.ops[op.proj_down].vC;
                         q.w3 = op.w_proj; q.b3 = op.bias_proj;
                     } else {
                         q.w3 = op.w; q.b3 = op.bias;
-                        q.res = (const half_t*)slot_ptr(m, in, op.res, 0, batch);
+                        q.res = (const half_t*)src_of(op, op.res);
                     }
                     q.y = (half_t*)dst;
-                    q.w1 = nx.w; q.b1 = nx.bias; q.z = (half_t*)slot_ptr(m, in, nx.out, nx.out_ref, batch);
+                    q.w1 = nx.w; q.b1 = nx.bias; q.z = (half_t*)dst_of(nx);
                     q.M = batch * op.P * op.Q; q.K1 = op.vC; q.N1 = op.K; q.N2 = nx.K; q.act1 = op.act; q.act2 = nx.act; q.hp = hp;
                     rc = launch_pointwise_pair(q, stream);
                     fused_away = i + op.pair;
@@ -1158,7 +1179,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                 }
                 ConvParams p{};
                 p.x = (const half_t*)src; p.w = op.w; p.bias = op.bias;
-                p.res = (const half_t*)slot_ptr(m, in, op.res, 0, batch);
+                p.res = (const half_t*)src_of(op, op.res);
                 p.y = dst;
                 p.M = batch * op.P * op.Q; p.PQ = op.P * op.Q; p.Q = op.Q;
                 p.H = op.vH; p.W = op.vW; p.C = op.vC; p.R = op.vR; p.S = op.vS;
@@ -1169,19 +1190,19 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                 if (how == 3) {
                     const Op& dn = m.ops[op.proj_down];
                     p.w = op.w_proj; p.bias = op.bias_proj; p.res = nullptr;
-                    p.x2 = (const half_t*)slot_ptr(m, in, dn.in, 0, batch);
+                    p.x2 = (const half_t*)src_of(dn, dn.in);
                     p.K2 = dn.vC; p.stride2 = dn.stride; p.sH2 = dn.sH; p.sW2 = dn.sW; p.sN2 = dn.sN;
                     p.Kg = op.vC + dn.vC; p.ldw = p.Kg;
                 }
                 const bool fold_in = folded(op.ln_in), fold_res = folded(op.ln_res), fold_out = folded(op.ln_out);
                 if (fold_in || fold_res || fold_out) {
                     const Op* l = fold_in ? &m.ops[op.ln_in] : fold_res ? &m.ops[op.ln_res] : nullptr;
-                    if (l) { p.ln_stats = in.ln_stats[l->ln_slot]; p.ln_eps = l->eps; }
+                    if (l) { p.ln_stats = stats_of(*l, l->ln_slot); p.ln_eps = l->eps; }
                     if (fold_in) {
-                        p.x = (const half_t*)slot_ptr(m, in, l->in, 0, batch);
+                        p.x = (const half_t*)src_of(*l, l->in);
                         p.w = op.w_ln; p.bias = op.bias_ln; p.ln_csum = op.csum_ln;
                     } else if (fold_res) {
-                        p.res = (const half_t*)slot_ptr(m, in, l->in, 0, batch);
+                        p.res = (const half_t*)src_of(*l, l->in);
                         p.ln_g = l->bias; p.ln_b = l->beta;
                     }
                     // (behind a folded residual the kernel always leaves statistics: where nobody reads them, in the other buffer)
@@ -1191,8 +1212,8 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                                                       (folded(m.ops[o + 1].ln_out) || folded(m.ops[o + 1].ln_res)); };
                     p.y_sliced = fold_in && sliced(i) && !(read_last && i == last_layer);
                     p.x_sliced = !fold_in && i > 0 && sliced(i - 1);
-                    if (fold_out) p.stats_out = in.ln_stats[m.ops[op.ln_out].ln_slot];
-                    else if (fold_res) p.stats_out = in.ln_stats[1 - l->ln_slot];
+                    if (fold_out) p.stats_out = stats_of(m.ops[op.ln_out], m.ops[op.ln_out].ln_slot);
+                    else if (fold_res) p.stats_out = stats_of(*l, 1 - l->ln_slot);
                     rc = launch_gemm_ln(p, stream);
                     break;
                 }
@@ -1205,7 +1226,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                 if (op.stem_next >= 0 && op.stem_next <= last_layer && m.ctx->pair_min_pixels > 0) {
                     const Op& c1 = m.ops[op.stem_next];
                     rc = launch_stem_pool((const half_t*)src, op.w, op.bias, batch, op.H, op.W, (half_t*)dst, hp, stream, c1.w, c1.bias,
-                                          (half_t*)slot_ptr(m, in, c1.out, c1.out_ref, batch));
+                                          (half_t*)dst_of(c1));
                     stem_next_done = op.stem_next;
                     break;
                 }
@@ -1216,7 +1237,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                     // with the first block's depthwise layer behind it in the same launch: the stem's output stays in LDS
                     const Op& dw = m.ops[i + 1];
                     rc = launch_stem3x3s2_dw((const half_t*)src, op.w, op.bias, op.act, dw.w, dw.bias, dw.act, batch, op.H, op.W,
-                                             (half_t*)slot_ptr(m, in, dw.out, dw.out_ref, batch), hp, stream);
+                                             (half_t*)dst_of(dw), hp, stream);
                     fused_away = i + 1;
                     break;
                 }
@@ -1226,7 +1247,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                 if (op.w && i + 1 <= last_layer && m.ctx->pair_min_pixels > 0 && stem3x3s1_pays(batch, op.H, op.W)) {
                     const Op& cv = m.ops[i + 1];
                     rc = launch_stem3x3s1((const half_t*)src, op.w, cv.bias, batch, op.H, op.W, cv.K, cv.act,
-                                          (half_t*)slot_ptr(m, in, cv.out, cv.out_ref, batch), hp, stream);
+                                          (half_t*)dst_of(cv), hp, stream);
                     fused_away = i + 1;
                     break;
                 }
@@ -1251,7 +1272,7 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
                 rc = launch_vit_tokens((const half_t*)src, op.bias, op.beta, batch, op.P - 1, op.K, (half_t*)dst, hp, stream);
                 break;
             case OP_ATTENTION:
-                rc = launch_attention((const half_t*)src, in.dev_valid, batch, op.seq, op.heads, (half_t*)dst, hp, stream);
+                rc = launch_attention((const half_t*)src, in.dev_valid + base, batch, op.seq, op.heads, (half_t*)dst, hp, stream);
                 break;
             default:
                 set_error("unknown op kind %d", op.kind);
@@ -1268,6 +1289,58 @@ int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int 
     }
     if (timed) HIP_TRY(hipEventRecord(in.layer_ev[last_layer + 1], main_stream));
     return 0;
+}
+
+// Tensors that ops from `cut` on read and ops before it have written, as (slot, the op that wrote it).
+static std::vector<std::pair<int, int>> live_at(const Model& m, int cut) {
+    std::vector<std::pair<int, int>> live;
+    std::set<int> seen;                                // written behind the cut, or noted already
+    auto reads = [&](int slot) {
+        if (slot < 0 || !seen.insert(slot).second) return;
+        int w = cut - 1;
+        while (w >= 0 && m.ops[w].out != slot) --w;
+        live.push_back({slot, w});
+    };
+    for (int i = cut; i < (int)m.ops.size(); ++i) {
+        const Op& op = m.ops[i];
+        reads(op.in);
+        reads(op.res);
+        if (op.proj_down >= 0) reads(m.ops[op.proj_down].in);
+        for (int ln : {op.ln_in, op.ln_res}) if (ln >= 0) reads(m.ops[ln].in);
+        if (op.out >= 0) seen.insert(op.out);
+    }
+    return live;
+}
+
+// Whether a batch's layers in front of `cut` can be computed part by part before the rest is computed for all of it: no launch spans the cut, the tensors that are alive there lie in
+// activation buffers (or are the input), and no part writes where an earlier part's lie.  Sample i of a tensor of e elements lies at i e of its buffer: a part that begins at
+// sample i writes from i e' on, which is behind all that the samples before it left there if e' >= e for every tensor that the layers in front put into that buffer.
+static bool can_cut(const Model& m, int cut) {
+    auto size = [&](int i) { return (size_t)m.ops[i].P * m.ops[i].Q * m.ops[i].K; };
+    for (int i = 0; i < cut; ++i) {
+        const Op& op = m.ops[i];
+        if (op.out < 0 || i + op.pair >= cut || op.stem_next >= cut || op.proj_of >= cut || (op.dw_next && i + 1 >= cut) || (op.kind == OP_PACK && i + 1 >= cut)) return false;
+    }
+    if (cut < (int)m.ops.size() && m.ops[cut - 1].kind == OP_CONV && m.ops[cut - 1].ln_in >= 0 && m.ops[cut].kind == OP_CONV) return false;     // (laid out in slices of all rows)
+    for (const auto& t : live_at(m, cut)) {
+        if (t.second < 0) return false;
+        for (int i = 0; i < cut; ++i)
+            if (m.ops[i].out == t.first && size(i) < size(t.second)) return false;
+    }
+    return true;
+}
+
+int lead_layers(const Model& m, int part, int last) {
+    const double link_us = m.in_bytes(part) / 53e3;    // of a part's input
+    double us = 0;
+    int lead = 0;
+    for (int i = 0; i + 1 < last; ++i) {
+        const strait_layer_info& l = m.ops[i].info;
+        us += 4 + std::max(2.0 * l.macs_per_sample * part / 0.8e9, (double)l.bytes_per_sample * part / 4.5e6);
+        if (us > link_us) break;
+        if (m.cuts[i + 1]) lead = i + 1;
+    }
+    return lead;
 }
 
 int classify_out_first(const Model& m, int batch) {

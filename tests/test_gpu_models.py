@@ -841,3 +841,37 @@ def test_submit_from_the_staging_buffer_makes_no_host_copy_and_gives_the_same_re
         m.wait(t)
     finally:
         m.free()
+
+
+@pytest.mark.parametrize("arch,kw,batch", [("mobilenet_v2", dict(hw=96), 171),                                      # 43, 86 and 42 images
+                                           ("mobilenet_v2", dict(hw=96), 700),                                      # eight full parts and one of a half
+                                           ("vgg19", dict(hw=64, classes=50, fc=64), 389),
+                                           ("vit", dict(hw=96, classes=100, layers=2, hidden=128, heads=2, ffn=256), 171),
+                                           ("encoder", dict(layers=3, hidden=128, heads=2, ffn=256, seq=40), 1001)])
+def test_a_large_batch_begun_while_its_input_is_on_the_way(ctx, arch, kw, batch):
+    """A staged input of 9 MB and more: the first layers of each part run while the next is on the link (the record's phases overlap).  Every sample's result is that of the same batch
+    computed whole, to within what its layers' roundings to fp16 differ by where a part's products sum in another order."""
+    S = ctx.S
+    md = getattr(synth, arch)(21, **kw)
+    x, vl = synth.token_batch(md, batch, 8) if arch == "encoder" else (synth.default_image_batch(md, batch, 8), None)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    try:
+        whole, parts = m.new_output(batch), m.new_output(batch)
+        m.wait(m.submit(S.PRIO_LOW, x, vl, whole))                        # ordinary memory: in one go
+        st = m.staging(0, batch)
+        st[:] = x
+        want = m.decode(whole, batch)
+        key = "hidden" if arch == "encoder" else "logits"
+        want = want[key].astype(np.float64).copy()
+        for prio in (S.PRIO_HIGH, S.PRIO_LOW, S.PRIO_HIGH):
+            parts[:] = 0
+            rec = m.wait(m.submit(prio, st, vl, parts))
+            got = m.decode(parts, batch)[key].astype(np.float64)
+            if arch == "encoder":
+                for i in range(batch):
+                    check_kernel(got[i, :vl[i]], want[i, :vl[i]], f"sequence {i}", rel=2.0 ** -8, abs_rel=1e-2)
+            else:
+                check_kernel(got, want, f"{arch} b{batch}", rel=2.0 ** -8, abs_rel=1e-2)
+            assert rec.h2d_ms + rec.kernel_ms + rec.d2h_ms > rec.total_ms, (rec.h2d_ms, rec.kernel_ms, rec.d2h_ms, rec.total_ms)
+    finally:
+        m.free()
