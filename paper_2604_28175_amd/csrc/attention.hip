@@ -55,13 +55,14 @@ __device__ __forceinline__ float2 both_halves(float v) {
 }
 
 __global__ void __launch_bounds__(64 * ATT_WAVES, 4) attention_kernel(const half_t* __restrict__ qkv, const int32_t* __restrict__ valid_len, int S, int heads,
-                                                                      int seq_heads, int blocks_per_wg, half_t* __restrict__ out, int hp) {
+                                                                      int seq_heads, int blocks_per_wg, half_t* __restrict__ out, int hp, Divisor by_heads) {
     extern __shared__ __attribute__((aligned(16))) char att_lds[];      // K rows, then V rows, valid_len rounded up to 16 of each
     if (hp) __builtin_amdgcn_s_setprio(3);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
-    const int part = blockIdx.x / seq_heads, sh = blockIdx.x - part * seq_heads;
-    const int b = sh / heads, h = sh - b * heads;
+    // (at most two parts; the two divisions took 80 dependent instructions in front of the first load)
+    const int part = (int)blockIdx.x >= seq_heads ? 1 : 0, sh = blockIdx.x - part * seq_heads;
+    const int b = divide(sh, by_heads), h = sh - b * heads;
     const int nq = (S + 31) >> 5;
     const int qb0 = part * blocks_per_wg, qb1 = qb0 + blocks_per_wg < nq ? qb0 + blocks_per_wg : nq;
     const int hidden = heads * ATT_D, pitch = 3 * hidden;
@@ -208,7 +209,7 @@ int launch_attention(const half_t* qkv, const int32_t* valid_len, int B, int S, 
     const int parts = nq > ATT_WAVES && 2LL * seq_heads <= 768 ? 2 : 1;
     const size_t lds = (size_t)((S + 15) / 16 * 16) * 2 * ATT_ROW;      // at most 64 KB
     hipLaunchKernelGGL(attention_kernel, dim3((unsigned)(seq_heads * parts)), dim3(64 * ATT_WAVES), lds, stream, qkv, valid_len, S, heads, seq_heads,
-                       (nq + parts - 1) / parts, out, hp);
+                       (nq + parts - 1) / parts, out, hp, divisor(heads));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("attention launch: %s", hipGetErrorString(e)); return -2; }
     return 0;
