@@ -579,6 +579,19 @@ def test_expand_dw_every_cut(S, case):
     assert S.torch.equal(y, y2)
 
 
+@pytest.mark.parametrize("w", [466000, 470001])          # 18 rows of 128 channels: one side and the other of 2^31 bytes
+def test_expand_dw_long_rows(S, w):
+    """Rows that a tile's 32-bit offsets do not span are read through addresses: bit for bit what the two stand-alone kernels give."""
+    t = S.torch
+    x = t.randn((1, 2, w, 128), device="cuda", dtype=t.float16)
+    w1, b1 = dev(S, f16(R.standard_normal((8, 128)) * 0.125)), dev(S, R.standard_normal(8).astype(np.float32))
+    wd, bd = dev(S, f16(R.standard_normal((3, 3, 8)) * 0.47)), dev(S, R.standard_normal(8).astype(np.float32))
+    y = S.k_expand_dw(x, w1, b1, wd, bd, 1)
+    y2 = S.k_dwconv3x3(S.k_conv2d(x, w1.reshape(8, 1, 1, 128), b1, 1, 0, 2), wd, bd, 1, 2)
+    t.cuda.synchronize()
+    assert t.equal(y, y2)
+
+
 def test_expand_dw_errors(S):
     x = dev(S, np.zeros((1, 8, 8, 12), np.float16))
     with pytest.raises(S.StraitError):       # Cin % 8 != 0
