@@ -142,7 +142,8 @@ strait_status strait_ctx_set_graphs(strait_ctx* ctx, int32_t enabled);
  * 1.210 ms, batch 16 0.552 -> 0.543 ms; at batch 8 and below the two launches, which may split their reductions, are 1 %
  * faster); 0 = always two launches, and every other fusion of launches off as well (projection shortcuts, the first
  * block's opening convolution inside the stem launch, LayerNorms inside the products on their two sides, a 3x3/1 first layer that reads the image
- * itself, a classifier's softmax, and a small head's pooling and product with it, on the result's way out): the layer-by-layer plan.  A pair's results are those of its two launches, bit for bit; those of a projection shortcut, a folded LayerNorm or a classifier's end
+ * itself, a classifier's softmax, and a small head's pooling and product or a whole small
+ * network with it, on the result's way out): the layer-by-layer plan.  A pair's results are those of its two launches, bit for bit; those of a projection shortcut, a folded LayerNorm or a classifier's end
  * are not: inside one launch a sum is not rounded to fp16 on its way, or is formed in another order.  A graph that strait_ctx_set_graphs has
  * already captured keeps the launches it was captured with: set this before the first batch. */
 strait_status strait_ctx_set_pair_fusion(strait_ctx* ctx, int64_t min_pixels);
