@@ -1100,7 +1100,7 @@ static int choose_conv(ConvParams& p, int* mode_out, bool* staged_out) {
 // The same for a dense product with a LayerNorm folded in: the LDS-direct kernel only, on the tiles that gemm_ln.hip instantiates (slices of 64).  The
 // estimates are the plain products', whose epilogues are shorter by 0.6 to 1 us a round (gemm_ln.hip); among tiles that they put within a few per
 // cent of each other the choice is not better founded than that.
-int choose_gemm_ln(ConvParams& p) {
+static int gemm_ln_tile(ConvParams& p) {
     int mode = 0;
     bool staged = false;
     const int rc = choose_conv(p, &mode, &staged);     // checks the parameters and fills in what is derived
@@ -1121,11 +1121,37 @@ int choose_gemm_ln(ConvParams& p) {
     return best;
 }
 
+// A part of a batch (ConvParams::whole_M) may take another kernel than the whole one only where both add in the same order, so that a batch's result is the same
+// bit for bit whether it is computed in parts or not, which depends on what else the GPU has to do.  The LDS-direct kernel adds up the reduction in steps of 16 on
+// all tiles on which one group of wavefronts does; every other kernel, or way of splitting the reduction, has an order of its own.
+static bool same_order(int a, const ConvParams& pa, int b, const ConvParams& pb) {
+    auto one_group = [](int id) { return id < T_DMA && tile_info[id].kg == 1; };
+    return pa.ksplit == pb.ksplit && pa.res_f32 == pb.res_f32 && (a == b || (one_group(a) && one_group(b)));
+}
+
+int choose_gemm_ln(ConvParams& p) {
+    const int id = gemm_ln_tile(p);
+    if (id < 0 || p.whole_M <= p.M) return id;
+    ConvParams whole = p;
+    whole.M = p.whole_M;
+    const int as_whole = gemm_ln_tile(whole);
+    return as_whole < 0 || !same_order(id, p, as_whole, whole) ? as_whole : id;
+}
+
 int launch_conv(const ConvParams& params, hipStream_t stream) {
     ConvParams p = params;
     int mode = 0;
     bool staged = false;
-    const int id = choose_conv(p, &mode, &staged);
+    int id = choose_conv(p, &mode, &staged);
+    if (id >= 0 && p.whole_M > p.M) {                  // (a kernel that takes the whole takes a part)
+        ConvParams whole = p;
+        whole.M = p.whole_M;
+        const int as_whole = choose_conv(whole, &mode, &staged);
+        if (as_whole < 0 || !same_order(id, p, as_whole, whole)) {
+            id = as_whole;
+            p.ksplit = whole.ksplit; p.res_f32 = whole.res_f32;
+        }
+    }
     return id < 0 ? id : launch_tile_id(p, (TileId)id, mode, staged, stream);
 }
 size_t conv_workspace_bytes(const ConvParams& params, size_t limit) {

@@ -60,6 +60,7 @@ struct ConvParams {
     size_t ws_bytes;
     int ksplit;              // filled in by launch_conv
     int res_f32;             // add the residual in fp32, before the rounding; filled in by launch_conv
+    int whole_M;             // of rows that are a part of a larger launch's: the number of all of them, whose order of summation they get (0: M)
     TileOrder order;         // filled in by the launcher (set_tile_order), like the divisors and kchunk
     Divisor by_pq, by_q, by_c, by_s, by_row, by_image;   // PQ, Q, C, S; W + 1 and (H + 1)(W + 1), the pixels of a bordered row and image
     int kchunk;              // slices of a part of the reduction

@@ -876,3 +876,29 @@ def test_a_large_batch_begun_while_its_input_is_on_the_way(ctx, arch, kw, batch)
                 assert rec.h2d_ms + rec.kernel_ms + rec.d2h_ms > rec.total_ms, (rec.h2d_ms, rec.kernel_ms, rec.d2h_ms, rec.total_ms)
     finally:
         m.free()
+
+
+@pytest.mark.parametrize("arch,kw,batch", [("vit", dict(hw=96, classes=100, layers=2, hidden=128, heads=2, ffn=256), 171),        # a part's products would split their reductions
+                                           ("vit", dict(hw=96, classes=100, layers=2, hidden=128, heads=2, ffn=256), 613),
+                                           ("vit", dict(hw=224, classes=100, layers=2), 45),
+                                           ("encoder", dict(layers=3, hidden=128, heads=2, ffn=256, seq=40), 1001),
+                                           ("encoder", dict(layers=2, hidden=768, heads=12, ffn=3072, seq=128), 50),
+                                           ("mobilenet_v2", dict(hw=96), 171), ("mobilenet_v2", dict(hw=224), 64),
+                                           ("vgg19", dict(hw=64, classes=50, fc=64), 389)])
+def test_a_batch_in_parts_gives_the_bytes_of_the_whole(ctx, arch, kw, batch):
+    """Whether a staged batch of 9 MB and more goes in parts depends on what else is on its way.  Its result does not: parts take kernels that add in the whole batch's order."""
+    S = ctx.S
+    md = getattr(synth, arch)(22, **kw)
+    x, vl = synth.token_batch(md, batch, 9) if arch == "encoder" else (synth.default_image_batch(md, batch, 9), None)
+    m = ctx.load(synth.pack(md), max_batch=batch, n_instances=1)
+    try:
+        whole, parts = m.new_output(batch), m.new_output(batch)
+        m.wait(m.submit(S.PRIO_LOW, x, vl, whole))                        # ordinary memory: in one go
+        st = m.staging(0, batch)
+        st[:] = x
+        for prio in (S.PRIO_HIGH, S.PRIO_LOW):
+            parts[:] = 0
+            m.wait(m.submit(prio, st, vl, parts))
+            assert np.array_equal(parts, whole), (arch, batch, prio)
+    finally:
+        m.free()
