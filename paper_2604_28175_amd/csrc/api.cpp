@@ -551,10 +551,10 @@ static bool input_by_kernel(const strait_model* m, int batch) {
 // up: 64 images of 224 x 224 at 2.05 ms, 40 us.  There the whole input is timed, and what the host's copying adds is known from when
 // it handed the pieces over (link_ms).  That needs a stream with nothing else on it: an input that finds another batch's ahead goes in one
 // piece, as the link has work meanwhile (`alone`), and once another's has come between, the rest goes as one with a start of its own.
-// With `part` (a staged input through copy engines), pieces of that many samples, the first of half as many, go through two copy streams in turn: what a record behind a piece holds its stream
+// With `parts` (a staged input through copy engines), pieces of so many samples go through two copy streams in turn: what a record behind a piece holds its stream
 // up by, 40 us, the other one's transfer fills.  Each is followed by in.ev_h2d and part_sent(its first sample, the sample behind its last); the valid lengths go ahead of them.
 static int send_input(const strait_model* m, Instance& in, int batch, const void* host_in, const int32_t* valid_len, bool by_kernel, bool alone, int ci, hipStream_t s,
-                      InputTiming* timing, int part = 0, const std::function<int(int, int)>& part_sent = nullptr) {
+                      InputTiming* timing, const Parts& parts = Parts(), const std::function<int(int, int)>& part_sent = nullptr) {
     Context* c = m->ctx;
     const size_t inb = m->in_bytes(batch), off = (m->in_bytes(m->max_batch) + 255) / 256 * 256;
     const size_t lens = m->arch == STRAIT_ARCH_ENCODER ? (size_t)batch * 4 : 0;
@@ -565,7 +565,8 @@ static int send_input(const strait_model* m, Instance& in, int batch, const void
     const void* lsrc = lens ? (const char*)in.pinned_in_dev + off : nullptr;
     void* ldst = lens ? in.dev_valid : nullptr;
     const bool staged = host_in == in.pinned_in;
-    size_t piece = part ? m->in_bytes(part) : staged ? inb : by_kernel ? 512u << 10 : alone ? 4u << 20 : inb;
+    const bool part = parts.layers > 0;
+    size_t piece = part ? m->in_bytes(parts.each) : staged ? inb : by_kernel ? 512u << 10 : alone ? 4u << 20 : inb;
     timing->by_kernel = by_kernel;
     timing->last_timed = false;
     unsigned seq[2] = {0, 0};                          // of this batch's previous piece on a stream
@@ -575,7 +576,7 @@ static int send_input(const strait_model* m, Instance& in, int batch, const void
         size_t n = inb - at <= piece + piece / 2 || k == MAX_PIECES - 1 ? inb - at : piece;
         const int turn = part ? k & 1 : 0;
         if (part) {
-            if (k == 0) n = m->in_bytes((part + 1) / 2);
+            if (k == 0) n = m->in_bytes(parts.first);
             ci = (first_ci + turn) % (int)c->copy.size();
             s = c->copy[ci];
         }
@@ -676,16 +677,15 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
         const bool alone = c->copy_outstanding[cidx].fetch_add(1, std::memory_order_acq_rel) == 0;
         // A large input that is staged and that nothing else is on its way beside: the first layers of each part run while the next part is on the link, where 64 images of
         // 224 x 224 are 365 us.  MobileNetV2 64 images 948 -> 888 us, 128 images 1617 -> 1460, beside ResNet-50 eight 1160 -> 1067; ViT 64 images 3648 -> 3544, 32 images 2078 -> 2057, VGG-19
-        // 64 images 3115 -> 3031, encoder 64 sequences 2787 -> 2757.  Parts of 4.5 MB: the layers of 2.2 MB leave units idle, with 9 MB less is hidden (MobileNetV2 64 images 903, 873 and 912).
+        // 64 images 3115 -> 3031, encoder 64 sequences 2787 -> 2757.
         // An input that is not staged waits for the host's copying, which these launches would hold up; a captured kernel sequence is one piece.
-        constexpr size_t PART = 4500u << 10;
-        const size_t inb = m->in_bytes(batch);
-        if (host_in == in.pinned_in && !yielding && !by_kernel && !c->use_graphs && c->copy.size() > 1 && batch > 1 && inb >= 2 * PART && w->outstanding.load(std::memory_order_acquire) == 0) {
+        if (host_in == in.pinned_in && !yielding && !by_kernel && !c->use_graphs && c->copy.size() > 1 && w->outstanding.load(std::memory_order_acquire) == 0) {
             int others = -1;
             for (const auto& n : c->copy_outstanding) others += n.load(std::memory_order_acquire);
-            const int parts = (int)std::min<size_t>(inb / PART, 16), part = (batch + parts - 1) / parts;
-            if (others == 0 && (lead = lead_layers(*m, part, t->out_first)) > 0)
-                return send_input(m, in, batch, host_in, valid_len, false, true, (int)cidx, cs, &t->input, part, [&](int first, int end) {
+            Parts parts;
+            if (others == 0) parts = plan_parts(*m, batch, t->out_first);
+            if ((lead = parts.layers) > 0)
+                return send_input(m, in, batch, host_in, valid_len, false, true, (int)cidx, cs, &t->input, parts, [&](int first, int end) {
                     if (!slk.owns_lock()) slk.lock();
                     if (hipStreamWaitEvent(s, in.ev_h2d, 0) != hipSuccess) return (int)STRAIT_E_HIP;
                     if (first == 0 && launch_stamp(in.ctl_dev, STAMP_K0, s)) return (int)STRAIT_E_HIP;

@@ -118,7 +118,7 @@ struct Model {
     int hyper[8] = {0};
     int max_batch = 0;
     std::vector<Op> ops;
-    std::vector<char> cuts;            // [i]: a batch can be computed part by part up to layer i (lead_layers)
+    std::vector<char> cuts;            // [i]: 0, or that a batch can be computed part by part up to layer i, in parts that begin at a multiple of so many samples (plan_parts)
     std::vector<size_t> buf_elems;     // per-sample elements of each activation buffer
     size_t in_elems = 0;               // per-sample fp16 input elements
     int classes = 0;                   // CNN
@@ -214,13 +214,14 @@ int build_plan(Model& m, const void* blob, size_t bytes);
 int finish_plan(Model& m);             // after the instances' buffers
 // Enqueues layers first_layer..last_layer (last_layer < 0: up to the end) of the plan for `batch` samples on `stream`.
 // read_last: the output of last_layer is going to be read by the caller (a layer folded or laid out for the next one is then computed as it is).
-// base, whole_batch: the samples are those from `base` on of a batch of whole_batch whose first layers are computed part by part (layers 0..lead_layers - 1),
+// base, whole_batch: the samples are those from `base` on of a batch of whole_batch whose first layers are computed part by part (layers 0..Parts::layers - 1),
 // or, with first_layer > 0, all of it, for which that is done.
 int run_plan(Model& m, Instance& in, int batch, hipStream_t stream, int hp, int last_layer, bool timed, int first_layer = 0, bool read_last = false, int base = 0, int whole_batch = 0);
-// The number of layers that a batch whose input comes in parts of `part` samples has computed for a part as soon as it is there, while the next one is on the link: as many
+// The parts that a large batch's input comes in, and the number of layers that are computed for each as soon as it is there, while the next one is on the link: as many
 // as take no longer than that does, by the estimate of a launch's 4 us and a rate (0.8 PFLOP/s, 4.5 TB/s) for each, fewer than `last`,
-// and as can be computed so (0: none).
-int lead_layers(const Model& m, int part, int last);
+// and as can be computed so.  The first part is half as large as the others, the last one what is left; all begin where the kernels can read and write 16 bytes at a time.
+struct Parts { int layers = 0, first = 0, each = 0; };     // layers 0: in one piece
+Parts plan_parts(const Model& m, int batch, int last);
 // The first op of those that enqueue_classify_out computes on the result's way out; the number of ops where it computes none, as in
 // the layer-by-layer plan (strait_ctx_set_pair_fusion).  Asked once per batch (Ticket::out_first), so that its sequence, also one in segments or a captured
 // one, ends where the launch behind it begins.

@@ -884,7 +884,11 @@ def test_a_large_batch_begun_while_its_input_is_on_the_way(ctx, arch, kw, batch)
                                            ("encoder", dict(layers=3, hidden=128, heads=2, ffn=256, seq=40), 1001),
                                            ("encoder", dict(layers=2, hidden=768, heads=12, ffn=3072, seq=128), 50),
                                            ("mobilenet_v2", dict(hw=96), 171), ("mobilenet_v2", dict(hw=224), 64),
-                                           ("vgg19", dict(hw=64, classes=50, fc=64), 389)])
+                                           ("vgg19", dict(hw=64, classes=50, fc=64), 389),
+                                           # images' bytes and tokens' statistics that are no multiples of 16
+                                           ("mobilenet_v2", dict(hw=250), 64), ("mobilenet_v2", dict(hw=226), 57), ("tiny_cnn", dict(hw=30), 1801),
+                                           ("encoder", dict(layers=2, hidden=64, heads=1, ffn=256, seq=37), 2001),
+                                           ("vit", dict(hw=224, classes=100, layers=2, hidden=192, heads=3, ffn=768), 33)])
 def test_a_batch_in_parts_gives_the_bytes_of_the_whole(ctx, arch, kw, batch):
     """Whether a staged batch of 9 MB and more goes in parts depends on what else is on its way.  Its result does not: parts take kernels that add in the whole batch's order."""
     S = ctx.S

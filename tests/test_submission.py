@@ -1,0 +1,87 @@
+"""What is enqueued for a batch, and what its record says of it: host code, followed without a GPU.  tests/native/runtime_standin.cpp stands in for the HIP runtime and
+keeps time: a kernel takes 5 us, a stamp 2, the host link brings 53 bytes a ns, the host takes none.  Every program runs in a process of its own.
+"""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2604_28175_amd", "csrc")
+CLANG = "/opt/rocm/llvm/bin/clang++"
+pytestmark = pytest.mark.skipif(not os.path.exists(CLANG), reason="ROCm clang++ not found")
+
+SETUP = """
+import ctypes, sys
+standin = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)            # ahead of the runtime that the library brings along
+sys.path.insert(0, sys.argv[2])
+import numpy as np
+import paper_2604_28175_amd as S
+from paper_2604_28175_amd import binding
+import synth
+standin.standin_notes.restype = ctypes.c_char_p
+standin.standin_advance.argtypes = [ctypes.c_longlong]
+HP, LP, COPY = [0x1000], [0x2000], [0x3000, 0x4000]                     # streams: names, for the stand-in
+def context(n_copy=2):
+    d = binding.CtxDesc()
+    d.device, d.n_hp, d.n_lp, d.n_copy = 0, 1, 1, n_copy
+    d.hp_streams[0], d.lp_streams[0] = HP[0], LP[0]
+    for i in range(n_copy):
+        d.copy_streams[i] = COPY[i]
+    c = S.Context.__new__(S.Context)
+    c.handle = ctypes.c_void_p()
+    assert binding.lib.strait_ctx_create(ctypes.byref(d), ctypes.byref(c.handle)) == 0
+    return c
+def notes(clear=True):
+    n = [l.split() for l in standin.standin_notes().decode().splitlines()]
+    if clear:
+        standin.standin_reset()
+    return n
+def lengths(md, batch):
+    return np.full(batch, md.hyper[4], np.int32) if md.arch == synth.ARCH_ENCODER else None
+"""
+
+
+@pytest.fixture(scope="session")
+def standin(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("standin") / "standin.so")
+    subprocess.run([CLANG, "-std=c++17", "-O1", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC,
+                    os.path.join(ROOT, "tests", "native", "runtime_standin.cpp"), "-o", lib], check=True)
+    return lib
+
+
+def run(standin, program):
+    r = subprocess.run([sys.executable, "-c", SETUP + program, standin, ROOT], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
+    return r.stdout
+
+
+def test_parts_of_a_large_batch_begin_on_16_bytes(standin):
+    """Images whose bytes, and token sequences whose statistics, are no multiples of 16: every staged batch of 9 MB and more is taken, in parts that the kernels can
+    read, or whole."""
+    out = run(standin, """
+c = context()
+took = {}
+for name, md, batches in (("250", synth.mobilenet_v2(1, hw=250), list(range(24, 129))), ("226", synth.mobilenet_v2(1, hw=226), list(range(28, 129))),
+                          ("30", synth.tiny_cnn(1, hw=30), [1746, 1747, 1801, 2500, 3000]), ("1250", synth.mobilenet_v2(1, hw=1250), [1, 2, 3, 4, 5, 9]),
+                          ("sequences of 37", synth.encoder(1, layers=2, hidden=64, heads=1, ffn=256, seq=37), [2000, 2001, 2350]),
+                          ("197 tokens of 192", synth.vit(1, hw=224, classes=100, layers=2, hidden=192, heads=3, ffn=768), list(range(31, 40)))):
+    m = c.load(synth.pack(md), max(batches), 1)
+    for b in batches:
+        notes()
+        m.wait(m.submit(S.PRIO_LOW, m.staging(0, b), lengths(md, b), m.new_output(b)))
+        standin.standin_idle()
+        n = notes()
+        sent = [int(l[1]) for l in n if l[0] == "memcpy"]
+        assert sum(sent) in (m.io_bytes(b)[0], 0), (name, b, sent)
+        one = m.io_bytes(1)[0]
+        assert all(s % one == 0 for s in sent)
+        took[name] = max(took.get(name, 0), len(sent))
+        starts = [sum(sent[:i]) for i in range(len(sent))]
+        assert all(s % 16 == 0 for s in starts), (name, b, starts)
+    m.free()
+print(took)
+assert took["250"] > 3 and took["226"] > 3 and took["30"] > 1 and took["sequences of 37"] > 1 and took["197 tokens of 192"] > 1
+""")
+    print(out)
