@@ -604,8 +604,9 @@ static int send_input(const strait_model* m, Instance& in, int batch, const void
             if (k == 0 && launch_stamp(in.ctl_dev, STAMP_PIECES, s, lsrc, ldst, part ? lens : 0)) return STRAIT_E_HIP;
             if (timing->last_timed && launch_stamp(in.ctl_dev, STAMP_LAST, s)) return STRAIT_E_HIP;
             HIP_TRY(hipMemcpyAsync((char*)in.dev_in + at, (const char*)in.pinned_in + at, n, hipMemcpyHostToDevice, s));
-            if (part) HIP_TRY(hipEventRecord(in.ev_h2d, s));
             if (last && launch_stamp(in.ctl_dev, STAMP_PIECES + 1, s, lsrc, ldst, part ? 0 : lens)) return STRAIT_E_HIP;
+            // (behind the stamp: the record is read, and the instance given to another batch, once the kernels that wait for this event are done)
+            if (part) HIP_TRY(hipEventRecord(in.ev_h2d, s));
         }
         if (part) {
             lk.unlock();

@@ -85,3 +85,28 @@ print(took)
 assert took["250"] > 3 and took["226"] > 3 and took["30"] > 1 and took["sequences of 37"] > 1 and took["197 tokens of 192"] > 1
 """)
     print(out)
+
+
+def test_the_kernels_wait_for_the_input_s_end_stamp(standin):
+    """The stamp that ends an input's transfer lies in front of what the compute stream waits for: a record that is read when the result is there holds this batch's, and a
+    later batch's is not written over."""
+    run(standin, """
+c = context()
+md = synth.mobilenet_v2(1)
+m = c.load(synth.pack(md), 64, 1)
+x = np.zeros((64, 224, 224, 3), np.float16)
+for staged in (True, False):
+    for prio in (S.PRIO_LOW, S.PRIO_HIGH):
+        notes()
+        m.wait(m.submit(prio, m.staging(0, 64) if staged else x, None, m.new_output(64)))
+        standin.standin_idle()
+        n = notes()
+        end = [i for i, l in enumerate(n) if l[:2] == ["stamp", "9"]]                # (8 and 9: a transfer's start and end)
+        assert len(end) == 1
+        stream, done = n[end[0]][2], int(n[end[0]][3]) + 2000
+        records = [l for l in n[end[0]:] if l[0] == "record" and l[2] == stream]
+        assert records and int(records[0][3]) >= done, (staged, n[end[0] - 3:end[0] + 3])
+        waits = [l for l in n[end[0]:] if l[0] == "wait" and l[1] == records[0][1]]
+        assert waits and int(waits[-1][3]) >= done
+        assert sum(l[0] == "memcpy" for l in n) > 1
+""")
