@@ -1316,15 +1316,17 @@ static std::vector<std::pair<int, int>> live_at(const Model& m, int cut) {
 // Whether a batch's layers in front of `cut` can be computed part by part before the rest is computed for all of it: no launch spans the cut, the tensors that are alive there lie in
 // activation buffers (or are the input), and no part writes where an earlier part's lie.  Sample i of a tensor of e elements lies at i e of its buffer: a part that begins at
 // sample i writes from i e' on, which is behind all that the samples before it left there if e' >= e for every tensor that the layers in front put into that buffer.
-// No product in front normalises rows by their statistics: the compiler rounds its sums to fp16 in one step in some of a tile's rows and in two in others (5 of 100000 outputs of a
-// 6327 x 384 x 128 product differ when its rows move by 32), and a part's rows lie elsewhere in their tiles than the whole batch's.
+// No product without GELU in front normalises its input by the rows' statistics: the compiler rounds those sums to fp16 in one step in some of a tile's rows and in two in others (5 of
+// 100000 outputs of a 6327 x 384 x 128 product differ when its rows move by 32), and a part's rows lie elsewhere in their tiles than the whole batch's.  (All other
+// products and layers give a row the same bits wherever it lies.)
 static bool can_cut(const Model& m, int cut) {
     auto size = [&](int i) { return (size_t)m.ops[i].P * m.ops[i].Q * m.ops[i].K; };
     for (int i = 0; i < cut; ++i) {
         const Op& op = m.ops[i];
         if (op.out < 0 || i + op.pair >= cut || op.stem_next >= cut || op.proj_of >= cut || (op.dw_next && i + 1 >= cut) || (op.kind == OP_PACK && i + 1 >= cut) ||
-            op.ln_in >= 0 || op.ln_res >= 0) return false;
+            (op.ln_in >= 0 && op.act != ACT_GELU)) return false;
     }
+    if (cut < (int)m.ops.size() && m.ops[cut - 1].kind == OP_CONV && m.ops[cut - 1].ln_in >= 0 && m.ops[cut].kind == OP_CONV) return false;     // (laid out in slices of all rows)
     for (const auto& t : live_at(m, cut)) {
         if (t.second < 0) return false;
         for (int i = 0; i < cut; ++i)
