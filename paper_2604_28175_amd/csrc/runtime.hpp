@@ -162,7 +162,7 @@ struct Ticket {
     bool k0_stamped = false;           // kernel start has a stamp of its own (else it is the end of the input copy)
     unsigned seq = 0;
     InputTiming input;
-    bool by_copy_stream = false;       // counted in Context::copy_outstanding
+    int copies = 0;                    // copy streams that bring its input, from `copy` on (Context::copy_outstanding); 2: in parts
     size_t worker = 0;                 // index of its compute stream in Context::workers
     size_t copy = 0;                   // index of its copy stream in Context::copy
     unsigned chunks = 0;               // of its result
@@ -203,6 +203,7 @@ struct Context {
     long long proj_min_pixels = 1;          // the same for pairs that absorb a projection shortcut: three launches become one
     long long pair_min_pixels = 40000;      // from this many output pixels on, marked pairs of pointwise convolutions run as one launch (0 = never)
     int lp_yield_layers = 0;                // > 0: low-priority batches are issued in segments of this many layers and yield between them
+    std::atomic<int> low_in_parts{0};       // low-priority batches whose input came in parts, over two copy streams, and whose result has not arrived
     std::atomic<int> hp_in_flight{0};       // high-priority batches submitted and not yet complete
     bool branch_streams = true;             // independent branches of a plan go to the instance's side stream
     size_t h2d_kernel_limit = 8u << 20;   // inputs up to this size go in by a copy kernel, larger ones by hipMemcpyAsync

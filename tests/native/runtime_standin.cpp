@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -11,6 +12,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <vector>
 
 #include "kernels.hpp"
 #include "small_net.hpp"
@@ -23,6 +25,8 @@ static std::map<const void*, long long> stream_ns, event_ns;
 static long long link_ns, now_ns;                          // the link is free, the host is there
 static std::string notes;
 static thread_local struct { dim3 grid, block; size_t lds; hipStream_t stream; } call;
+static std::atomic<bool> held{false};                      // results are not there yet
+static std::vector<std::pair<uint32_t*, uint32_t>> to_set;
 static char streams_made[64];
 static int n_streams_made;
 
@@ -39,6 +43,10 @@ static long long& clock_of(hipStream_t s) {
     long long& t = stream_ns[s];
     return t = std::max(t, now_ns);
 }
+static void set_flag(uint32_t* flag, uint32_t seq) {
+    if (held) to_set.push_back({flag, seq});
+    else __atomic_store_n(flag, seq, __ATOMIC_RELEASE);
+}
 static void stamp(HostControl* ctl, int which, long long ns) { ctl->stamp[which] = (uint64_t)(ns / 10); }
 static long long transfer(hipStream_t s, size_t bytes) {   // returns its start
     long long& t = clock_of(s);
@@ -49,12 +57,24 @@ static long long transfer(hipStream_t s, size_t bytes) {   // returns its start
 
 extern "C" {
 
-const char* standin_notes() { return notes.c_str(); }
-void standin_reset() { notes.clear(); }
+const char* standin_notes() {                              // since it was asked last
+    static std::string given;
+    std::lock_guard<std::mutex> lk(mu);
+    given = std::move(notes);
+    notes.clear();
+    return given.c_str();
+}
 void standin_idle() {                                      // everything that was enqueued is done
+    std::lock_guard<std::mutex> lk(mu);
     for (auto& s : stream_ns) now_ns = std::max(now_ns, s.second);
 }
-void standin_advance(long long ns) { now_ns += ns; }
+void standin_hold() { held = true; }
+void standin_release() {
+    std::lock_guard<std::mutex> lk(mu);
+    held = false;
+    for (auto& f : to_set) __atomic_store_n(f.first, f.second, __ATOMIC_RELEASE);
+    to_set.clear();
+}
 
 void** __hipRegisterFatBinary(const void*) { static void* module; return &module; }
 void __hipUnregisterFatBinary(void**) {}
@@ -73,7 +93,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
     auto is = [&](const char* part) { return name.find(part) != std::string::npos; };
     auto finished = [&](HostControl* ctl, unsigned chunks, unsigned seq, long long ns) {
         stamp(ctl, STAMP_DONE, ns);
-        for (unsigned c = 0; c < chunks; ++c) __atomic_store_n(&ctl->flag[c], seq, __ATOMIC_RELEASE);
+        for (unsigned c = 0; c < chunks; ++c) set_flag(&ctl->flag[c], seq);
     };
     long long& t = clock_of(s);
     if (is("stamp_kernel")) {
@@ -83,7 +103,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
         if (n4) memcpy(*(void**)args[3], *(void**)args[2], n4 * 4);
         note("stamp %d %p %lld", which, (void*)s, t);
         stamp(ctl, which, t);
-        if (seq) __atomic_store_n(&ctl->k1_seq, seq, __ATOMIC_RELEASE);
+        if (seq) set_flag(&ctl->k1_seq, seq);
         t += 2000;
     } else if (is("copy_in_kernel")) {
         HostControl* ctl = *(HostControl**)args[6];
@@ -154,7 +174,7 @@ hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return held ? hipErrorNotReady : hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 }

@@ -21,7 +21,6 @@ import paper_2604_28175_amd as S
 from paper_2604_28175_amd import binding
 import synth
 standin.standin_notes.restype = ctypes.c_char_p
-standin.standin_advance.argtypes = [ctypes.c_longlong]
 HP, LP, COPY = [0x1000], [0x2000], [0x3000, 0x4000]                     # streams: names, for the stand-in
 def context(n_copy=2):
     d = binding.CtxDesc()
@@ -33,11 +32,8 @@ def context(n_copy=2):
     c.handle = ctypes.c_void_p()
     assert binding.lib.strait_ctx_create(ctypes.byref(d), ctypes.byref(c.handle)) == 0
     return c
-def notes(clear=True):
-    n = [l.split() for l in standin.standin_notes().decode().splitlines()]
-    if clear:
-        standin.standin_reset()
-    return n
+def notes():
+    return [l.split() for l in standin.standin_notes().decode().splitlines()]
 def lengths(md, batch):
     return np.full(batch, md.hyper[4], np.int32) if md.arch == synth.ARCH_ENCODER else None
 """
@@ -109,4 +105,42 @@ for staged in (True, False):
         waits = [l for l in n[end[0]:] if l[0] == "wait" and l[1] == records[0][1]]
         assert waits and int(waits[-1][3]) >= done
         assert sum(l[0] == "memcpy" for l in n) > 1
+""")
+
+
+def test_a_batch_in_parts_counts_on_both_copy_streams(standin):
+    """While a low-priority batch's parts are on both copy streams, another input finds neither of them empty, and a small high-priority one goes in on its compute
+    stream, also where that has work: on a copy stream it would wait for half of the parts.  Everything is counted down again."""
+    run(standin, """
+c = context()
+md, small = synth.mobilenet_v2(1), synth.resnet50(1)
+lp = c.load(synth.pack(md), 128, 1)
+big = c.load(synth.pack(md), 64, 2)
+hp = c.load(synth.pack(small), 8, 3)
+x = np.zeros((64, 224, 224, 3), np.float16)
+for again in range(2):
+    notes()
+    standin.standin_hold()
+    a = hp.submit(S.PRIO_HIGH, hp.staging(0, 8), None, hp.new_output(8))
+    l = lp.submit(S.PRIO_LOW, lp.staging(0, 128), None, lp.new_output(128))
+    assert sum(n[0] == "memcpy" for n in notes()) > 4
+    b = hp.submit(S.PRIO_HIGH, hp.staging(1, 8), None, hp.new_output(8))             # behind the first, on a stream that is not idle
+    assert [n[2] for n in notes() if n[0] == "copy_in"] == ["0x1000"]
+    o = big.submit(S.PRIO_LOW, x, None, big.new_output(64))                          # ordinary memory: pieces only where the stream is empty
+    sent = [n for n in notes() if n[0] == "memcpy"]
+    assert len(sent) == 1, sent
+    standin.standin_release()
+    for m, t in ((hp, a), (hp, b), (lp, l), (big, o)):
+        m.wait(t)
+    standin.standin_idle()
+    notes()
+    big.wait(big.submit(S.PRIO_LOW, x, None, big.new_output(64)))
+    assert sum(n[0] == "memcpy" for n in notes()) > 1                                # alone again
+    standin.standin_hold()
+    a = hp.submit(S.PRIO_HIGH, hp.staging(0, 8), None, hp.new_output(8))
+    b = hp.submit(S.PRIO_HIGH, hp.staging(1, 8), None, hp.new_output(8))
+    standin.standin_release()
+    assert [n[2] in ("0x3000", "0x4000") for n in notes() if n[0] == "copy_in"] == [False, True]
+    hp.wait(a), hp.wait(b)
+    standin.standin_idle()
 """)
