@@ -21,6 +21,7 @@
 #include <functional>
 #include <new>
 
+#include "phases.hpp"
 #include "runtime.hpp"
 
 namespace strait {
@@ -692,7 +693,7 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
         // 64 images 3115 -> 3031, encoder 64 sequences 2787 -> 2757.
         // An input that is not staged waits for the host's copying, which these launches would hold up; a captured kernel sequence is one piece.
         Parts parts;
-        if (host_in == in.pinned_in && !yielding && !by_kernel && !c->use_graphs && c->copy.size() > 1 && w->outstanding.load(std::memory_order_acquire) == 0)
+        if (host_in == in.pinned_in && !yielding && !by_kernel && !c->use_graphs && !InputFirst::wanted() && c->copy.size() > 1 && w->outstanding.load(std::memory_order_acquire) == 0)
             parts = plan_parts(*m, batch, t->out_first);
         if (parts.layers) {
             std::atomic<int>& second = c->copy_outstanding[(cidx + 1) % c->copy.size()];

@@ -8,7 +8,7 @@
 // batches, scatter the outputs and report the measured kernel latency and transfer time to the policy.
 //
 // Layering: this file uses the library's own C entry points (strait_model_*, strait_submit, strait_wait,
-// strait_sched_*) and nothing beneath them.
+// strait_sched_*) and nothing beneath them but the wish that inputs come first (phases.hpp).
 #include <time.h>
 
 #include <algorithm>
@@ -26,6 +26,7 @@
 
 #include "../../include/strait.h"
 #include "kernels.hpp"
+#include "phases.hpp"
 
 using strait::set_error;
 
@@ -136,6 +137,7 @@ struct strait_server {
         int rc = strait_model_staging(mq.d.model, b.instance, &stage, &cap);
         if (rc != STRAIT_OK) return rc;
         for (int i = 0; i < n; ++i) memcpy((char*)stage + (size_t)i * mq.in1, b.reqs[i].in, mq.in1);
+        const strait::InputFirst in_order;
         return strait_submit(mq.d.model, (strait_priority)mq.d.priority, n, stage, b.valid.data(),
                              mq.out_buf[b.instance].data(), &b.ticket);
     }
@@ -388,6 +390,7 @@ strait_status strait_server_start(strait_server* s) {
         // replay switched on in the context, the second run captures that key's graph), then every instance of every model
         // is submitted at once, three times over (the runtime grows its per-stream pools the first time streams are
         // that deep, which stalls the submitting thread for milliseconds).
+        const strait::InputFirst in_order;
         std::vector<strait_ticket> burst;
         for (auto& kv : s->models) {
             ModelQ& mq = kv.second;
@@ -546,6 +549,7 @@ strait_status strait_model_profile(strait_model* m, strait_priority prio, int32_
     std::vector<int32_t> valid(batch, arch == STRAIT_ARCH_ENCODER ? hyper[4] : 0);
     std::vector<double> t_inf, t_h2d, t_ker;
     const int warm = 3;
+    const strait::InputFirst in_order;
     for (int i = 0; i < warm + reps; ++i) {
         strait_ticket tk = nullptr;
         rc = strait_submit(m, prio, batch, stage, valid.data(), host_out.data(), &tk);

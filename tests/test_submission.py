@@ -163,3 +163,44 @@ for md, batch in ((synth.mobilenet_v2(1), 64), (synth.mobilenet_v2(1), 128), (sy
         assert parts > 1 or not staged
     m.free()
 """)
+
+
+def test_what_the_scheduling_policy_is_fed_is_a_transfer_and_then_kernels(standin):
+    """The policy adds a batch's transfer to its kernels (Eq. 1 to 3, 6).  Profiles, and batches of the serving front end, are not begun before their input is complete."""
+    run(standin, """
+c = context()
+md, batch = synth.mobilenet_v2(1), 64
+m = c.load(synth.pack(md), batch, 1)
+def kernels_us(n):
+    first, last = [i for i, l in enumerate(n) if l[0] == "memcpy"][0], [i for i, l in enumerate(n) if l[0] == "memcpy"][-1]
+    return 5 * sum(l[0] == "kernel" for l in n), first == last
+notes()
+m.wait(m.submit(S.PRIO_LOW, m.staging(0, batch), None, m.new_output(batch)))         # a program's own: in parts
+standin.standin_idle()
+parted, whole = kernels_us(notes())
+assert not whole
+p = S.profile_model(m, S.PRIO_LOW, batch, 1)
+n = notes()
+us = 5 * sum(l[0] == "kernel" for l in n) / 4                                       # three to warm up, one that counts
+assert sum(l[0] == "memcpy" for l in n) == 4
+assert abs(p.t_kernel_isol_ns - 1e3 * us) <= 2e3 + 10 and us < parted, (p.t_kernel_isol_ns, us, parted)
+standin.standin_idle()
+sched = S.Scheduler(1)
+profs = [(1e6, 1000, 1e6, [0.1] * 5, 0.1, 0.1)] * batch
+sched.set_profile(7, S.PRIO_LOW, profs)
+srv = S.Server(sched, 2, 100000)
+srv.add_model(m, 7, S.PRIO_LOW, batch, 10_000_000_000, 50_000_000)
+x, out = np.zeros((batch, 224, 224, 3), np.float16), np.zeros((batch, m.io_bytes(1)[1]), np.uint8)
+srv.start()
+warm = notes()
+assert max(int(l[1]) for l in warm if l[0] == "memcpy") == m.io_bytes(batch)[0]
+for i in range(batch):
+    srv.request(7, x[i], out[i])
+srv.wait_idle(20.0)
+n = notes()
+assert sum(int(l[1]) for l in n if l[0] == "memcpy") == m.io_bytes(batch)[0]
+assert sum(l[0] == "memcpy" for l in n) == 1, [l for l in n if l[0] == "memcpy"]
+r = srv.results()
+assert len(r) == batch and all(q.status == 0 and q.batch == batch for q in r), [(q.status, q.batch) for q in r]
+srv.stop()
+""")
