@@ -51,6 +51,13 @@ static int64_t now_ns() {
 // four of those, so two copy streams may be one queue), the next batches' inputs for instance.
 static const size_t kOutOnCopyStream = 4u << 20;
 
+// Whether a batch's result, on its way out, has another batch's kernels beside it: another compute stream's, or, on a copy stream, its own stream's next one's.
+static bool others_run(Context* ctx, const Ticket* t) {
+    for (size_t i = 0; i < ctx->workers.size(); ++i)
+        if (ctx->workers[i]->outstanding.load(std::memory_order_acquire) > (i == t->worker && t->out_pending ? 1 : 0) && (i != t->worker || t->out_pending)) return true;
+    return false;
+}
+
 // Enqueues the result's way out behind the kernel sequence on `s`.
 static int enqueue_output(Model& m, Instance& in, Ticket* t, hipStream_t s) {
     const size_t bytes = m.out_bytes(t->batch);
@@ -59,7 +66,7 @@ static int enqueue_output(Model& m, Instance& in, Ticket* t, hipStream_t s) {
     t->out_pending = bytes >= kOutOnCopyStream;
     if (t->out_pending) return launch_stamp(in.ctl_dev, STAMP_K1, s, nullptr, nullptr, 0, t->seq);
     if (t->out_first < (int)m.ops.size()) return enqueue_classify_out(m, in, t->batch, t->out_first, s, t->hp, t->seq);
-    return launch_copy_out(in.dev_out, in.pinned_out_dev, bytes, in.ctl_dev, in.counters + 1, t->seq, false, t->hp, s);
+    return launch_copy_out(in.dev_out, in.pinned_out_dev, bytes, in.ctl_dev, in.counters + 1, t->seq, false, t->hp, others_run(m.ctx, t), s);
 }
 
 // A yielding low-priority batch (strait_ctx_set_lp_yield): its kernel sequence is enqueued by the stream's worker thread
@@ -140,7 +147,7 @@ static int await_result(Context* ctx, StreamWorker* w, Ticket* t, int64_t* done)
         if (await_flag(&in.ctl->k1_seq, t->seq, w->stream, ctx->compute_mu[t->worker])) return STRAIT_E_HIP;
         std::lock_guard<std::mutex> lk(ctx->copy_mu[t->copy]);
         ++ctx->copy_seq[t->copy];
-        if (launch_copy_out(in.dev_out, in.pinned_out_dev, t->model->out_bytes(t->batch), in.ctl_dev, in.counters + 1, t->seq, true, t->hp, s)) return STRAIT_E_HIP;
+        if (launch_copy_out(in.dev_out, in.pinned_out_dev, t->model->out_bytes(t->batch), in.ctl_dev, in.counters + 1, t->seq, true, t->hp, others_run(ctx, t), s)) return STRAIT_E_HIP;
     }
     if (t->chunks > 1) {
         std::lock_guard<std::mutex> lk(ctx->mu);

@@ -57,9 +57,10 @@ int launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {
 // thread a chain of 2.3 us kernels beside a copy of 2.4 MB took 22 us a kernel, that is, stood still, and the copy 48.5 us; 80 KB under way still fill the link:
 //   workgroups of 256, one load a thread    32         24         20         16         12
 //   copy us, chain us a kernel              45.1 10.1  45.3 8.1   46.0 7.0   49.1 6.6   63.6 6.4
-// and on the way out, four stores a thread  16: 44.7 5.5   8: 45.3 3.7   4: 53.4 2.9.  128 requests served by two models side by side 4.55 -> 4.25 ms, eight images
+// and on the way out, four stores a thread  16: 44.7 5.5   8: 45.3 3.7   4: 53.4 2.9.  Where no other stream has a batch 16 do it: with 8 a workgroup's waits, for what it loads
+// and behind each part for its stores, leave the link idle (eight sequences' 1.6 MB 34.9 -> 30.2 us, 64 sequences' 12.6 MB 253 -> 229).  128 requests served by two models side by side 4.55 -> 4.25 ms, eight images
 // of ResNet-50 alone 485 -> 477 us.
-constexpr unsigned COPY_IN_BLOCKS = 20, COPY_OUT_BLOCKS = 8;
+constexpr unsigned COPY_IN_BLOCKS = 20, COPY_OUT_BLOCKS = 16, COPY_OUT_BLOCKS_BESIDE = 8;
 __device__ __forceinline__ void copy_range(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, size_t n4, unsigned block, unsigned blocks) {
     const size_t n16 = n4 >> 2;
     const size_t step = (size_t)blocks * 256;
@@ -162,7 +163,7 @@ __global__ void __launch_bounds__(256) copy_out_kernel(const char* __restrict__ 
         }
     }
 }
-int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, hipStream_t stream) {
+int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, bool beside, hipStream_t stream) {
     if (!src || !dst || !ctl || !counters || bytes == 0 || (bytes & 3) ||
         ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15)) {
         set_error("copy out: 16-byte aligned buffers and a multiple of 4 bytes required"); return -1;
@@ -170,7 +171,7 @@ int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, 
     const size_t chunk = out_chunk_bytes(bytes), part = chunk / OUT_PARTS;
     const unsigned chunks = (unsigned)((bytes + chunk - 1) / chunk);
     const unsigned parts = (unsigned)((bytes + part - 1) / part);
-    const unsigned blocks = std::min(parts, COPY_OUT_BLOCKS);
+    const unsigned blocks = std::min(parts, beside ? COPY_OUT_BLOCKS_BESIDE : COPY_OUT_BLOCKS);
     hipLaunchKernelGGL(copy_out_kernel, dim3(blocks), dim3(256), 0, stream, (const char*)src, (char*)dst, bytes, part, parts, chunks, ctl, counters, seq,
                        k1_taken ? 1 : 0, hp);
     STRAIT_CHECK_LAUNCH("copy out");

@@ -216,7 +216,8 @@ struct ClassifyOut {
 bool classify_out_takes(long long rows, int n);
 bool classify_out_pools(int HW, int C, int n);
 int launch_classify_out(const ClassifyOut& p, hipStream_t stream);
-int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, hipStream_t stream);
+// beside: another stream has a batch, whose launches this one's requests hold up
+int launch_copy_out(const void* src, void* dst, size_t bytes, HostControl* ctl, unsigned* counters, unsigned seq, bool k1_taken, int hp, bool beside, hipStream_t stream);
 
 void set_error(const char* fmt, ...);
 

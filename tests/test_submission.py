@@ -204,3 +204,33 @@ r = srv.results()
 assert len(r) == batch and all(q.status == 0 and q.batch == batch for q in r), [(q.status, q.batch) for q in r]
 srv.stop()
 """)
+
+
+def test_a_result_leaves_by_sixteen_workgroups_where_nothing_runs_beside_it(standin):
+    """Eight leave the launches of other streams' batches alone, but take up to 15 % longer."""
+    run(standin, """
+c = context()
+md, small = synth.encoder(1, layers=1), synth.resnet50(1)
+m, hp = c.load(synth.pack(md), 64, 3), c.load(synth.pack(small), 8, 1)
+def out_grids():
+    return [int(l[-1]) for l in notes() if l[0] == "copy_out" and int(l[1]) > 1 << 20]
+def batch(i, b):
+    return m.submit(S.PRIO_LOW, m.staging(i, b), lengths(md, b), m.new_output(b))
+for b in (8, 64):                                                                    # behind its kernels; on a copy stream
+    notes()
+    m.wait(batch(0, b))
+    assert out_grids() == [16], b
+    standin.standin_hold()
+    two = [batch(i, b) for i in range(2)]                                            # one behind the other on one stream
+    standin.standin_release()
+    for t in two:
+        m.wait(t)
+    assert out_grids() == [16, 16] if b == 8 else 8 in out_grids(), b                # (of the second nothing is left when the first is through, or it is)
+    standin.standin_idle()
+standin.standin_hold()
+h = hp.submit(S.PRIO_HIGH, hp.staging(0, 8), None, hp.new_output(8))
+t = batch(0, 8)
+standin.standin_release()
+m.wait(t), hp.wait(h)
+assert out_grids() == [8]
+""")
