@@ -14,19 +14,21 @@ enum Act { ACT_NONE = 0, ACT_RELU = 1, ACT_RELU6 = 2, ACT_GELU = 3 };
 
 // Division by a number that is the same for a whole launch, prepared on the host: n / d = floor(2 n mul / 2^32) >> shift, exact for 0 <= n < 2^31 and
 // 1 <= d < 2^31 (shift = ceil(log2 d), mul = floor(2^(31 + shift) / d) + 1: the error, less than 2 n d / 2^(32 + shift) <= n / 2^31 of one, reaches no next
-// quotient).  A division by an unknown number is 30 to 40 instructions that depend on each other, at one wavefront per SIMD 100 ns; a launch of a
+// quotient); by more it is 0.  A division by an unknown number is 30 to 40 instructions that depend on each other, at one wavefront per SIMD 100 ns; a launch of a
 // small batch, 4 to 6 us long, began with four to eleven of them.
 struct Divisor { unsigned mul, shift; };
 inline Divisor divisor(long long d) {
     Divisor r{1u, 0u};
     if (d < 1) return r;
+    if (d > 0x7fffffffLL) return {0u, 0u};
     while ((1LL << r.shift) < d) ++r.shift;
     r.mul = (unsigned)((1ULL << (31 + r.shift)) / (unsigned long long)d + 1);
     return r;
 }
 #ifdef __HIPCC__
-__host__ __device__ inline int divide(int n, Divisor d) { return (int)((unsigned)(((unsigned long long)((unsigned)n << 1) * d.mul) >> 32) >> d.shift); }
+__host__ __device__
 #endif
+inline int divide(int n, Divisor d) { return (int)((unsigned)(((unsigned long long)((unsigned)n << 1) * d.mul) >> 32) >> d.shift); }
 // Tiles are numbered down groups of cw tile columns (row-major inside a group), so that the contiguous range an XCD gets covers a rectangle of about equal
 // extent in pixels and channels: its L2 then fetches the fewest operand rows.  Of `full` whole groups and one of the `last` columns.
 struct TileOrder { int tiles, cw, full, last, group; Divisor by_tiles, by_group, by_cw, by_last; };   // group: tiles of a whole one
