@@ -24,7 +24,7 @@ static void check(long long d) {
         }
     };
     for (long long k = 0; k < 64; ++k) { one(k); one(0x7fffffffLL - k); }
-    for (long long m = 1; m <= 16; ++m)                    // on both sides of multiples: the first, the last, and some
+    for (long long m = 1; m <= 16 && d <= 0x7fffffffLL; ++m)     // on both sides of multiples: the first, the last, and some
         for (long long e = -1; e <= 1; ++e) { one(m * d + e); one((0x7fffffffLL / d - m + 1) * d + e); }
     for (int k = 0; k < 64; ++k) {
         one(next_random());
