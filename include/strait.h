@@ -103,7 +103,7 @@ typedef struct {
     int64_t t_issued_ns;       /* host time when everything had been enqueued               */
     int64_t t_done_ns;         /* host time the result was seen to be in host memory        */
     float h2d_ms;              /* input copy: its own time on the link, without waits between the pieces it travels in */
-    float kernel_ms;           /* first kernel start to last kernel end (of a batch that is begun before its input is complete: without the waits for the rest of it) */
+    float kernel_ms;           /* first kernel start to last kernel end (of a large batch's: before its input is complete) */
     float d2h_ms;              /* output copy (that of 4 MB or more starts some us after the kernels, which only total_ms holds) */
     float total_ms;            /* start of input copy to end of output copy                 */
 } strait_record;
@@ -179,8 +179,8 @@ strait_status strait_ctx_set_branch_streams(strait_ctx* ctx, int32_t enabled);
  * serving the asynchronous copy call of such sizes was measured to block its caller for milliseconds
  * now and then, a kernel launch never.  0 = always hipMemcpyAsync.
  * A staged input of 9 MB or more that goes by hipMemcpyAsync with nothing else on the way (n_copy > 1, no graphs, no yielding) travels in parts over two copy
- * streams, and where the plan allows it the batch's first layers are computed for each part as it arrives: h2d_ms, kernel_ms and d2h_ms then add up to more than total_ms.  Not what the
- * front end (strait_server) and strait_model_profile submit: the scheduling policy takes a batch for a transfer and then kernels. */
+ * streams, and where the plan allows it the batch's first layers are computed for each part as it arrives: kernel_ms, from the first part's arrival on, and h2d_ms then overlap.  Not
+ * what the front end (strait_server) and strait_model_profile submit: the scheduling policy takes a batch for a transfer and then kernels. */
 strait_status strait_ctx_set_h2d_kernel_limit(strait_ctx* ctx, int64_t max_bytes);
 
 strait_status strait_model_load(strait_ctx* ctx, const strait_model_desc* desc, strait_model** out);

@@ -208,11 +208,6 @@ static void complete_ticket(Context* ctx, StreamWorker* w, Ticket* t) {
             t->rec.h2d_ms = link_ms(it, start, ms(piece[0], piece[1]), it.last_timed ? ms(st[STAMP_LAST], piece[1]) : 0.f);
         }
         t->rec.kernel_ms = ms(k0, st[STAMP_K1]);
-        if (t->copies > 1) {                           // in parts: without the waits for the next one
-            const volatile uint64_t* part = st + STAMP_PARTS;
-            t->rec.kernel_ms = ms(part[2 * it.pieces - 2], st[STAMP_K1]);
-            for (int i = 0; i + 1 < it.pieces; ++i) t->rec.kernel_ms += ms(part[2 * i], part[2 * i + 1]);
-        }
         t->rec.d2h_ms = ms(st[t->out_pending ? STAMP_D2H0 : STAMP_K1], st[STAMP_DONE]);
         t->rec.total_ms = ms(piece[0], st[STAMP_DONE]);
     }
@@ -711,12 +706,11 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
                 lead = parts.layers;
                 t->copies = 2;
                 if (prio == STRAIT_PRIO_LOW) c->low_in_parts.fetch_add(1, std::memory_order_acq_rel);
-                int stamp = STAMP_PARTS;
                 return send_input(m, in, batch, host_in, valid_len, false, true, (int)cidx, cs, &t->input, parts, [&](int first, int end) {
                     if (!slk.owns_lock()) slk.lock();
-                    int r = hipStreamWaitEvent(s, in.ev_h2d, 0) == hipSuccess ? launch_stamp(in.ctl_dev, stamp++, s) : STRAIT_E_HIP;
-                    if (!r) r = run_plan(*m, in, end - first, s, t->hp, lead - 1, false, 0, false, first, batch);
-                    if (!r && end < batch) r = launch_stamp(in.ctl_dev, stamp++, s);
+                    if (hipStreamWaitEvent(s, in.ev_h2d, 0) != hipSuccess) return (int)STRAIT_E_HIP;
+                    if (first == 0 && launch_stamp(in.ctl_dev, STAMP_K0, s)) return (int)STRAIT_E_HIP;
+                    const int r = run_plan(*m, in, end - first, s, t->hp, lead - 1, false, 0, false, first, batch);
                     if (end < batch) slk.unlock();
                     return r;
                 });

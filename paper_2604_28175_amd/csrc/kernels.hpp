@@ -184,10 +184,8 @@ int launch_argmax_f16(const half_t* x, int rows, int n, long long row_stride, in
 int launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 // ---- transfers by kernel, with the timestamps and the completion flags of a batch (elementwise.hip)
 // STAMP_PIECES + 2 i, + 2 i + 1: start and end of the i-th piece of an input that goes in by kernel; of one that copy engines bring, the
-// first pair holds its start and end, STAMP_LAST the start of a last piece that follows another batch's.  STAMP_PARTS + 2 i, + 2 i + 1: where the first layers are
-// computed as the pieces come in, start and end of those of the i-th (of the last one the start only)
-enum { STAMP_K0 = 0, STAMP_K1 = 1, STAMP_D2H0 = 2, STAMP_DONE = 3, STAMP_LAST = 4, STAMP_PIECES = 8, MAX_PIECES = 32, STAMP_PARTS = STAMP_PIECES + 2 * MAX_PIECES,
-       STAMP_COUNT = STAMP_PARTS + 2 * MAX_PIECES };
+// first pair holds its start and end, STAMP_LAST the start of a last piece that follows another batch's
+enum { STAMP_K0 = 0, STAMP_K1 = 1, STAMP_D2H0 = 2, STAMP_DONE = 3, STAMP_LAST = 4, STAMP_PIECES = 8, MAX_PIECES = 32, STAMP_COUNT = STAMP_PIECES + 2 * MAX_PIECES };
 constexpr unsigned OUT_PARTS = 8, OUT_MAX_CHUNKS = 4096;
 inline size_t out_chunk_bytes(size_t bytes) {          // of a result: 256 KB, doubled while it has more chunks than there are flags (beyond 1 GiB)
     size_t c = 256u << 10;

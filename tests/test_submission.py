@@ -146,25 +146,6 @@ for again in range(2):
 """)
 
 
-def test_kernel_time_of_a_batch_in_parts_holds_no_waits_for_its_input(standin):
-    """kernel_ms of a batch that is begun before its input is complete: the time of its kernels, as of one that is not (5 us a kernel, here), and of a stamp (2 us) a part."""
-    run(standin, """
-c = context()
-for md, batch in ((synth.mobilenet_v2(1), 64), (synth.mobilenet_v2(1), 128), (synth.encoder(1, layers=2), 100), (synth.vgg19(1, fc=64), 64)):
-    m = c.load(synth.pack(md), batch, 1)
-    for staged in (True, False):
-        x = m.staging(0, batch) if staged else np.zeros((batch, *m.staging(0, 1).shape[1:]), np.float16)
-        notes()
-        r = m.wait(m.submit(S.PRIO_LOW, x, lengths(md, batch), m.new_output(batch)))
-        standin.standin_idle()
-        n = notes()
-        us, parts = 5e-3 * sum(l[0] == "kernel" for l in n), sum(l[0] == "memcpy" for l in n) if staged else 1
-        assert us - 1e-4 <= r.kernel_ms <= us + 2e-3 * parts + 1e-4, (md.arch, batch, staged, us, r.kernel_ms, r.total_ms)
-        assert parts > 1 or not staged
-    m.free()
-""")
-
-
 def test_what_the_scheduling_policy_is_fed_is_a_transfer_and_then_kernels(standin):
     """The policy adds a batch's transfer to its kernels (Eq. 1 to 3, 6).  Profiles, and batches of the serving front end, are not begun before their input is complete."""
     run(standin, """
