@@ -906,3 +906,40 @@ def test_a_batch_in_parts_gives_the_bytes_of_the_whole(ctx, arch, kw, batch):
             assert np.array_equal(parts, whole), (arch, batch, prio)
     finally:
         m.free()
+
+
+def test_other_threads_submit_while_a_batch_goes_in_parts(ctx):
+    """Two threads with a large staged batch each and one with small batches share a compute stream, a fourth has the other level's: batches are enqueued between the parts of another one.
+    Every result is that of the batch by itself."""
+    import threading
+    S = ctx.S
+    big, small = synth.mobilenet_v2(23), synth.tiny_cnn(23, hw=64)
+    mb, ms = ctx.load(synth.pack(big), max_batch=64, n_instances=2), ctx.load(synth.pack(small), max_batch=8, n_instances=2)
+    try:
+        xb = [synth.default_image_batch(big, n, 30 + n) for n in (64, 50)]
+        xs = [synth.default_image_batch(small, 8, 40 + i) for i in range(2)]
+        want_b = [mb.infer(x, prio=S.PRIO_LOW)[0]["logits"].copy() for x in xb]
+        want_s = [ms.infer(x, prio=S.PRIO_LOW)[0]["logits"].copy() for x in xs]
+        staged = [mb.staging(i, len(xb[i])) for i in range(2)] + [ms.staging(i, 8) for i in range(2)]
+        for st, x in zip(staged, xb + xs):
+            st[:] = x
+        bad, gate = [], threading.Barrier(4)
+
+        def work(model, st, prio, want, times):
+            out = model.new_output(len(st))
+            gate.wait()
+            for k in range(times):
+                rec = model.wait(model.submit(prio, st, None, out))
+                if not np.array_equal(model.decode(out, len(st))["logits"], want) or not rec.kernel_ms <= rec.total_ms:
+                    bad.append((model.arch, len(st), prio, k, rec.kernel_ms, rec.total_ms))
+
+        jobs = [(mb, staged[0], S.PRIO_LOW, want_b[0], 25), (mb, staged[1], S.PRIO_LOW, want_b[1], 25), (ms, staged[2], S.PRIO_LOW, want_s[0], 200), (ms, staged[3], S.PRIO_HIGH, want_s[1], 200)]
+        th = [threading.Thread(target=work, args=j) for j in jobs]
+        for t in th:
+            t.start()
+        for t in th:
+            t.join()
+        assert not bad, bad[:5]
+    finally:
+        mb.free()
+        ms.free()
