@@ -27,6 +27,8 @@ static std::string notes;
 static thread_local struct { dim3 grid, block; size_t lds; hipStream_t stream; } call;
 static std::atomic<bool> held{false};                      // results are not there yet
 static std::vector<std::pair<uint32_t*, uint32_t>> to_set;
+static std::atomic<int> held_stamp{-1};                    // nor is this stamp
+static std::vector<std::pair<uint64_t*, uint64_t>> to_stamp;
 static char streams_made[64];
 static int n_streams_made;
 
@@ -47,7 +49,10 @@ static void set_flag(uint32_t* flag, uint32_t seq) {
     if (held) to_set.push_back({flag, seq});
     else __atomic_store_n(flag, seq, __ATOMIC_RELEASE);
 }
-static void stamp(HostControl* ctl, int which, long long ns) { ctl->stamp[which] = (uint64_t)(ns / 10); }
+static void stamp(HostControl* ctl, int which, long long ns) {
+    if (which == held_stamp) to_stamp.push_back({&ctl->stamp[which], (uint64_t)(ns / 10) + 1});
+    else __atomic_store_n(&ctl->stamp[which], (uint64_t)(ns / 10) + 1, __ATOMIC_RELEASE);
+}
 static long long transfer(hipStream_t s, size_t bytes) {   // returns its start
     long long& t = clock_of(s);
     const long long start = std::max(t, link_ns);
@@ -69,9 +74,13 @@ void standin_idle() {                                      // everything that wa
     for (auto& s : stream_ns) now_ns = std::max(now_ns, s.second);
 }
 void standin_hold() { held = true; }
+void standin_hold_stamp(int which) { held_stamp = which; }
 void standin_release() {
     std::lock_guard<std::mutex> lk(mu);
     held = false;
+    held_stamp = -1;
+    for (auto& f : to_stamp) __atomic_store_n(f.first, f.second, __ATOMIC_RELEASE);
+    to_stamp.clear();
     for (auto& f : to_set) __atomic_store_n(f.first, f.second, __ATOMIC_RELEASE);
     to_set.clear();
 }
@@ -174,7 +183,7 @@ hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t) { return held ? hipErrorNotReady : hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return held || held_stamp >= 0 ? hipErrorNotReady : hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 }

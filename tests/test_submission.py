@@ -83,28 +83,34 @@ assert took["250"] > 3 and took["226"] > 3 and took["30"] > 1 and took["sequence
     print(out)
 
 
-def test_the_kernels_wait_for_the_input_s_end_stamp(standin):
-    """The stamp that ends an input's transfer lies in front of what the compute stream waits for: a record that is read when the result is there holds this batch's, and a
-    later batch's is not written over."""
+def test_a_batch_is_done_when_its_input_s_end_is_stamped(standin):
+    """The stamp that ends an input's transfer lies in front of what the kernels wait for, or, of an input in parts, is waited for itself: the record that is read holds
+    this batch's, and a late stamp is not written into a later batch's."""
     run(standin, """
+import time
 c = context()
 md = synth.mobilenet_v2(1)
 m = c.load(synth.pack(md), 64, 1)
 x = np.zeros((64, 224, 224, 3), np.float16)
-for staged in (True, False):
-    for prio in (S.PRIO_LOW, S.PRIO_HIGH):
-        notes()
-        m.wait(m.submit(prio, m.staging(0, 64) if staged else x, None, m.new_output(64)))
+for prio in (S.PRIO_LOW, S.PRIO_HIGH):
+    notes()
+    m.wait(m.submit(prio, x, None, m.new_output(64)))
+    standin.standin_idle()
+    n = notes()
+    end = [i for i, l in enumerate(n) if l[:2] == ["stamp", "9"]]                    # (8 and 9: a transfer's start and end)
+    assert len(end) == 1 and ["record", n[end[0]][2]] in [[l[0], l[2]] for l in n[end[0]:] if l[0] == "record"]
+    for late in (True, False):
+        if late:
+            standin.standin_hold_stamp(9)
+        t = m.submit(prio, m.staging(0, 64), None, m.new_output(64))
+        assert sum(l[0] == "memcpy" for l in notes()) > 1
+        if late:
+            time.sleep(0.05)
+            assert not m.poll(t)                                                     # its result is there
+            standin.standin_release()
+        r = m.wait(t)
+        assert r.total_ms > 0
         standin.standin_idle()
-        n = notes()
-        end = [i for i, l in enumerate(n) if l[:2] == ["stamp", "9"]]                # (8 and 9: a transfer's start and end)
-        assert len(end) == 1
-        stream, done = n[end[0]][2], int(n[end[0]][3]) + 2000
-        records = [l for l in n[end[0]:] if l[0] == "record" and l[2] == stream]
-        assert records and int(records[0][3]) >= done, (staged, n[end[0] - 3:end[0] + 3])
-        waits = [l for l in n[end[0]:] if l[0] == "wait" and l[1] == records[0][1]]
-        assert waits and int(waits[-1][3]) >= done
-        assert sum(l[0] == "memcpy" for l in n) > 1
 """)
 
 
