@@ -179,8 +179,9 @@ strait_status strait_ctx_set_branch_streams(strait_ctx* ctx, int32_t enabled);
  * serving the asynchronous copy call of such sizes was measured to block its caller for milliseconds
  * now and then, a kernel launch never.  0 = always hipMemcpyAsync.
  * A staged input of 9 MB or more that goes by hipMemcpyAsync with nothing else on the way (n_copy > 1, no graphs, no yielding) travels in parts over two copy
- * streams, and where the plan allows it the batch's first layers are computed for each part as it arrives: kernel_ms, from the first part's arrival on, and h2d_ms then overlap.  Not
- * what the front end (strait_server) and strait_model_profile submit: the scheduling policy takes a batch for a transfer and then kernels. */
+ * streams, and where the plan allows it the batch's first layers are computed for each part as it arrives: kernel_ms, from the first part's arrival on, and h2d_ms then overlap; the
+ * results are those of the batch in one piece, bit for bit.  Not what the front end (strait_server) and strait_model_profile
+ * submit: the scheduling policy takes a batch for a transfer and then kernels. */
 strait_status strait_ctx_set_h2d_kernel_limit(strait_ctx* ctx, int64_t max_bytes);
 
 strait_status strait_model_load(strait_ctx* ctx, const strait_model_desc* desc, strait_model** out);

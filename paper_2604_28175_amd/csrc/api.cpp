@@ -702,8 +702,8 @@ strait_status strait_submit(strait_model* m, strait_priority prio, int32_t batch
         const bool alone = c->copy_outstanding[cidx].fetch_add(1, std::memory_order_acq_rel) == 0;
         t->copies = 1;
         // A large input that is staged and that nothing else is on its way beside: the first layers of each part run while the next part is on the link, where 64 images of
-        // 224 x 224 are 365 us.  MobileNetV2 64 images 948 -> 888 us, 128 images 1617 -> 1460, beside ResNet-50 eight 1160 -> 1067; ViT 64 images 3648 -> 3544, 32 images 2078 -> 2057, VGG-19
-        // 64 images 3115 -> 3031, encoder 64 sequences 2787 -> 2757.
+        // 224 x 224 are 365 us.  In one piece (replayed from a graph) and in parts: MobileNetV2 64 images 940 -> 873 us, 128 images 1625 -> 1463, 31 images 601 -> 588; ViT 64 images 3700 ->
+        // 3608, 45 images 2834 -> 2786; VGG-19 64 images 3161 -> 3099; encoder 64 sequences 2848 -> 2799, 100 sequences 4084 -> 3939.
         // An input that is not staged waits for the host's copying, which these launches would hold up; a captured kernel sequence is one piece.
         Parts parts;
         if (host_in == in.pinned_in && !yielding && !by_kernel && !c->use_graphs && !InputFirst::wanted() && c->copy.size() > 1 && w->outstanding.load(std::memory_order_acquire) == 0)

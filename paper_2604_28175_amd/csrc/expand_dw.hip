@@ -123,12 +123,11 @@ __global__ void __launch_bounds__(256) expand_dw_kernel(const ExpandDwParams p) 
     load_w1(g_begin, wf, bv);
     load_wd(g_begin, wv, bdv);
 
-    // (A thread takes the same piece of every PSTEP-th pixel, and what lies outside reads as zero by its offset.  Working out each piece's pixel, its being inside and a
-    // 64-bit address took 600 to 1400 instructions in front of the first MFMA, at one wavefront per SIMD half of a small launch: a third fewer now.  MobileNetV2
-    // five images 281 -> 262 us.)
     // ---- A: the input tile: its 16-byte pieces are requested into registers (several before the first is waited for; a piece outside the image has an offset
     // beyond the buffer and reads as zero) and deposited in LDS.  Where a thread holds few enough of them, the next tile's are requested while this
-    // tile is computed.  Threads take the same piece of every PSTEP-th pixel, so that nothing but the pixel's row and column is worked out per piece.
+    // tile is computed.  Threads take the same piece of every PSTEP-th pixel, so that nothing but the pixel's row and column is worked out per piece: a division, being
+    // inside and a 64-bit address for each took 600 to 1400 instructions in front of the first MFMA, half of a small launch at one wavefront per SIMD, and a third of
+    // them are gone (MobileNetV2 five images 281 -> 262 us).
     constexpr int CH = KS * 2;                                                 // 16-byte pieces per pixel, zero-padded
     constexpr int PSTEP = 256 / CH, NIT = (ROWS + PSTEP - 1) / PSTEP;
     constexpr bool AHEAD = NIT <= 12;

@@ -1,7 +1,7 @@
 // A whole small classifier in one launch (paper Section 3.2, all of step (2) and step (3)): three 3x3 convolutions with ReLU, of stride 1, 2 and 2 and 16, 32 and
 // 64 channels, global average pooling, the fully connected layer, softmax, top-1 and the result's way to the host.
 //
-// Layer by layer such a network is nothing but launches: four dependent ones of 4 to 7 us for 6 MFLOP an image.  Here a workgroup of eight wavefronts takes an
+// Layer by layer such a network is nothing but launches: four dependent ones of 4 to 7 us, behind the input's copy, for 6 MFLOP an image.  Here a workgroup of eight wavefronts takes an
 // image from the input to the host's buffer, all activations in LDS (77 KB at 32 x 32) with a border of zeros, so that no tap asks
 // whether it is inside:
 //   - a wavefront's weights, all three layers', are fragments of v_mfma_f32_16x16x32_f16 in registers (17 of them), requested before anything else;
@@ -9,8 +9,10 @@
 //     neighbouring pixel, whose infinities times a weight of zero would not be zero);
 //   - 16 channels: an MFMA takes two taps, the tenth reads zeros; 32 channels: one tap;
 //   - the last layer's activations are rounded to fp16 as everywhere, added up in the registers and never stored.
-// Rounding points are those of the launches.  MI355X, a pass from host memory to host memory in us, launches / this: four 32 x 32 images 35 / 25, 32 images 41 / 31, 256 images 115 / 91.
-// What is left: 8 us of kernel, 3.5 until the weights and the image are there, 4 of LDS reads and chains of MFMAs, half of it at LDS's rate.
+// Rounding points are those of the launches.  MI355X, from submission to result in us, those four launches / this: four 32 x 32 images 30.2 / 21.1, 32 images 35.0 / 25.9, 256 images
+// 79.7 / 54.8.
+// What is left: 12.7 us a launch in a trace, 3.5 of them until the weights and the image are there, 4 of LDS reads and chains of MFMAs, half of it at LDS's rate; the others are the launch
+// itself, the head and the result's way to the host.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
