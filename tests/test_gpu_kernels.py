@@ -970,3 +970,21 @@ def test_split_reduction_under_capture(S):
         assert np.array_equal(y.cpu().numpy().astype(np.float64), want)
         assert S.torch.equal(S.k_gemm(dx, dw, None, 0, None, True), eager)
     assert np.array_equal(eager.cpu().numpy().astype(np.float64), want)
+
+
+@pytest.mark.parametrize("n,k,act,res", [(576, 96, 2, False), (384, 128, 0, False), (768, 768, 1, True), (3072, 768, 3, False), (1280, 320, 2, False), (768, 3072, 0, False)])
+def test_products_of_fewer_rows_on_other_tiles_have_the_same_bits(S, n, k, act, res):
+    """What batches that are computed part by part rely on: on all tiles on which one group of wavefronts reduces, a row's result is the same bit for bit, wherever in a tile it lies."""
+    t = S.torch
+    full = 25600
+    x, w = t.randn((full, k), device="cuda").half(), (t.randn((n, k), device="cuda") * (2.0 / k) ** 0.5).half()
+    b, r = t.randn(n, device="cuda") * 0.02, t.randn((full, n), device="cuda").half() if res else None
+    y, tiles = S.k_gemm(x, w, b, act=act, res=r), set()
+    for at, m in ((0, 60), (100, 200), (7, 900), (0, 1500), (4000, 3300), (33, 5000), (1000, 12600), (95, 20000)):
+        tile = S.k_conv2d_kernel(m, 1, 1, k, n, 1, 1, 0, act=act, res=res)
+        if not tile[0].isdigit() or "groups" in tile:
+            continue
+        tiles.add(tile)
+        part = S.k_gemm(x[at:at + m].contiguous(), w, b, act=act, res=r[at:at + m].contiguous() if res else None)
+        assert t.equal(part, y[at:at + m]), (tile, m, int((part != y[at:at + m]).sum()))
+    assert len(tiles) >= 3, tiles
